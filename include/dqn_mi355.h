@@ -55,7 +55,8 @@ typedef struct {
     int32_t num_actions;   /* A, 1..32 (the paper's games use 4..18)                              */
     int32_t max_batch;     /* largest minibatch dqn_train_step will see (Table 5: 32)              */
     int32_t max_envs;      /* largest W dqn_act will see (Section 4)                              */
-    int32_t precision;     /* DQN_PRECISION_FP32: fp32 operands on fp32 MFMA;
+    int32_t precision;     /* DQN_PRECISION_FP32: fp32 operands on fp32 MFMA (conv1, whose other operand is a
+                              byte: as exact sums of three bf16 parts on bf16 MFMA), fp32 accumulation;
                               DQN_PRECISION_BF16: bf16 operands on bf16 MFMA, fp32 accumulation,
                               fp32 master parameters and optimiser state                           */
     int32_t double_dqn;    /* 0: Eq. 1 (max over theta^-); 1: argmax from theta, value from theta^- */

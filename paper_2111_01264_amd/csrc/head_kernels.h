@@ -516,13 +516,6 @@ __device__ inline void small_grads_block(const BiasGradArgs& args, int block, un
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void bias_grad_kernel(BiasGradArgs args)
-{
-    extern __shared__ __attribute__((aligned(16))) unsigned char sg_smem[];
-    small_grads_block<T>(args, static_cast<int>(blockIdx.x), sg_smem);
-}
-
 // ---- optimiser --------------------------------------------------------------------------------
 
 struct RmsArgs {
@@ -537,7 +530,7 @@ struct RmsArgs {
     int centered;
     int flat_blocks; // after the kRmsConvBlocks conv-weight blocks: [0, flat_blocks) elementwise, then fc1_tiles fc1.w tiles, then the bias blocks
     int fc1_tiles;   // 16 * 49 (32 x 64 tiles of fc1.w)
-    // second stage of the bias gradients (conv1..3, fc1): chunk sums written by bias_grad_kernel
+    // second stage of the bias gradients (conv1..3, fc1): chunk sums (conv layers: one per weight-gradient slice)
     const float* bias_partial;
     int bias_chunks[4];
     int bias_first[4];

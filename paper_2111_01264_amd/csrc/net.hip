@@ -16,8 +16,8 @@
 #include "conv_tower_bwd.h"
 #include "fc_as.h"
 #include "wgrad_all.h"
+#include "wgrad_f32.h"
 #include "head_kernels.h"
-#include "layers.h"
 
 namespace dqn {
 
@@ -27,8 +27,8 @@ enum KernelId {
     K_RMSPROP, K_WGRAD_ALL, K_EVENT_PAIR, K_TOWER_BWD, K_COUNT
 };
 static const char* const kKernelNames[K_COUNT] = {
-    "none", "conv_tower", "(conv2_fwd)", "(conv3_fwd)", "fc1_fwd", "head_td", "(unused)", "fc1_wgrad",
-    "fc1_dgrad", "conv3_wgrad", "conv3_dgrad", "conv2_wgrad", "conv2_dgrad", "conv1_wgrad", "small_grads",
+    "none", "conv_tower", "(conv2_fwd)", "(conv3_fwd)", "fc1_fwd", "head_td", "(unused)", "(fc1_wgrad)",
+    "fc1_dgrad", "(conv3_wgrad)", "conv3_dgrad", "(conv2_wgrad)", "conv2_dgrad", "(conv1_wgrad)", "(small_grads)",
     "rmsprop", "wgrad_all", "event_pair", "conv_tower_bwd"};
 constexpr size_t kProfPairs = 4096;
 
@@ -140,12 +140,14 @@ namespace dqn {
 constexpr int kMaxFc1Slices = 49;
 // deferred split-K scratch of the three conv weight gradients
 constexpr size_t kWgMaxSplits = 64, kWgMaxSplits1 = 128;   // conv1's gradient is small: more slices are cheap
-constexpr size_t kWgFp32Splits = 32;                       // fp32 mode (separate launches per layer)
 // Reduced precision: slices per conv layer at most (conv2 / conv3 run 2 / 3 workgroups per slice, one per column block).
 // 44 and not the 64 the buffers allow: with 128 + 2 * 64 + 3 * 64 conv workgroups next to fc1's 200 tiles the grid was far
 // beyond the 512 workgroups that are resident at once and fc1's tiles started when the first conv workgroups left;
 // 128 + 2 * 43 + 3 * 43 leaves them room from the start (batch 256: 90.4 -> 87.5 us per train step, batch 128: 74.3 -> 70.1).
 constexpr int kWgSlices1 = 128, kWgSlices23 = 44;
+// fp32: the work of a sample is 10.5 k cycles of a workgroup per column block for conv2 (two of them), 4.8 k for conv3 (three),
+// about 2.5 k per quarter for conv1: workgroups of about 20 - 45 k cycles at batch 256, next to fc1's 200 tiles of 16 k.
+constexpr int kWgSlicesF32_1 = 128, kWgSlicesF32_2 = 64, kWgSlicesF32_3 = 44;
 // Smallest minibatch handled through descriptors.  Below it the assembled states are the faster form: the byte gather
 // rides for free in the previous step's head kernel (which leaves most of the chip idle at small batches), and the
 // fused conv kernel starts on states that are contiguous and cache-warm instead of after a descriptor round trip
@@ -155,7 +157,7 @@ constexpr int kDescMinBatch = 96;
 constexpr size_t kWgOff1 = 0, kWgOff2 = kWgMaxSplits1 * 32 * 256, kWgOff3 = kWgOff2 + kWgMaxSplits * 64 * 512;
 constexpr size_t kWgTotal = kWgOff3 + kWgMaxSplits * 64 * 576;
 
-static int alloc_ws(Workspace& ws, int cap, int groups, int A, size_t esize, bool training)
+static int alloc_ws(Workspace& ws, int cap, int groups, int A, size_t esize)
 {
     const size_t n = static_cast<size_t>(cap) * groups;
     DQN_HIP(hipMalloc(&ws.act1, n * 12800 * esize));
@@ -164,8 +166,6 @@ static int alloc_ws(Workspace& ws, int cap, int groups, int A, size_t esize, boo
     DQN_HIP(hipMalloc(&ws.h, static_cast<size_t>(cap) * 512 * esize));
     DQN_HIP(hipMalloc((void**)&ws.q, n * A * sizeof(float)));
     ws.partial_cap = n * kMaxFc1Slices * 512;
-    const size_t wgrad = static_cast<size_t>(256) * 64 * 576;   // up to 256 split-K slices of the largest filter
-    if (training && ws.partial_cap < wgrad) ws.partial_cap = wgrad;
     DQN_HIP(hipMalloc((void**)&ws.partial, ws.partial_cap * sizeof(float)));
     return DQN_OK;
 }
@@ -194,6 +194,8 @@ static hipError_t raise_lds_limits()
             result = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_tower_bwd_kernel<1>), hipFuncAttributeMaxDynamicSharedMemorySize, kTowerBwdSmem);
         if (result == hipSuccess)
             result = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_tower_bwd_kernel<5>), hipFuncAttributeMaxDynamicSharedMemorySize, kTowerBwdSmem);
+        if (result == hipSuccess)
+            result = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_f32_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kWgradF32Smem);
     });
     return result;
 }
@@ -209,28 +211,6 @@ static ProfPair prof_pair(dqn_ctx* c, int id)
         ++c->prof_used;
     }
     return p;
-}
-
-static int pick_splits(int tiles, int K, int BK, int max_splits)
-{
-    const int target = 512;   // about two workgroups per compute unit
-    int s = target / (tiles > 0 ? tiles : 1);
-    const int by_k = K / (2 * BK) > 0 ? K / (2 * BK) : 1;
-    if (s > by_k) s = by_k;
-    if (s > max_splits) s = max_splits;
-    return s < 1 ? 1 : s;
-}
-
-// Split-K factor of a conv weight gradient with K contraction rows and `n_blocks` column blocks:
-// up to 256 workgroups in total, at least two 32-row k-tiles each, at most max_splits slices (every
-// slice is a full copy of the gradient that the optimiser kernel has to read back).
-static int wgrad_splits(int K, int n_blocks, int max_splits)
-{
-    int s = 256 / n_blocks;
-    const int by_k = K / 64 > 0 ? K / 64 : 1;
-    if (s > by_k) s = by_k;
-    if (s > max_splits) s = max_splits;
-    return s < 1 ? 1 : s;
 }
 
 // Number of fc1 k-slices for n rows per group: enough workgroups to fill the chip, few enough that
@@ -523,8 +503,8 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     bg.dz[1] = dz2; bg.rows[1] = B * 81;  bg.chans[1] = 64;
     bg.dz[2] = dz3; bg.rows[2] = B * 49;  bg.chans[2] = 64;
     bg.dz[3] = dzh; bg.rows[3] = B;       bg.chans[3] = 512;
-    // reduced precision: the conv layers' bias gradients come out of their weight-gradient workgroups (dZ is in LDS there)
-    if (std::is_same<T, bf16_t>::value) bg.rows[0] = bg.rows[1] = bg.rows[2] = 0;
+    // the conv layers' bias gradients come out of their weight-gradient workgroups (dZ is in LDS there)
+    bg.rows[0] = bg.rows[1] = bg.rows[2] = 0;
     bg.first_block[0] = 0;
     {
         int pofs = 0;
@@ -560,78 +540,63 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     ra.wg_scale[0] = 1.f / 255.f;   // conv1 reads raw bytes: the input scale is applied to its gradient by the optimiser
     for (int l = 0; l < 4; ++l) { ra.bias_chunks[l] = 0; ra.bias_first[l] = 0; }
 
-    if constexpr (std::is_same<T, bf16_t>::value) {
-        // one launch: conv1/conv2/conv3/fc1 weight gradients and the small reductions
+    // one launch: conv1/conv2/conv3/fc1 weight gradients and the small reductions.  Conv layers: split-K over samples, workgroup
+    // j writes slice j (conv1's unit is half a sample, fp32: a quarter)
+    WgConvArgs w1{}, w2{}, w3{};
+    w1.dz = dz1; w1.in = s; w1.partial = c->wg_partial + kWgOff1; w1.n = B;
+    w1.desc = src ? src->desc : nullptr; w1.ring = src ? src->ring : nullptr;
+    w2.dz = dz2; w2.in = act1; w2.partial = c->wg_partial + kWgOff2; w2.n = B;
+    w3.dz = dz3; w3.in = act2; w3.partial = c->wg_partial + kWgOff3; w3.n = B;
+    // (items per workgroup: one, or -- `pairs` -- an even number where the kernel walks several in pairs: an odd range costs a padding item)
+    auto split = [](int items, int max_slices, bool pairs, int* per) {
+        *per = (items + max_slices - 1) / max_slices;
+        if (pairs && *per > 1) *per = (*per + 1) / 2 * 2;
+        return (items + *per - 1) / *per;
+    };
+    constexpr bool kBf16 = std::is_same<T, bf16_t>::value;
+    constexpr int kSl1 = kBf16 ? kWgSlices1 : kWgSlicesF32_1, kSl2 = kBf16 ? kWgSlices23 : kWgSlicesF32_2, kSl3 = kBf16 ? kWgSlices23 : kWgSlicesF32_3;
+    wg_splits[0] = split((kBf16 ? WgConv1::ITEMS : WgConv1F32::ITEMS) * B, kSl1, true, &w1.per);
+    wg_splits[1] = split(B, kSl2, kBf16, &w2.per);
+    wg_splits[2] = split(B, kSl3, kBf16, &w3.per);
+    // their bias gradients: one partial row [C_out] per slice, added in slice order by the optimiser kernel
+    constexpr int kConvBiasOff = 16384;
+    static_assert(kConvBiasOff + kSl1 * 32 + (kSl2 + kSl3) * 64 <= 65536, "bias partials fit their buffer");
+    bias_first[0] = kConvBiasOff;
+    bias_first[1] = bias_first[0] + kSl1 * 32;
+    bias_first[2] = bias_first[1] + kSl2 * 64;
+    for (int l = 0; l < 3; ++l) bias_chunks[l] = wg_splits[l];
+    w1.bias_partial = c->bias_partial + bias_first[0];
+    w2.bias_partial = c->bias_partial + bias_first[1];
+    w3.bias_partial = c->bias_partial + bias_first[2];
+    const ProfPair wg_pr = prof_pair(c, K_WGRAD_ALL);
+    if constexpr (kBf16) {
         WgradAllArgs wa{};
-        // conv layers: split-K over samples, workgroup j writes slice j (conv1's unit is half a sample)
-        // (items per workgroup: one, or an even number, because the kernel walks several in pairs -- an odd range costs a padding item)
-        auto split = [](int items, int max_slices, int* per, int* slices) {
-            *per = (items + max_slices - 1) / max_slices;
-            if (*per > 1) *per = (*per + 1) / 2 * 2;
-            *slices = (items + *per - 1) / *per;
-        };
-        int n1 = 0, n2 = 0, n3 = 0;
-        wa.c1.dz = dz1; wa.c1.in = s; wa.c1.partial = c->wg_partial + kWgOff1; wa.c1.n = B;
-        wa.c1.desc = src ? src->desc : nullptr; wa.c1.ring = src ? src->ring : nullptr;
-        split(2 * B, kWgSlices1, &wa.c1.per, &n1);
-        wa.c2.dz = dz2; wa.c2.in = act1; wa.c2.partial = c->wg_partial + kWgOff2; wa.c2.n = B;
-        split(B, kWgSlices23, &wa.c2.per, &n2);
-        wa.c3.dz = dz3; wa.c3.in = act2; wa.c3.partial = c->wg_partial + kWgOff3; wa.c3.n = B;
-        split(B, kWgSlices23, &wa.c3.per, &n3);
-        wg_splits[0] = n1; wg_splits[1] = n2; wg_splits[2] = n3;
-        // their bias gradients: one partial row [C_out] per slice, added in slice order by the optimiser kernel
-        constexpr int kConvBiasOff = 16384;
-        bias_chunks[0] = n1; bias_first[0] = kConvBiasOff;
-        bias_chunks[1] = n2; bias_first[1] = bias_first[0] + kWgSlices1 * 32;
-        bias_chunks[2] = n3; bias_first[2] = bias_first[1] + kWgSlices23 * 64;
-        static_assert(kConvBiasOff + kWgSlices1 * 32 + 2 * kWgSlices23 * 64 <= 65536, "bias partials fit their buffer");
-        wa.c1.bias_partial = c->bias_partial + bias_first[0];
-        wa.c2.bias_partial = c->bias_partial + bias_first[1];
-        wa.c3.bias_partial = c->bias_partial + bias_first[2];
+        wa.c1 = w1; wa.c2 = w2; wa.c3 = w3;
         wa.f1.dz = dzh; wa.f1.x = act3; wa.f1.B = B; wa.f1.grad = c->grad + o.wf1;
         wa.small = bg;
         wa.first[0] = 0;
-        wa.first[1] = wa.first[0] + n1;
-        wa.first[2] = wa.first[1] + n2 * WgConv2::CS;
-        wa.first[3] = wa.first[2] + n3 * WgConv3::CS;
+        wa.first[1] = wa.first[0] + wg_splits[0];
+        wa.first[2] = wa.first[1] + wg_splits[1] * WgConv2::CS;
+        wa.first[3] = wa.first[2] + wg_splits[2] * WgConv3::CS;
         wa.first[4] = wa.first[3] + kWgF1Cols * kWgF1Rows;
         wa.first[5] = wa.first[4] + small_blocks;
-        const ProfPair pr = prof_pair(c, K_WGRAD_ALL);
-        launch_timed(wgrad_all_kernel, dim3(wa.first[5]), dim3(256), kWgradAllSmem, st, pr.begin, pr.end, wa.first[1], wa.first[2], wa.first[3], wa.first[4],
+        launch_timed(wgrad_all_kernel, dim3(wa.first[5]), dim3(256), kWgradAllSmem, st, wg_pr.begin, wg_pr.end, wa.first[1], wa.first[2], wa.first[3], wa.first[4],
                      wa.c1.dz, wa.c1.in, wa.c1.n, wa.c1.per, wa.c1.desc, wa.c1.ring, wa);
-        DQN_LAUNCH_CHECK();
     } else {
-        {   // fc1 weight gradient: dW[o][f] = sum_b dZ[b][o] act3[b][f]
-            DenseM<T> al{}; DenseM<T> bl{}; EpiGrad ep{c->grad + o.wf1, 3136, 1.f};
-            al.p[0] = dzh; al.ld = 512; bl.p[0] = act3; bl.ld = 3136;
-            const ProfPair pr = prof_pair(c, K_FC1_WGRAD);
-            DQN_HIP((launch_gemm<T, 64, 128, 32, 2>(st, al, bl, ep, 512, 3136, B, 1, 1, ws.partial, ws.partial_cap, pr.begin, pr.end)));
-        }
-        {   // conv3 weight gradient
-            DenseM<T> al{}; WgradB<T, 64, 9, 9, 7, 7, 3, 1> bl{act2}; EpiGrad ep{c->grad + o.w3, 576, 1.f};
-            al.p[0] = dz3; al.ld = 64;
-            const ProfPair pr = prof_pair(c, K_CONV3_WGRAD);
-            DQN_HIP((launch_gemm<T, 64, 64, 32, 2>(st, al, bl, ep, 64, 576, B * 49, 1, pick_splits(9, B * 49, 32, kWgFp32Splits),
-                                                    c->wg_partial + kWgOff3, kWgMaxSplits * 64 * 576, pr.begin, pr.end, &wg_splits[2])));
-        }
-        {   // conv2 weight gradient
-            DenseM<T> al{}; WgradB<T, 32, 20, 20, 9, 9, 4, 2> bl{act1}; EpiGrad ep{c->grad + o.w2, 512, 1.f};
-            al.p[0] = dz2; al.ld = 64;
-            const ProfPair pr = prof_pair(c, K_CONV2_WGRAD);
-            DQN_HIP((launch_gemm<T, 64, 64, 32, 2>(st, al, bl, ep, 64, 512, B * 81, 1, pick_splits(8, B * 81, 32, kWgFp32Splits),
-                                                    c->wg_partial + kWgOff2, kWgMaxSplits * 64 * 512, pr.begin, pr.end, &wg_splits[1])));
-        }
-        {   // conv1 weight gradient (the input scale 1/255 is applied by the optimiser kernel)
-            DenseM<T> al{}; Conv1WgradB<T> bl{s}; EpiGrad ep{c->grad + o.w1, 256, 1.f};
-            al.p[0] = dz1; al.ld = 32;
-            const ProfPair pr = prof_pair(c, K_CONV1_WGRAD);
-            DQN_HIP((launch_gemm<T, 32, 128, 32, 1>(st, al, bl, ep, 32, 256, B * 400, 1, pick_splits(2, B * 400, 32, kWgFp32Splits),
-                                                     c->wg_partial + kWgOff1, kWgMaxSplits * 32 * 256, pr.begin, pr.end, &wg_splits[0])));
-        }
-        const ProfPair pr = prof_pair(c, K_BIAS_GRAD);
-        launch_timed(bias_grad_kernel<T>, dim3(small_blocks), dim3(256), kSmallGradsSmem, st, pr.begin, pr.end, bg);
-        DQN_LAUNCH_CHECK();
+        WgradF32Args wa{};
+        wa.c1 = w1; wa.c2 = w2; wa.c3 = w3;
+        wa.f1.dz = dzh; wa.f1.x = act3; wa.f1.B = B; wa.f1.grad = c->grad + o.wf1;
+        wa.small = bg;
+        wa.first[0] = 0;
+        wa.first[1] = wa.first[0] + wg_splits[1] * WgConv2F32::CS;
+        wa.first[2] = wa.first[1] + wg_splits[0];
+        wa.first[3] = wa.first[2] + wg_splits[2] * WgConv3F32::CS;
+        wa.first[4] = wa.first[3] + kWgF1fCols * kWgF1fRows;
+        wa.first[5] = wa.first[4] + small_blocks;
+        DQN_HIP(raise_lds_limits());
+        launch_timed(wgrad_f32_kernel, dim3(wa.first[5]), dim3(256), kWgradF32Smem, st, wg_pr.begin, wg_pr.end, wa);
     }
+    DQN_LAUNCH_CHECK();
     {
         const ProfPair pr = prof_pair(c, K_RMSPROP);
         for (int l = 0; l < 3; ++l) ra.wg_splits[l] = wg_splits[l];
@@ -643,7 +608,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     return DQN_OK;
 }
 
-// Public blob (OIHW, fc1 input index c*49 + h*7 + w)  <->  device layout (see layers.h).
+// Public blob (OIHW, fc1 input index c*49 + h*7 + w)  <->  device layout (see gemm_mfma.h).
 static void permute_blob(const Offsets& o, const float* src, float* dst, bool to_device)
 {
     memcpy(dst, src, o.total * sizeof(float));
@@ -743,9 +708,9 @@ int dqn_create(const dqn_config* cfg, void* act_stream, void* train_stream, dqn_
             c->sh = c->theta;
             c->sh_t = c->theta_t;
         }
-        int rc = alloc_ws(c->train_ws, cfg->max_batch, 3, c->A, c->esize, true);
+        int rc = alloc_ws(c->train_ws, cfg->max_batch, 3, c->A, c->esize);
         if (rc != DQN_OK) return rc;
-        rc = alloc_ws(c->act_ws, cfg->max_envs, 1, c->A, c->esize, false);
+        rc = alloc_ws(c->act_ws, cfg->max_envs, 1, c->A, c->esize);
         if (rc != DQN_OK) return rc;
         DQN_HIP(hipMalloc(&c->bsh, kBshTotal * c->esize));
         DQN_HIP(hipMemset(c->bsh, 0, kBshTotal * c->esize));

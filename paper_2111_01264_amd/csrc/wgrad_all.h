@@ -7,7 +7,6 @@
 #pragma once
 #include "gemm_tn_tr.h"
 #include "head_kernels.h"
-#include "layers.h"
 #include "wgrad_conv.h"
 #include "wgrad_fc1.h"
 
@@ -32,7 +31,7 @@ constexpr size_t kWgradAllSmem = []() {
 // The leading scalar parameters repeat the four block boundaries (first[1..4]) and what conv1's workgroups -- the longest
 // ones -- need before their first load (c1.dz, in, n, per, desc, ring): the kernel arguments' first 14 dwords are preloaded
 // into scalar registers when a wavefront starts (see conv_tower_kernel); the other layers read their part of the struct.
-__global__ __launch_bounds__(256, 2) void wgrad_all_kernel(int f1, int f2, int f3, int f4, const bf16_t* c1_dz, const void* c1_in, int c1_n, int c1_per,
+__global__ __launch_bounds__(256, 2) void wgrad_all_kernel(int f1, int f2, int f3, int f4, const void* c1_dz, const void* c1_in, int c1_n, int c1_per,
                                                            const int32_t* c1_desc, const uint8_t* c1_ring, WgradAllArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char wg_smem[];

@@ -32,35 +32,44 @@ namespace dqn {
 
 typedef uint32_t wg_u32x4 __attribute__((ext_vector_type(4)));   // a 16-byte vector the compiler keeps in registers (HIP's uint4 struct, in an array, went to scratch memory)
 
-template <int CIN_, int HIN_, int WIN_, int COUT_, int HOUT_, int WOUT_, int KS_, int S_, int PITCH_, bool U8_, int CS_>
+// DZ_ = float (full precision, conv1 only): dZ is staged as three bf16 planes whose sum is the fp32 value exactly (8 + 8 + 8
+// significand bits: hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid).  The other operand, a pixel byte, is exact in bf16,
+// so every product is exact and what is summed in fp32 is what the fp32 matrix instruction would sum -- at three bf16
+// instructions (96 cycles) instead of eight fp32 ones (512 cycles) per sixteen pixels.  Against the fp64 oracle conv1's gradient
+// is off by 3.1e-7 (l2, batch 32), with fp32 instructions it was 4.7e-7.  ITEMS_: items per sample.
+template <int CIN_, int HIN_, int WIN_, int COUT_, int HOUT_, int WOUT_, int KS_, int S_, int PITCH_, bool U8_, int CS_, typename DZ_ = bf16_t, int ITEMS_ = U8_ ? 2 : 1>
 struct WgGeo {
+    typedef DZ_ DZ;
+    static constexpr int PL = sizeof(DZ_) == 4 ? 3 : 1;        // bf16 planes of dZ
+    static constexpr int EPV = 16 / static_cast<int>(sizeof(DZ_));   // elements of dZ per 16-byte vector
     static constexpr int CIN = CIN_, HIN = HIN_, WIN = WIN_, COUT = COUT_, HOUT = HOUT_, WOUT = WOUT_, KS = KS_, S = S_;
     static constexpr int PITCH = PITCH_;                       // LDS elements per input pixel (channels-last layers)
     static constexpr bool U8 = U8_;                            // conv1: uint8 planes [c][row][col], filter element n = (c, p, q)
-    static constexpr int ITEMS = U8_ ? 2 : 1;                  // items per sample
+    static constexpr int ITEMS = ITEMS_;                       // items per sample
     static constexpr int ROWS = HOUT_ / ITEMS;                 // output rows per item
-    static constexpr int KPIX = ROWS * WOUT_;                  // contraction rows per item: 200, 81, 49
-    static constexpr int KPAD = (KPIX + 15) / 16 * 16;         // 208, 96, 64
+    static constexpr int KPIX = ROWS * WOUT_;                  // contraction rows per item: 200 (fp32: 100), 81, 49
+    static constexpr int KPAD = (KPIX + 15) / 16 * 16;         // 208 (112), 96, 64
     static constexpr int N = KS_ * KS_ * CIN_;                 // 256, 512, 576
     static constexpr int CS = CS_;                             // column blocks: a workgroup owns N / CS filter elements (its accumulators must fit the register file twice per SIMD)
     static constexpr int MT = COUT_ / 32, NT = N / 32 / CS_, NTW = (NT + 3) / 4;   // 32 x 32 tiles per workgroup, per wavefront
     static constexpr int LDA = COUT_ + 16;                     // LDS pitch of a dZ row
-    static constexpr int IN_ROWS = U8_ ? S_ * (ROWS - 1) + KS_ : HIN_;           // conv1: 44 image rows per item
+    static constexpr int IN_ROWS = U8_ ? S_ * (ROWS - 1) + KS_ : HIN_;           // conv1: 44 (24) image rows per item
     static constexpr int IN_ELEMS = U8_ ? CIN_ * IN_ROWS * WIN_ : HIN_ * WIN_ * PITCH_;
     static constexpr int IN_VECS = U8_ ? CIN_ * (IN_ROWS * WIN_ / 16) : HIN_ * WIN_ * CIN_ / 8;   // 16-byte vectors per item
-    static constexpr int DZ_VECS = KPIX * COUT_ / 8;
+    static constexpr int DZ_VECS = KPIX * COUT_ / EPV;
     static constexpr int NVI = (IN_VECS + 255) / 256, NVD = (DZ_VECS + 255) / 256;
-    static constexpr size_t SMEM = static_cast<size_t>(IN_ELEMS) * 2 + static_cast<size_t>(KPAD) * LDA * 2;
+    static constexpr size_t SMEM = static_cast<size_t>(IN_ELEMS) * 2 + static_cast<size_t>(PL) * KPAD * LDA * 2;
     static_assert(!U8_ || (IN_ROWS * WIN_) % 16 == 0, "a channel's rows of one item are whole 16-byte vectors");
     static_assert(!U8_ || (S_ * ROWS * WIN_) % 16 == 0, "the second item of a sample starts on a 16-byte boundary");
     static_assert(IN_ELEMS % 8 == 0 && (KPAD * LDA) % 2 == 0, "LDS regions stay 16-byte / 4-byte aligned");
 };
 typedef WgGeo<4, 84, 84, 32, 20, 20, 8, 4, 0, true, 1> WgConv1;
+typedef WgGeo<4, 84, 84, 32, 20, 20, 8, 4, 0, true, 1, float, 4> WgConv1F32;
 typedef WgGeo<32, 20, 20, 64, 9, 9, 4, 2, 40, false, 2> WgConv2;
 typedef WgGeo<64, 9, 9, 64, 7, 7, 3, 1, 72, false, 3> WgConv3;
 
 struct WgConvArgs {
-    const bf16_t* dz;        // [n][HOUT][WOUT][COUT]
+    const void* dz;          // bf16 or fp32 [n][HOUT][WOUT][COUT]
     const void* in;          // conv2 / conv3: bf16 [n][HIN][WIN][CIN];  conv1: uint8 [n][4][84][84], unused with desc
     float* partial;          // [slices][COUT][N] fp32
     float* bias_partial;     // [slices][COUT] fp32: column sums of dZ over the slice's items (the bias gradient)
@@ -114,6 +123,8 @@ __device__ inline bf16x8 bf16x8_from_bytes(uint32_t lo, uint32_t hi)
 template <class G>
 __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, unsigned char* smem)
 {
+    typedef typename G::DZ DZ;
+    constexpr int PL = G::PL, EPV = G::EPV, PLANE = G::KPAD * G::LDA;
     constexpr int LDA = G::LDA, MT = G::MT, NT = G::NT, NTW = G::NTW, NVI = G::NVI, NVD = G::NVD, KSTEPS = G::KPAD / 16;
     bf16_t* sIn = reinterpret_cast<bf16_t*>(smem);
     bf16_t* sDz = sIn + G::IN_ELEMS;
@@ -123,7 +134,9 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
     if (first >= last) return;
 
     // once per workgroup: zero rows of dZ beyond the item's pixels (their products vanish whatever the B operand reads)
-    for (int e = tid; e < (G::KPAD - G::KPIX) * LDA; e += 256) sDz[G::KPIX * LDA + e] = static_cast<bf16_t>(0.f);
+    for (int e = tid; e < (G::KPAD - G::KPIX) * LDA; e += 256)
+#pragma unroll
+        for (int p = 0; p < PL; ++p) sDz[p * PLANE + G::KPIX * LDA + e] = static_cast<bf16_t>(0.f);
 
     // this lane's share of an operand fragment (see gemm_tn_tr.h): contraction row inside a 16-step, first of its four columns
     const int G4 = lane >> 4, s16 = lane & 15;
@@ -157,11 +170,13 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
     // The bias gradient (column sums of dZ) is taken on the way: a thread's dZ vectors all belong to the same eight
-    // channels (256 is a multiple of the vectors per row), so it adds them up in eight registers while it stores them to
+    // (fp32: four) channels (256 is a multiple of the vectors per row), so it adds them up in as many registers while it stores them to
     // LDS; the threads' sums meet in LDS once, at the end, in thread order.  (A reduction kernel of its own read every
     // dZ tensor from memory a second time.)
-    float bsum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    static_assert(256 % (G::COUT / 8) == 0, "a thread's dZ vectors share their channel chunk");
+    float bsum[EPV];
+#pragma unroll
+    for (int e = 0; e < EPV; ++e) bsum[e] = 0.f;
+    static_assert(256 % (G::COUT / EPV) == 0, "a thread's dZ vectors share their channel chunk");
 
     // Operands are requested TWO items ahead into registers (one dependent round trip to memory takes about as long as
     // two items' matrix work; with one item ahead every item waited for its loads).
@@ -190,11 +205,11 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
         live[ps] = item_ < last ? ~0u : 0u;
         const int item = min(item_, last - 1);
         const int b = item / G::ITEMS, h = item % G::ITEMS;
-        const wg_u32x4* dzp = reinterpret_cast<const wg_u32x4*>(a.dz + (static_cast<size_t>(b) * G::HOUT * G::WOUT + h * G::KPIX) * G::COUT);
+        const wg_u32x4* dzp = reinterpret_cast<const wg_u32x4*>(static_cast<const DZ*>(a.dz) + (static_cast<size_t>(b) * G::HOUT * G::WOUT + h * G::KPIX) * G::COUT);
 #pragma unroll
         for (int u = 0; u < NVD; ++u) pdz[ps][u] = dzp[min(tid + u * 256, G::DZ_VECS - 1)];
         if constexpr (G::U8) {
-            constexpr int VPC = G::IN_ROWS * G::WIN / 16;   // vectors per channel: 231
+            constexpr int VPC = G::IN_ROWS * G::WIN / 16;   // vectors per channel: 231 (126)
 #pragma unroll
             for (int u = 0; u < NVI; ++u) {
                 const int v = min(tid + u * 256, G::IN_VECS - 1), c = v / VPC, w = v % VPC;
@@ -223,12 +238,25 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
         for (int u = 0; u < NVD; ++u) {
             const int v = min(tid + u * 256, G::DZ_VECS - 1);
             const wg_u32x4 d = pdz[ps][u] & live[ps];
-            *reinterpret_cast<wg_u32x4*>(sDz + (v / (G::COUT / 8)) * LDA + (v % (G::COUT / 8)) * 8) = d;
+            bf16_t* dst = sDz + (v / (G::COUT / EPV)) * LDA + (v % (G::COUT / EPV)) * EPV;
+            typedef DZ dz_vec __attribute__((ext_vector_type(EPV)));
+            const dz_vec dv = __builtin_bit_cast(dz_vec, d);
+            if constexpr (PL == 1) *reinterpret_cast<wg_u32x4*>(dst) = d;
+            else {
+                bf16x4 part[PL];
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) {
+                    float r = dv[e];
+#pragma unroll
+                    for (int p = 0; p < PL; ++p) { part[p][e] = static_cast<bf16_t>(r); r -= static_cast<float>(part[p][e]); }
+                }
+#pragma unroll
+                for (int p = 0; p < PL; ++p) *reinterpret_cast<bf16x4*>(dst + p * PLANE) = part[p];
+            }
             if (cb == 0) {
-                const bf16x8 dv = __builtin_bit_cast(bf16x8, d);
                 const float w = (G::DZ_VECS % 256 == 0 || tid + u * 256 < G::DZ_VECS) ? 1.f : 0.f;   // surplus threads hold a copy
 #pragma unroll
-                for (int e = 0; e < 8; ++e) bsum[e] += w * static_cast<float>(dv[e]);
+                for (int e = 0; e < EPV; ++e) bsum[e] += w * static_cast<float>(dv[e]);
             }
         }
 #pragma unroll
@@ -247,11 +275,13 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
     };
     // the item staged in LDS: sixteen pixels per step, the fragments of step ks + 1 requested before the matrix work of step ks
     auto contract = [&]() {
-        bf16x8 fa[2][MT], fb[2][NTW];
+        bf16x8 fa[2][PL][MT], fb[2][NTW];
         auto frags = [&](auto buf_, auto ks_) {
             constexpr int buf = decltype(buf_)::value, ks = decltype(ks_)::value;
 #pragma unroll
-            for (int i = 0; i < MT; ++i) fa[buf][i] = tr_fragment(sDz + (ks * 16 + krow) * LDA + i * 32 + col4, 4 * LDA);
+            for (int p = 0; p < PL; ++p)
+#pragma unroll
+                for (int i = 0; i < MT; ++i) fa[buf][p][i] = tr_fragment(sDz + p * PLANE + (ks * 16 + krow) * LDA + i * 32 + col4, 4 * LDA);
 #pragma unroll
             for (int j = 0; j < NTW; ++j)
                 if (NT % 4 == 0 || wave + 4 * j < NT)
@@ -265,7 +295,9 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
             for (int j = 0; j < NTW; ++j)
                 if (NT % 4 == 0 || wave + 4 * j < NT)
 #pragma unroll
-                    for (int i = 0; i < MT; ++i) mma_32x32x16(acc[i][j], fa[buf][i], fb[buf][j]);
+                    for (int p = 0; p < PL; ++p)
+#pragma unroll
+                        for (int i = 0; i < MT; ++i) mma_32x32x16(acc[i][j], fa[buf][PL - 1 - p][i], fb[buf][j]);   // smallest part first
             __builtin_amdgcn_sched_barrier(0);
         };
         static_for<0, KSTEPS>(step);
@@ -305,18 +337,18 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
         float* sSum = reinterpret_cast<float*>(smem);   // [8][256 threads]
         static_assert(8 * LDS_E * 4 <= G::SMEM, "the partial sums fit the operand buffers");
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sSum[e * LDS_E + tid] = bsum[e];
+        for (int e = 0; e < EPV; ++e) sSum[e * LDS_E + tid] = bsum[e];
         __syncthreads();
-        // channel ch is held by the threads t = ch / 8 + CH * k (k = 0 .. 256 / CH - 1).  P adjacent lanes share a channel:
-        // lane p adds eight consecutive k (eight independent LDS reads), the P sums meet in a fixed shuffle tree.  (One lane
+        // channel ch is held by the threads t = ch / EPV + CH * k (k = 0 .. 256 / CH - 1).  P adjacent lanes share a channel:
+        // lane p adds EPV consecutive k (as many independent LDS reads), the P sums meet in a fixed shuffle tree.  (One lane
         // per channel walking all 256 / CH values was a chain of dependent LDS reads: 1.5 - 2.4 us at the end of every block.)
         {
-            constexpr int CH = G::COUT / 8, P = 256 / G::COUT, PER = 256 / CH / P;
-            static_assert(PER == 8 && (P == 4 || P == 8), "eight values per lane, a power-of-two group of lanes per channel");
+            constexpr int CH = G::COUT / EPV, P = 256 / G::COUT, PER = 256 / CH / P;
+            static_assert(PER == EPV && (P == 4 || P == 8), "a few values per lane, a power-of-two group of lanes per channel");
             const int ch = tid / P, p = tid % P;
             float v[PER];
 #pragma unroll
-            for (int k = 0; k < PER; ++k) v[k] = sSum[(ch & 7) * LDS_E + (ch >> 3) + CH * (p * PER + k)];
+            for (int k = 0; k < PER; ++k) v[k] = sSum[(ch % EPV) * LDS_E + ch / EPV + CH * (p * PER + k)];
             float sum = 0.f;
 #pragma unroll
             for (int k = 0; k < PER; ++k) sum += v[k];
