@@ -178,8 +178,8 @@ int replay_push_step(replay* rb, const uint8_t* frames, const int32_t* actions, 
  * transaction per step for all W environments): exactly replay_push_step(rb, push_frames, push_actions,
  * push_rewards, push_terminals) -- the experiences the previous step produced -- followed by
  * dqn_act(ctx, states, W, epsilon, act_step, use_target, actions, q_out) on the states that step led
- * to; in the reduced-precision mode the append rides in the first kernel of the act step instead of
- * costing a dependent launch of its own.  push_actions may be the `actions` buffer of the previous
+ * to; the append rides in the first kernel of the act step instead of costing a dependent launch of
+ * its own.  push_actions may be the `actions` buffer of the previous
  * call (it is read before this call's actions are written).  The replay memory's push stream must be
  * the context's act stream.  Arguments, results and errors as for the two calls; DQN_EINVAL also if
  * the streams differ. */

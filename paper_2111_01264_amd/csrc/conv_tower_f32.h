@@ -1,0 +1,298 @@
+// Fused conv1 -> conv2 -> conv3 of the Q-network in full precision: the fp32 counterpart of conv_tower.h (same workgroups of 8
+// wavefronts walking (group, sample) items or bands of one, activations of conv1 and conv2 in LDS), with another division of the
+// work inside an item, because here the matrix core is what bounds it: a sample is 7.7 MMAC = 60 k cycles of a compute unit's
+// fp32 matrix rate (conv1's 25 k become 5 k, see below), and nothing else comes near that.
+//
+//   * conv2 and conv3 use the 16x16x4 fp32 instruction: lane l holds row / column l % 16 at contraction index l / 16, and since
+//     the contraction index may be assigned freely as long as both operands agree, a lane reads FOUR consecutive channels (one
+//     16-byte access) for four instructions.  Sixteen-pixel tiles waste less of 81 and 49 pixels than 32-pixel ones cut per
+//     k-quarter, and a wavefront (channel tile w % 4, half w / 4 of the pixel tiles) sums all of K by itself: no exchange between
+//     wavefronts, three barriers per item.
+//   * weights are not resident: 16 rows x 64 bytes of the row-major matrix are one load instruction (whole 64-byte pieces), which
+//     feeds 128 matrix cycles per pixel tile; they stream from L2 through a ring of registers whose first entries are requested
+//     a layer ahead.
+//   * conv1 multiplies pixel BYTES, which are exact in bf16, by weights that are split into three bf16 parts whose sum is the
+//     fp32 weight exactly (8 + 8 + 8 significand bits): all products are exact, the sum is accumulated in fp32 as before, and
+//     three bf16 instructions (96 cycles) replace eight fp32 ones (512 cycles).  The split is made while the weights are staged.
+//
+// One launch per layer (weights or operands re-read from cache by every wavefront) took 10 + 12 + 12 us for a minibatch of 32,
+// 43 + 46 + 55 us for 256, 5 + 12 + 12 us plus two gaps for a round of one to eight samplers; this launch takes FILL_IN.
+#pragma once
+#include "conv_tower.h"
+#include "wgrad_conv.h"
+
+namespace dqn {
+
+typedef float tf_f32x4 __attribute__((ext_vector_type(4)));
+
+struct TowerF32Args {
+    int n, groups;
+    int per;                       // items per workgroup
+    int tower_blocks;              // workgroups [0, tower_blocks) run the tower, the next push.L ones the append
+    const uint8_t* x[kMaxGroups];  // [n][4][84][84], 16-byte aligned
+    const float* w1[kMaxGroups];   // [32][256]
+    const float* w2[kMaxGroups];   // [64][512]
+    const float* w3[kMaxGroups];   // [64][576]
+    const float* b1[kMaxGroups];
+    const float* b2[kMaxGroups];
+    const float* b3[kMaxGroups];
+    float* act1[kMaxGroups];       // [n][400][32] or null
+    float* act2[kMaxGroups];       // [n][81][64] or null
+    float* act3[kMaxGroups];       // [n][49][64]
+    PushStepPlan push;             // optional (L = 0: none): one experience per lane into the temporary buffers
+};
+
+constexpr int kTfP1 = 36, kTfP2 = 68;                  // LDS pixel pitch (floats) of conv1 / conv2 outputs
+constexpr int kTfW1Plane = 32 * 256;                   // one bf16 part of conv1's weights, fragment order
+constexpr size_t kTowerF32Smem = kTowerXBytes + 3 * kTfW1Plane * 2 + 400 * kTfP1 * 4 + 81 * kTfP2 * 4 + kTowerThreads * 4;
+static_assert(kTowerF32Smem <= 160 * 1024, "one workgroup per compute unit");
+
+// acc[t] += (16 weight rows) x (16 pixels of tile t) over filter rows 0 .. ROWS - 1 with STEPS k-steps of sixteen each; `base`
+// points at this lane's pixel (its window's top-left corner, this lane's four channels), `w` at its weight row, `ring` holds the
+// weights of the first D steps.  k-step s of a filter row: tap s / CPT, channels 16 * (s % CPT) ..
+template <int NT, int ROWS, int STEPS, int CPT, int ROW_PITCH, int PITCH, int D>
+__device__ inline void tower_f32_rows(tf_f32x4 (&acc)[NT], const float* (&base)[NT], const float* w, tf_f32x4 (&ring)[D])
+{
+    static_assert(STEPS % D == 0 || D % STEPS == 0, "the ring slot of a step is the same in every filter row");
+    static_assert(STEPS % D == 0 && STEPS % 2 == 0, "ring and double buffer start every filter row at slot 0");
+    tf_f32x4 px[2][NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) px[0][t] = *reinterpret_cast<const tf_f32x4*>(base[t]);
+    for (int p = 0; p < ROWS; ++p) {
+        // past the last row the requests repeat the row's own first steps (never used, never skipped)
+        const float* wn = p + 1 < ROWS ? w + STEPS * 16 : w;
+        const int down = p + 1 < ROWS ? ROW_PITCH : 0;
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            const tf_f32x4 wv = ring[s % D];
+            ring[s % D] = *reinterpret_cast<const tf_f32x4*>(s + D < STEPS ? w + (s + D) * 16 : wn + (s + D - STEPS) * 16);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                px[(s + 1) & 1][t] = *reinterpret_cast<const tf_f32x4*>(s + 1 < STEPS ? base[t] + ((s + 1) / CPT) * PITCH + ((s + 1) % CPT) * 16 : base[t] + down);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], px[s & 1][t][e], acc[t], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        w = wn;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) base[t] += down;
+    }
+}
+
+// PARTS: a workgroup runs a whole sample, or one half / third / seventh of its output rows with the rows of conv2 and conv1 these
+// depend on (see conv_tower_kernel; thirds and sevenths are the same bands).  By the matrix cycles of its busiest SIMD an item
+// takes 49 k cycles whole, 30 k as a half, 25 k as a third, 16 k as a seventh; the host takes the smallest part for which the
+// chip still holds every workgroup at once.
+template <int PARTS>
+__global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, int groups_, int per_, int tower_blocks_, const uint8_t* x0_,
+                                                                       const uint8_t* x1_, const float* w1_0_, const float* w2_0_, TowerF32Args a)
+{
+    static_assert(PARTS == 1 || PARTS == 2 || PARTS == 3 || PARTS == 7, "whole samples, halves, thirds or sevenths");
+    extern __shared__ __attribute__((aligned(16))) unsigned char tf_smem[];
+    uint8_t* sX = tf_smem;
+    bf16_t* sW1 = reinterpret_cast<bf16_t*>(tf_smem + kTowerXBytes);
+    float* sA1 = reinterpret_cast<float*>(sW1 + 3 * kTfW1Plane);
+    float* sA2 = sA1 + 400 * kTfP1;
+    float* sB1 = sA2 + 81 * kTfP2;   // biases: conv1 [32], conv2 [64], conv3 [64]
+    float* sB2 = sB1 + 32;
+    float* sB3 = sB2 + 64;
+
+    if (static_cast<int>(blockIdx.x) >= tower_blocks_) {
+        push_step_block(a.push, static_cast<int>(blockIdx.x) - tower_blocks_);
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int total = n_ * groups_;
+    const int part = PARTS == 1 ? 0 : static_cast<int>(blockIdx.x % PARTS);
+    const int first = PARTS == 1 ? blockIdx.x * per_ : static_cast<int>(blockIdx.x / PARTS), last = PARTS == 1 ? min(total, first + per_) : min(total, first + 1);
+    if (first >= last) return;
+    // first conv3 row and pixel counts of this part (conv3 rows [r, r') need conv2 rows [r, r' + 2), those conv1 rows [2 r, 2 r' + 6))
+    const int r3_lo = PARTS == 1 ? 0 : PARTS == 2 ? 4 * part : PARTS == 7 ? part : (part == 0 ? 0 : part == 1 ? 3 : 5);
+    const int rows3 = PARTS == 1 ? 7 : PARTS == 2 ? 4 - part : PARTS == 7 ? 1 : (part == 0 ? 3 : 2);
+    const int n3 = 7 * rows3, n2 = 9 * (rows3 + 2), n1 = 20 * (2 * rows3 + 6);
+    constexpr int T2 = PARTS == 1 ? 6 : PARTS == 2 ? 4 : PARTS == 3 ? 3 : 2, T3 = PARTS == 1 ? 4 : PARTS == 7 ? 1 : 2;   // 16-pixel tiles of conv2 / conv3
+    constexpr int T1 = PARTS == 1 ? 13 : PARTS == 2 ? 9 : PARTS == 3 ? 8 : 5;                                            // 32-pixel tiles of conv1
+
+    constexpr int kXVecs = kTowerXBytes / 16;   // 1764
+    const int last_vec = tid + 1536 < kXVecs ? tid + 1536 : kXVecs - 1;
+    uint4 xv0, xv1, xv2, xv3;                   // the state of the item to come, 16 bytes per lane and load (the last one clamped)
+    auto fetch_state = [&](int g_, int b_) {
+        const uint8_t* xg = g_ == 0 ? x0_ : g_ == 1 ? x1_ : a.x[g_];
+        const uint4* xs = reinterpret_cast<const uint4*>(xg + static_cast<size_t>(b_) * kTowerXBytes);
+        xv0 = xs[tid]; xv1 = xs[tid + 512]; xv2 = xs[tid + 1024]; xv3 = xs[last_vec];
+    };
+    int g = 0, b = first;
+    while (b >= n_) { b -= n_; ++g; }
+    fetch_state(g, b);
+
+    const int lp = lane & 31, kg = lane >> 5;        // conv1: pixel / row of a 32x32 tile, k-half
+    const int lq = lane & 15, kq = lane >> 4;        // conv2, conv3: pixel / row of a 16x16 tile, k-quarter
+    const int ct = wave & 3, ph = wave >> 2;         // channel tile; pixel tiles ph, ph + 2, ...
+    constexpr int D2 = 8, D3 = 6;
+    int cur_g = kMaxGroups;   // no group (and not -1: the part variants then indexed the biases with 0 whatever g was -- a compiler error, seen in its output)
+    for (int it = first; it < last; ++it, ++b) {
+        if (b == n_) { b = 0; ++g; }
+        if (PARTS > 1 || g != cur_g) {   // first item, or the range crosses into the next group: conv1's weights and the biases
+            if (it != first) __syncthreads();   // the previous item's biases have been read
+            cur_g = g;
+            const float* w1g = g == 0 ? w1_0_ : a.w1[g];
+            const int o = tid >> 4, kc = tid & 15;   // row o, k = 16 * kc .. + 15
+            tf_f32x4 w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) w[u] = *reinterpret_cast<const tf_f32x4*>(w1g + o * 256 + kc * 16 + u * 4);
+            const int bt = tid < 160 ? tid : 159;
+            const float* bp = bt < 32 ? a.b1[g] + bt : (bt < 96 ? a.b2[g] + (bt - 32) : a.b3[g] + (bt - 96));
+            const float bias = *bp;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                bf16x8 p[3];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    float r = w[2 * h + (e >> 2)][e & 3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) { p[q][e] = static_cast<bf16_t>(r); r -= static_cast<float>(p[q][e]); }
+                }
+#pragma unroll
+                for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x8*>(sW1 + q * kTfW1Plane + ((kc * 64) + h * 32 + o) * 8) = p[q];
+            }
+            sB1[tid] = bias;
+        }
+        {
+            uint4* d = reinterpret_cast<uint4*>(sX);
+            d[tid] = xv0; d[tid + 512] = xv1; d[tid + 1024] = xv2; d[last_vec] = xv3;   // clamped lanes rewrite the last vector with itself
+        }
+        const float* w2p = (g == 0 ? w2_0_ : a.w2[g]) + (ct * 16 + lq) * 512 + kq * 4;
+        const float* w3p = a.w3[g] + (ct * 16 + lq) * 576 + kq * 4;
+        tf_f32x4 ring2[D2], ring3[D3];
+#pragma unroll
+        for (int u = 0; u < D2; ++u) ring2[u] = *reinterpret_cast<const tf_f32x4*>(w2p + u * 16);
+        if (it + 1 < last) { if (b + 1 < n_) fetch_state(g, b + 1); else fetch_state(g + 1, 0); }
+        __syncthreads();
+
+        // ---- conv1: k = (c, p, q); k-step k covers c = k / 4, p = 2 * (k % 4) + kg, q = 0..7 --------------------------
+        {
+            float* g1 = a.act1[g];
+            auto run = [&](auto nt_) {
+                constexpr int NT = decltype(nt_)::value;   // pixel tiles of this wavefront: w (and w + 8)
+                const uint8_t* base[NT];
+                f32x16 acc[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const int lpx = (wave + 8 * t) * 32 + lp;
+                    const int pc = 2 * r3_lo * 20 + (lpx < n1 ? lpx : n1 - 1);
+                    base[t] = sX + (4 * (pc / 20) + kg) * 84 + 4 * (pc % 20);
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+                }
+                auto fetch_px = [&](int t, int k) {
+                    const uint32_t* wp = reinterpret_cast<const uint32_t*>(base[t] + (k / 4) * 7056 + ((k % 4) * 2) * 84);
+                    return make_uint2(wp[0], wp[1]);
+                };
+                uint2 px[2][NT];
+                bf16x8 wf[2][3];
+                auto fetch = [&](int buf, int k) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) wf[buf][q] = *reinterpret_cast<const bf16x8*>(sW1 + q * kTfW1Plane + (k * 64 + lane) * 8);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) px[buf][t] = fetch_px(t, k);
+                };
+                fetch(0, 0);
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    if (k + 1 < 16) fetch((k + 1) & 1, k + 1);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        const bf16x8 x = bf16x8_from_bytes(px[k & 1][t].x, px[k & 1][t].y);
+#pragma unroll
+                        for (int q = 2; q >= 0; --q) mma_32x32x16(acc[t], wf[k & 1][q], x);   // smallest part first
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const int lpx = (wave + 8 * t) * 32 + lp, px1 = 2 * r3_lo * 20 + lpx;
+                    if (lpx < n1) {
+                        constexpr float kScale = 1.f / 255.f;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const int ch = 8 * q + 4 * kg;
+                            const float4 bv = *reinterpret_cast<const float4*>(sB1 + ch);
+                            const float v0 = fmaxf(acc[t][4 * q] * kScale + bv.x, 0.f), v1 = fmaxf(acc[t][4 * q + 1] * kScale + bv.y, 0.f);
+                            const float v2 = fmaxf(acc[t][4 * q + 2] * kScale + bv.z, 0.f), v3 = fmaxf(acc[t][4 * q + 3] * kScale + bv.w, 0.f);
+                            store4<float>(sA1 + px1 * kTfP1 + ch, v0, v1, v2, v3);
+                            if (g1) store4<float>(g1 + (static_cast<size_t>(b) * 400 + px1) * 32 + ch, v0, v1, v2, v3);
+                        }
+                    }
+                }
+            };
+            if (T1 > 8 && wave < T1 - 8) run(std::integral_constant<int, 2>{}); else if (wave < T1) run(std::integral_constant<int, 1>{});
+        }
+#pragma unroll
+        for (int u = 0; u < D3; ++u) ring3[u] = *reinterpret_cast<const tf_f32x4*>(w3p + u * 16);
+        __syncthreads();
+
+        // ---- conv2: k = (p, q, c), eight k-steps per filter row -----------------------------------------------------
+        {
+            const int ch = ct * 16 + 4 * kq;
+            const float4 bv = *reinterpret_cast<const float4*>(sB2 + ch);
+            float* g2 = a.act2[g];
+            auto run = [&](auto nt_) {
+                constexpr int NT = decltype(nt_)::value;
+                const float* base[NT];
+                tf_f32x4 acc[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const int lpx = (ph + 2 * t) * 16 + lq, pc = r3_lo * 9 + (lpx < n2 ? lpx : n2 - 1);
+                    base[t] = sA1 + (2 * (pc / 9) * 20 + 2 * (pc % 9)) * kTfP1 + kq * 4;
+                    acc[t] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+                tower_f32_rows<NT, 4, 8, 2, 20 * kTfP1, kTfP1, D2>(acc, base, w2p, ring2);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const int lpx = (ph + 2 * t) * 16 + lq, px = r3_lo * 9 + lpx;
+                    if (lpx < n2) {
+                        const float v0 = fmaxf(acc[t][0] + bv.x, 0.f), v1 = fmaxf(acc[t][1] + bv.y, 0.f), v2 = fmaxf(acc[t][2] + bv.z, 0.f), v3 = fmaxf(acc[t][3] + bv.w, 0.f);
+                        store4<float>(sA2 + px * kTfP2 + ch, v0, v1, v2, v3);
+                        if (g2) store4<float>(g2 + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v0, v1, v2, v3);
+                    }
+                }
+            };
+            constexpr int NA = (T2 + 1) / 2, NB = T2 / 2;
+            if (NA == NB || ph == 0) run(std::integral_constant<int, NA>{}); else run(std::integral_constant<int, NB>{});
+        }
+        __syncthreads();
+
+        // ---- conv3: k = (p, q, c), twelve k-steps per filter row ----------------------------------------------------
+        {
+            const int ch = ct * 16 + 4 * kq;
+            const float4 bv = *reinterpret_cast<const float4*>(sB3 + ch);
+            auto run = [&](auto nt_) {
+                constexpr int NT = decltype(nt_)::value;
+                const float* base[NT];
+                tf_f32x4 acc[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const int lpx = (ph + 2 * t) * 16 + lq, pc = r3_lo * 7 + (lpx < n3 ? lpx : n3 - 1);
+                    base[t] = sA2 + ((pc / 7) * 9 + pc % 7) * kTfP2 + kq * 4;
+                    acc[t] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+                tower_f32_rows<NT, 3, 12, 4, 9 * kTfP2, kTfP2, D3>(acc, base, w3p, ring3);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const int lpx = (ph + 2 * t) * 16 + lq, px = r3_lo * 7 + lpx;
+                    if (lpx < n3)
+                        store4<float>(a.act3[g] + (static_cast<size_t>(b) * 49 + px) * 64 + ch, fmaxf(acc[t][0] + bv.x, 0.f), fmaxf(acc[t][1] + bv.y, 0.f),
+                                      fmaxf(acc[t][2] + bv.z, 0.f), fmaxf(acc[t][3] + bv.w, 0.f));
+                }
+            };
+            constexpr int NA = (T3 + 1) / 2, NB = T3 / 2;
+            if (NA == NB || ph == 0) run(std::integral_constant<int, NA>{});
+            else if constexpr (NB > 0) run(std::integral_constant<int, NB>{});
+        }
+        // no barrier: conv3 reads act2 only, and the next item writes act2 behind two barriers of its own; state and act1 are free
+    }
+}
+
+}  // namespace dqn

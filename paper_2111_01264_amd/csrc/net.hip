@@ -14,6 +14,7 @@
 
 #include "conv_tower.h"
 #include "conv_tower_bwd.h"
+#include "conv_tower_f32.h"
 #include "fc_as.h"
 #include "wgrad_all.h"
 #include "wgrad_f32.h"
@@ -33,8 +34,6 @@ static const char* const kKernelNames[K_COUNT] = {
 constexpr size_t kProfPairs = 4096;
 
 // Layer geometries (Section 5: the Nature-DQN network).
-template <typename T> using Conv2Geo = FwdGeo<T, 32, 20, 20, 64, 9, 9, 4, 2>;
-template <typename T> using Conv3Geo = FwdGeo<T, 64, 9, 9, 64, 7, 7, 3, 1>;
 template <typename T> using Conv3DgradGeo = DgradGeo<T, 64, 9, 9, 64, 7, 7, 3, 1>;
 template <typename T> using Conv2DgradGeo = DgradGeo<T, 32, 20, 20, 64, 9, 9, 4, 2>;
 
@@ -176,26 +175,28 @@ static void free_ws(Workspace& ws)
     (void)hipFree(ws.q); (void)hipFree(ws.partial);
 }
 
-// The two fused conv kernels need more dynamic LDS than the default limit: raised once per process, whichever host
+// The fused kernels need more dynamic LDS than the default limit: raised once per process, whichever host
 // thread gets there first (the act and the train thread may both be on their first call).
 static hipError_t raise_lds_limits()
 {
     static std::once_flag once;
     static hipError_t result = hipSuccess;
     std::call_once(once, [] {
-        result = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_tower_kernel<false, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, kTowerSmem);
-        if (result == hipSuccess)
-            result = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_tower_kernel<false, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, kTowerSmem);
-        if (result == hipSuccess)
-            result = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_tower_kernel<false, 7>), hipFuncAttributeMaxDynamicSharedMemorySize, kTowerSmem);
-        if (result == hipSuccess)
-            result = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_tower_kernel<true, 1>), hipFuncAttributeMaxDynamicSharedMemorySize, kTowerSmem);
-        if (result == hipSuccess)
-            result = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_tower_bwd_kernel<1>), hipFuncAttributeMaxDynamicSharedMemorySize, kTowerBwdSmem);
-        if (result == hipSuccess)
-            result = hipFuncSetAttribute(reinterpret_cast<const void*>(conv_tower_bwd_kernel<5>), hipFuncAttributeMaxDynamicSharedMemorySize, kTowerBwdSmem);
-        if (result == hipSuccess)
-            result = hipFuncSetAttribute(reinterpret_cast<const void*>(wgrad_f32_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kWgradF32Smem);
+        const struct { const void* kernel; size_t bytes; } big[] = {
+            {reinterpret_cast<const void*>(conv_tower_kernel<false, 1>), kTowerSmem},
+            {reinterpret_cast<const void*>(conv_tower_kernel<false, 3>), kTowerSmem},
+            {reinterpret_cast<const void*>(conv_tower_kernel<false, 7>), kTowerSmem},
+            {reinterpret_cast<const void*>(conv_tower_kernel<true, 1>), kTowerSmem},
+            {reinterpret_cast<const void*>(conv_tower_bwd_kernel<1>), kTowerBwdSmem},
+            {reinterpret_cast<const void*>(conv_tower_bwd_kernel<5>), kTowerBwdSmem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<1>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<2>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<3>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<7>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(wgrad_f32_kernel), kWgradF32Smem},
+        };
+        for (const auto& k : big)
+            if (result == hipSuccess) result = hipFuncSetAttribute(k.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(k.bytes));
     });
     return result;
 }
@@ -284,42 +285,32 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         else launch_timed(conv_tower_kernel<false, 1>, g3, b3, kTowerSmem, st, pr.begin, pr.end, a.n, a.groups, a.per, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
         DQN_LAUNCH_CHECK();
     } else {
-        // fp32 mode: layer by layer; the event pair brackets all three launches
-        const size_t e_act1 = static_cast<size_t>(n) * 12800, e_act2 = static_cast<size_t>(n) * 5184;
+        // the same fusion on the fp32 matrix instructions
+        TowerF32Args a{};
+        for (int g = 0; g < groups; ++g) {
+            const T* w = static_cast<const T*>(shadow[g]);
+            a.x[g] = x[g];
+            a.w1[g] = w + o.w1; a.w2[g] = w + o.w2; a.w3[g] = w + o.w3;
+            a.b1[g] = master[g] + o.b1; a.b2[g] = master[g] + o.b2; a.b3[g] = master[g] + o.b3;
+            a.act1[g] = (timed && g == 0) ? act1 : nullptr;
+            a.act2[g] = (timed && g == 0) ? act2 : nullptr;
+            a.act3[g] = act3 + g * e_act3;
+        }
+        a.n = n; a.groups = groups;
+        DQN_HIP(raise_lds_limits());
+        // the smallest part of an item for which every workgroup is resident at once (see the kernel)
+        const int total = n * groups;
+        const int parts = 7 * total <= c->num_cus ? 7 : (3 * total <= c->num_cus ? 3 : (2 * total <= c->num_cus ? 2 : 1));
+        const int grid = parts > 1 ? parts * total : (total < c->num_cus ? total : c->num_cus);
+        a.per = parts > 1 ? 1 : (total + grid - 1) / grid;
+        a.tower_blocks = grid;
+        a.push.L = 0;
+        if (push) a.push = *push;
         const ProfPair pr = pp(K_CONV1_FWD);
-        {   // conv1 on the uint8 state, 1/255 folded into the epilogue
-            ConvWsArgs<T, Conv1Geo<T>> a{};
-            for (int g = 0; g < groups; ++g) {
-                a.x[g] = x[g];
-                a.w[g] = static_cast<const T*>(shadow[g]) + o.w1;
-                a.bias[g] = master[g] + o.b1;
-                a.out[g] = act1 + g * e_act1;
-            }
-            a.M = n * 400; a.scale = 1.f / 255.f;
-            DQN_HIP((launch_conv_ws<T, Conv1Geo<T>, kEpiBiasRelu>(st, a, groups, pr.begin, nullptr)));
-        }
-        {
-            ConvWsArgs<T, Conv2Geo<T>> a{};
-            for (int g = 0; g < groups; ++g) {
-                a.x[g] = act1 + g * e_act1;
-                a.w[g] = static_cast<const T*>(shadow[g]) + o.w2;
-                a.bias[g] = master[g] + o.b2;
-                a.out[g] = act2 + g * e_act2;
-            }
-            a.M = n * 81; a.scale = 1.f;
-            DQN_HIP((launch_conv_ws<T, Conv2Geo<T>, kEpiBiasRelu>(st, a, groups)));
-        }
-        {
-            ConvWsArgs<T, Conv3Geo<T>> a{};
-            for (int g = 0; g < groups; ++g) {
-                a.x[g] = act2 + g * e_act2;
-                a.w[g] = static_cast<const T*>(shadow[g]) + o.w3;
-                a.bias[g] = master[g] + o.b3;
-                a.out[g] = act3 + g * e_act3;
-            }
-            a.M = n * 49; a.scale = 1.f;
-            DQN_HIP((launch_conv_ws<T, Conv3Geo<T>, kEpiBiasRelu>(st, a, groups, nullptr, pr.end)));
-        }
+        auto kern = parts == 7 ? conv_tower_f32_kernel<7> : parts == 3 ? conv_tower_f32_kernel<3> : parts == 2 ? conv_tower_f32_kernel<2> : conv_tower_f32_kernel<1>;
+        launch_timed(kern, dim3(grid + a.push.L), dim3(kTowerThreads), kTowerF32Smem, st, pr.begin, pr.end, a.n, a.groups, a.per, a.tower_blocks, a.x[0], a.x[1],
+                     a.w1[0], a.w2[0], a);
+        DQN_LAUNCH_CHECK();
     }
     // fc1 as k-slices of fp32 partial sums [groups][slices][n][512]; the head kernel adds them
     if (n <= 32) {
@@ -875,11 +866,6 @@ int dqn_act_push_step(dqn_ctx* c, replay* rb, const uint8_t* push_frames, const 
     if (!c || !rb) return fail(DQN_EINVAL, "dqn_act_push_step: ctx or rb is null");
     if (replay_push_stream(rb) != c->act_stream)
         return fail(DQN_EINVAL, "dqn_act_push_step: the replay memory's push stream is not the context's act stream");
-    if (c->cfg.precision != DQN_PRECISION_BF16) {
-        // fp32 mode has no fused launch to ride in: the two calls, in order
-        const int rc = replay_push_step(rb, push_frames, push_actions, push_rewards, push_terminals);
-        return rc != DQN_OK ? rc : dqn_act(c, states, W, epsilon, act_step, use_target, actions, q_out);
-    }
     if (W < 1 || W > c->cfg.max_envs) return fail(DQN_EINVAL, "dqn_act_push_step: W = %d outside 1..%d", W, c->cfg.max_envs);
     if (!states || !actions) return fail(DQN_EINVAL, "dqn_act_push_step: null pointer");
     if (!aligned16(states)) return fail(DQN_EINVAL, "dqn_act_push_step: states not 16-byte aligned");
@@ -892,7 +878,9 @@ int dqn_act_push_step(dqn_ctx* c, replay* rb, const uint8_t* push_frames, const 
         online_lock.lock();
         DQN_HIP(wait_for_train(c));
     }
-    rc = act_impl<bf16_t>(c, c->act_ws, states, W, epsilon, act_step, use_target, actions, q_out, &plan);
+    rc = c->cfg.precision == DQN_PRECISION_BF16
+             ? act_impl<bf16_t>(c, c->act_ws, states, W, epsilon, act_step, use_target, actions, q_out, &plan)
+             : act_impl<float>(c, c->act_ws, states, W, epsilon, act_step, use_target, actions, q_out, &plan);
     if (rc != DQN_OK) return rc;
     replay_commit_push_step(rb);
     if (!use_target) {

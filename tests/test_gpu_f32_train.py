@@ -1,5 +1,6 @@
 """Full-precision train step against the fp64 oracle at the minibatch sizes where its kernels change shape: one sample, a pair,
-the last small-batch size and its neighbours, several samples per weight-gradient workgroup with a ragged last range.
+the last small-batch size and its neighbours, the last one whose samples are run in sevenths / thirds / halves, several samples per
+workgroup with a ragged last range.
 
 On inputs where no ReLU can flip (see test_gpu_bf16_backward.py) what is left is fp32 rounding: a gradient element is a sum of
 up to 400 B products whose accumulator chain is at most 5,000 additions long; their roundings (2^-24 of the running sum) add like
@@ -21,7 +22,7 @@ TOL = 1e-4
 REWARDS = np.array([-30.0, -2.0, 2.0, 30.0], dtype=np.float32)
 
 
-@pytest.mark.parametrize("B,split,double_dqn", [(1, True, 0), (2, False, 1), (31, True, 1), (33, True, 0), (52, False, 0), (65, True, 1), (131, True, 0), (257, False, 1)])
+@pytest.mark.parametrize("B,split,double_dqn", [(1, True, 0), (2, False, 1), (18, True, 0), (31, True, 1), (33, True, 0), (42, False, 0), (64, True, 0), (65, True, 1), (131, True, 0), (257, False, 1)])
 def test_f32_train_step_max_norm_no_relu_flips(B, split, double_dqn):
     A, seed, lr = 6, 5200 + B, 2.5e-5
     cfg = make_cfg(A, max_batch=B, max_envs=8, precision=P.DQN_PRECISION_FP32, double_dqn=double_dqn, seed=seed)
@@ -44,8 +45,9 @@ def test_f32_train_step_max_norm_no_relu_flips(B, split, double_dqn):
         P.dqn_train_step(ctx, dev(s), dev(a), dev(r), dev(s2), dev(d), B, loss)
         torch.cuda.synchronize()
         wloss, q_sa, _ = orc.train_step(s, a, r, s2, d)
-        q_on, _, _ = P.dqn_get_train_q(ctx, B, A, bool(double_dqn))
+        q_on, q_nt, _ = P.dqn_get_train_q(ctx, B, A, bool(double_dqn))
         assert rel_err(q_on, q_sa) <= TOL
+        assert rel_err(q_nt, odqn.forward(orc.desc, theta_t.astype(np.float64), odqn.scale_states(s2))[0]) <= TOL
         assert abs(float(loss.item()) - wloss) <= TOL * abs(wloss)
         g = P.dqn_get_params(ctx, P.DQN_PARAMS_GRAD)
         th = P.dqn_get_params(ctx, P.DQN_PARAMS_ONLINE)
