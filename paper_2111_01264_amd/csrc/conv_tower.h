@@ -50,6 +50,19 @@ __host__ __device__ inline size_t tower_frag_index(int o, int k, int K)
     return ((static_cast<size_t>(o >> 5) * (K >> 4) + (k >> 4)) * 64 + (((k >> 3) & 1) << 5) + (o & 31)) * 8 + (k & 7);
 }
 
+// The same for fp32 operands.  16x16x4 instruction (conv layers): 1 KB rows of 16 channels x 16 k, four consecutive k per lane
+// (lane = 16 * ((k % 16) / 4) + o % 16).  32x32x2 (fc layers): two 1 KB halves per 32 rows x 16 k, lanes as above, the lane's
+// k 0..3 in the first half and 4..7 in the second, so that each half is one contiguous load.
+__host__ __device__ inline size_t frag16_index(int o, int k, int K)
+{
+    return (static_cast<size_t>(o >> 4) * (K >> 4) + (k >> 4)) * 256 + ((((k >> 2) & 3) << 4) + (o & 15)) * 4 + (k & 3);
+}
+template <typename T> __host__ __device__ inline size_t frag_index(int o, int k, int K)
+{
+    if (sizeof(T) == 2) return tower_frag_index(o, k, K);
+    return (static_cast<size_t>(o >> 5) * (K >> 4) + (k >> 4)) * 512 + ((k >> 2) & 1) * 256 + ((((k >> 3) & 1) << 5) + (o & 31)) * 4 + (k & 3);
+}
+
 // Eight bytes -> eight fp16 subnormals (value = byte * 2^-24).  v_perm_b32 picks result bytes out of
 // {src0, src1}: selector 0..3 = byte of src1, 0x0c = constant zero.
 __device__ inline f16x8 bytes_as_f16_subnormals(uint32_t lo, uint32_t hi)

@@ -8,15 +8,17 @@
 //     16-byte access) for four instructions.  Sixteen-pixel tiles waste less of 81 and 49 pixels than 32-pixel ones cut per
 //     k-quarter, and a wavefront (channel tile w % 4, half w / 4 of the pixel tiles) sums all of K by itself: no exchange between
 //     wavefronts, three barriers per item.
-//   * weights are not resident: 16 rows x 64 bytes of the row-major matrix are one load instruction (whole 64-byte pieces), which
-//     feeds 128 matrix cycles per pixel tile; they stream from L2 through a ring of registers whose first entries are requested
-//     a layer ahead.
+//   * weights are not resident: one 1 KB row of the copy in fragment order (frag16_index: 16 channels x 16 k) is one load
+//     instruction and feeds 128 matrix cycles per pixel tile; they stream from L2 through a ring of registers whose first entries
+//     are requested a layer ahead.  (Read from the row-major matrix, the sixteen 64-byte pieces of a load lie 2 KB apart, in one
+//     channel of the L2.)
 //   * conv1 multiplies pixel BYTES, which are exact in bf16, by weights that are split into three bf16 parts whose sum is the
 //     fp32 weight exactly (8 + 8 + 8 significand bits): all products are exact, the sum is accumulated in fp32 as before, and
 //     three bf16 instructions (96 cycles) replace eight fp32 ones (512 cycles).  The split is made while the weights are staged.
 //
 // One launch per layer (weights or operands re-read from cache by every wavefront) took 10 + 12 + 12 us for a minibatch of 32,
-// 43 + 46 + 55 us for 256, 5 + 12 + 12 us plus two gaps for a round of one to eight samplers; this launch takes FILL_IN.
+// 43 + 46 + 55 us for 256, 5 + 12 + 12 us plus two gaps for a round of one to eight samplers; this launch takes
+// 19, 61 and 13 us (rocprofv3; whole samples keep the matrix core busy 77 % of the time, at about 2.15 GHz).
 #pragma once
 #include "conv_tower.h"
 #include "wgrad_conv.h"
@@ -31,8 +33,8 @@ struct TowerF32Args {
     int tower_blocks;              // workgroups [0, tower_blocks) run the tower, the next push.L ones the append
     const uint8_t* x[kMaxGroups];  // [n][4][84][84], 16-byte aligned
     const float* w1[kMaxGroups];   // [32][256]
-    const float* w2[kMaxGroups];   // [64][512]
-    const float* w3[kMaxGroups];   // [64][576]
+    const float* w2[kMaxGroups];   // [64][512], fragment order
+    const float* w3[kMaxGroups];   // [64][576], fragment order
     const float* b1[kMaxGroups];
     const float* b2[kMaxGroups];
     const float* b3[kMaxGroups];
@@ -47,11 +49,27 @@ constexpr int kTfW1Plane = 32 * 256;                   // one bf16 part of conv1
 constexpr size_t kTowerF32Smem = kTowerXBytes + 3 * kTfW1Plane * 2 + 400 * kTfP1 * 4 + 81 * kTfP2 * 4 + kTowerThreads * 4;
 static_assert(kTowerF32Smem <= 160 * 1024, "one workgroup per compute unit");
 
+// The value, computed no earlier than here: addresses that depend on a lane's pixel are the same for every item, and the compiler
+// otherwise computes those of all stages in front of the item loop and keeps them in registers throughout.
+__device__ inline int here(int v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Element `lane` of the 1 KB row at p (wavefront-uniform), as a scalar base plus a lane offset.  Left alone, the compiler adds the
+// lane's part to the base once and keeps a 64-bit vector address for every row of an unrolled stream.
+__device__ inline tf_f32x4 load_row(const float* p, unsigned lane)
+{
+    asm volatile("" : "+s"(p));
+    return reinterpret_cast<const tf_f32x4*>(p)[lane];
+}
+
 // acc[t] += (16 weight rows) x (16 pixels of tile t) over filter rows 0 .. ROWS - 1 with STEPS k-steps of sixteen each; `base`
-// points at this lane's pixel (its window's top-left corner, this lane's four channels), `w` at its weight row, `ring` holds the
-// weights of the first D steps.  k-step s of a filter row: tap s / CPT, channels 16 * (s % CPT) ..
+// points at this lane's pixel (its window's top-left corner, this lane's four channels), `w` at the channel tile's weights, `ring`
+// holds this lane's share of the first D steps.  k-step s of a filter row: tap s / CPT, channels 16 * (s % CPT) ..
 template <int NT, int ROWS, int STEPS, int CPT, int ROW_PITCH, int PITCH, int D>
-__device__ inline void tower_f32_rows(tf_f32x4 (&acc)[NT], const float* (&base)[NT], const float* w, tf_f32x4 (&ring)[D])
+__device__ inline void tower_f32_rows(tf_f32x4 (&acc)[NT], const float* (&base)[NT], const float* w, unsigned lane, tf_f32x4 (&ring)[D])
 {
     static_assert(STEPS % D == 0 || D % STEPS == 0, "the ring slot of a step is the same in every filter row");
     static_assert(STEPS % D == 0 && STEPS % 2 == 0, "ring and double buffer start every filter row at slot 0");
@@ -60,12 +78,12 @@ __device__ inline void tower_f32_rows(tf_f32x4 (&acc)[NT], const float* (&base)[
     for (int t = 0; t < NT; ++t) px[0][t] = *reinterpret_cast<const tf_f32x4*>(base[t]);
     for (int p = 0; p < ROWS; ++p) {
         // past the last row the requests repeat the row's own first steps (never used, never skipped)
-        const float* wn = p + 1 < ROWS ? w + STEPS * 16 : w;
+        const float* wn = p + 1 < ROWS ? w + STEPS * 256 : w;
         const int down = p + 1 < ROWS ? ROW_PITCH : 0;
 #pragma unroll
         for (int s = 0; s < STEPS; ++s) {
             const tf_f32x4 wv = ring[s % D];
-            ring[s % D] = *reinterpret_cast<const tf_f32x4*>(s + D < STEPS ? w + (s + D) * 16 : wn + (s + D - STEPS) * 16);
+            ring[s % D] = load_row(s + D < STEPS ? w + (s + D) * 256 : wn + (s + D - STEPS) * 256, lane);
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 px[(s + 1) & 1][t] = *reinterpret_cast<const tf_f32x4*>(s + 1 < STEPS ? base[t] + ((s + 1) / CPT) * PITCH + ((s + 1) % CPT) * 16 : base[t] + down);
@@ -79,6 +97,36 @@ __device__ inline void tower_f32_rows(tf_f32x4 (&acc)[NT], const float* (&base)[
 #pragma unroll
         for (int t = 0; t < NT; ++t) base[t] += down;
     }
+}
+
+// The same sum for a workgroup that runs one item and ends: its weights come from memory nobody has touched yet, so what counts is
+// how many are in flight.  The k-steps of both layers are one stream of weight vectors with a ring of kTfStream entries (step S of
+// the stream sits in slot S % kTfStream): the first layer finds its weights requested, and requests the next one's as it goes.
+// 24 entries are 96 registers; 32 spill in the thirds.  (Rings of 8 and 6 as above: 15.5 / 21.6 us for sevenths / thirds.)
+// S0: stream position of the layer's first step, TOTAL: length of the stream; KS_ROW: k-steps per filter row.
+constexpr int kTfStream = 24;
+template <int NT, int S0, int STEPS, int KS_ROW, int CPT, int ROW_PITCH, int PITCH, int TOTAL, class Weights>
+__device__ inline void tower_f32_stream(tf_f32x4 (&acc)[NT], const float* const (&base)[NT], tf_f32x4 (&ring)[kTfStream], Weights& weights)
+{
+    tf_f32x4 px[2][NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) px[0][t] = *reinterpret_cast<const tf_f32x4*>(base[t]);
+    auto step = [&](auto s_) {
+        constexpr int s = decltype(s_)::value, slot = (S0 + s) % kTfStream, n = s + 1;
+        const tf_f32x4 wv = ring[slot];
+        if constexpr (S0 + s + kTfStream < TOTAL) ring[slot] = weights(S0 + s + kTfStream);
+        if constexpr (n < STEPS) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                px[n & 1][t] = *reinterpret_cast<const tf_f32x4*>(base[t] + (n / KS_ROW) * ROW_PITCH + (n % KS_ROW / CPT) * PITCH + (n % CPT) * 16);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], px[s & 1][t][e], acc[t], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    static_for<0, STEPS>(step);
 }
 
 // PARTS: a workgroup runs a whole sample, or one half / third / seventh of its output rows with the rows of conv2 and conv1 these
@@ -128,7 +176,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
     fetch_state(g, b);
 
     const int lp = lane & 31, kg = lane >> 5;        // conv1: pixel / row of a 32x32 tile, k-half
-    const int lq = lane & 15, kq = lane >> 4;        // conv2, conv3: pixel / row of a 16x16 tile, k-quarter
+    const int kq = lane >> 4;                        // conv2, conv3: k-quarter (and lane & 15: pixel / row of a 16x16 tile)
     const int ct = wave & 3, ph = wave >> 2;         // channel tile; pixel tiles ph, ph + 2, ...
     constexpr int D2 = 8, D3 = 6;
     int cur_g = kMaxGroups;   // no group (and not -1: the part variants then indexed the biases with 0 whatever g was -- a compiler error, seen in its output)
@@ -163,11 +211,14 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
             uint4* d = reinterpret_cast<uint4*>(sX);
             d[tid] = xv0; d[tid + 512] = xv1; d[tid + 1024] = xv2; d[last_vec] = xv3;   // clamped lanes rewrite the last vector with itself
         }
-        const float* w2p = (g == 0 ? w2_0_ : a.w2[g]) + (ct * 16 + lq) * 512 + kq * 4;
-        const float* w3p = a.w3[g] + (ct * 16 + lq) * 576 + kq * 4;
-        tf_f32x4 ring2[D2], ring3[D3];
+        const float* w2p = (g == 0 ? w2_0_ : a.w2[g]) + ct * 32 * 256;
+        const float* w3p = a.w3[g] + ct * 36 * 256;
+        tf_f32x4 ring2[D2], ring3[D3], stream[kTfStream];
+        auto weights = [&](int S) { return load_row(S < 32 ? w2p + S * 256 : w3p + (S - 32) * 256, lane); };
+        if constexpr (PARTS == 1) {
 #pragma unroll
-        for (int u = 0; u < D2; ++u) ring2[u] = *reinterpret_cast<const tf_f32x4*>(w2p + u * 16);
+            for (int u = 0; u < D2; ++u) ring2[u] = weights(u);
+        }
         if (it + 1 < last) { if (b + 1 < n_) fetch_state(g, b + 1); else fetch_state(g + 1, 0); }
         __syncthreads();
 
@@ -202,6 +253,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
 #pragma unroll
                 for (int k = 0; k < 16; ++k) {
                     if (k + 1 < 16) fetch((k + 1) & 1, k + 1);
+                    if constexpr (PARTS > 1) { stream[2 * k] = weights(2 * k); stream[2 * k + 1] = weights(2 * k + 1); }   // two requests per k-step: all at once they would stand in front of conv1
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         const bf16x8 x = bf16x8_from_bytes(px[k & 1][t].x, px[k & 1][t].y);
@@ -227,10 +279,17 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                     }
                 }
             };
-            if (T1 > 8 && wave < T1 - 8) run(std::integral_constant<int, 2>{}); else if (wave < T1) run(std::integral_constant<int, 1>{});
-        }
+            if (T1 > 8 && wave < T1 - 8) run(std::integral_constant<int, 2>{});
+            else if (T1 >= 8 || wave < T1) run(std::integral_constant<int, 1>{});
+            else if constexpr (PARTS > 1) {   // no tile of conv1 for this wavefront
 #pragma unroll
-        for (int u = 0; u < D3; ++u) ring3[u] = *reinterpret_cast<const tf_f32x4*>(w3p + u * 16);
+                for (int u = 0; u < kTfStream; ++u) stream[u] = weights(u);
+            }
+        }
+        if constexpr (PARTS == 1) {
+#pragma unroll
+            for (int u = 0; u < D3; ++u) ring3[u] = weights(32 + u);
+        }
         __syncthreads();
 
         // ---- conv2: k = (p, q, c), eight k-steps per filter row -----------------------------------------------------
@@ -242,13 +301,15 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                 constexpr int NT = decltype(nt_)::value;
                 const float* base[NT];
                 tf_f32x4 acc[NT];
+                const int lq = here(lane & 15);
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const int lpx = (ph + 2 * t) * 16 + lq, pc = r3_lo * 9 + (lpx < n2 ? lpx : n2 - 1);
                     base[t] = sA1 + (2 * (pc / 9) * 20 + 2 * (pc % 9)) * kTfP1 + kq * 4;
                     acc[t] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
                 }
-                tower_f32_rows<NT, 4, 8, 2, 20 * kTfP1, kTfP1, D2>(acc, base, w2p, ring2);
+                if constexpr (PARTS == 1) tower_f32_rows<NT, 4, 8, 2, 20 * kTfP1, kTfP1, D2>(acc, base, w2p, lane, ring2);
+                else tower_f32_stream<NT, 0, 32, 8, 2, 20 * kTfP1, kTfP1, 68>(acc, base, stream, weights);
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const int lpx = (ph + 2 * t) * 16 + lq, px = r3_lo * 9 + lpx;
@@ -272,13 +333,15 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                 constexpr int NT = decltype(nt_)::value;
                 const float* base[NT];
                 tf_f32x4 acc[NT];
+                const int lq = here(lane & 15);
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const int lpx = (ph + 2 * t) * 16 + lq, pc = r3_lo * 7 + (lpx < n3 ? lpx : n3 - 1);
                     base[t] = sA2 + ((pc / 7) * 9 + pc % 7) * kTfP2 + kq * 4;
                     acc[t] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
                 }
-                tower_f32_rows<NT, 3, 12, 4, 9 * kTfP2, kTfP2, D3>(acc, base, w3p, ring3);
+                if constexpr (PARTS == 1) tower_f32_rows<NT, 3, 12, 4, 9 * kTfP2, kTfP2, D3>(acc, base, w3p, lane, ring3);
+                else tower_f32_stream<NT, 32, 36, 12, 4, 9 * kTfP2, kTfP2, 68>(acc, base, stream, weights);
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const int lpx = (ph + 2 * t) * 16 + lq, px = r3_lo * 7 + lpx;
@@ -291,6 +354,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
             if (NA == NB || ph == 0) run(std::integral_constant<int, NA>{});
             else if constexpr (NB > 0) run(std::integral_constant<int, NB>{});
         }
+        if constexpr (PARTS > 1) break;
         // no barrier: conv3 reads act2 only, and the next item writes act2 behind two barriers of its own; state and act1 are free
     }
 }

@@ -8,9 +8,9 @@
 // consecutive k per lane).  MFMA A = weights (row i = output feature), B = samples (column j = b),
 // so lane l ends up with sample (l % 32) and four consecutive features per register quad.
 //
-// 16-bit weights arrive in MFMA fragment order (tower_frag_index over [feature][k]): the operand of k-step ks of
-// feature tile nt is the contiguous 1 KB row (nt * K/16 + ks); row-major weights (fp32 mode) are read as 32 separate
-// 32-byte pieces per wavefront load, which is bound by the address unit (a full pass per cache line).
+// Weights arrive in MFMA fragment order (frag_index over [feature][k]): the operand of k-step ks of feature tile nt is
+// the contiguous 1 KB (fp32: 2 KB) row (nt * K/16 + ks); row-major weights would be 32 separate 32-byte pieces per
+// wavefront load, which is bound by the address unit (a full pass per cache line).
 //
 // K may be split over blockIdx.z: each slice then writes fp32 partial sums [slice][b][n], which the
 // consumer kernel adds in slice order while it loads them (no separate reduction pass).
@@ -34,11 +34,16 @@ template <typename T> struct FcAsArgs {
 
 constexpr int kFcPartial = 0, kFcReluMask = 1;
 
-// Pointer to this lane's 8 weights of k-step ks (16 k each) of the 32-feature tile nt; w is [N][K].
-template <typename T> __device__ inline const T* fc_weight_fragment(const T* w, int nt, int ks, int K, int lane)
+// This lane's 8 weights of k-step ks (16 k each) of the 32-feature tile nt; w is [N][K] in fragment order.
+template <typename T> __device__ inline typename Vec8<T>::type fc_weights(const T* w, int nt, int ks, int K, int lane)
 {
-    if constexpr (sizeof(T) == 2) return w + (static_cast<size_t>(nt * (K >> 4) + ks) * 64 + lane) * 8;
-    else return w + static_cast<size_t>(nt * 32 + (lane & 31)) * K + ks * 16 + (lane >> 5) * 8;
+    const T* row = w + static_cast<size_t>(nt * (K >> 4) + ks) * 512;
+    if constexpr (sizeof(T) == 2) return *reinterpret_cast<const typename Vec8<T>::type*>(row + lane * 8);
+    else {
+        typedef float f32x4 __attribute__((ext_vector_type(4)));
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(row + lane * 4), hi = *reinterpret_cast<const f32x4*>(row + 256 + lane * 4);
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
 }
 
 template <typename T, int EPI, int TB, int WAVES>
@@ -64,7 +69,7 @@ __global__ __launch_bounds__(WAVES * 64) void fc_as_kernel(FcAsArgs<T> a)
     constexpr int D = sizeof(T) == 2 ? 16 : 8;   // 16 KB per wavefront in flight: a step waits for the fragment requested D steps earlier, so the stream runs at D fragments per memory round trip
     const int steps = klen >> 4;
     auto wload = [&](int st) {
-        return *reinterpret_cast<const V8*>(fc_weight_fragment<T>(a.w[g], ntile, ks0 + (st < steps ? st : steps - 1), a.ldw, lane));
+        return fc_weights<T>(a.w[g], ntile, ks0 + (st < steps ? st : steps - 1), a.ldw, lane);
     };
     V8 ring[D];
 #pragma unroll
@@ -198,7 +203,7 @@ __global__ __launch_bounds__(256) void fc_sk_kernel(const T* x0_, const T* x1_, 
     V8 wf[KPW], xf[KPW];
 #pragma unroll
     for (int s = 0; s < KPW; ++s) {
-        wf[s] = *reinterpret_cast<const V8*>(fc_weight_fragment<T>(wg, ntile, ks0 + s, ldw_, lane));
+        wf[s] = fc_weights<T>(wg, ntile, ks0 + s, ldw_, lane);
         xf[s] = *reinterpret_cast<const V8*>(xp + s * 16);
     }
     // thread t finishes accumulator slots (v, l) = (4*(t/64) + e, t%64), e = 0..3: one quad of features of one sample.

@@ -53,18 +53,6 @@ template <typename T> __device__ inline typename Vec8<T>::type vec8_keep(const t
 template <typename T> __device__ inline T from_float(float x) { return static_cast<T>(x); }
 template <typename T> __device__ inline float to_float(T x) { return static_cast<float>(x); }
 
-// Eight uint8 pixels (already in two 32-bit words) -> eight operand elements; exact in bf16.
-template <typename T> __device__ inline typename Vec8<T>::type vec8_from_u8(uint32_t lo, uint32_t hi)
-{
-    typename Vec8<T>::type v;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        v[i] = static_cast<T>(static_cast<float>((lo >> (8 * i)) & 0xFFu));
-        v[4 + i] = static_cast<T>(static_cast<float>((hi >> (8 * i)) & 0xFFu));
-    }
-    return v;
-}
-
 __device__ inline void mma_32x32x16(f32x16& acc, const bf16x8& a, const bf16x8& b)
 {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);

@@ -31,9 +31,9 @@ inline Offsets make_offsets(int A)
 // Backward operand copies ("transposed shadows"), one buffer of T:
 //   conv2: [4 parity classes][32 c][(p2, q2, o) = 256]   conv3: [64 c][(p, q, o) = 576]
 //   fc1:   [3136 f][512 o]
-// In reduced precision all three are kept in MFMA fragment order (tower_frag_index over [row][k]: conv per
-// (class,) [c][k], fc1 over [f][o]), the order their consumers load them in: one operand of a 32x32x16 MFMA is then
-// one contiguous 1 KB row instead of 32 separate cache lines; fp32 keeps them row-major.
+// All three are kept in MFMA fragment order (over [row][k]: conv per (class,) [c][k], fc1 over [f][o]), the order their
+// consumers load them in: one operand of a matrix instruction is then one contiguous 1 KB row instead of 16 or 32 separate
+// cache lines (in full precision with the conv taps reversed, see conv_tower_bwd_f32.h).
 constexpr size_t kBshW2 = 0, kBshW3 = 4 * 32 * 256, kBshWf1 = kBshW3 + 64 * 576;
 constexpr size_t kBshTotal = kBshWf1 + static_cast<size_t>(3136) * 512;
 
@@ -41,37 +41,37 @@ constexpr size_t kBshTotal = kBshWf1 + static_cast<size_t>(3136) * 512;
 template <typename T> __host__ __device__ inline size_t bsh_index_w2(int r)
 {
     const int c = r % 32, q = (r / 32) % 4, p = (r / 128) % 4, oc = r / 512;
-    const int cls = (p % 2) * 2 + (q % 2), k = ((p / 2) * 2 + (q / 2)) * 64 + oc;
-    return kBshW2 + static_cast<size_t>(cls) * 32 * 256 + (sizeof(T) == 2 ? tower_frag_index(c, k, 256) : static_cast<size_t>(c) * 256 + k);
+    const int cls = (p % 2) * 2 + (q % 2), tap = (p / 2) * 2 + (q / 2);
+    return kBshW2 + static_cast<size_t>(cls) * 32 * 256 + (sizeof(T) == 2 ? tower_frag_index(c, tap * 64 + oc, 256) : frag16_index(c, (3 - tap) * 64 + oc, 256));
 }
 template <typename T> __host__ __device__ inline size_t bsh_index_w3(int r)
 {
     const int c = r % 64, q = (r / 64) % 3, p = (r / 192) % 3, oc = r / 576;
-    const int k = (p * 3 + q) * 64 + oc;
-    return kBshW3 + (sizeof(T) == 2 ? tower_frag_index(c, k, 576) : static_cast<size_t>(c) * 576 + k);
+    const int tap = p * 3 + q;
+    return kBshW3 + (sizeof(T) == 2 ? tower_frag_index(c, tap * 64 + oc, 576) : frag16_index(c, (8 - tap) * 64 + oc, 576));
 }
 
 template <typename T> __host__ __device__ inline size_t bsh_index_wf1(int o, int f)
 {
-    return kBshWf1 + (sizeof(T) == 2 ? tower_frag_index(f, o, 512) : static_cast<size_t>(f) * 512 + o);
+    return kBshWf1 + frag_index<T>(f, o, 512);
 }
 
-// Where blob element e lives in the 16-bit forward copy: identical, except that the conv weights and fc1's are
-// kept in MFMA fragment order (of the fused conv kernel / the fc kernels).  conv1's weights are stored there as fp16 (that
+// Where blob element e lives in the forward copy: identical, except that the weights of conv2, conv3 and fc1 (bf16 mode: conv1
+// too) are kept in MFMA fragment order of the kernels that load them.  bf16 mode stores conv1's weights as fp16 (that
 // kernel runs conv1 on the f16 matrix instruction), everything else as bf16: shadow_store converts.
-__host__ __device__ inline size_t shadow_index(const Offsets& off, size_t e)
+template <typename T> __host__ __device__ inline size_t shadow_index(const Offsets& off, size_t e)
 {
-    if (e >= off.w1 && e < off.b1) { const int r = static_cast<int>(e - off.w1); return off.w1 + tower_frag_index(r / 256, r % 256, 256); }
-    if (e >= off.w2 && e < off.b2) { const int r = static_cast<int>(e - off.w2); return off.w2 + tower_frag_index(r / 512, r % 512, 512); }
-    if (e >= off.w3 && e < off.b3) { const int r = static_cast<int>(e - off.w3); return off.w3 + tower_frag_index(r / 576, r % 576, 576); }
-    if (e >= off.wf1 && e < off.bf1) { const int r = static_cast<int>(e - off.wf1); return off.wf1 + tower_frag_index(r / 3136, r % 3136, 3136); }
+    if (sizeof(T) == 2 && e >= off.w1 && e < off.b1) { const int r = static_cast<int>(e - off.w1); return off.w1 + tower_frag_index(r / 256, r % 256, 256); }
+    if (e >= off.w2 && e < off.b2) { const int r = static_cast<int>(e - off.w2); return off.w2 + (sizeof(T) == 2 ? tower_frag_index(r / 512, r % 512, 512) : frag16_index(r / 512, r % 512, 512)); }
+    if (e >= off.w3 && e < off.b3) { const int r = static_cast<int>(e - off.w3); return off.w3 + (sizeof(T) == 2 ? tower_frag_index(r / 576, r % 576, 576) : frag16_index(r / 576, r % 576, 576)); }
+    if (e >= off.wf1 && e < off.bf1) { const int r = static_cast<int>(e - off.wf1); return off.wf1 + frag_index<T>(r / 3136, r % 3136, 3136); }
     return e;
 }
 
 template <typename T> __device__ inline void shadow_store(T* sh, const Offsets& off, size_t e, float v)
 {
-    if (e >= off.w1 && e < off.b1) reinterpret_cast<_Float16*>(sh)[shadow_index(off, e)] = static_cast<_Float16>(v);
-    else sh[shadow_index(off, e)] = from_float<T>(v);
+    if (sizeof(T) == 2 && e >= off.w1 && e < off.b1) reinterpret_cast<_Float16*>(sh)[shadow_index<T>(off, e)] = static_cast<_Float16>(v);
+    else sh[shadow_index<T>(off, e)] = from_float<T>(v);
 }
 
 // ---- network head, forward: finish fc1, fc2 on the matrix cores, then action selection (act step)
@@ -523,7 +523,7 @@ struct RmsArgs {
     const float* grad;
     float* v;
     float* m;
-    void* sh;        // forward operand copy (bf16 mode) or null
+    void* sh;        // forward operand copy
     void* bsh;       // backward operand copies
     Offsets off;
     float lr, alpha, eps;
@@ -561,22 +561,22 @@ __device__ inline void rms_update(const RmsArgs& a, float& th, float g, float& v
     th -= a.lr * g / (sqrtf(var) + a.eps);
 }
 
-template <typename T, bool SHADOW>
+template <typename T>
 __device__ inline void publish(const RmsArgs& a, size_t e, float th)
 {
-    if (SHADOW) shadow_store<T>(static_cast<T*>(a.sh), a.off, e, th);
+    shadow_store<T>(static_cast<T*>(a.sh), a.off, e, th);
     if (e >= a.off.w2 && e < a.off.b2) static_cast<T*>(a.bsh)[bsh_index_w2<T>(static_cast<int>(e - a.off.w2))] = from_float<T>(th);
     else if (e >= a.off.w3 && e < a.off.b3) static_cast<T*>(a.bsh)[bsh_index_w3<T>(static_cast<int>(e - a.off.w3))] = from_float<T>(th);
 }
 
 // Centered RMSProp (Appendix B) fused with the refresh of the operand copies.  The conv weights come first
 // (their gradient is finished here from split-K slices), elementwise blocks cover the rest except fc1.w and the
-// hidden-layer biases; fc1.w is walked in 32 x 64 tiles whose two 16-bit copies (forward [o][f] and backward
-// [f][o], both in fragment order; fp32: the row-major [f][o] copy) are written in whole 512-byte pieces via LDS.
+// hidden-layer biases; fc1.w is walked in 32 x 64 tiles whose two operand copies (forward [o][f] and backward
+// [f][o], both in fragment order) are written in whole 512-byte pieces via LDS.
 // The leading scalar parameters repeat RmsArgs::theta, grad, v, m, flat_blocks, fc1_tiles and off.wf1 (what the fc1.w
 // tiles, 95 % of the parameters, need before their first load): the kernel arguments' first 14 dwords are preloaded into
 // scalar registers when a wavefront starts (see conv_tower_kernel).
-template <typename T, bool SHADOW>
+template <typename T>
 __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float* grad_, float* v_, float* m_, int flat_blocks_,
                                                       int fc1_tiles_, size_t wf1_, RmsArgs a)
 {
@@ -632,10 +632,10 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
         *reinterpret_cast<float4*>(theta_ + e) = th;
         *reinterpret_cast<float4*>(v_ + e) = vv;
         if (a.centered) *reinterpret_cast<float4*>(m_ + e) = mm;
-        publish<T, SHADOW>(a, e, th.x);
-        publish<T, SHADOW>(a, e + 1, th.y);
-        publish<T, SHADOW>(a, e + 2, th.z);
-        publish<T, SHADOW>(a, e + 3, th.w);
+        publish<T>(a, e, th.x);
+        publish<T>(a, e + 1, th.y);
+        publish<T>(a, e + 2, th.z);
+        publish<T>(a, e + 3, th.w);
         return;
     }
     const int block = static_cast<int>(blockIdx.x) - kRmsConvBlocks;
@@ -659,10 +659,10 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
             *reinterpret_cast<float4*>(theta_ + e) = th;
             *reinterpret_cast<float4*>(v_ + e) = vv;
             if (a.centered) *reinterpret_cast<float4*>(m_ + e) = mm;
-            publish<T, SHADOW>(a, e, th.x);
-            publish<T, SHADOW>(a, e + 1, th.y);
-            publish<T, SHADOW>(a, e + 2, th.z);
-            publish<T, SHADOW>(a, e + 3, th.w);
+            publish<T>(a, e, th.x);
+            publish<T>(a, e + 1, th.y);
+            publish<T>(a, e + 2, th.z);
+            publish<T>(a, e + 3, th.w);
         } else if (i < n4 + (n_flat - 4 * n4)) {
             const size_t e = to_blob(4 * n4 + (i - n4));
             float th = theta_[e], vv = v_[e], mm = m_[e];
@@ -670,7 +670,7 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
             theta_[e] = th;
             v_[e] = vv;
             if (a.centered) m_[e] = mm;
-            publish<T, SHADOW>(a, e, th);
+            publish<T>(a, e, th);
         }
         return;
     }
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
         theta_[e] = th;
         v_[e] = vv;
         if (a.centered) m_[e] = mm;
-        if (SHADOW) static_cast<T*>(a.sh)[e] = from_float<T>(th);
+        static_cast<T*>(a.sh)[e] = from_float<T>(th);
         return;
     }
     // fc1.w tile: rows o0 .. o0+31, columns f0 .. f0+63
@@ -740,7 +740,7 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
             const V8 val = *reinterpret_cast<const V8*>(&tile[ft * 32 + rr][k8]);
             *reinterpret_cast<V8*>(static_cast<T*>(a.bsh) + bsh_index_wf1<T>(o0 + k8, f0 + ft * 32 + rr)) = val;
         }
-        if (SHADOW) {   // forward copy, rows = o, k = f
+        {   // forward copy, rows = o, k = f
             const int k8 = piece * 8;
             V8 val;
 #pragma unroll
@@ -748,21 +748,27 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
             *reinterpret_cast<V8*>(static_cast<T*>(a.sh) + wf1_ + tower_frag_index(o0 + rr, f0 + k8, 3136)) = val;
         }
     } else {
-        const int f = tid / 4, part = (tid % 4) * 8;
-        const V8 val = *reinterpret_cast<const V8*>(&tile[f][part]);
-        *reinterpret_cast<V8*>(static_cast<T*>(a.bsh) + kBshWf1 + static_cast<size_t>(f0 + f) * 512 + o0 + part) = val;
+        // the same for fp32: sixteen (32 rows x 4 k) pieces of 512 contiguous bytes per copy
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int piece = (tid >> 5) + 8 * u, rr = tid & 31;
+            const int ft = piece >> 3, ob = (piece & 7) * 4, fb = piece * 4;
+            *reinterpret_cast<float4*>(static_cast<T*>(a.bsh) + bsh_index_wf1<T>(o0 + ob, f0 + ft * 32 + rr)) = *reinterpret_cast<const float4*>(&tile[ft * 32 + rr][ob]);
+            *reinterpret_cast<float4*>(static_cast<T*>(a.sh) + wf1_ + frag_index<T>(o0 + rr, f0 + fb, 3136)) =
+                make_float4(tile[fb][rr], tile[fb + 1][rr], tile[fb + 2][rr], tile[fb + 3][rr]);
+        }
     }
 }
 
 // Builds every operand copy of theta from the fp32 master (after dqn_set_params).
-template <typename T, bool SHADOW>
+template <typename T>
 __global__ __launch_bounds__(256) void build_copies_kernel(const float* __restrict__ theta, T* __restrict__ sh,
                                                            T* __restrict__ bsh, Offsets off)
 {
     const size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
     if (e >= off.total) return;
     const T val = from_float<T>(theta[e]);
-    if (SHADOW) shadow_store<T>(sh, off, e, theta[e]);
+    shadow_store<T>(sh, off, e, theta[e]);
     if (bsh) {
         if (e >= off.w2 && e < off.b2) bsh[bsh_index_w2<T>(static_cast<int>(e - off.w2))] = val;
         else if (e >= off.w3 && e < off.b3) bsh[bsh_index_w3<T>(static_cast<int>(e - off.w3))] = val;
@@ -773,15 +779,15 @@ __global__ __launch_bounds__(256) void build_copies_kernel(const float* __restri
     }
 }
 
-// theta^- <- theta: fp32 master (bitwise) and, if present, the forward operand copy.
-template <typename T, bool SHADOW>
+// theta^- <- theta: fp32 master (bitwise) and the forward operand copy.
+template <typename T>
 __global__ __launch_bounds__(256) void target_copy_kernel(const float* __restrict__ theta, float* __restrict__ theta_t,
                                                           const T* __restrict__ sh, T* __restrict__ sh_t, size_t n)
 {
     const size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
     if (i < n) {
         theta_t[i] = theta[i];
-        if (SHADOW) sh_t[i] = sh[i];
+        sh_t[i] = sh[i];
     }
 }
 

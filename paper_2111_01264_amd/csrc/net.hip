@@ -15,6 +15,7 @@
 #include "conv_tower.h"
 #include "conv_tower_bwd.h"
 #include "conv_tower_f32.h"
+#include "conv_tower_bwd_f32.h"
 #include "fc_as.h"
 #include "wgrad_all.h"
 #include "wgrad_f32.h"
@@ -29,13 +30,9 @@ enum KernelId {
 };
 static const char* const kKernelNames[K_COUNT] = {
     "none", "conv_tower", "(conv2_fwd)", "(conv3_fwd)", "fc1_fwd", "head_td", "(unused)", "(fc1_wgrad)",
-    "fc1_dgrad", "(conv3_wgrad)", "conv3_dgrad", "(conv2_wgrad)", "conv2_dgrad", "(conv1_wgrad)", "(small_grads)",
+    "fc1_dgrad", "(conv3_wgrad)", "(conv3_dgrad)", "(conv2_wgrad)", "(conv2_dgrad)", "(conv1_wgrad)", "(small_grads)",
     "rmsprop", "wgrad_all", "event_pair", "conv_tower_bwd"};
 constexpr size_t kProfPairs = 4096;
-
-// Layer geometries (Section 5: the Nature-DQN network).
-template <typename T> using Conv3DgradGeo = DgradGeo<T, 64, 9, 9, 64, 7, 7, 3, 1>;
-template <typename T> using Conv2DgradGeo = DgradGeo<T, 32, 20, 20, 64, 9, 9, 4, 2>;
 
 }  // namespace dqn
 
@@ -99,7 +96,7 @@ struct dqn_ctx {
     size_t esize;           // bytes per operand element
     hipStream_t act_stream, train_stream;
     float *theta = nullptr, *theta_t = nullptr, *v = nullptr, *m = nullptr, *grad = nullptr;
-    void *sh = nullptr, *sh_t = nullptr;   // forward operand copies; alias theta / theta_t in fp32 mode
+    void *sh = nullptr, *sh_t = nullptr;   // forward operand copies
     void* bsh = nullptr;                   // backward operand copies of theta
     Workspace train_ws, act_ws;
     void *dzh = nullptr, *dz3 = nullptr, *dz2 = nullptr, *dz1 = nullptr;
@@ -193,6 +190,9 @@ static hipError_t raise_lds_limits()
             {reinterpret_cast<const void*>(conv_tower_f32_kernel<2>), kTowerF32Smem},
             {reinterpret_cast<const void*>(conv_tower_f32_kernel<3>), kTowerF32Smem},
             {reinterpret_cast<const void*>(conv_tower_f32_kernel<7>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_bwd_f32_kernel<1>), kTowerBwdF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_bwd_f32_kernel<2>), kTowerBwdF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_bwd_f32_kernel<5>), kTowerBwdF32Smem},
             {reinterpret_cast<const void*>(wgrad_f32_kernel), kWgradF32Smem},
         };
         for (const auto& k : big)
@@ -383,7 +383,7 @@ static int act_impl(dqn_ctx* c, Workspace& ws, const uint8_t* states, int W, flo
     return DQN_OK;
 }
 
-template <typename T, bool SHADOW>
+template <typename T>
 static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const float* r, const uint8_t* s2,
                       const float* done, int B, float* loss_out, const GatherPlan* ride = nullptr, int32_t* ride_desc = nullptr,
                       const StateSource* src = nullptr)
@@ -469,22 +469,17 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
                          ta.act2, ta.act1, ta.dz2, ta.dz1);
         DQN_LAUNCH_CHECK();
     } else {
-        {   // conv3 data gradient through conv2's ReLU
-            ConvWsArgs<T, Conv3DgradGeo<T>> ca{};
-            ca.x[0] = dz3; ca.w[0] = bsh + kBshW3; ca.out[0] = dz2; ca.mask = act2;
-            ca.M = B * 81; ca.scale = 1.f;
-            const ProfPair pr = prof_pair(c, K_CONV3_DGRAD);
-            DQN_HIP((launch_conv_ws<T, Conv3DgradGeo<T>, kEpiReluMask>(st, ca, 1, pr.begin, pr.end)));
-        }
-        {   // conv2 data gradient through conv1's ReLU: one problem per stride-parity class
-            ConvWsArgs<T, Conv2DgradGeo<T>> ca{};
-            for (int g = 0; g < 4; ++g) {
-                ca.x[g] = dz2; ca.w[g] = bsh + kBshW2 + static_cast<size_t>(g) * 32 * 256; ca.out[g] = dz1;
-            }
-            ca.mask = act1; ca.M = B * 100; ca.scale = 1.f;
-            const ProfPair pr = prof_pair(c, K_CONV2_DGRAD);
-            DQN_HIP((launch_conv_ws<T, Conv2DgradGeo<T>, kEpiReluMask>(st, ca, 4, pr.begin, pr.end)));
-        }
+        TowerBwdF32Args ta{};
+        ta.dz3 = dz3; ta.act2 = act2; ta.act1 = act1; ta.w3d = bsh + kBshW3; ta.w2d = bsh + kBshW2;
+        ta.dz2 = dz2; ta.dz1 = dz1; ta.n = B;
+        DQN_HIP(raise_lds_limits());
+        const int parts = 5 * B <= c->num_cus ? 5 : (2 * B <= c->num_cus ? 2 : 1);
+        const int grid = parts > 1 ? parts * B : (B < c->num_cus ? B : c->num_cus);
+        ta.per = parts > 1 ? 1 : (B + grid - 1) / grid;
+        const ProfPair pr = prof_pair(c, K_TOWER_BWD);
+        auto kern = parts == 5 ? conv_tower_bwd_f32_kernel<5> : parts == 2 ? conv_tower_bwd_f32_kernel<2> : conv_tower_bwd_f32_kernel<1>;
+        launch_timed(kern, dim3(grid), dim3(kTowerThreads), kTowerBwdF32Smem, st, pr.begin, pr.end, ta.n, ta.per, ta.dz3, ta.w3d, ta.w2d, ta.act2, ta.act1, ta.dz2, ta.dz1);
+        DQN_LAUNCH_CHECK();
     }
 
     // ---- weight gradients and small reductions ------------------------------------------------------
@@ -517,7 +512,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
 
     RmsArgs ra;
     ra.theta = c->theta; ra.grad = c->grad; ra.v = c->v; ra.m = c->m;
-    ra.sh = SHADOW ? c->sh : nullptr; ra.bsh = c->bsh; ra.off = o;
+    ra.sh = c->sh; ra.bsh = c->bsh; ra.off = o;
     ra.lr = c->cfg.lr; ra.alpha = c->cfg.rms_alpha; ra.eps = c->cfg.rms_eps; ra.centered = c->cfg.centered;
     {
         const size_t n_flat = o.total - static_cast<size_t>(512) * 3136;
@@ -592,7 +587,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         const ProfPair pr = prof_pair(c, K_RMSPROP);
         for (int l = 0; l < 3; ++l) ra.wg_splits[l] = wg_splits[l];
         for (int l = 0; l < 4; ++l) { ra.bias_chunks[l] = bias_chunks[l]; ra.bias_first[l] = bias_first[l]; }
-        launch_timed(rmsprop_kernel<T, SHADOW>, dim3(kRmsConvBlocks + ra.flat_blocks + ra.fc1_tiles + kRmsBiasBlocks), dim3(256), 0, st, pr.begin, pr.end, ra.theta,
+        launch_timed(rmsprop_kernel<T>, dim3(kRmsConvBlocks + ra.flat_blocks + ra.fc1_tiles + kRmsBiasBlocks), dim3(256), 0, st, pr.begin, pr.end, ra.theta,
                      ra.grad, ra.v, ra.m, ra.flat_blocks, ra.fc1_tiles, ra.off.wf1, ra);
         DQN_LAUNCH_CHECK();
     }
@@ -690,14 +685,9 @@ int dqn_create(const dqn_config* cfg, void* act_stream, void* train_stream, dqn_
             DQN_HIP(hipMalloc((void**)p, (n + 8) * sizeof(float)));
             DQN_HIP(hipMemset(*p, 0, (n + 8) * sizeof(float)));
         }
-        if (cfg->precision == DQN_PRECISION_BF16) {
-            DQN_HIP(hipMalloc(&c->sh, (n + 8) * 2));
-            DQN_HIP(hipMalloc(&c->sh_t, (n + 8) * 2));
-            DQN_HIP(hipMemset(c->sh, 0, (n + 8) * 2));
-            DQN_HIP(hipMemset(c->sh_t, 0, (n + 8) * 2));
-        } else {
-            c->sh = c->theta;
-            c->sh_t = c->theta_t;
+        for (void** p : {&c->sh, &c->sh_t}) {
+            DQN_HIP(hipMalloc(p, (n + 8) * c->esize));
+            DQN_HIP(hipMemset(*p, 0, (n + 8) * c->esize));
         }
         int rc = alloc_ws(c->train_ws, cfg->max_batch, 3, c->A, c->esize);
         if (rc != DQN_OK) return rc;
@@ -745,8 +735,7 @@ int dqn_destroy(dqn_ctx* c)
     if (!c) return DQN_OK;
     (void)hipStreamSynchronize(c->act_stream);
     (void)hipStreamSynchronize(c->train_stream);
-    if (c->sh != c->theta) (void)hipFree(c->sh);
-    if (c->sh_t != c->theta_t) (void)hipFree(c->sh_t);
+    (void)hipFree(c->sh); (void)hipFree(c->sh_t);
     (void)hipFree(c->theta); (void)hipFree(c->theta_t); (void)hipFree(c->v); (void)hipFree(c->m); (void)hipFree(c->grad);
     free_ws(c->train_ws); free_ws(c->act_ws);
     (void)hipFree(c->dzh); (void)hipFree(c->dz3); (void)hipFree(c->dz2); (void)hipFree(c->dz1);
@@ -778,18 +767,13 @@ int dqn_set_params(dqn_ctx* c, int which, const float* host_src, size_t n)
     float* dst = blob_of(c, which);
     DQN_HIP(hipMemcpy(dst, dev.data(), n * sizeof(float), hipMemcpyHostToDevice));
     const unsigned blocks = static_cast<unsigned>((n + 255) / 256);
-    if (which == DQN_PARAMS_ONLINE) {
+    if (which == DQN_PARAMS_ONLINE || which == DQN_PARAMS_TARGET) {   // the network's operand copies (backward ones: theta only)
+        const bool online = which == DQN_PARAMS_ONLINE;
+        void *sh = online ? c->sh : c->sh_t, *bsh = online ? c->bsh : nullptr;
         if (c->cfg.precision == DQN_PRECISION_BF16)
-            hipLaunchKernelGGL((build_copies_kernel<bf16_t, true>), dim3(blocks), dim3(256), 0, c->train_stream, dst,
-                               static_cast<bf16_t*>(c->sh), static_cast<bf16_t*>(c->bsh), c->off);
+            hipLaunchKernelGGL(build_copies_kernel<bf16_t>, dim3(blocks), dim3(256), 0, c->train_stream, dst, static_cast<bf16_t*>(sh), static_cast<bf16_t*>(bsh), c->off);
         else
-            hipLaunchKernelGGL((build_copies_kernel<float, false>), dim3(blocks), dim3(256), 0, c->train_stream, dst,
-                               static_cast<float*>(nullptr), static_cast<float*>(c->bsh), c->off);
-        DQN_LAUNCH_CHECK();
-        DQN_HIP(hipStreamSynchronize(c->train_stream));
-    } else if (which == DQN_PARAMS_TARGET && c->cfg.precision == DQN_PRECISION_BF16) {
-        hipLaunchKernelGGL((build_copies_kernel<bf16_t, true>), dim3(blocks), dim3(256), 0, c->train_stream, dst,
-                           static_cast<bf16_t*>(c->sh_t), static_cast<bf16_t*>(nullptr), c->off);
+            hipLaunchKernelGGL(build_copies_kernel<float>, dim3(blocks), dim3(256), 0, c->train_stream, dst, static_cast<float*>(sh), static_cast<float*>(bsh), c->off);
         DQN_LAUNCH_CHECK();
         DQN_HIP(hipStreamSynchronize(c->train_stream));
     }
@@ -900,8 +884,8 @@ int dqn_train_step(dqn_ctx* c, const uint8_t* s, const int32_t* a, const float* 
     std::lock_guard<std::mutex> online_lock(c->online_mu);
     DQN_HIP(wait_for_online_act(c));
     int rc;
-    if (c->cfg.precision == DQN_PRECISION_BF16) rc = train_impl<bf16_t, true>(c, s, a, r, s2, done, B, loss_out);
-    else rc = train_impl<float, false>(c, s, a, r, s2, done, B, loss_out);
+    if (c->cfg.precision == DQN_PRECISION_BF16) rc = train_impl<bf16_t>(c, s, a, r, s2, done, B, loss_out);
+    else rc = train_impl<float>(c, s, a, r, s2, done, B, loss_out);
     if (rc != DQN_OK) return rc;
     c->train_unrecorded.store(true, std::memory_order_release);   // the event is recorded by the first reader, if any
     c->last_B = B;
@@ -947,12 +931,12 @@ int dqn_train_step_sampled(dqn_ctx* c, replay* rb, int32_t B, uint64_t sample_st
     int rc;
     if (by_desc) {
         const StateSource src{c->mb_desc[buf], replay_ring_frames(rb), nullptr};   // nobody needs the assembled state
-        rc = train_impl<bf16_t, true>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride,
+        rc = train_impl<bf16_t>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride,
                                       ride ? c->mb_desc[buf ^ 1] : nullptr, &src);
     } else if (c->cfg.precision == DQN_PRECISION_BF16)
-        rc = train_impl<bf16_t, true>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride);
+        rc = train_impl<bf16_t>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride);
     else
-        rc = train_impl<float, false>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride);
+        rc = train_impl<float>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride);
     if (rc != DQN_OK) return rc;
     c->train_unrecorded.store(true, std::memory_order_release);
     c->last_B = B;
@@ -1035,14 +1019,11 @@ int dqn_sync_target(dqn_ctx* c, replay* rb, int32_t blocking)
         if (rc != DQN_OK) return rc;
     }
     const size_t n = c->off.total;
+    const dim3 grid(static_cast<unsigned>((n + 255) / 256)), block(256);
     if (c->cfg.precision == DQN_PRECISION_BF16)
-        hipLaunchKernelGGL((target_copy_kernel<bf16_t, true>), dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0,
-                           c->train_stream, c->theta, c->theta_t, static_cast<const bf16_t*>(c->sh),
-                           static_cast<bf16_t*>(c->sh_t), n);
+        hipLaunchKernelGGL(target_copy_kernel<bf16_t>, grid, block, 0, c->train_stream, c->theta, c->theta_t, static_cast<const bf16_t*>(c->sh), static_cast<bf16_t*>(c->sh_t), n);
     else
-        hipLaunchKernelGGL((target_copy_kernel<float, false>), dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0,
-                           c->train_stream, c->theta, c->theta_t, static_cast<const float*>(nullptr),
-                           static_cast<float*>(nullptr), n);
+        hipLaunchKernelGGL(target_copy_kernel<float>, grid, block, 0, c->train_stream, c->theta, c->theta_t, static_cast<const float*>(c->sh), static_cast<float*>(c->sh_t), n);
     DQN_LAUNCH_CHECK();
     DQN_HIP(hipEventRecord(c->ev_sync, c->train_stream));
     DQN_HIP(hipStreamWaitEvent(c->act_stream, c->ev_sync, 0));
