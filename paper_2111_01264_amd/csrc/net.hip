@@ -98,6 +98,8 @@ struct dqn_ctx {
     float *theta = nullptr, *theta_t = nullptr, *v = nullptr, *m = nullptr, *grad = nullptr;
     void *sh = nullptr, *sh_t = nullptr;   // forward operand copies
     void* bsh = nullptr;                   // backward operand copies of theta
+    float* blob = nullptr;                 // a blob in the public layout, on its way in or out (dqn_set_params / dqn_get_params)
+    std::mutex blob_mu;
     Workspace train_ws, act_ws;
     void *dzh = nullptr, *dz3 = nullptr, *dz2 = nullptr, *dz1 = nullptr;
     float *dqv = nullptr, *lossv = nullptr, *loss_keep = nullptr;
@@ -594,29 +596,30 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     return DQN_OK;
 }
 
-// Public blob (OIHW, fc1 input index c*49 + h*7 + w)  <->  device layout (see gemm_mfma.h).
-static void permute_blob(const Offsets& o, const float* src, float* dst, bool to_device)
+// Public blob (OIHW, fc1 input index c*49 + h*7 + w)  <->  device layout (see gemm_mfma.h): the element of the public blob
+// that element e of the device layout holds.
+__device__ inline size_t public_index(const Offsets& o, size_t e)
 {
-    memcpy(dst, src, o.total * sizeof(float));
-    auto conv = [&](size_t off, int O, int C, int K) {
-        for (int oc = 0; oc < O; ++oc)
-            for (int c = 0; c < C; ++c)
-                for (int p = 0; p < K; ++p)
-                    for (int q = 0; q < K; ++q) {
-                        const size_t pub = off + ((static_cast<size_t>(oc) * C + c) * K + p) * K + q;
-                        const size_t dev = off + ((static_cast<size_t>(oc) * K + p) * K + q) * C + c;
-                        if (to_device) dst[dev] = src[pub]; else dst[pub] = src[dev];
-                    }
+    auto conv = [&](size_t off, int C, int K) {   // device [o][p][q][c], public [o][c][p][q]
+        const int r = static_cast<int>(e - off), c = r % C, q = r / C % K, p = r / (C * K) % K, oc = r / (C * K * K);
+        return off + ((static_cast<size_t>(oc) * C + c) * K + p) * K + q;
     };
-    conv(o.w2, 64, 32, 4);
-    conv(o.w3, 64, 64, 3);
-    for (int oc = 0; oc < 512; ++oc)
-        for (int c = 0; c < 64; ++c)
-            for (int hw = 0; hw < 49; ++hw) {
-                const size_t pub = o.wf1 + static_cast<size_t>(oc) * 3136 + c * 49 + hw;
-                const size_t dev = o.wf1 + static_cast<size_t>(oc) * 3136 + hw * 64 + c;
-                if (to_device) dst[dev] = src[pub]; else dst[pub] = src[dev];
-            }
+    if (e >= o.w2 && e < o.b2) return conv(o.w2, 32, 4);
+    if (e >= o.w3 && e < o.b3) return conv(o.w3, 64, 3);
+    if (e >= o.wf1 && e < o.bf1) {
+        const int r = static_cast<int>(e - o.wf1), c = r % 64, hw = r / 64 % 49, oc = r / 3136;
+        return o.wf1 + static_cast<size_t>(oc) * 3136 + c * 49 + hw;
+    }
+    return e;
+}
+// The change of layout runs on the device (a few microseconds; on the host it was most of the 1 ms that either call took).
+template <bool TO_DEVICE>
+__global__ __launch_bounds__(256) void permute_blob_kernel(const float* __restrict__ src, float* __restrict__ dst, Offsets off)
+{
+    const size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
+    if (e >= off.total) return;
+    const size_t pub = public_index(off, e);
+    if (TO_DEVICE) dst[e] = src[pub]; else dst[pub] = src[e];
 }
 
 static float* blob_of(dqn_ctx* c, int which)
@@ -685,6 +688,7 @@ int dqn_create(const dqn_config* cfg, void* act_stream, void* train_stream, dqn_
             DQN_HIP(hipMalloc((void**)p, (n + 8) * sizeof(float)));
             DQN_HIP(hipMemset(*p, 0, (n + 8) * sizeof(float)));
         }
+        DQN_HIP(hipMalloc((void**)&c->blob, n * sizeof(float)));
         for (void** p : {&c->sh, &c->sh_t}) {
             DQN_HIP(hipMalloc(p, (n + 8) * c->esize));
             DQN_HIP(hipMemset(*p, 0, (n + 8) * c->esize));
@@ -735,7 +739,7 @@ int dqn_destroy(dqn_ctx* c)
     if (!c) return DQN_OK;
     (void)hipStreamSynchronize(c->act_stream);
     (void)hipStreamSynchronize(c->train_stream);
-    (void)hipFree(c->sh); (void)hipFree(c->sh_t);
+    (void)hipFree(c->sh); (void)hipFree(c->sh_t); (void)hipFree(c->blob);
     (void)hipFree(c->theta); (void)hipFree(c->theta_t); (void)hipFree(c->v); (void)hipFree(c->m); (void)hipFree(c->grad);
     free_ws(c->train_ws); free_ws(c->act_ws);
     (void)hipFree(c->dzh); (void)hipFree(c->dz3); (void)hipFree(c->dz2); (void)hipFree(c->dz1);
@@ -762,11 +766,12 @@ int dqn_set_params(dqn_ctx* c, int which, const float* host_src, size_t n)
     if (which < DQN_PARAMS_ONLINE || which > DQN_PARAMS_RMS_M) return fail(DQN_EINVAL, "dqn_set_params: which = %d", which);
     int rc = sync_both(c);
     if (rc != DQN_OK) return rc;
-    std::vector<float> dev(n);
-    permute_blob(c->off, host_src, dev.data(), true);
     float* dst = blob_of(c, which);
-    DQN_HIP(hipMemcpy(dst, dev.data(), n * sizeof(float), hipMemcpyHostToDevice));
     const unsigned blocks = static_cast<unsigned>((n + 255) / 256);
+    std::lock_guard<std::mutex> blob_lock(c->blob_mu);
+    DQN_HIP(hipMemcpyAsync(c->blob, host_src, n * sizeof(float), hipMemcpyHostToDevice, c->train_stream));
+    hipLaunchKernelGGL(permute_blob_kernel<true>, dim3(blocks), dim3(256), 0, c->train_stream, c->blob, dst, c->off);
+    DQN_LAUNCH_CHECK();
     if (which == DQN_PARAMS_ONLINE || which == DQN_PARAMS_TARGET) {   // the network's operand copies (backward ones: theta only)
         const bool online = which == DQN_PARAMS_ONLINE;
         void *sh = online ? c->sh : c->sh_t, *bsh = online ? c->bsh : nullptr;
@@ -775,8 +780,8 @@ int dqn_set_params(dqn_ctx* c, int which, const float* host_src, size_t n)
         else
             hipLaunchKernelGGL(build_copies_kernel<float>, dim3(blocks), dim3(256), 0, c->train_stream, dst, static_cast<float*>(sh), static_cast<float*>(bsh), c->off);
         DQN_LAUNCH_CHECK();
-        DQN_HIP(hipStreamSynchronize(c->train_stream));
     }
+    DQN_HIP(hipStreamSynchronize(c->train_stream));
     return DQN_OK;
 }
 
@@ -788,9 +793,11 @@ int dqn_get_params(dqn_ctx* c, int which, float* host_dst, size_t n)
     if (!src) return fail(DQN_EINVAL, "dqn_get_params: which = %d", which);
     int rc = sync_both(c);
     if (rc != DQN_OK) return rc;
-    std::vector<float> dev(n);
-    DQN_HIP(hipMemcpy(dev.data(), src, n * sizeof(float), hipMemcpyDeviceToHost));
-    permute_blob(c->off, dev.data(), host_dst, false);
+    std::lock_guard<std::mutex> blob_lock(c->blob_mu);
+    hipLaunchKernelGGL(permute_blob_kernel<false>, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, c->train_stream, src, c->blob, c->off);
+    DQN_LAUNCH_CHECK();
+    DQN_HIP(hipMemcpyAsync(host_dst, c->blob, n * sizeof(float), hipMemcpyDeviceToHost, c->train_stream));
+    DQN_HIP(hipStreamSynchronize(c->train_stream));
     return DQN_OK;
 }
 
