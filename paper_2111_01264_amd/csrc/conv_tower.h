@@ -128,7 +128,6 @@ struct TowerArgs {
     bf16_t* act1[kMaxGroups];   // [n][400][32] or null
     bf16_t* act2[kMaxGroups];   // [n][81][64] or null
     bf16_t* act3[kMaxGroups];   // [n][49][64]
-    uint8_t* s_out;             // with desc: group 0 also stores the state it assembled, [n][4][84][84] (the weight gradient of conv1 reads it)
     PushStepPlan push;          // optional (L = 0: none): one experience per lane into the temporary buffers
 };
 
@@ -280,10 +279,6 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_kernel(int n_, int g
         {
             uint4* d = reinterpret_cast<uint4*>(sX);
             d[tid] = xv0; d[tid + 512] = xv1; d[tid + 1024] = xv2; d[last_vec] = xv3;   // clamped lanes rewrite the last vector with itself
-            if (use_desc && g == 0 && a.s_out) {   // the assembled state, kept for the weight gradient of conv1
-                uint4* so = reinterpret_cast<uint4*>(a.s_out + static_cast<size_t>(b) * kTowerXBytes);
-                so[tid] = xv0; so[tid + 512] = xv1; so[tid + 1024] = xv2; so[last_vec] = xv3;
-            }
         }
         // conv2/conv3 fragments of a new group: requested a few k-steps apart inside conv1's (conv2's weights) and conv2's
         // (conv3's weights) MFMA streams (17 KB per wavefront -- requested in one go they hold every wavefront ~0.5 us in

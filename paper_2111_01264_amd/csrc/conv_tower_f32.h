@@ -31,7 +31,9 @@ struct TowerF32Args {
     int n, groups;
     int per;                       // items per workgroup
     int tower_blocks;              // workgroups [0, tower_blocks) run the tower, the next push.L ones the append
-    const uint8_t* x[kMaxGroups];  // [n][4][84][84], 16-byte aligned
+    const uint8_t* x[kMaxGroups];  // [n][4][84][84], 16-byte aligned (unused with a descriptor table)
+    const int32_t* desc;           // the minibatch as per-sample replay slots ([n][8], see TowerArgs), or null
+    const uint8_t* ring;           // with desc: the replay memory's frame array
     const float* w1[kMaxGroups];   // [32][256]
     const float* w2[kMaxGroups];   // [64][512], fragment order
     const float* w3[kMaxGroups];   // [64][576], fragment order
@@ -133,10 +135,12 @@ __device__ inline void tower_f32_stream(tf_f32x4 (&acc)[NT], const float* const 
 // depend on (see conv_tower_kernel; thirds and sevenths are the same bands).  By the matrix cycles of its busiest SIMD an item
 // takes 49 k cycles whole, 30 k as a half, 25 k as a third, 16 k as a seventh; the host takes the smallest part for which the
 // chip still holds every workgroup at once.
-template <int PARTS>
+// DESC: the frames of a state come from the replay memory by descriptor, as in conv_tower_kernel.
+template <bool DESC, int PARTS>
 __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, int groups_, int per_, int tower_blocks_, const uint8_t* x0_,
                                                                        const uint8_t* x1_, const float* w1_0_, const float* w2_0_, TowerF32Args a)
 {
+    static_assert(!DESC || PARTS == 1, "descriptors come with minibatches that fill the chip");
     static_assert(PARTS == 1 || PARTS == 2 || PARTS == 3 || PARTS == 7, "whole samples, halves, thirds or sevenths");
     extern __shared__ __attribute__((aligned(16))) unsigned char tf_smem[];
     uint8_t* sX = tf_smem;
@@ -166,14 +170,35 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
     constexpr int kXVecs = kTowerXBytes / 16;   // 1764
     const int last_vec = tid + 1536 < kXVecs ? tid + 1536 : kXVecs - 1;
     uint4 xv0, xv1, xv2, xv3;                   // the state of the item to come, 16 bytes per lane and load (the last one clamped)
+    // DESC: vector v of the state belongs to frame v / 441, so each of a thread's loads chooses between two neighbouring frames; a zero
+    // frame (slot -1) is loaded from slot 0 and masked when it is stored.  The slots of an item are requested an item ahead.
+    const bool hi0 = tid >= 441, hi1 = tid + 512 >= 882, hi2 = tid + 1024 >= 1323;
+    int dn[4] = {0, 0, 0, 0};
+    uint32_t keep = 15u;
+    auto fetch_desc = [&](int g_, int b_) {
+        const int32_t* dp = a.desc + static_cast<size_t>(b_) * kDescInts + (g_ > 0 ? 4 : 0);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) dn[f] = dp[f];
+    };
     auto fetch_state = [&](int g_, int b_) {
-        const uint8_t* xg = g_ == 0 ? x0_ : g_ == 1 ? x1_ : a.x[g_];
-        const uint4* xs = reinterpret_cast<const uint4*>(xg + static_cast<size_t>(b_) * kTowerXBytes);
-        xv0 = xs[tid]; xv1 = xs[tid + 512]; xv2 = xs[tid + 1024]; xv3 = xs[last_vec];
+        if constexpr (DESC) {
+            const int s[4] = {hi0 ? dn[1] : dn[0], hi1 ? dn[2] : dn[1], hi2 ? dn[3] : dn[2], dn[3]};
+            const int w[4] = {tid - (hi0 ? 441 : 0), tid + 512 - (hi1 ? 882 : 441), tid + 1024 - (hi2 ? 1323 : 882), last_vec - 1323};
+            const uint4* r = reinterpret_cast<const uint4*>(a.ring);
+            auto vec = [&](int i) { return r[static_cast<size_t>(s[i] < 0 ? 0 : s[i]) * kFrameVec16 + w[i]]; };
+            xv0 = vec(0); xv1 = vec(1); xv2 = vec(2); xv3 = vec(3);
+            keep = (s[0] < 0 ? 0u : 1u) | (s[1] < 0 ? 0u : 2u) | (s[2] < 0 ? 0u : 4u) | (s[3] < 0 ? 0u : 8u);
+        } else {
+            const uint8_t* xg = g_ == 0 ? x0_ : g_ == 1 ? x1_ : a.x[g_];
+            const uint4* xs = reinterpret_cast<const uint4*>(xg + static_cast<size_t>(b_) * kTowerXBytes);
+            xv0 = xs[tid]; xv1 = xs[tid + 512]; xv2 = xs[tid + 1024]; xv3 = xs[last_vec];
+        }
     };
     int g = 0, b = first;
     while (b >= n_) { b -= n_; ++g; }
+    if constexpr (DESC) fetch_desc(g, b);
     fetch_state(g, b);
+    if (DESC && first + 1 < last) { if (b + 1 < n_) fetch_desc(g, b + 1); else fetch_desc(g + 1, 0); }
 
     const int lp = lane & 31, kg = lane >> 5;        // conv1: pixel / row of a 32x32 tile, k-half
     const int kq = lane >> 4;                        // conv2, conv3: k-quarter (and lane & 15: pixel / row of a 16x16 tile)
@@ -209,6 +234,10 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
         }
         {
             uint4* d = reinterpret_cast<uint4*>(sX);
+            if constexpr (DESC) {
+                auto mask = [&](uint4& v, int i) { const uint32_t m = (keep >> i) & 1u ? ~0u : 0u; v.x &= m; v.y &= m; v.z &= m; v.w &= m; };
+                mask(xv0, 0); mask(xv1, 1); mask(xv2, 2); mask(xv3, 3);
+            }
             d[tid] = xv0; d[tid + 512] = xv1; d[tid + 1024] = xv2; d[last_vec] = xv3;   // clamped lanes rewrite the last vector with itself
         }
         const float* w2p = (g == 0 ? w2_0_ : a.w2[g]) + ct * 32 * 256;
@@ -219,7 +248,14 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
 #pragma unroll
             for (int u = 0; u < D2; ++u) ring2[u] = weights(u);
         }
-        if (it + 1 < last) { if (b + 1 < n_) fetch_state(g, b + 1); else fetch_state(g + 1, 0); }
+        if (it + 1 < last) {
+            if (b + 1 < n_) fetch_state(g, b + 1); else fetch_state(g + 1, 0);
+            if (DESC && it + 2 < last) {
+                int g2 = g, b2 = b + 2;
+                while (b2 >= n_) { b2 -= n_; ++g2; }
+                fetch_desc(g2, b2);
+            }
+        }
         __syncthreads();
 
         // ---- conv1: k = (c, p, q); k-step k covers c = k / 4, p = 2 * (k % 4) + kg, q = 0..7 --------------------------

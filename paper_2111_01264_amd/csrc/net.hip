@@ -118,7 +118,7 @@ struct dqn_ctx {
     int32_t* mb_a[2] = {nullptr, nullptr};
     float* mb_r[2] = {nullptr, nullptr};
     float* mb_d[2] = {nullptr, nullptr};
-    int32_t* mb_desc[2] = {nullptr, nullptr};   // reduced precision: the minibatch as per-sample descriptors (sample_desc)
+    int32_t* mb_desc[2] = {nullptr, nullptr};   // large minibatches: per-sample descriptors (sample_desc)
     bool pre_valid = false;
     const replay* pre_rb = nullptr;
     int pre_B = 0, pre_buf = 0;
@@ -188,10 +188,11 @@ static hipError_t raise_lds_limits()
             {reinterpret_cast<const void*>(conv_tower_kernel<true, 1>), kTowerSmem},
             {reinterpret_cast<const void*>(conv_tower_bwd_kernel<1>), kTowerBwdSmem},
             {reinterpret_cast<const void*>(conv_tower_bwd_kernel<5>), kTowerBwdSmem},
-            {reinterpret_cast<const void*>(conv_tower_f32_kernel<1>), kTowerF32Smem},
-            {reinterpret_cast<const void*>(conv_tower_f32_kernel<2>), kTowerF32Smem},
-            {reinterpret_cast<const void*>(conv_tower_f32_kernel<3>), kTowerF32Smem},
-            {reinterpret_cast<const void*>(conv_tower_f32_kernel<7>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<false, 1>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<true, 1>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<false, 2>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<false, 3>), kTowerF32Smem},
+            {reinterpret_cast<const void*>(conv_tower_f32_kernel<false, 7>), kTowerF32Smem},
             {reinterpret_cast<const void*>(conv_tower_bwd_f32_kernel<1>), kTowerBwdF32Smem},
             {reinterpret_cast<const void*>(conv_tower_bwd_f32_kernel<2>), kTowerBwdF32Smem},
             {reinterpret_cast<const void*>(conv_tower_bwd_f32_kernel<5>), kTowerBwdF32Smem},
@@ -229,11 +230,10 @@ static int fc1_slices(int n, int groups)
 }
 
 // A minibatch given by descriptors (sample_desc) instead of assembled states: the fused conv kernel reads the frames
-// from the replay memory's frame array itself and leaves the state of the online pass in s_out.
+// from the replay memory's frame array itself.
 struct StateSource {
     const int32_t* desc;
     const uint8_t* ring;
-    uint8_t* s_out;
 };
 
 __global__ __launch_bounds__(256) void sample_desc_kernel(GatherPlan plan, int32_t* desc)
@@ -266,7 +266,7 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
             a.act3[g] = act3 + g * e_act3;
         }
         a.n = n; a.groups = groups;
-        if (src) { a.desc = src->desc; a.ring = src->ring; a.s_out = src->s_out; }
+        if (src) { a.desc = src->desc; a.ring = src->ring; }
         DQN_HIP(raise_lds_limits());
         // Few items (a round of synchronized samplers, a minibatch of 32): seven or three workgroups per item, a seventh or
         // a third of its output rows each, while that still fits the chip -- the chain of layers of one sample is what the
@@ -302,14 +302,15 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         DQN_HIP(raise_lds_limits());
         // the smallest part of an item for which every workgroup is resident at once (see the kernel)
         const int total = n * groups;
-        const int parts = 7 * total <= c->num_cus ? 7 : (3 * total <= c->num_cus ? 3 : (2 * total <= c->num_cus ? 2 : 1));
+        if (src) { a.desc = src->desc; a.ring = src->ring; }
+        const int parts = a.desc ? 1 : 7 * total <= c->num_cus ? 7 : (3 * total <= c->num_cus ? 3 : (2 * total <= c->num_cus ? 2 : 1));
         const int grid = parts > 1 ? parts * total : (total < c->num_cus ? total : c->num_cus);
         a.per = parts > 1 ? 1 : (total + grid - 1) / grid;
         a.tower_blocks = grid;
         a.push.L = 0;
         if (push) a.push = *push;
         const ProfPair pr = pp(K_CONV1_FWD);
-        auto kern = parts == 7 ? conv_tower_f32_kernel<7> : parts == 3 ? conv_tower_f32_kernel<3> : parts == 2 ? conv_tower_f32_kernel<2> : conv_tower_f32_kernel<1>;
+        auto kern = a.desc ? conv_tower_f32_kernel<true, 1> : parts == 7 ? conv_tower_f32_kernel<false, 7> : parts == 3 ? conv_tower_f32_kernel<false, 3> : parts == 2 ? conv_tower_f32_kernel<false, 2> : conv_tower_f32_kernel<false, 1>;
         launch_timed(kern, dim3(grid + a.push.L), dim3(kTowerThreads), kTowerF32Smem, st, pr.begin, pr.end, a.n, a.groups, a.per, a.tower_blocks, a.x[0], a.x[1],
                      a.w1[0], a.w2[0], a);
         DQN_LAUNCH_CHECK();
@@ -906,10 +907,9 @@ int dqn_train_step_sampled(dqn_ctx* c, replay* rb, int32_t B, uint64_t sample_st
     if (replay_sample_stream(rb) != c->train_stream)
         return fail(DQN_EINVAL, "dqn_train_step_sampled: the replay's sample stream must be the train stream");
     std::lock_guard<std::mutex> online_lock(c->online_mu);
-    // Reduced precision, large minibatch: the minibatch is only DESCRIBED (replay slots per frame, a, r, done); the fused
-    // conv kernel and conv1's weight gradient read the frames from the replay memory themselves.  Otherwise the states are
+    // Large minibatch: it is only DESCRIBED (replay slots per frame, a, r, done); the fused conv kernel and conv1's weight gradient read the frames from the replay memory themselves.  Otherwise the states are
     // assembled (replay_sample_gather's kernel, riding in the previous step's head kernel where it can).
-    const bool by_desc = c->cfg.precision == DQN_PRECISION_BF16 && B >= kDescMinBatch;
+    const bool by_desc = B >= kDescMinBatch;
     int buf = 0;
     if (c->pre_valid && c->pre_rb == rb && c->pre_B == B && c->pre_step == sample_step && c->pre_epoch == replay_epoch(rb)) {
         buf = c->pre_buf;   // prepared inside the previous call's launches, and no flush since
@@ -926,8 +926,7 @@ int dqn_train_step_sampled(dqn_ctx* c, replay* rb, int32_t B, uint64_t sample_st
     c->pre_valid = false;
     GatherPlan plan;
     const GatherPlan* ride = nullptr;
-    // full precision has only the head kernel to ride in, and beyond a few hundred samples the byte gather outlasts it
-    if (prefetch_next && (by_desc || B <= 256)) {
+    if (prefetch_next) {
         const int nb = buf ^ 1;
         const int rc = replay_plan_sample_gather(rb, B, sample_step + 1, nullptr, c->mb_s[nb], c->mb_s2[nb], c->mb_a[nb], c->mb_r[nb],
                                                  c->mb_d[nb], nullptr, &plan);
@@ -936,14 +935,10 @@ int dqn_train_step_sampled(dqn_ctx* c, replay* rb, int32_t B, uint64_t sample_st
     }
     DQN_HIP(wait_for_online_act(c));
     int rc;
-    if (by_desc) {
-        const StateSource src{c->mb_desc[buf], replay_ring_frames(rb), nullptr};   // nobody needs the assembled state
-        rc = train_impl<bf16_t>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride,
-                                      ride ? c->mb_desc[buf ^ 1] : nullptr, &src);
-    } else if (c->cfg.precision == DQN_PRECISION_BF16)
-        rc = train_impl<bf16_t>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride);
-    else
-        rc = train_impl<float>(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride);
+    const StateSource src{c->mb_desc[buf], replay_ring_frames(rb)};
+    int32_t* ride_desc = ride && by_desc ? c->mb_desc[buf ^ 1] : nullptr;
+    auto train = c->cfg.precision == DQN_PRECISION_BF16 ? train_impl<bf16_t> : train_impl<float>;
+    rc = train(c, c->mb_s[buf], c->mb_a[buf], c->mb_r[buf], c->mb_s2[buf], c->mb_d[buf], B, loss_out, ride, ride_desc, by_desc ? &src : nullptr);
     if (rc != DQN_OK) return rc;
     c->train_unrecorded.store(true, std::memory_order_release);
     c->last_B = B;
