@@ -16,6 +16,9 @@ constexpr int kMaxActions = 32;
 struct Offsets {
     size_t w1, b1, w2, b2, w3, b3, wf1, bf1, wf2, bf2, total;
 };
+// (all but the end of the blob are the same for every number of actions)
+constexpr size_t kOffW1 = 0, kOffB1 = kOffW1 + 32 * 256, kOffW2 = kOffB1 + 32, kOffB2 = kOffW2 + 64 * 512, kOffW3 = kOffB2 + 64, kOffB3 = kOffW3 + 64 * 576,
+                 kOffWf1 = kOffB3 + 64, kOffBf1 = kOffWf1 + 512 * 3136, kOffWf2 = kOffBf1 + 512;
 inline Offsets make_offsets(int A)
 {
     Offsets o;
@@ -375,9 +378,19 @@ __global__ __launch_bounds__(256) void head_fwd_kernel(const float* partial_, in
 //    Each block owns 16 columns o; thread (o, part) accumulates the samples b = part (mod 16) in
 //    increasing order into its own LDS column, the sixteen parts are then added in order.
 constexpr int kBiasRows = 1024;
-constexpr int kRmsConvLanes = 8;                                    // lanes per float4 of a conv weight in the optimiser's conv blocks
-constexpr int kRmsConvQuads = (32 * 256 + 64 * 512 + 64 * 576) / 4;
-constexpr int kRmsConvBlocks = (kRmsConvQuads * kRmsConvLanes + 255) / 256;
+// The optimiser's conv blocks: lanes per four weights, slices per lane and round trip (64 of conv1's at most 128 slices in flight, 48
+// of the at most 44 -- fp32: 64 -- of the others).
+constexpr int kRmsLanes1 = 8, kRmsTrip1 = 8, kRmsLanes23 = 4, kRmsTrip23 = 12;
+constexpr int kRmsQuads1 = 32 * 256 / 4, kRmsQuads2 = 64 * 512 / 4, kRmsQuads3 = 64 * 576 / 4;
+constexpr int kRmsBlocks1 = kRmsQuads1 * kRmsLanes1 / 256, kRmsBlocks2 = kRmsQuads2 * kRmsLanes23 / 256, kRmsBlocks3 = kRmsQuads3 * kRmsLanes23 / 256;
+constexpr int kRmsConvBlocks = kRmsBlocks1 + kRmsBlocks2 + kRmsBlocks3;   // 64 + 128 + 144
+static_assert(kRmsBlocks1 * 256 == kRmsQuads1 * kRmsLanes1 && kRmsBlocks2 * 256 == kRmsQuads2 * kRmsLanes23 && kRmsBlocks3 * 256 == kRmsQuads3 * kRmsLanes23, "whole blocks");
+constexpr int kRmsFc1Tiles = 8 * 49;                                // 64 x 64 tiles of fc1.w
+// Split-K slices of the conv weight gradients, [slice][tensor] fp32 for each layer, in one buffer (conv1's gradient is small: more
+// slices are cheap).
+constexpr size_t kWgMaxSplits = 64, kWgMaxSplits1 = 128;
+constexpr size_t kWgOff1 = 0, kWgOff2 = kWgMaxSplits1 * 32 * 256, kWgOff3 = kWgOff2 + kWgMaxSplits * 64 * 512;
+constexpr size_t kWgTotal = kWgOff3 + kWgMaxSplits * 64 * 576;
 constexpr int kRmsBiasLanes = 8;                                    // lanes per channel in the optimiser's bias blocks
 constexpr int kRmsBiasBlocks = (672 * kRmsBiasLanes + 255) / 256;  // 32 + 64 + 64 + 512 hidden-layer bias channels
 struct BiasGradArgs {
@@ -520,7 +533,7 @@ __device__ inline void small_grads_block(const BiasGradArgs& args, int block, un
 
 struct RmsArgs {
     float* theta;
-    const float* grad;
+    float* grad;
     float* v;
     float* m;
     void* sh;        // forward operand copy
@@ -528,27 +541,11 @@ struct RmsArgs {
     Offsets off;
     float lr, alpha, eps;
     int centered;
-    int flat_blocks; // after the kRmsConvBlocks conv-weight blocks: [0, flat_blocks) elementwise, then fc1_tiles fc1.w tiles, then the bias blocks
-    int fc1_tiles;   // 16 * 49 (32 x 64 tiles of fc1.w)
     // second stage of the bias gradients (conv1..3, fc1): chunk sums (conv layers: one per weight-gradient slice)
     const float* bias_partial;
     int bias_chunks[4];
     int bias_first[4];
-    // deferred split-K sums of the conv weight gradients: [splits][tensor] fp32 each
-    const float* wg_partial[3];
-    int wg_splits[3];
-    float wg_scale[3];
 };
-
-// Index of the hidden-layer bias vector that blob element e belongs to, or -1.
-__device__ inline int hidden_bias_layer(const Offsets& o, size_t e)
-{
-    if (e >= o.b1 && e < o.w2) return 0;
-    if (e >= o.b2 && e < o.w3) return 1;
-    if (e >= o.b3 && e < o.wf1) return 2;
-    if (e >= o.bf1 && e < o.wf2) return 3;
-    return -1;
-}
 
 __device__ inline void rms_update(const RmsArgs& a, float& th, float g, float& vv, float& mm)
 {
@@ -561,93 +558,131 @@ __device__ inline void rms_update(const RmsArgs& a, float& th, float g, float& v
     th -= a.lr * g / (sqrtf(var) + a.eps);
 }
 
-template <typename T>
-__device__ inline void publish(const RmsArgs& a, size_t e, float th)
+// Conv weights of layer CONV: the gradient arrives as `ns` split-K slices.  LANES adjacent lanes share four weights: lane j requests
+// slices j, j + LANES, ... (TRIP per round trip) and adds them in that order, the sums meet in a fixed tree, lanes 0 .. 3 update one
+// weight each.  What counts is the length of the dependent chain: everything an address needs is a constant or comes with the
+// wavefront, and the parameters are requested with the slices.  (Offsets and counts read from the argument struct, one lane updating
+// all four weights and eight lanes per quad everywhere: these blocks alone were a launch of 8.1 us, now 4.2 us, and the whole
+// kernel 10.7 / 12.1 us at batch 32 / 256, now 9.2 / 10.5 us, back to back.)
+template <typename T, int CONV, int LANES, int TRIP>
+__device__ inline void rms_conv_block(float* theta, float* grad, float* v, float* m, const float* slices, int ns, const RmsArgs& a, int block)
 {
-    shadow_store<T>(static_cast<T*>(a.sh), a.off, e, th);
-    if (e >= a.off.w2 && e < a.off.b2) static_cast<T*>(a.bsh)[bsh_index_w2<T>(static_cast<int>(e - a.off.w2))] = from_float<T>(th);
-    else if (e >= a.off.w3 && e < a.off.b3) static_cast<T*>(a.bsh)[bsh_index_w3<T>(static_cast<int>(e - a.off.w3))] = from_float<T>(th);
+    constexpr size_t E0 = CONV == 0 ? kOffW1 : CONV == 1 ? kOffW2 : kOffW3, TSIZE = CONV == 0 ? 32 * 256 : CONV == 1 ? 64 * 512 : 64 * 576;
+    const int idx = block * 256 + static_cast<int>(threadIdx.x), j = idx % LANES;
+    const int r = idx / LANES * 4;
+    const float* p = slices + (CONV == 0 ? kWgOff1 : CONV == 1 ? kWgOff2 : kWgOff3) + r;
+    const size_t e = E0 + r + (j & 3);
+    float4 v4[TRIP];
+#pragma unroll
+    for (int u = 0; u < TRIP; ++u) v4[u] = *reinterpret_cast<const float4*>(p + static_cast<size_t>(min(j + u * LANES, ns - 1)) * TSIZE);
+    float th = theta[e], vv = v[e], mm = m[e];
+    __builtin_amdgcn_sched_barrier(0);
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s0 = j; s0 < ns; s0 += TRIP * LANES) {
+#pragma unroll
+        for (int u = 0; u < TRIP; ++u)
+            if (s0 + u * LANES < ns) { sum.x += v4[u].x; sum.y += v4[u].y; sum.z += v4[u].z; sum.w += v4[u].w; }
+        if (s0 + TRIP * LANES < ns) {
+#pragma unroll
+            for (int u = 0; u < TRIP; ++u) v4[u] = *reinterpret_cast<const float4*>(p + static_cast<size_t>(min(s0 + (TRIP + u) * LANES, ns - 1)) * TSIZE);
+        }
+    }
+#pragma unroll
+    for (int d = LANES / 2; d >= 1; d >>= 1) {
+        sum.x += __shfl_xor(sum.x, d, LANES); sum.y += __shfl_xor(sum.y, d, LANES);
+        sum.z += __shfl_xor(sum.z, d, LANES); sum.w += __shfl_xor(sum.w, d, LANES);
+    }
+    if (j >= 4) return;
+    float g = j == 0 ? sum.x : j == 1 ? sum.y : j == 2 ? sum.z : sum.w;
+    if (CONV == 0) g *= 1.f / 255.f;
+    grad[e] = g;
+    rms_update(a, th, g, vv, mm);
+    theta[e] = th;
+    v[e] = vv;
+    if (a.centered) m[e] = mm;
+    const int el = r + j;
+    if (CONV == 0) {
+        if (sizeof(T) == 2) reinterpret_cast<_Float16*>(a.sh)[tower_frag_index(el / 256, el % 256, 256)] = static_cast<_Float16>(th);
+        else static_cast<T*>(a.sh)[el] = from_float<T>(th);
+    } else {
+        constexpr int K = CONV == 1 ? 512 : 576;
+        static_cast<T*>(a.sh)[E0 + (sizeof(T) == 2 ? tower_frag_index(el / K, el % K, K) : frag16_index(el / K, el % K, K))] = from_float<T>(th);
+        static_cast<T*>(a.bsh)[CONV == 1 ? bsh_index_w2<T>(el) : bsh_index_w3<T>(el)] = from_float<T>(th);
+    }
 }
 
-// Centered RMSProp (Appendix B) fused with the refresh of the operand copies.  The conv weights come first
-// (their gradient is finished here from split-K slices), elementwise blocks cover the rest except fc1.w and the
-// hidden-layer biases; fc1.w is walked in 32 x 64 tiles whose two operand copies (forward [o][f] and backward
-// [f][o], both in fragment order) are written in whole 512-byte pieces via LDS.
-// The leading scalar parameters repeat RmsArgs::theta, grad, v, m, flat_blocks, fc1_tiles and off.wf1 (what the fc1.w
-// tiles, 95 % of the parameters, need before their first load): the kernel arguments' first 14 dwords are preloaded into
-// scalar registers when a wavefront starts (see conv_tower_kernel).
+// Centered RMSProp (Appendix B) fused with the refresh of the operand copies.  The conv weights' blocks come first (a dependent chain);
+// fc1.w (95 % of the parameters) is walked in 64 x 64 tiles whose two operand copies (forward [o][f] and backward [f][o], both in
+// fragment order) are written in whole 512-byte pieces via LDS; then fc2 element by element and the hidden-layer biases.  Bound by memory traffic (62 MB at batch 32: 6.8
+// TB/s back to back).
+// The leading scalar parameters repeat RmsArgs' pointers and what the blocks need before their first load (splits: slices per conv
+// layer, one byte each): the kernel arguments' first 14 dwords are preloaded into scalar registers when a wavefront starts (see
+// conv_tower_kernel).
 template <typename T>
-__global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float* grad_, float* v_, float* m_, int flat_blocks_,
-                                                      int fc1_tiles_, size_t wf1_, RmsArgs a)
+__global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, float* grad_, float* v_, float* m_, const float* slices_, uint32_t splits_, int flat_blocks_, RmsArgs a)
 {
-    __shared__ T tile[64][32 + 8];
+    __shared__ T tile[64][64 + 8];   // [f][o]
     const int tid = threadIdx.x;
-    if (static_cast<int>(blockIdx.x) < kRmsConvBlocks) {
-        // Conv weights: their gradient arrives as split-K slices (up to 128 of them at small batches).  Eight adjacent
-        // lanes share four weights: lane j requests slices j, j + 8, ... (eight per round trip) and adds them in that order, the
-        // eight sums meet in a fixed tree, lane 0 updates.  (One lane walking all slices, eight loads at a time, was a
-        // chain of dependent round trips that outlasted the streaming of every other parameter.)
-        const int idx = blockIdx.x * 256 + tid;
-        const int q = idx / kRmsConvLanes, j = idx % kRmsConvLanes;
-        if (q >= kRmsConvQuads) return;   // whole lane groups leave together
-        int conv = 2;
-        size_t r = static_cast<size_t>(q - (32 * 256 + 64 * 512) / 4) * 4, tsize = 64 * 576, e = a.off.w3 + r;
-        if (q < 32 * 256 / 4) { conv = 0; r = static_cast<size_t>(q) * 4; tsize = 32 * 256; e = a.off.w1 + r; }
-        else if (q < (32 * 256 + 64 * 512) / 4) { conv = 1; r = static_cast<size_t>(q - 32 * 256 / 4) * 4; tsize = 64 * 512; e = a.off.w2 + r; }
-        const float* p = a.wg_partial[conv] + r;
-        const int ns = a.wg_splits[conv];
-        float4 th = make_float4(0.f, 0.f, 0.f, 0.f), vv = th, mm = th;
-        if (j == 0) {
-            th = *reinterpret_cast<float4*>(theta_ + e);
-            vv = *reinterpret_cast<float4*>(v_ + e);
-            mm = *reinterpret_cast<float4*>(m_ + e);
-        }
-        constexpr int kPerLane = 8;       // slices per lane and round trip: one trip up to 64 slices, two up to 128
-        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int s0 = j; s0 < ns; s0 += kPerLane * kRmsConvLanes) {
-            float4 v4[kPerLane];
-#pragma unroll
-            for (int u = 0; u < kPerLane; ++u) {
-                const int sl = s0 + u * kRmsConvLanes;
-                v4[u] = *reinterpret_cast<const float4*>(p + static_cast<size_t>(sl < ns ? sl : ns - 1) * tsize);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int u = 0; u < kPerLane; ++u)
-                if (s0 + u * kRmsConvLanes < ns) { sum.x += v4[u].x; sum.y += v4[u].y; sum.z += v4[u].z; sum.w += v4[u].w; }
-        }
-#pragma unroll
-        for (int d = kRmsConvLanes / 2; d >= 1; d >>= 1) {
-            sum.x += __shfl_down(sum.x, d, kRmsConvLanes); sum.y += __shfl_down(sum.y, d, kRmsConvLanes);
-            sum.z += __shfl_down(sum.z, d, kRmsConvLanes); sum.w += __shfl_down(sum.w, d, kRmsConvLanes);
-        }
-        if (j != 0) return;
-        const float sc = a.wg_scale[conv];
-        const float4 g = make_float4(sum.x * sc, sum.y * sc, sum.z * sc, sum.w * sc);
-        *reinterpret_cast<float4*>(const_cast<float*>(grad_) + e) = g;   // kept for readers of the gradient
-        rms_update(a, th.x, g.x, vv.x, mm.x);
-        rms_update(a, th.y, g.y, vv.y, mm.y);
-        rms_update(a, th.z, g.z, vv.z, mm.z);
-        rms_update(a, th.w, g.w, vv.w, mm.w);
-        *reinterpret_cast<float4*>(theta_ + e) = th;
-        *reinterpret_cast<float4*>(v_ + e) = vv;
-        if (a.centered) *reinterpret_cast<float4*>(m_ + e) = mm;
-        publish<T>(a, e, th.x);
-        publish<T>(a, e + 1, th.y);
-        publish<T>(a, e + 2, th.z);
-        publish<T>(a, e + 3, th.w);
+    int block = static_cast<int>(blockIdx.x);
+    if (block < kRmsConvBlocks) {
+        if (block < kRmsBlocks1) rms_conv_block<T, 0, kRmsLanes1, kRmsTrip1>(theta_, grad_, v_, m_, slices_, splits_ & 255, a, block);
+        else if (block < kRmsBlocks1 + kRmsBlocks2)
+            rms_conv_block<T, 1, kRmsLanes23, kRmsTrip23>(theta_, grad_, v_, m_, slices_, (splits_ >> 8) & 255, a, block - kRmsBlocks1);
+        else rms_conv_block<T, 2, kRmsLanes23, kRmsTrip23>(theta_, grad_, v_, m_, slices_, (splits_ >> 16) & 255, a, block - kRmsBlocks1 - kRmsBlocks2);
         return;
     }
-    const int block = static_cast<int>(blockIdx.x) - kRmsConvBlocks;
+    block -= kRmsConvBlocks;
+    if (block < kRmsFc1Tiles) {   // rows o0 .. o0+63, columns f0 .. f0+63; a thread's sixteen parameters are in flight at once
+        const int o0 = (block / 49) * 64, f0 = (block % 49) * 64;
+        const int r0 = tid / 16, c4 = (tid % 16) * 4;
+        float4 th[4], g[4], vv[4], mm[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const size_t e = kOffWf1 + static_cast<size_t>(o0 + r0 + 16 * u) * 3136 + f0 + c4;
+            th[u] = *reinterpret_cast<float4*>(theta_ + e);
+            g[u] = *reinterpret_cast<const float4*>(grad_ + e);
+            vv[u] = *reinterpret_cast<float4*>(v_ + e);
+            mm[u] = *reinterpret_cast<float4*>(m_ + e);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = r0 + 16 * u;
+            const size_t e = kOffWf1 + static_cast<size_t>(o0 + r) * 3136 + f0 + c4;
+            rms_update(a, th[u].x, g[u].x, vv[u].x, mm[u].x);
+            rms_update(a, th[u].y, g[u].y, vv[u].y, mm[u].y);
+            rms_update(a, th[u].z, g[u].z, vv[u].z, mm[u].z);
+            rms_update(a, th[u].w, g[u].w, vv[u].w, mm[u].w);
+            *reinterpret_cast<float4*>(theta_ + e) = th[u];
+            *reinterpret_cast<float4*>(v_ + e) = vv[u];
+            if (a.centered) *reinterpret_cast<float4*>(m_ + e) = mm[u];
+            tile[c4 + 0][r] = from_float<T>(th[u].x);
+            tile[c4 + 1][r] = from_float<T>(th[u].y);
+            tile[c4 + 2][r] = from_float<T>(th[u].z);
+            tile[c4 + 3][r] = from_float<T>(th[u].w);
+        }
+        __syncthreads();
+        // pieces of 32 rows x 16 bytes of consecutive k, one per 32 threads
+        constexpr int E = 16 / static_cast<int>(sizeof(T)), PIECES = 64 * 64 / (32 * E), KP = 64 / E;
+        typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+        const int rr = tid & 31;
+#pragma unroll
+        for (int u = 0; u < PIECES / 8; ++u) {
+            const int piece = (tid >> 5) + 8 * u, row = piece / KP * 32 + rr, k = piece % KP * E;
+            *reinterpret_cast<vec*>(static_cast<T*>(a.bsh) + bsh_index_wf1<T>(o0 + k, f0 + row)) = *reinterpret_cast<const vec*>(&tile[row][k]);   // rows f, k = o
+            vec val;                                                                                                                         // rows o, k = f
+#pragma unroll
+            for (int j = 0; j < E; ++j) val[j] = tile[k + j][row];
+            *reinterpret_cast<vec*>(static_cast<T*>(a.sh) + kOffWf1 + frag_index<T>(o0 + row, f0 + k, 3136)) = val;
+        }
+        return;
+    }
+    block -= kRmsFc1Tiles;
     if (block < flat_blocks_) {
-        const size_t n_flat = a.off.total - static_cast<size_t>(512) * 3136;
-        const size_t n4 = n_flat / 4;
+        const size_t n = a.off.total - kOffWf2, n4 = n / 4;   // fc2's weights and biases: the end of the blob, 4-aligned
         const size_t i = block * static_cast<size_t>(256) + tid;
-        auto to_blob = [&](size_t f) { return f < wf1_ ? f : f + static_cast<size_t>(512) * 3136; };
         if (i < n4) {
-            const size_t e = to_blob(4 * i);
-            if (hidden_bias_layer(a.off, e) >= 0) return;   // bias vectors are 4-aligned: handled by the bias blocks
-            if (e < a.off.b1 || (e >= a.off.w2 && e < a.off.b2) || (e >= a.off.w3 && e < a.off.b3)) return;   // conv weights: the blocks above
+            const size_t e = kOffWf2 + 4 * i;
             float4 th = *reinterpret_cast<float4*>(theta_ + e);
             const float4 g = *reinterpret_cast<const float4*>(grad_ + e);
             float4 vv = *reinterpret_cast<float4*>(v_ + e);
@@ -659,26 +694,23 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
             *reinterpret_cast<float4*>(theta_ + e) = th;
             *reinterpret_cast<float4*>(v_ + e) = vv;
             if (a.centered) *reinterpret_cast<float4*>(m_ + e) = mm;
-            publish<T>(a, e, th.x);
-            publish<T>(a, e + 1, th.y);
-            publish<T>(a, e + 2, th.z);
-            publish<T>(a, e + 3, th.w);
-        } else if (i < n4 + (n_flat - 4 * n4)) {
-            const size_t e = to_blob(4 * n4 + (i - n4));
+            store4<T>(static_cast<T*>(a.sh) + e, th.x, th.y, th.z, th.w);
+        } else if (i < n4 + (n - 4 * n4)) {
+            const size_t e = kOffWf2 + 4 * n4 + (i - n4);
             float th = theta_[e], vv = v_[e], mm = m_[e];
             rms_update(a, th, grad_[e], vv, mm);
             theta_[e] = th;
             v_[e] = vv;
             if (a.centered) m_[e] = mm;
-            publish<T>(a, e, th);
+            static_cast<T*>(a.sh)[e] = from_float<T>(th);
         }
         return;
     }
-    if (block >= flat_blocks_ + fc1_tiles_) {
+    {
         // hidden-layer biases: finish the gradient, then update.  Eight adjacent lanes share a channel: lane j
         // adds chunks j, j + 8, ... in order, then the eight sums meet in a fixed tree -- a large batch has
         // hundreds of chunks and one lane walking them alone was the tail of this kernel.
-        const int idx = (block - flat_blocks_ - fc1_tiles_) * 256 + tid;
+        const int idx = (block - flat_blocks_) * 256 + tid;
         const int ch = idx / kRmsBiasLanes, j = idx % kRmsBiasLanes;
         const bool live = ch < 32 + 64 + 64 + 512;
         int layer = 3, c = 0;
@@ -696,7 +728,7 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
         g += __shfl_down(g, 2, kRmsBiasLanes);
         g += __shfl_down(g, 1, kRmsBiasLanes);
         if (!live || j != 0) return;
-        const_cast<float*>(grad_)[e] = g;
+        grad_[e] = g;
         float th = theta_[e], vv = v_[e], mm = m_[e];
         rms_update(a, th, g, vv, mm);
         theta_[e] = th;
@@ -704,59 +736,6 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, const float
         if (a.centered) m_[e] = mm;
         static_cast<T*>(a.sh)[e] = from_float<T>(th);
         return;
-    }
-    // fc1.w tile: rows o0 .. o0+31, columns f0 .. f0+63
-    const int t = block - flat_blocks_;
-    const int o0 = (t / 49) * 32, f0 = (t % 49) * 64;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-        const int v4 = tid + u * 256;            // 512 float4 per tile
-        const int r = v4 / 16, c4 = (v4 % 16) * 4;
-        const size_t e = wf1_ + static_cast<size_t>(o0 + r) * 3136 + f0 + c4;
-        float4 th = *reinterpret_cast<float4*>(theta_ + e);
-        const float4 g = *reinterpret_cast<const float4*>(grad_ + e);
-        float4 vv = *reinterpret_cast<float4*>(v_ + e);
-        float4 mm = *reinterpret_cast<float4*>(m_ + e);
-        rms_update(a, th.x, g.x, vv.x, mm.x);
-        rms_update(a, th.y, g.y, vv.y, mm.y);
-        rms_update(a, th.z, g.z, vv.z, mm.z);
-        rms_update(a, th.w, g.w, vv.w, mm.w);
-        *reinterpret_cast<float4*>(theta_ + e) = th;
-        *reinterpret_cast<float4*>(v_ + e) = vv;
-        if (a.centered) *reinterpret_cast<float4*>(m_ + e) = mm;
-        tile[c4 + 0][r] = from_float<T>(th.x);
-        tile[c4 + 1][r] = from_float<T>(th.y);
-        tile[c4 + 2][r] = from_float<T>(th.z);
-        tile[c4 + 3][r] = from_float<T>(th.w);
-    }
-    __syncthreads();
-    typedef typename Vec8<T>::type V8;
-    if constexpr (sizeof(T) == 2) {
-        // Both 16-bit copies of the tile in fragment order: a copy's eight (32 rows x 8 k) pieces are 512 contiguous
-        // bytes each, one piece per 32 threads.
-        const int piece = tid >> 5, rr = tid & 31;
-        {   // backward copy, rows = f (two 32-row tiles), k = o
-            const int ft = piece >> 2, k8 = (piece & 3) * 8;
-            const V8 val = *reinterpret_cast<const V8*>(&tile[ft * 32 + rr][k8]);
-            *reinterpret_cast<V8*>(static_cast<T*>(a.bsh) + bsh_index_wf1<T>(o0 + k8, f0 + ft * 32 + rr)) = val;
-        }
-        {   // forward copy, rows = o, k = f
-            const int k8 = piece * 8;
-            V8 val;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) val[j] = tile[k8 + j][rr];
-            *reinterpret_cast<V8*>(static_cast<T*>(a.sh) + wf1_ + tower_frag_index(o0 + rr, f0 + k8, 3136)) = val;
-        }
-    } else {
-        // the same for fp32: sixteen (32 rows x 4 k) pieces of 512 contiguous bytes per copy
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int piece = (tid >> 5) + 8 * u, rr = tid & 31;
-            const int ft = piece >> 3, ob = (piece & 7) * 4, fb = piece * 4;
-            *reinterpret_cast<float4*>(static_cast<T*>(a.bsh) + bsh_index_wf1<T>(o0 + ob, f0 + ft * 32 + rr)) = *reinterpret_cast<const float4*>(&tile[ft * 32 + rr][ob]);
-            *reinterpret_cast<float4*>(static_cast<T*>(a.sh) + wf1_ + frag_index<T>(o0 + rr, f0 + fb, 3136)) =
-                make_float4(tile[fb][rr], tile[fb + 1][rr], tile[fb + 2][rr], tile[fb + 3][rr]);
-        }
     }
 }
 

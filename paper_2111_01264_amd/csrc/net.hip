@@ -136,8 +136,6 @@ struct dqn_ctx {
 namespace dqn {
 
 constexpr int kMaxFc1Slices = 49;
-// deferred split-K scratch of the three conv weight gradients
-constexpr size_t kWgMaxSplits = 64, kWgMaxSplits1 = 128;   // conv1's gradient is small: more slices are cheap
 // Reduced precision: slices per conv layer at most (conv2 / conv3 run 2 / 3 workgroups per slice, one per column block).
 // 44 and not the 64 the buffers allow: with 128 + 2 * 64 + 3 * 64 conv workgroups next to fc1's 200 tiles the grid was far
 // beyond the 512 workgroups that are resident at once and fc1's tiles started when the first conv workgroups left;
@@ -152,9 +150,6 @@ constexpr int kWgSlicesF32_1 = 128, kWgSlicesF32_2 = 64, kWgSlicesF32_3 = 44;
 // (per train step through descriptors / through assembled states: batch 32: 52.4 / 51.8 us, batch 64: 62.8 / 62.9,
 // batch 96: 64.9 / 67.1, batch 128: 68.1 / 72.0).
 constexpr int kDescMinBatch = 96;
-constexpr size_t kWgOff1 = 0, kWgOff2 = kWgMaxSplits1 * 32 * 256, kWgOff3 = kWgOff2 + kWgMaxSplits * 64 * 512;
-constexpr size_t kWgTotal = kWgOff3 + kWgMaxSplits * 64 * 576;
-
 static int alloc_ws(Workspace& ws, int cap, int groups, int A, size_t esize)
 {
     const size_t n = static_cast<size_t>(cap) * groups;
@@ -513,22 +508,6 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     bg.g_w2 = c->grad + o.wf2; bg.g_b2 = c->grad + o.bf2; bg.loss_out = loss_out; bg.loss_keep = c->loss_keep;
     const int small_blocks = bg.first_block[4] + kSmallGradsExtraBlocks;
 
-    RmsArgs ra;
-    ra.theta = c->theta; ra.grad = c->grad; ra.v = c->v; ra.m = c->m;
-    ra.sh = c->sh; ra.bsh = c->bsh; ra.off = o;
-    ra.lr = c->cfg.lr; ra.alpha = c->cfg.rms_alpha; ra.eps = c->cfg.rms_eps; ra.centered = c->cfg.centered;
-    {
-        const size_t n_flat = o.total - static_cast<size_t>(512) * 3136;
-        ra.flat_blocks = static_cast<int>((n_flat / 4 + 4 + 255) / 256);
-    }
-    ra.fc1_tiles = 16 * 49;
-    ra.bias_partial = c->bias_partial;
-    ra.wg_partial[0] = c->wg_partial + kWgOff1; ra.wg_partial[1] = c->wg_partial + kWgOff2;
-    ra.wg_partial[2] = c->wg_partial + kWgOff3;
-    for (int l = 0; l < 3; ++l) { ra.wg_splits[l] = 1; ra.wg_scale[l] = 1.f; }
-    ra.wg_scale[0] = 1.f / 255.f;   // conv1 reads raw bytes: the input scale is applied to its gradient by the optimiser
-    for (int l = 0; l < 4; ++l) { ra.bias_chunks[l] = 0; ra.bias_first[l] = 0; }
-
     // one launch: conv1/conv2/conv3/fc1 weight gradients and the small reductions.  Conv layers: split-K over samples, workgroup
     // j writes slice j (conv1's unit is half a sample, fp32: a quarter)
     WgConvArgs w1{}, w2{}, w3{};
@@ -549,6 +528,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     wg_splits[2] = split(B, kSl3, kBf16, &w3.per);
     // their bias gradients: one partial row [C_out] per slice, added in slice order by the optimiser kernel
     constexpr int kConvBiasOff = 16384;
+    static_assert(kSl1 <= static_cast<int>(kWgMaxSplits1) && kSl2 <= static_cast<int>(kWgMaxSplits) && kSl3 <= static_cast<int>(kWgMaxSplits), "slices fit their buffer");
     static_assert(kConvBiasOff + kSl1 * 32 + (kSl2 + kSl3) * 64 <= 65536, "bias partials fit their buffer");
     bias_first[0] = kConvBiasOff;
     bias_first[1] = bias_first[0] + kSl1 * 32;
@@ -588,10 +568,16 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     DQN_LAUNCH_CHECK();
     {
         const ProfPair pr = prof_pair(c, K_RMSPROP);
-        for (int l = 0; l < 3; ++l) ra.wg_splits[l] = wg_splits[l];
+        RmsArgs ra;
+        ra.theta = c->theta; ra.grad = c->grad; ra.v = c->v; ra.m = c->m;
+        ra.sh = c->sh; ra.bsh = c->bsh; ra.off = o;
+        ra.lr = c->cfg.lr; ra.alpha = c->cfg.rms_alpha; ra.eps = c->cfg.rms_eps; ra.centered = c->cfg.centered;
+        ra.bias_partial = c->bias_partial;
         for (int l = 0; l < 4; ++l) { ra.bias_chunks[l] = bias_chunks[l]; ra.bias_first[l] = bias_first[l]; }
-        launch_timed(rmsprop_kernel<T>, dim3(kRmsConvBlocks + ra.flat_blocks + ra.fc1_tiles + kRmsBiasBlocks), dim3(256), 0, st, pr.begin, pr.end, ra.theta,
-                     ra.grad, ra.v, ra.m, ra.flat_blocks, ra.fc1_tiles, ra.off.wf1, ra);
+        const int flat_blocks = static_cast<int>(((o.total - o.wf2) / 4 + 4 + 255) / 256);
+        const uint32_t splits = static_cast<uint32_t>(wg_splits[0] | wg_splits[1] << 8 | wg_splits[2] << 16);   // at most 128, 64, 64
+        launch_timed(rmsprop_kernel<T>, dim3(kRmsFc1Tiles + kRmsConvBlocks + flat_blocks + kRmsBiasBlocks), dim3(256), 0, st, pr.begin, pr.end, ra.theta, ra.grad, ra.v, ra.m,
+                     static_cast<const float*>(c->wg_partial), splits, flat_blocks, ra);
         DQN_LAUNCH_CHECK();
     }
     return DQN_OK;
