@@ -4,6 +4,8 @@
 
 namespace dqn {
 
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+
 template <typename T> __device__ inline void store4(T* dst, float a, float b, float c, float d);
 template <> __device__ inline void store4<float>(float* dst, float a, float b, float c, float d)
 {

@@ -92,7 +92,7 @@ constexpr int kHeadRows = 2;
 
 struct HeadArgs {
     const float* partial;        // [groups][slices][rows][512]
-    int slices, rows, A, groups;
+    int slices, rows, A;
     int head_blocks;             // workgroups of the head proper (the first ones of the grid)
     const float* b1[3];
     const void* w2[3];           // T [A][512]
@@ -103,7 +103,6 @@ struct HeadArgs {
     int32_t* actions;
     float* q_out;                // [rows][A] or null
     // train step
-    int double_dqn;
     const int32_t* act;
     const float* rew;
     const float* done;
@@ -123,22 +122,37 @@ struct HeadArgs {
     GatherPlan gather;
 };
 
-constexpr int kHeadAct = 0, kHeadTrain = 1;
+// fc2's operands for the 16x16 matrix instructions: a step is 16 rows x KS contraction elements, each lane holding E consecutive ones.
+template <typename T> struct HeadMma;
+template <> struct HeadMma<bf16_t> {
+    typedef bf16x8 vec;
+    static constexpr int KS = 32, E = 8;
+    __device__ static void mma(f32x4v& acc, const vec& w, const vec& h) { acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, h, acc, 0, 0, 0); }
+};
+template <> struct HeadMma<float> {
+    typedef f32x4v vec;
+    static constexpr int KS = 16, E = 4;
+    __device__ static void mma(f32x4v& acc, const vec& w, const vec& h)
+    {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[e], h[e], acc, 0, 0, 0);
+    }
+};
 
-// The leading scalar parameters repeat HeadArgs::partial, slices, rows, A, groups, head_blocks, w2[0], b1[0], b2[0] and
-// epsilon: the kernel arguments' first 14 dwords are preloaded into scalar registers when a wavefront starts (see
-// conv_tower_kernel); everything else is read from the struct.
-template <typename T, int MODE>
-__global__ __launch_bounds__(256) void head_fwd_kernel(const float* partial_, int slices_, int rows_, int A_, int groups_, int head_blocks_,
+// G: problems (act step: 1, else train step: 2, with Double DQN 3); NTA: 16-action tiles (1 for A <= 16, else 2).  The leading scalar parameters repeat HeadArgs::partial, slices, rows, A,
+// head_blocks, w2[0], b1[0], b2[0] and epsilon: the kernel arguments' first 14 dwords are preloaded into scalar registers when a
+// wavefront starts (see conv_tower_kernel); everything else is read from the struct.
+template <typename T, int G, int NTA>
+__global__ __launch_bounds__(256, sizeof(T) == 4 && G == 3 && NTA == 2 ? 1 : 2) void head_fwd_kernel(const float* partial_, int slices_, int rows_, int A_, int head_blocks_,
                                                        const void* w2_0_, const float* b1_0_, const float* b2_0_, float epsilon_, HeadArgs a)
 {
-    typedef typename Vec8<T>::type V8;
-    constexpr int G = MODE == kHeadAct ? 1 : 3;
-    constexpr int LDH = 512 + 8;
+    typedef HeadMma<T> M;
+    typedef typename M::vec V;
+    constexpr bool TRAIN = G > 1;
+    constexpr int LDH = 512 + 8, STEPS = 128 / M::KS;
     __shared__ __attribute__((aligned(32))) T s_h[G][kHeadRows][LDH];
-    __shared__ float s_red[G][4][16][64];   // fc2 partial accumulators: [group][k-quarter wavefront][slot][lane]
-    __shared__ float s_dq[kHeadRows];
-    if constexpr (MODE == kHeadTrain) {
+    __shared__ __attribute__((aligned(16))) float s_red[G][4][kHeadRows][16 * NTA];   // fc2 partial sums: [group][k-quarter wavefront][row][action]
+    if constexpr (TRAIN) {
         if (static_cast<int>(blockIdx.x) >= head_blocks_) {
             const int i = static_cast<int>(blockIdx.x) - head_blocks_;
             if (a.desc_out) {
@@ -151,131 +165,128 @@ __global__ __launch_bounds__(256) void head_fwd_kernel(const float* partial_, in
     float h0[4] = {0.f, 0.f, 0.f, 0.f};   // this thread's four features of h (online pass on s)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row0 = blockIdx.x * kHeadRows;
-    const int lr = lane & 31, kg = lane >> 5;
-    const int arow = lr < A_ ? lr : A_ - 1;
-
-    // Every global operand is requested here, before anything waits: a cold round trip to memory costs
-    // over a microsecond, and the stages below would otherwise pay one each (fc2's bias, the transition's
-    // reward / terminal flag / action, the taken action's row of W2).
+    const int lq = lane & 15, kq = lane >> 4;
     const int hr = tid >> 7, hf0 = (tid & 127) * 4;                 // stage (1) and the dzh epilogue: row, features
     const int hrow = row0 + hr < rows_ ? row0 + hr : rows_ - 1;
-    const int trow_ = lane >> 5;                                      // tail: row of this lane
-    const int trow_c = row0 + trow_ < rows_ ? row0 + trow_ : rows_ - 1;
-    int act_taken = 0, act_tail = 0;
+    const int trow = lane >> 5, tk = lane & 31, tkc = tk < A_ ? tk : A_ - 1;   // tail: row, action of this lane
+    const int trow_c = row0 + trow < rows_ ? row0 + trow : rows_ - 1;
+
+    // Every global operand is requested here, before anything waits (a cold round trip to memory costs over a microsecond), in the
+    // order in which they are needed, and first those whose addresses came with the wavefront: fc1's slices of ALL groups, fc2's
+    // weights, the biases; then what the struct's pointers lead to (a load of them stands in front of every later request).
+    const size_t sstride = static_cast<size_t>(rows_) * 512, gstride = sstride * slices_;
+    const float* p0 = partial_ + static_cast<size_t>(hrow) * 512 + hf0;
+    float4 v[G][7];
+    auto fetch_slices = [&](int s0) {   // seven at a time from a clamped row and slice: no load is ever skipped
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int u = 0; u < 7; ++u) v[g][u] = *reinterpret_cast<const float4*>(p0 + g * gstride + static_cast<size_t>(min(s0 + u, slices_ - 1)) * sstride);
+    };
+    fetch_slices(0);
+    float4 b1v[G];
+    b1v[0] = *reinterpret_cast<const float4*>(b1_0_ + hf0);
+    V wf[G][NTA][STEPS];
+    auto fetch_w2 = [&](int g, const void* w2) {
+#pragma unroll
+        for (int ta = 0; ta < NTA; ++ta) {
+            const T* wp = static_cast<const T*>(w2) + static_cast<size_t>(min(ta * 16 + lq, A_ - 1)) * 512 + wave * 128 + kq * M::E;
+#pragma unroll
+            for (int s = 0; s < STEPS; ++s) wf[g][ta][s] = *reinterpret_cast<const V*>(wp + s * M::KS);
+        }
+    };
+    fetch_w2(0, w2_0_);
+    float b2_tail[G];
+    b2_tail[0] = b2_0_[tkc];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int g = 1; g < G; ++g) {
+        b1v[g] = *reinterpret_cast<const float4*>(a.b1[g] + hf0);
+        fetch_w2(g, a.w2[g]);
+        b2_tail[g] = a.b2[g][tkc];
+    }
+    int act_tail = 0;
     float rew_tail = 0.f, done_tail = 0.f;
     bool act_ok = true;   // tail: the stored action of this lane's row lies in [0, A)
-    if constexpr (MODE == kHeadTrain) {
+    float4 w2row = make_float4(0.f, 0.f, 0.f, 0.f);   // the taken action's row of W2 at this thread's features
+    Philox4 draw{};       // act step: the exploration draw of this lane's row
+    if constexpr (TRAIN) {
         // A stored action outside [0, A) (replay_sample_gather marks a row it could not assemble with -1) must not
         // address anything: such a row gets loss 0 and gradient 0, and every index derived from it is clamped.
-        act_taken = a.act[hrow];
-        act_taken = static_cast<unsigned>(act_taken) < static_cast<unsigned>(A_) ? act_taken : 0;
+        int act_taken = a.act[hrow];
         act_tail = a.act[trow_c];
-        act_ok = static_cast<unsigned>(act_tail) < static_cast<unsigned>(A_);
-        act_tail = act_ok ? act_tail : 0;
         rew_tail = a.rew[trow_c];
         done_tail = a.done[trow_c];
+        __builtin_amdgcn_sched_barrier(0);
+        act_taken = static_cast<unsigned>(act_taken) < static_cast<unsigned>(A_) ? act_taken : 0;
+        act_ok = static_cast<unsigned>(act_tail) < static_cast<unsigned>(A_);
+        act_tail = act_ok ? act_tail : 0;
+        float w[4];
+        load4<T>(static_cast<const T*>(w2_0_) + static_cast<size_t>(act_taken) * 512 + hf0, w);   // used last of all
+        w2row = make_float4(w[0], w[1], w[2], w[3]);
+    } else {
+        draw = philox_draw(a.seed, kTagAct, a.act_step, static_cast<uint32_t>(row0 + trow));
+        // computed HERE, under the slices' latency (left alone, the compiler moves the ten rounds into the
+        // tail, where only lane 0 of a row uses them and nothing hides them)
+        asm volatile("" :: "v"(draw.x[0]), "v"(draw.x[1]));
     }
-    Philox4 draw{};   // act step: the exploration draw of this lane's row
-    float b2_tail[G];   // fc2 bias of this lane's action in the tail (which reads its Q values straight from the partials)
-#pragma unroll
-    for (int g = 0; g < G; ++g) b2_tail[g] = (g == 0 || g >= groups_ ? b2_0_ : a.b2[g])[(lane & 31) < A_ ? (lane & 31) : A_ - 1];   // never skipped
-    __builtin_amdgcn_sched_barrier(0);
-    // fc2 weight fragments of every group: consumed last
-    V8 wf[G][8];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-        if (g < groups_) {
-            const T* wp = static_cast<const T*>(g == 0 ? w2_0_ : a.w2[g]) + static_cast<size_t>(arow) * 512 + wave * 128 + kg * 8;
-#pragma unroll
-            for (int s = 0; s < 8; ++s) wf[g][s] = *reinterpret_cast<const V8*>(wp + s * 16);
-        }
-
-    float4 b1v[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-        if (g < groups_) b1v[g] = *reinterpret_cast<const float4*>((g == 0 ? b1_0_ : a.b1[g]) + hf0);
-    float4 w2row = make_float4(0.f, 0.f, 0.f, 0.f);   // train step: the taken action's row of W2 at this thread's features
     __builtin_amdgcn_sched_barrier(0);
 
-    // (1) finish fc1: thread -> (row r = tid / 128, features 4 * (tid % 128) .. + 3).  The slices of ALL groups are
-    // requested before any is added (group by group, each group's sum waited for its own round trip), from a clamped
-    // row (no load is ever skipped); what depends on an earlier load (the taken action's row of W2) or on nothing
-    // (the exploration draw) follows the requests and is covered by their latency.
+    // (1) finish fc1: thread -> (row r = tid / 128, features 4 * (tid % 128) .. + 3), slices added in slice order
     {
-        const int r = hr, f0 = hf0;
-        const int row = row0 + r;
-        const size_t sstride = static_cast<size_t>(rows_) * 512, gstride = sstride * slices_;
-        const float* p0 = partial_ + static_cast<size_t>(hrow) * 512 + f0;
+        const int row = row0 + hr;
         float4 acc[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) acc[g] = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int s0 = 0; s0 < slices_; s0 += 7) {
-            float4 v[G][7];
+            if (s0 != 0) fetch_slices(s0);
 #pragma unroll
             for (int g = 0; g < G; ++g)
-                if (g < groups_) {
 #pragma unroll
-                    for (int u = 0; u < 7; ++u) {
-                        const int sl = s0 + u < slices_ ? s0 + u : slices_ - 1;
-                        v[g][u] = *reinterpret_cast<const float4*>(p0 + g * gstride + sl * sstride);
-                    }
-                }
-            __builtin_amdgcn_sched_barrier(0);
-            if (s0 == 0) {
-                if constexpr (MODE == kHeadTrain) {
-                    float w[4];
-                    load4<T>(static_cast<const T*>(w2_0_) + static_cast<size_t>(act_taken) * 512 + hf0, w);
-                    w2row = make_float4(w[0], w[1], w[2], w[3]);
-                } else {
-                    draw = philox_draw(a.seed, kTagAct, a.act_step, static_cast<uint32_t>(row0 + trow_));
-                    // computed HERE, under the slices' latency (left alone, the compiler moves the ten rounds into the
-                    // tail, where only lane 0 of a row uses them and nothing hides them)
-                    asm volatile("" :: "v"(draw.x[0]), "v"(draw.x[1]));
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                if (g < groups_) {
-#pragma unroll
-                    for (int u = 0; u < 7; ++u)
-                        if (s0 + u < slices_) { acc[g].x += v[g][u].x; acc[g].y += v[g][u].y; acc[g].z += v[g][u].z; acc[g].w += v[g][u].w; }
-                }
+                for (int u = 0; u < 7; ++u)
+                    if (s0 + u < slices_) { acc[g].x += v[g][u].x; acc[g].y += v[g][u].y; acc[g].z += v[g][u].z; acc[g].w += v[g][u].w; }
         }
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-            if (g < groups_) {
-                const float4 bv = b1v[g];
-                const float4 hv = make_float4(fmaxf(acc[g].x + bv.x, 0.f), fmaxf(acc[g].y + bv.y, 0.f), fmaxf(acc[g].z + bv.z, 0.f),
-                                              fmaxf(acc[g].w + bv.w, 0.f));
-                store4<T>(&s_h[g][r][f0], hv.x, hv.y, hv.z, hv.w);   // a row past the batch repeats the last one; nobody reads its Q
-                if (MODE == kHeadTrain && g == 0) {
-                    h0[0] = hv.x; h0[1] = hv.y; h0[2] = hv.z; h0[3] = hv.w;
-                    if (row < rows_)
-                        store4<T>(static_cast<T*>(a.h_online) + static_cast<size_t>(row) * 512 + f0, hv.x, hv.y, hv.z, hv.w);
-                }
+        for (int g = 0; g < G; ++g) {
+            const float4 bv = b1v[g];
+            const float4 hv = make_float4(fmaxf(acc[g].x + bv.x, 0.f), fmaxf(acc[g].y + bv.y, 0.f), fmaxf(acc[g].z + bv.z, 0.f),
+                                          fmaxf(acc[g].w + bv.w, 0.f));
+            store4<T>(&s_h[g][hr][hf0], hv.x, hv.y, hv.z, hv.w);   // a row past the batch repeats the last one; nobody reads its Q
+            if (TRAIN && g == 0) {
+                h0[0] = hv.x; h0[1] = hv.y; h0[2] = hv.z; h0[3] = hv.w;
+                if (row < rows_)
+                    store4<T>(static_cast<T*>(a.h_online) + static_cast<size_t>(row) * 512 + hf0, hv.x, hv.y, hv.z, hv.w);
             }
+        }
     }
     __syncthreads();
-    // (2) fc2 per group: every wavefront's k-quarter of the accumulator goes to LDS, one barrier for all groups
+    // (2) fc2: W2 rows (actions) x h columns on the 16x16 instruction; only columns 0 and 1 -- this workgroup's rows -- mean anything
+    // (the others repeat them).  The groups' accumulation chains are independent and run side by side; every wavefront's k-quarter
+    // goes to LDS, one barrier for all groups.
+    {
+        f32x4v acc[G][NTA];
 #pragma unroll
-    for (int g = 0; g < G; ++g)
-        if (g < groups_) {
-            f32x16 acc;
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+            for (int ta = 0; ta < NTA; ++ta) acc[g][ta] = f32x4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int s = 0; s < 8; ++s) {
-                V8 hf = vec8_zero<T>();
-                if (lr < kHeadRows) hf = *reinterpret_cast<const V8*>(&s_h[g][lr][wave * 128 + s * 16 + kg * 8]);
-                mma_32x32x16(acc, wf[g][s], hf);
+        for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const V hf = *reinterpret_cast<const V*>(&s_h[g][lq & 1][wave * 128 + s * M::KS + kq * M::E]);
+#pragma unroll
+                for (int ta = 0; ta < NTA; ++ta) M::mma(acc[g][ta], wf[g][ta][s], hf);
             }
+        if (lq < kHeadRows) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) s_red[g][wave][v][lane] = acc[v];
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int ta = 0; ta < NTA; ++ta) *reinterpret_cast<f32x4v*>(&s_red[g][wave][lq][ta * 16 + 4 * kq]) = acc[g][ta];
         }
+    }
     __syncthreads();
 
-    // Tail: wavefront 0, 32 lanes per row (kHeadRows = 2), lane k owns action k.  argmax with the lowest index
+    // Tail: 32 lanes per row (kHeadRows = 2), lane k owns action k.  argmax with the lowest index
     // among equal values (the tie rule of the greedy policy, Section 2.1), as a butterfly over the 32 lanes.
     static_assert(kHeadRows == 2 && kMaxActions <= 32, "tail layout: one wavefront, 32 lanes per row");
     // "Better" is a total order on (value, index), so the pairs may meet in any tree: inside a row of sixteen lanes through
@@ -302,16 +313,10 @@ __global__ __launch_bounds__(256) void head_fwd_kernel(const float* partial_, in
         meet(__builtin_bit_cast(float, hv), hb);
         return best;
     };
-    const int trow = lane >> 5, tk = lane & 31;    // tail row / action of this lane (wavefront 0 only)
     const float kNegInf = -__builtin_huge_valf();
-    // Q_g(row trow, action tk): accumulator layout is sample lane % 32, action 8*(v/4) + 4*(lane/32) + (v%4); the four
-    // k-quarter partials of that slot are added in wavefront order, then the bias
-    const int tkc = tk < A_ ? tk : A_ - 1;
-    const int qslot = 4 * (tkc >> 3) + (tkc & 3), qsrc = ((tkc >> 2) & 1) * 32 + trow;
-    auto q_of = [&](int g) {
-        return (((s_red[g][0][qslot][qsrc] + s_red[g][1][qslot][qsrc]) + s_red[g][2][qslot][qsrc]) + s_red[g][3][qslot][qsrc]) + b2_tail[g];
-    };
-    if constexpr (MODE == kHeadAct) {
+    // Q_g(row trow, action tk): the four k-quarter partials are added in wavefront order, then the bias
+    auto q_of = [&](int g) { return (((s_red[g][0][trow][tkc] + s_red[g][1][trow][tkc]) + s_red[g][2][trow][tkc]) + s_red[g][3][trow][tkc]) + b2_tail[g]; };
+    if constexpr (!TRAIN) {
         if (wave != 0) return;
         const int row = row0 + trow;
         const float qv = tk < A_ ? q_of(0) : kNegInf;
@@ -325,46 +330,38 @@ __global__ __launch_bounds__(256) void head_fwd_kernel(const float* partial_, in
             a.actions[row] = act;
         }
     } else {
+        __shared__ float s_dq[kHeadRows];
         if (wave == 0) {
+            const float q0 = q_of(0), q1 = q_of(1);
+            const float q2 = G > 2 ? q_of(G - 1) : 0.f;   // Double DQN: Q(s', .; theta) selects the action
+            const int astar = argmax_lowest(tk < A_ ? (G > 2 ? q2 : q1) : kNegInf, tk);
             const int row = row0 + trow;
             const bool live = row < rows_;
-            const float q0 = q_of(0), q1 = q_of(1);
-            const float q2 = groups_ > 2 ? q_of(G - 1) : 0.f;   // Double DQN: Q(s', .; theta) selects the action
-            const float qt = tk < A_ ? q1 : kNegInf;
-            const float qsel = a.double_dqn ? (tk < A_ ? q2 : kNegInf) : qt;
-            const int astar = argmax_lowest(qsel, tk);
             if (live && tk < A_) {
-                a.q_all[(static_cast<size_t>(0) * rows_ + row) * A_ + tk] = q0;
-                a.q_all[(static_cast<size_t>(1) * rows_ + row) * A_ + tk] = q1;
-                if (groups_ > 2) a.q_all[(static_cast<size_t>(2) * rows_ + row) * A_ + tk] = q2;
+                float* q = a.q_all + static_cast<size_t>(row) * A_ + tk;
+                const size_t gs = static_cast<size_t>(rows_) * A_;
+                q[0] = q0;
+                q[gs] = q1;
+                if (G > 2) q[2 * gs] = q2;
             }
             // the two values the TD error needs sit in other lanes of this row: Q(s', a*; theta^-) and Q(s, a_b; theta)
             const float q1_star = __shfl(q1, astar, 32), q0_taken = __shfl(q0, act_tail, 32);
             if (tk == 0) {
-                float dq = 0.f;
-                int act_b = 0;
-                if (live && !act_ok) { a.lossv[row] = 0.f; a.dqv[row] = 0.f; }
-                if (live && act_ok) {
-                    const float y = rew_tail + a.gamma * (1.f - done_tail) * q1_star;
-                    act_b = act_tail;
-                    const float delta = q0_taken - y;
-                    const float ad = fabsf(delta);
-                    a.lossv[row] = ad <= a.huber ? 0.5f * delta * delta : a.huber * (ad - 0.5f * a.huber);
-                    dq = fminf(fmaxf(delta, -a.huber), a.huber) / static_cast<float>(rows_);
-                    a.dqv[row] = dq;
-                }
+                const float y = rew_tail + a.gamma * (1.f - done_tail) * q1_star;
+                const float delta = q0_taken - y, ad = fabsf(delta);
+                const float loss = act_ok ? (ad <= a.huber ? 0.5f * delta * delta : a.huber * (ad - 0.5f * a.huber)) : 0.f;
+                const float dq = act_ok ? fminf(fmaxf(delta, -a.huber), a.huber) / static_cast<float>(rows_) : 0.f;
                 s_dq[trow] = dq;
+                if (live) { a.lossv[row] = loss; a.dqv[row] = dq; }
             }
         }
         __syncthreads();
         // fc2's data gradient through fc1's ReLU for this workgroup's rows: dQ has one non-zero per row
-        const int r = tid >> 7, f0 = (tid & 127) * 4;
-        const int row = row0 + r;
+        const int row = row0 + hr;
         if (row < rows_) {
-            const float w[4] = {w2row.x, w2row.y, w2row.z, w2row.w};
-            const float dq = s_dq[r];
-            store4<T>(static_cast<T*>(a.dzh) + static_cast<size_t>(row) * 512 + f0, h0[0] > 0.f ? dq * w[0] : 0.f,
-                      h0[1] > 0.f ? dq * w[1] : 0.f, h0[2] > 0.f ? dq * w[2] : 0.f, h0[3] > 0.f ? dq * w[3] : 0.f);
+            const float dq = s_dq[hr];
+            store4<T>(static_cast<T*>(a.dzh) + static_cast<size_t>(row) * 512 + hf0, h0[0] > 0.f ? dq * w2row.x : 0.f,
+                      h0[1] > 0.f ? dq * w2row.y : 0.f, h0[2] > 0.f ? dq * w2row.z : 0.f, h0[3] > 0.f ? dq * w2row.w : 0.f);
         }
     }
 }

@@ -370,13 +370,14 @@ static int act_impl(dqn_ctx* c, Workspace& ws, const uint8_t* states, int W, flo
     const int rc = forward_to_fc1<T>(c, c->act_stream, ws, 1, x, shadow, master, W, false, &slices, push);
     if (rc != DQN_OK) return rc;
     HeadArgs ha{};
-    ha.partial = ws.partial; ha.slices = slices; ha.rows = W; ha.A = c->A; ha.groups = 1;
+    ha.partial = ws.partial; ha.slices = slices; ha.rows = W; ha.A = c->A;
     ha.b1[0] = master[0] + c->off.bf1; ha.w2[0] = static_cast<const T*>(shadow[0]) + c->off.wf2; ha.b2[0] = master[0] + c->off.bf2;
     ha.epsilon = epsilon; ha.seed = c->cfg.seed; ha.act_step = act_step; ha.actions = actions; ha.q_out = q_out;
     ha.head_blocks = (W + kHeadRows - 1) / kHeadRows;
     ha.gather.B = 0;
-    hipLaunchKernelGGL((head_fwd_kernel<T, kHeadAct>), dim3(ha.head_blocks), dim3(256), 0, c->act_stream, ha.partial, ha.slices, ha.rows, ha.A, ha.groups,
-                       ha.head_blocks, ha.w2[0], ha.b1[0], ha.b2[0], ha.epsilon, ha);
+    auto kern = c->A <= 16 ? head_fwd_kernel<T, 1, 1> : head_fwd_kernel<T, 1, 2>;
+    hipLaunchKernelGGL(kern, dim3(ha.head_blocks), dim3(256), 0, c->act_stream, ha.partial, ha.slices, ha.rows, ha.A, ha.head_blocks,
+                       ha.w2[0], ha.b1[0], ha.b2[0], ha.epsilon, ha);
     DQN_LAUNCH_CHECK();
     return DQN_OK;
 }
@@ -413,11 +414,11 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     {
         const ProfPair pr = prof_pair(c, K_FC2_TD);
         HeadArgs ha{};
-        ha.partial = ws.partial; ha.slices = slices; ha.rows = B; ha.A = c->A; ha.groups = groups;
+        ha.partial = ws.partial; ha.slices = slices; ha.rows = B; ha.A = c->A;
         for (int g = 0; g < groups; ++g) {
             ha.b1[g] = master[g] + o.bf1; ha.w2[g] = static_cast<const T*>(shadow[g]) + o.wf2; ha.b2[g] = master[g] + o.bf2;
         }
-        ha.double_dqn = c->cfg.double_dqn; ha.act = a; ha.rew = r; ha.done = done;
+        ha.act = a; ha.rew = r; ha.done = done;
         ha.gamma = c->cfg.gamma; ha.huber = c->cfg.huber_delta;
         ha.h_online = h; ha.dzh = dzh; ha.q_all = ws.q; ha.dqv = c->dqv; ha.lossv = c->lossv;
         ha.head_blocks = (B + kHeadRows - 1) / kHeadRows;
@@ -426,8 +427,9 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         ha.desc_out = ride_desc;
         if (ride) ha.gather = *ride;
         const int riders = !ride ? 0 : (ride_desc ? (ride->B + 255) / 256 : 5 * ride->B);
-        launch_timed(head_fwd_kernel<T, kHeadTrain>, dim3(ha.head_blocks + riders), dim3(256), 0, st, pr.begin, pr.end, ha.partial, ha.slices, ha.rows, ha.A,
-                     ha.groups, ha.head_blocks, ha.w2[0], ha.b1[0], ha.b2[0], ha.epsilon, ha);
+        auto kern = groups == 2 ? (c->A <= 16 ? head_fwd_kernel<T, 2, 1> : head_fwd_kernel<T, 2, 2>) : (c->A <= 16 ? head_fwd_kernel<T, 3, 1> : head_fwd_kernel<T, 3, 2>);
+        launch_timed(kern, dim3(ha.head_blocks + riders), dim3(256), 0, st, pr.begin, pr.end, ha.partial, ha.slices, ha.rows, ha.A,
+                     ha.head_blocks, ha.w2[0], ha.b1[0], ha.b2[0], ha.epsilon, ha);
         DQN_LAUNCH_CHECK();
     }
     // ---- data-gradient chain: fc1 -> conv3 -> conv2 ------------------------------------------------
