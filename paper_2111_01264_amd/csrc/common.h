@@ -107,22 +107,61 @@ struct GatherPlan {
     int32_t B;                  // 0 = nothing to gather
 };
 
-// Global index of the transition that draw b of the call selects (or that idx_in names).
-__device__ inline int64_t sampled_index(const GatherPlan& p, int b)
+// The transition that draw b of the call selects (or that idx_in names): its global index, lane and age j in the lane, and
+// whether its five-frame window (ages j-3 .. j+1) lies in the lane.  A chain of round trips and 64-bit divisions here is what a gather
+// used to wait for: the lanes' table is read eight entries at a time (one request each for counts and heads) instead of one lane per
+// trip, the lane and age of a draw come out of the walk, and ring positions wrap by one subtraction (window_slot).
+struct SampledRow {
+    int64_t idx, j;
+    int64_t lane0, base;   // first slot of the lane; ring position of its oldest frame, in [0, 2 M)
+    bool ok;
+};
+__device__ inline SampledRow sampled_row(const GatherPlan& p, int b)
 {
-    if (p.idx_in) return p.idx_in[b];
-    const Philox4 d = philox_draw(p.seed, kTagSample, p.sample_step, static_cast<uint32_t>(b));
-    const uint64_t u = (static_cast<uint64_t>(d.x[1]) << 32) | d.x[0];
-    int64_t k = static_cast<int64_t>(__umul64hi(u, static_cast<uint64_t>(p.V)));
+    SampledRow r;
+    int32_t count = 0, head = 0;
     int lane = 0;
-    for (;;) {
-        const int64_t v = p.tab.count[lane] > 4 ? p.tab.count[lane] - 4 : 0;
-        if (k < v || lane == p.L - 1) break;
-        k -= v;
-        ++lane;
+    if (p.idx_in) {
+        r.idx = p.idx_in[b];
+        r.ok = r.idx >= 0 && r.idx < static_cast<int64_t>(p.L) * p.M;
+        lane = r.ok ? static_cast<int>(r.idx / p.M) : 0;
+        r.j = r.ok ? r.idx - lane * p.M : 0;
+        count = p.tab.count[lane];
+        head = p.tab.head[lane];
+    } else {
+        const Philox4 d = philox_draw(p.seed, kTagSample, p.sample_step, static_cast<uint32_t>(b));
+        const uint64_t u = (static_cast<uint64_t>(d.x[1]) << 32) | d.x[0];
+        int64_t k = static_cast<int64_t>(__umul64hi(u, static_cast<uint64_t>(p.V)));
+        bool found = false;
+        for (int l0 = 0; l0 < p.L; l0 += 8) {   // (the table has kMaxLanes entries, a multiple of eight)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int l = l0 + q;
+                const int32_t c = p.tab.count[l], hd = p.tab.head[l];
+                const int64_t v = c > 4 ? c - 4 : 0;
+                const bool here = !found && l < p.L && (k < v || l == p.L - 1);
+                if (here) { lane = l; count = c; head = hd; }
+                else if (!found) k -= v;
+                found = found || here;
+            }
+        }
+        r.j = 3 + k;
+        r.idx = lane * p.M + r.j;
+        r.ok = true;
     }
-    return lane * p.M + 3 + k;
+    r.ok = r.ok && r.j >= 3 && r.j <= static_cast<int64_t>(count) - 2;
+    r.lane0 = lane * p.M;
+    r.base = static_cast<int64_t>(head) - count + p.M;
+    return r;
 }
+// Slot of the frame of age j - 3 + u of a valid row, 0 <= u <= 4: head + M - 1 is the newest frame's position before the wrap, so one
+// subtraction wraps.
+__device__ inline int64_t window_slot(const GatherPlan& p, const SampledRow& r, int u)
+{
+    const int64_t at = r.base + r.j - 3 + u;
+    return r.lane0 + (at >= p.M ? at - p.M : at);
+}
+static_assert(kMaxLanes % 8 == 0, "whole trips over the lanes' table");
 
 // The minibatch row of sample b as a DESCRIPTOR instead of copied frames: desc[0..3] = replay slots of the four frames
 // of s, desc[4..7] = those of s', -1 for a frame that is all zeros (a terminal flag lies between it and the stack's
@@ -132,30 +171,22 @@ __device__ inline int64_t sampled_index(const GatherPlan& p, int b)
 constexpr int kDescInts = 8;
 __device__ inline void sample_desc(const GatherPlan& p, int b, int32_t* __restrict__ desc)
 {
-    const int64_t idx = sampled_index(p, b);
-    bool ok = idx >= 0 && idx < static_cast<int64_t>(p.L) * p.M;
-    int lane = 0;
-    int64_t j = 0;
-    if (ok) {
-        lane = static_cast<int>(idx / p.M);
-        j = idx % p.M;
-        ok = j >= 3 && j <= static_cast<int64_t>(p.tab.count[lane]) - 2;
-    }
-    if (p.idx_out) p.idx_out[b] = idx;
-    if (!ok) {
+    const SampledRow row = sampled_row(p, b);
+    if (p.idx_out) p.idx_out[b] = row.idx;
+    if (!row.ok) {
 #pragma unroll
         for (int f = 0; f < kDescInts; ++f) desc[f] = -1;
         p.a[b] = -1; p.r[b] = 0.f; p.done[b] = 0.f;
         return;
     }
-    const int64_t base = static_cast<int64_t>(p.tab.head[lane]) - p.tab.count[lane] + p.M;  // >= 0
-    const int64_t lane0 = lane * p.M;
-    uint32_t t[4];   // terminal flags of ages j-3 .. j
-#pragma unroll
-    for (int u = 0; u < 4; ++u) t[u] = p.terminals[lane0 + (base + j - 3 + u) % p.M];
     int32_t slot[5];
 #pragma unroll
-    for (int f = 0; f < 5; ++f) slot[f] = static_cast<int32_t>(lane0 + (base + j - 3 + f) % p.M);
+    for (int f = 0; f < 5; ++f) slot[f] = static_cast<int32_t>(window_slot(p, row, f));
+    const int32_t act = p.actions[slot[3]];
+    const float rew = p.rewards[slot[3]];
+    uint32_t t[4];   // terminal flags of ages j-3 .. j
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = p.terminals[slot[u]];
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
         uint32_t any_s = 0, any_s2 = 0;
@@ -167,77 +198,64 @@ __device__ inline void sample_desc(const GatherPlan& p, int b, int32_t* __restri
         desc[f] = any_s ? -1 : slot[f];
         desc[4 + f] = any_s2 ? -1 : slot[f + 1];
     }
-    const int64_t tslot = lane0 + (base + j) % p.M;
-    p.a[b] = p.actions[tslot];
-    p.r[b] = p.rewards[tslot];
+    p.a[b] = act;
+    p.r[b] = rew;
     p.done[b] = t[3] ? 1.f : 0.f;
 }
 
-// Workgroup (frame f of the five-frame window ages j-3 .. j+1, sample b), 256 threads.  The frame is read once and
-// written into s (position f, f <= 3) and s2 (position f-1, f >= 1), each zeroed if a terminal flag lies between
-// the frame and the newest frame of that stack (Section 2.1: states are stacks of the four latest frames).
+// Workgroup (frame f of the five-frame window ages j-3 .. j+1, sample b), 256 threads.  The frame is written into s (position f,
+// f <= 3) and s2 (position f-1, f >= 1), each zeroed if a terminal flag lies between the frame and the newest frame of that
+// stack (Section 2.1: states are stacks of the four latest frames).  The chain is draw -> frame -> stores: the frame is
+// requested together with the flags that decide whether it counts, everything of it at once.
 __device__ inline void gather_block(const GatherPlan& p, int f, int b)
 {
-    const uint8_t* __restrict__ frames = p.frames; const int32_t* __restrict__ actions = p.actions;
-    const float* __restrict__ rewards = p.rewards; const uint8_t* __restrict__ terminals = p.terminals;
-    const LaneTable& tab = p.tab;
-    const int32_t L = p.L; const int64_t M = p.M, V = p.V; const uint64_t seed = p.seed, sample_step = p.sample_step;
-    const int64_t* __restrict__ idx_in = p.idx_in; uint8_t* __restrict__ s = p.s; uint8_t* __restrict__ s2 = p.s2;
-    int32_t* __restrict__ a = p.a; float* __restrict__ r = p.r; float* __restrict__ done = p.done; int64_t* __restrict__ idx_out = p.idx_out;
-    const int64_t idx = sampled_index(p, b);
-    bool ok = idx >= 0 && idx < static_cast<int64_t>(L) * M;
-    int lane = 0;
-    int64_t j = 0;
-    if (ok) {
-        lane = static_cast<int>(idx / M);
-        j = idx % M;
-        ok = j >= 3 && j <= static_cast<int64_t>(tab.count[lane]) - 2;
-    }
-    uint4* ds = (f <= 3) ? reinterpret_cast<uint4*>(s + (static_cast<int64_t>(b) * 4 + f) * kFrameBytes) : nullptr;
-    uint4* ds2 = (f >= 1) ? reinterpret_cast<uint4*>(s2 + (static_cast<int64_t>(b) * 4 + f - 1) * kFrameBytes) : nullptr;
-    const int ph = ds ? line_phase(ds) : 0, ph2 = ds2 ? line_phase(ds2) : 0;   // see copy_frame
-    if (!ok) {
-        const uint4 z = make_uint4(0, 0, 0, 0);
-        for (int v = threadIdx.x; v < kFrameVec16 + 3; v += blockDim.x) {
-            if (ds && v - ph >= 0 && v - ph < kFrameVec16) ds[v - ph] = z;
-            if (ds2 && v - ph2 >= 0 && v - ph2 < kFrameVec16) ds2[v - ph2] = z;
+    const SampledRow row = sampled_row(p, b);
+    uint4* ds = reinterpret_cast<uint4*>(p.s + (static_cast<int64_t>(b) * 4 + (f <= 3 ? f : 0)) * kFrameBytes);
+    uint4* ds2 = reinterpret_cast<uint4*>(p.s2 + (static_cast<int64_t>(b) * 4 + (f >= 1 ? f - 1 : 0)) * kFrameBytes);
+    // each destination with its own phase shift (see copy_frame): the second read of the frame comes from cache
+    const int v1 = static_cast<int>(threadIdx.x) - line_phase(ds), v2 = static_cast<int>(threadIdx.x) - line_phase(ds2);
+    static_assert(kFrameVec16 + 3 <= 512, "two vectors per thread and destination");
+    uint4 w1[2], w2[2];
+    uint32_t keep_s = 0, keep_s2 = 0;
+    if (row.ok) {   // uniform
+        uint32_t t[4];   // terminal flags of ages j-3 .. j
+#pragma unroll
+        for (int u = 0; u < 4; ++u) t[u] = p.terminals[window_slot(p, row, u)];
+        const uint4* src = reinterpret_cast<const uint4*>(p.frames + window_slot(p, row, f) * kFrameBytes);
+        auto clamped = [](int v) { return v < 0 ? 0 : (v < kFrameVec16 ? v : kFrameVec16 - 1); };
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            w1[u] = src[clamped(v1 + 256 * u)];
+            w2[u] = src[clamped(v2 + 256 * u)];
         }
         if (f == 0 && threadIdx.x == 0) {
-            a[b] = -1; r[b] = 0.f; done[b] = 0.f;
-            if (idx_out) idx_out[b] = idx;
+            const int64_t tslot = window_slot(p, row, 3);
+            p.a[b] = p.actions[tslot];
+            p.r[b] = p.rewards[tslot];
+            p.done[b] = t[3] ? 1.f : 0.f;
         }
-        return;
-    }
-    const int64_t base = static_cast<int64_t>(tab.head[lane]) - tab.count[lane] + M;  // >= 0
-    const int64_t lane0 = lane * M;
-    // terminal flags of ages j-3 .. j
-    uint32_t t[4];
+        // a frame behind a terminal flag is zeroed with a mask (a choice between the loaded vector and a zero vector made the
+        // compiler keep the zero vector in scratch memory and load through a pointer)
+        uint32_t any_s = 0, any_s2 = 0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t[u] = terminals[lane0 + (base + j - 3 + u) % M];
-    uint32_t any_s = 0, any_s2 = 0;
+        for (int u = 0; u < 4; ++u) {
+            if (u >= f && u <= 2) any_s |= t[u];
+            if (u >= f) any_s2 |= t[u];
+        }
+        keep_s = any_s ? 0u : 0xFFFFFFFFu;
+        keep_s2 = any_s2 ? 0u : 0xFFFFFFFFu;
+    } else {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        if (u >= f && u <= 2) any_s |= t[u];
-        if (u >= f) any_s2 |= t[u];
+        for (int u = 0; u < 2; ++u) w1[u] = w2[u] = make_uint4(0, 0, 0, 0);
+        if (f == 0 && threadIdx.x == 0) { p.a[b] = -1; p.r[b] = 0.f; p.done[b] = 0.f; }
     }
-    const int64_t slot = lane0 + (base + j - 3 + f) % M;
-    const uint4* src = reinterpret_cast<const uint4*>(frames + slot * kFrameBytes);
-    // a frame behind a terminal flag is zeroed with a mask (a choice between the loaded vector and a zero vector made the
-    // compiler keep the zero vector in scratch memory and load through a pointer)
-    const uint32_t keep_s = any_s ? 0u : 0xFFFFFFFFu, keep_s2 = any_s2 ? 0u : 0xFFFFFFFFu;
-    // each destination with its own phase shift; the second read of the frame comes from cache
-    for (int v = threadIdx.x; v < kFrameVec16 + 3; v += blockDim.x) {
-        const int v1 = v - ph, v2 = v - ph2;
-        if (ds && v1 >= 0 && v1 < kFrameVec16) { uint4 w = src[v1]; w.x &= keep_s; w.y &= keep_s; w.z &= keep_s; w.w &= keep_s; ds[v1] = w; }
-        if (ds2 && v2 >= 0 && v2 < kFrameVec16) { uint4 w = src[v2]; w.x &= keep_s2; w.y &= keep_s2; w.z &= keep_s2; w.w &= keep_s2; ds2[v2] = w; }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int a1 = v1 + 256 * u, a2 = v2 + 256 * u;
+        if (f <= 3 && a1 >= 0 && a1 < kFrameVec16) ds[a1] = make_uint4(w1[u].x & keep_s, w1[u].y & keep_s, w1[u].z & keep_s, w1[u].w & keep_s);
+        if (f >= 1 && a2 >= 0 && a2 < kFrameVec16) ds2[a2] = make_uint4(w2[u].x & keep_s2, w2[u].y & keep_s2, w2[u].z & keep_s2, w2[u].w & keep_s2);
     }
-    if (f == 0 && threadIdx.x == 0) {
-        const int64_t tslot = lane0 + (base + j) % M;
-        a[b] = actions[tslot];
-        r[b] = rewards[tslot];
-        done[b] = t[3] ? 1.f : 0.f;
-        if (idx_out) idx_out[b] = idx;
-    }
+    if (p.idx_out && f == 0 && threadIdx.x == 0) p.idx_out[b] = row.idx;
 }
 
 // Validates a replay_sample_gather call and fills `plan` without enqueuing anything.
