@@ -91,10 +91,13 @@ __device__ inline void push_step_block(const PushStepPlan& p, int lane)
     }
 }
 
+// The lanes as a gather sees them.  A lane of `count` visible frames holds count - 4 complete transitions (none if that is negative);
+// entries past the last lane read end = V, so that a walk over whole groups of eight needs no other bound.
 struct LaneTable {
     int32_t head[kMaxLanes];   // next write position inside the lane
-    int32_t count[kMaxLanes];  // visible frames in the lane
+    int32_t end[kMaxLanes];    // complete transitions in this lane and all before it (2^31 frames would be 15 TB)
 };
+static_assert(kMaxLanes % 8 == 0, "whole trips over the lanes' table");
 
 // One replay_sample_gather call as data for a kernel (for a caller that folds the gather into a launch of its own).
 struct GatherPlan {
@@ -108,61 +111,77 @@ struct GatherPlan {
 };
 
 // The transition that draw b of the call selects (or that idx_in names): its global index, lane and age j in the lane, and
-// whether its five-frame window (ages j-3 .. j+1) lies in the lane.  A chain of round trips and 64-bit divisions here is what a gather
-// used to wait for: the lanes' table is read eight entries at a time (one request each for counts and heads) instead of one lane per
-// trip, the lane and age of a draw come out of the walk, and ring positions wrap by one subtraction (window_slot).
+// whether its five-frame window (ages j-3 .. j+1) lies in the lane.  The chain in front of the frame's request is what a gather waits for, and
+// a read of the kernel arguments is a round trip of its own: everything is read here at once (the empty asm statements keep the
+// compiler from moving the reads to where they are used), the walk over the lanes is selects on eight entries at a time, and there is
+// no 64-bit division (ring positions wrap by one subtraction, see window_slot).
 struct SampledRow {
     int64_t idx, j;
-    int64_t lane0, base;   // first slot of the lane; ring position of its oldest frame, in [0, 2 M)
+    int64_t lane0, base, M;   // first slot of the lane; ring position of its oldest frame, in [0, 2 M); slots per lane
     bool ok;
 };
 __device__ inline SampledRow sampled_row(const GatherPlan& p, int b)
 {
     SampledRow r;
-    int32_t count = 0, head = 0;
-    int lane = 0;
-    if (p.idx_in) {
-        r.idx = p.idx_in[b];
-        r.ok = r.idx >= 0 && r.idx < static_cast<int64_t>(p.L) * p.M;
-        lane = r.ok ? static_cast<int>(r.idx / p.M) : 0;
-        r.j = r.ok ? r.idx - lane * p.M : 0;
-        count = p.tab.count[lane];
+    const uint64_t seed = p.seed, step = p.sample_step;
+    const int64_t V = p.V, M = p.M;
+    const int32_t L = p.L;
+    const int64_t* idx_in = p.idx_in;
+    int32_t e8[8], h8[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) { e8[q] = p.tab.end[q]; h8[q] = p.tab.head[q]; }
+    asm volatile("" :: "s"(seed), "s"(step), "s"(V), "s"(M), "s"(L), "s"(idx_in));
+    asm volatile("" :: "s"(e8[0]), "s"(e8[1]), "s"(e8[2]), "s"(e8[3]), "s"(e8[4]), "s"(e8[5]), "s"(e8[6]), "s"(e8[7]));
+    asm volatile("" :: "s"(h8[0]), "s"(h8[1]), "s"(h8[2]), "s"(h8[3]), "s"(h8[4]), "s"(h8[5]), "s"(h8[6]), "s"(h8[7]));
+    int32_t start = 0, end = 0, head = 0, lane = 0;
+    if (idx_in) {
+        r.idx = idx_in[b];
+        r.ok = r.idx >= 0 && r.idx < static_cast<int64_t>(L) * M;
+        lane = r.ok ? static_cast<int>(r.idx / M) : 0;
+        r.j = r.ok ? r.idx - lane * M : 0;
+        start = lane > 0 ? p.tab.end[lane - 1] : 0;
+        end = p.tab.end[lane];
         head = p.tab.head[lane];
     } else {
-        const Philox4 d = philox_draw(p.seed, kTagSample, p.sample_step, static_cast<uint32_t>(b));
+        const Philox4 d = philox_draw(seed, kTagSample, step, static_cast<uint32_t>(b));
         const uint64_t u = (static_cast<uint64_t>(d.x[1]) << 32) | d.x[0];
-        int64_t k = static_cast<int64_t>(__umul64hi(u, static_cast<uint64_t>(p.V)));
-        bool found = false;
-        for (int l0 = 0; l0 < p.L; l0 += 8) {   // (the table has kMaxLanes entries, a multiple of eight)
+        int32_t k = static_cast<int32_t>(__umul64hi(u, static_cast<uint64_t>(V)));
+        asm("" : "+v"(k));   // vector selects also where the draw is the same for a whole workgroup: scalar ones become branches
+        auto walk = [&](int l0, const int32_t (&e)[8], const int32_t (&hd)[8]) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int l = l0 + q;
-                const int32_t c = p.tab.count[l], hd = p.tab.head[l];
-                const int64_t v = c > 4 ? c - 4 : 0;
-                const bool here = !found && l < p.L && (k < v || l == p.L - 1);
-                if (here) { lane = l; count = c; head = hd; }
-                else if (!found) k -= v;
-                found = found || here;
+            for (int q = 0; q < 8; ++q) {   // lane l0 + q, if the draw lies past every lane before it
+                const bool past = k >= end;
+                start = past ? end : start;
+                head = past ? hd[q] : head;
+                lane = past ? l0 + q : lane;
+                end = past ? e[q] : end;
             }
+        };
+        walk(0, e8, h8);    // (end = 0 before the first lane)
+        for (int l0 = 8; l0 < L; l0 += 8) {
+            int32_t e[8], hd[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) { e[q] = p.tab.end[l0 + q]; hd[q] = p.tab.head[l0 + q]; }
+            walk(l0, e, hd);
         }
-        r.j = 3 + k;
-        r.idx = lane * p.M + r.j;
+        r.j = 3 + (k - start);
+        r.idx = lane * M + r.j;
         r.ok = true;
     }
+    const int32_t count = end - start + 4;   // (a lane with fewer than five frames holds no valid age)
     r.ok = r.ok && r.j >= 3 && r.j <= static_cast<int64_t>(count) - 2;
-    r.lane0 = lane * p.M;
-    r.base = static_cast<int64_t>(head) - count + p.M;
+    r.lane0 = lane * M;
+    r.M = M;
+    r.base = static_cast<int64_t>(head) - count + M;
     return r;
 }
 // Slot of the frame of age j - 3 + u of a valid row, 0 <= u <= 4: head + M - 1 is the newest frame's position before the wrap, so one
 // subtraction wraps.
-__device__ inline int64_t window_slot(const GatherPlan& p, const SampledRow& r, int u)
+__device__ inline int64_t window_slot(const SampledRow& r, int u)
 {
     const int64_t at = r.base + r.j - 3 + u;
-    return r.lane0 + (at >= p.M ? at - p.M : at);
+    return r.lane0 + (at >= r.M ? at - r.M : at);
 }
-static_assert(kMaxLanes % 8 == 0, "whole trips over the lanes' table");
-
 // The minibatch row of sample b as a DESCRIPTOR instead of copied frames: desc[0..3] = replay slots of the four frames
 // of s, desc[4..7] = those of s', -1 for a frame that is all zeros (a terminal flag lies between it and the stack's
 // newest frame, or the index is invalid); a, r, done (and idx_out) are written as gather_block writes them.  A kernel
@@ -181,7 +200,7 @@ __device__ inline void sample_desc(const GatherPlan& p, int b, int32_t* __restri
     }
     int32_t slot[5];
 #pragma unroll
-    for (int f = 0; f < 5; ++f) slot[f] = static_cast<int32_t>(window_slot(p, row, f));
+    for (int f = 0; f < 5; ++f) slot[f] = static_cast<int32_t>(window_slot(row, f));
     const int32_t act = p.actions[slot[3]];
     const float rew = p.rewards[slot[3]];
     uint32_t t[4];   // terminal flags of ages j-3 .. j
@@ -209,9 +228,13 @@ __device__ inline void sample_desc(const GatherPlan& p, int b, int32_t* __restri
 // requested together with the flags that decide whether it counts, everything of it at once.
 __device__ inline void gather_block(const GatherPlan& p, int f, int b)
 {
-    const SampledRow row = sampled_row(p, b);
-    uint4* ds = reinterpret_cast<uint4*>(p.s + (static_cast<int64_t>(b) * 4 + (f <= 3 ? f : 0)) * kFrameBytes);
-    uint4* ds2 = reinterpret_cast<uint4*>(p.s2 + (static_cast<int64_t>(b) * 4 + (f >= 1 ? f - 1 : 0)) * kFrameBytes);
+    uint8_t* s = p.s; uint8_t* s2 = p.s2;
+    const uint8_t* frames = p.frames; const uint8_t* terminals = p.terminals;
+    asm volatile("" :: "s"(s), "s"(s2), "s"(frames), "s"(terminals));
+    SampledRow row = sampled_row(p, b);
+    row.ok = __builtin_amdgcn_readfirstlane(row.ok);
+    uint4* ds = reinterpret_cast<uint4*>(s + (static_cast<int64_t>(b) * 4 + (f <= 3 ? f : 0)) * kFrameBytes);
+    uint4* ds2 = reinterpret_cast<uint4*>(s2 + (static_cast<int64_t>(b) * 4 + (f >= 1 ? f - 1 : 0)) * kFrameBytes);
     // each destination with its own phase shift (see copy_frame): the second read of the frame comes from cache
     const int v1 = static_cast<int>(threadIdx.x) - line_phase(ds), v2 = static_cast<int>(threadIdx.x) - line_phase(ds2);
     static_assert(kFrameVec16 + 3 <= 512, "two vectors per thread and destination");
@@ -220,8 +243,8 @@ __device__ inline void gather_block(const GatherPlan& p, int f, int b)
     if (row.ok) {   // uniform
         uint32_t t[4];   // terminal flags of ages j-3 .. j
 #pragma unroll
-        for (int u = 0; u < 4; ++u) t[u] = p.terminals[window_slot(p, row, u)];
-        const uint4* src = reinterpret_cast<const uint4*>(p.frames + window_slot(p, row, f) * kFrameBytes);
+        for (int u = 0; u < 4; ++u) t[u] = terminals[window_slot(row, u)];
+        const uint4* src = reinterpret_cast<const uint4*>(frames + window_slot(row, f) * kFrameBytes);
         auto clamped = [](int v) { return v < 0 ? 0 : (v < kFrameVec16 ? v : kFrameVec16 - 1); };
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -229,7 +252,7 @@ __device__ inline void gather_block(const GatherPlan& p, int f, int b)
             w2[u] = src[clamped(v2 + 256 * u)];
         }
         if (f == 0 && threadIdx.x == 0) {
-            const int64_t tslot = window_slot(p, row, 3);
+            const int64_t tslot = window_slot(row, 3);
             p.a[b] = p.actions[tslot];
             p.r[b] = p.rewards[tslot];
             p.done[b] = t[3] ? 1.f : 0.f;

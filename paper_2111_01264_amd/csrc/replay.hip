@@ -309,7 +309,12 @@ int replay_plan_sample_gather(replay* rb, int32_t B, uint64_t sample_step, const
     const int64_t V = replay_num_valid(rb);
     if (V <= 0) return fail(DQN_ESTATE, "replay_sample_gather: replay memory holds no complete transition");
     plan->frames = rb->frames; plan->actions = rb->actions; plan->rewards = rb->rewards; plan->terminals = rb->terminals;
-    for (int l = 0; l < rb->L; ++l) { plan->tab.head[l] = (int32_t)rb->head[l]; plan->tab.count[l] = (int32_t)rb->count[l]; }
+    int32_t end = 0;
+    for (int l = 0; l < kMaxLanes; ++l) {
+        if (l < rb->L) end += rb->count[l] > 4 ? (int32_t)rb->count[l] - 4 : 0;
+        plan->tab.head[l] = l < rb->L ? (int32_t)rb->head[l] : 0;
+        plan->tab.end[l] = end;
+    }
     plan->L = rb->L; plan->M = rb->M; plan->V = V; plan->seed = rb->seed; plan->sample_step = sample_step;
     plan->idx_in = idx_in; plan->s = s; plan->s2 = s2; plan->a = a; plan->r = r; plan->done = done; plan->idx_out = idx_out;
     plan->B = B;
