@@ -57,6 +57,12 @@ __host__ __device__ inline size_t frag16_index(int o, int k, int K)
 {
     return (static_cast<size_t>(o >> 4) * (K >> 4) + (k >> 4)) * 256 + ((((k >> 2) & 3) << 4) + (o & 15)) * 4 + (k & 3);
 }
+// An fp32 conv weight as three bf16 parts for the 16x16x32 instruction: 1 KB rows of 16 channels x 32 k, eight consecutive k per lane
+// (lane = 16 * ((k % 32) / 8) + o % 16), the three parts of the same weights in consecutive rows.
+__host__ __device__ inline size_t third_index(int o, int k, int K, int part)
+{
+    return ((static_cast<size_t>(o >> 4) * (K >> 5) + (k >> 5)) * 3 + part) * 512 + ((((k >> 3) & 3) << 4) + (o & 15)) * 8 + (k & 7);
+}
 template <typename T> __host__ __device__ inline size_t frag_index(int o, int k, int K)
 {
     if (sizeof(T) == 2) return tower_frag_index(o, k, K);

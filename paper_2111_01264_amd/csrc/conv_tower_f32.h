@@ -1,24 +1,22 @@
 // Fused conv1 -> conv2 -> conv3 of the Q-network in full precision: the fp32 counterpart of conv_tower.h (same workgroups of 8
-// wavefronts walking (group, sample) items or bands of one, activations of conv1 and conv2 in LDS), with another division of the
-// work inside an item, because here the matrix core is what bounds it: a sample is 7.7 MMAC = 60 k cycles of a compute unit's
-// fp32 matrix rate (conv1's 25 k become 5 k, see below), and nothing else comes near that.
+// wavefronts walking (group, sample) items or bands of one, activations of conv1 and conv2 in LDS), on the bf16 matrix
+// instructions.  An fp32 value is EXACTLY the sum of three bf16 parts (8 + 8 + 8 significand bits; values beyond the largest bf16, 3.39e38,
+// are the exception), a product of two bf16 is exact in fp32, and sums are kept in fp32 as the fp32 instruction keeps them:
 //
-//   * conv2 and conv3 use the 16x16x4 fp32 instruction: lane l holds row / column l % 16 at contraction index l / 16, and since
-//     the contraction index may be assigned freely as long as both operands agree, a lane reads FOUR consecutive channels (one
-//     16-byte access) for four instructions.  Sixteen-pixel tiles waste less of 81 and 49 pixels than 32-pixel ones cut per
-//     k-quarter, and a wavefront (channel tile w % 4, half w / 4 of the pixel tiles) sums all of K by itself: no exchange between
-//     wavefronts, three barriers per item.
-//   * weights are not resident: one 1 KB row of the copy in fragment order (frag16_index: 16 channels x 16 k) is one load
-//     instruction and feeds 128 matrix cycles per pixel tile; they stream from L2 through a ring of registers whose first entries
-//     are requested a layer ahead.  (Read from the row-major matrix, the sixteen 64-byte pieces of a load lie 2 KB apart, in one
-//     channel of the L2.)
-//   * conv1 multiplies pixel BYTES, which are exact in bf16, by weights that are split into three bf16 parts whose sum is the
-//     fp32 weight exactly (8 + 8 + 8 significand bits): all products are exact, the sum is accumulated in fp32 as before, and
-//     three bf16 instructions (96 cycles) replace eight fp32 ones (512 cycles).  The split is made while the weights are staged.
+//   * conv1 multiplies pixel BYTES, exact in bf16, by the weights' three parts: all products are exact.  The split is made while
+//     the weights are staged.
+//   * conv2 and conv3 take the six largest of the nine products of parts.  What is left out is below 2^-26 of a product, a quarter of
+//     the rounding of one fp32 addition, and there are fewer additions: six instructions per 32 k instead of eight of four k.  Against
+//     64 bits the error is that of the fp32 instruction (gradients 1e-7 .. 4e-7 of a tensor's norm, batch 16 to 256; Q rows
+//     1e-6 of the network's part, rows of 1 to 256 states).  Six bf16 instructions take 96 cycles of a matrix core where the
+//     fp32 ones take 256: 49 k cycles of a compute unit per sample become 21 k.
+//   * act1 and act2 are split when they are written to LDS, once, as three planes; conv2's and conv3's weights come split from the
+//     optimiser (third_index).  A wavefront owns 32 channels and a quarter of k, so that a weight is read by one wavefront only
+//     (weights stream from L2: 418 KB per item) and a pixel fragment feeds two channel tiles (LDS would otherwise be as busy as the
+//     matrix cores); the quarters meet in LDS, in their order.
 //
-// One launch per layer (weights or operands re-read from cache by every wavefront) took 10 + 12 + 12 us for a minibatch of 32,
-// 43 + 46 + 55 us for 256, 5 + 12 + 12 us plus two gaps for a round of one to eight samplers; this launch takes
-// 19, 61 and 13 us (rocprofv3; whole samples keep the matrix core busy 77 % of the time, at about 2.15 GHz).
+// Launch times (rocprofv3), fp32 instruction -> this: sevenths (one to twelve states) 13.6 -> 12.0 us, thirds (minibatch 32) 19.4 -> 15.0 us,
+// whole samples (minibatch 256) 63 -> 51 us; act step W = 1 20.3 -> 18.3 us.
 #pragma once
 #include "conv_tower.h"
 #include "wgrad_conv.h"
@@ -35,8 +33,8 @@ struct TowerF32Args {
     const int32_t* desc;           // the minibatch as per-sample replay slots ([n][8], see TowerArgs), or null
     const uint8_t* ring;           // with desc: the replay memory's frame array
     const float* w1[kMaxGroups];   // [32][256]
-    const float* w2[kMaxGroups];   // [64][512], fragment order
-    const float* w3[kMaxGroups];   // [64][576], fragment order
+    const bf16_t* w2[kMaxGroups];  // [64][512] in three parts, third_index order
+    const bf16_t* w3[kMaxGroups];  // [64][576]
     const float* b1[kMaxGroups];
     const float* b2[kMaxGroups];
     const float* b3[kMaxGroups];
@@ -46,10 +44,36 @@ struct TowerF32Args {
     PushStepPlan push;             // optional (L = 0: none): one experience per lane into the temporary buffers
 };
 
-constexpr int kTfP1 = 36, kTfP2 = 68;                  // LDS pixel pitch (floats) of conv1 / conv2 outputs
-constexpr int kTfW1Plane = 32 * 256;                   // one bf16 part of conv1's weights, fragment order
-constexpr size_t kTowerF32Smem = kTowerXBytes + 3 * kTfW1Plane * 2 + 400 * kTfP1 * 4 + 81 * kTfP2 * 4 + kTowerThreads * 4;
+constexpr int kTfW1Plane = 32 * 256;                   // one bf16 part of conv1's weights, fragment order (elements)
+constexpr int kTfA1Plane = 400 * 64, kTfA2Plane = 81 * 128;   // one bf16 part of act1 / act2 (bytes)
+constexpr int kTfXBytes = kTowerXBytes > 3 * kTfA2Plane ? kTowerXBytes : 3 * kTfA2Plane;
+constexpr size_t kTowerF32Smem = kTfXBytes + 3 * kTfW1Plane * 2 + 3 * kTfA1Plane + kTowerThreads * 4;
 static_assert(kTowerF32Smem <= 160 * 1024, "one workgroup per compute unit");
+static_assert(kTfXBytes % 16 == 0, "16-byte vectors");
+
+// act1 in LDS: a pixel is 64 bytes, four chunks of eight channels.  The even columns of a row come before the odd ones, so that the
+// stride-2 windows of consecutive output pixels start at consecutive pixels; the chunk is turned by the pixel's place in its
+// group of sixteen, so that conv1's stores (one chunk of 32 pixels) meet all banks as well as conv2's reads (all chunks of 16).
+__device__ inline int tf_px1(int row, int col) { return row * 20 + (col & 1) * 10 + (col >> 1); }
+__device__ inline int tf_a1(int px, int chunk) { return px * 64 + ((chunk ^ ((px >> 2) & 3)) << 4); }
+// act2: a pixel is 128 bytes, eight chunks, turned by the pixel
+__device__ inline int tf_a2(int px, int chunk) { return px * 128 + ((chunk ^ (px & 7)) << 4); }
+
+// Four consecutive channels into the three planes of an activation.
+template <int PLANE> __device__ inline void tf_store4(uint8_t* dst, float v0, float v1, float v2, float v3)
+{
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    const float v[4] = {v0, v1, v2, v3};
+    bf16x4 p[3];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float r = v[e];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) { p[q][e] = static_cast<bf16_t>(r); r -= static_cast<float>(p[q][e]); }
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<bf16x4*>(dst + q * PLANE) = p[q];
+}
 
 // The value, computed no earlier than here: addresses that depend on a lane's pixel are the same for every item, and the compiler
 // otherwise computes those of all stages in front of the item loop and keeps them in registers throughout.
@@ -65,6 +89,67 @@ __device__ inline tf_f32x4 load_row(const float* p, unsigned lane)
 {
     asm volatile("" : "+s"(p));
     return reinterpret_cast<const tf_f32x4*>(p)[lane];
+}
+
+__device__ inline bf16x8 load_row8(const bf16_t* p, unsigned lane)
+{
+    asm volatile("" : "+s"(p));
+    return reinterpret_cast<const bf16x8*>(p)[lane];
+}
+
+// acc[t][c] += (16 weight rows of channel half c) x (16 pixels of tile t) over NK k-steps of 32, every product of two fp32 values as the
+// six largest of the nine products of their bf16 parts, smallest first.  at(s, t): this lane's eight channels of tile t in
+// k-step s, first part.  The operand of tile t + 1 is requested before the matrix work of tile t; done(s) when the weights of step s are used up.
+template <int T, int NK, int PLANE, class At, class Done>
+__device__ inline void tower_f32_mma(tf_f32x4 (&acc)[T][2], bf16x8 (&w)[5][2][3], At& at, Done& done)
+{
+    bf16x8 x[2][3];
+    auto fetch = [&](auto i_) {
+        constexpr int i = decltype(i_)::value, s = i / T, t = i % T;
+        const uint8_t* p = at(std::integral_constant<int, s>{}, t);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[i & 1][q] = *reinterpret_cast<const bf16x8*>(p + q * PLANE);
+    };
+    fetch(std::integral_constant<int, 0>{});
+    auto step = [&](auto i_) {
+        constexpr int i = decltype(i_)::value, s = i / T, t = i % T;
+        if constexpr (i + 1 < NK * T) fetch(std::integral_constant<int, i + 1>{});
+        constexpr int wp[6] = {2, 0, 1, 1, 0, 0}, xp[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int u = 0; u < 6; ++u)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s][c][wp[u]], x[i & 1][xp[u]], acc[t][c], 0, 0, 0);
+        if constexpr (t == T - 1) done(std::integral_constant<int, s>{});
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    static_for<0, NK * T>(step);
+}
+
+// The k-quarters of the 2 T tiles of 32 channels meet: wavefront (cp, kq) finishes tiles [kq * OWN, + OWN), adds the quarters in their order and
+// hands the sums to finish(t, c, sum).  ex: 2 * 2 T * 3 KB of LDS that nobody reads any more.
+template <int T, class Finish>
+__device__ inline void tower_f32_exchange(const tf_f32x4 (&acc)[T][2], float* ex, int cp, int kq, int lane, Finish finish)
+{
+    constexpr int NS = 2 * T, OWN = (NS + 3) / 4;
+    static_assert(2 * NS * 3 * 1024 <= 3 * kTfA1Plane, "the partial sums fit act1's place");
+    tf_f32x4* slots = reinterpret_cast<tf_f32x4*>(ex) + cp * NS * 3 * 64 + lane;
+    tf_f32x4 own[OWN];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int o = j / OWN;
+        if (o == kq) own[j % OWN] = acc[j / 2][j % 2];
+        else slots[(j * 3 + (kq < o ? kq : kq - 1)) * 64] = acc[j / 2][j % 2];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+        const int j = kq * OWN + i;
+        if (j < NS) {
+            const tf_f32x4 r0 = slots[(j * 3) * 64], r1 = slots[(j * 3 + 1) * 64], r2 = slots[(j * 3 + 2) * 64];
+            const tf_f32x4 q0 = kq == 0 ? own[i] : r0, q1 = kq == 0 ? r0 : kq == 1 ? own[i] : r1, q2 = kq < 2 ? r1 : kq == 2 ? own[i] : r2, q3 = kq == 3 ? own[i] : r2;
+            finish(j / 2, j % 2, ((q0 + q1) + q2) + q3);
+        }
+    }
 }
 
 // acc[t] += (16 weight rows) x (16 pixels of tile t) over filter rows 0 .. ROWS - 1 with STEPS k-steps of sixteen each; `base`
@@ -132,22 +217,22 @@ __device__ inline void tower_f32_stream(tf_f32x4 (&acc)[NT], const float* const 
 }
 
 // PARTS: a workgroup runs a whole sample, or one half / third / seventh of its output rows with the rows of conv2 and conv1 these
-// depend on (see conv_tower_kernel; thirds and sevenths are the same bands).  By the matrix cycles of its busiest SIMD an item
-// takes 49 k cycles whole, 30 k as a half, 25 k as a third, 16 k as a seventh; the host takes the smallest part for which the
+// depend on (see conv_tower_kernel; thirds and sevenths are the same bands); the host takes the smallest part for which the
 // chip still holds every workgroup at once.
 // DESC: the frames of a state come from the replay memory by descriptor, as in conv_tower_kernel.
 template <bool DESC, int PARTS>
 __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, int groups_, int per_, int tower_blocks_, const uint8_t* x0_,
-                                                                       const uint8_t* x1_, const float* w1_0_, const float* w2_0_, TowerF32Args a)
+                                                                       const uint8_t* x1_, const float* w1_0_, const bf16_t* w2_0_, TowerF32Args a)
 {
     static_assert(!DESC || PARTS == 1, "descriptors come with minibatches that fill the chip");
     static_assert(PARTS == 1 || PARTS == 2 || PARTS == 3 || PARTS == 7, "whole samples, halves, thirds or sevenths");
     extern __shared__ __attribute__((aligned(16))) unsigned char tf_smem[];
-    uint8_t* sX = tf_smem;
-    bf16_t* sW1 = reinterpret_cast<bf16_t*>(tf_smem + kTowerXBytes);
-    float* sA1 = reinterpret_cast<float*>(sW1 + 3 * kTfW1Plane);
-    float* sA2 = sA1 + 400 * kTfP1;
-    float* sB1 = sA2 + 81 * kTfP2;   // biases: conv1 [32], conv2 [64], conv3 [64]
+    uint8_t* sX = tf_smem;             // the state; once conv1 has read it, act2's parts
+    uint8_t* sA2 = tf_smem;
+    bf16_t* sW1 = reinterpret_cast<bf16_t*>(tf_smem + kTfXBytes);
+    uint8_t* sA1 = reinterpret_cast<uint8_t*>(sW1 + 3 * kTfW1Plane);   // act1's parts; once conv2 has read them, partial sums on their way between wavefronts
+    float* sEx = reinterpret_cast<float*>(sA1);
+    float* sB1 = reinterpret_cast<float*>(sA1 + 3 * kTfA1Plane);   // biases: conv1 [32], conv2 [64], conv3 [64]
     float* sB2 = sB1 + 32;
     float* sB3 = sB2 + 64;
 
@@ -201,9 +286,8 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
     if (DESC && first + 1 < last) { if (b + 1 < n_) fetch_desc(g, b + 1); else fetch_desc(g + 1, 0); }
 
     const int lp = lane & 31, kg = lane >> 5;        // conv1: pixel / row of a 32x32 tile, k-half
-    const int kq = lane >> 4;                        // conv2, conv3: k-quarter (and lane & 15: pixel / row of a 16x16 tile)
-    const int ct = wave & 3, ph = wave >> 2;         // channel tile; pixel tiles ph, ph + 2, ...
-    constexpr int D2 = 8, D3 = 6;
+    const int lq = lane & 15, lk = lane >> 4;        // conv2, conv3: pixel / row of a 16x16 tile, eight of 32 k
+    const int cp = wave & 1, kq = wave >> 1;         // conv2, conv3: 32 channels, k-quarter
     int cur_g = kMaxGroups;   // no group (and not -1: the part variants then indexed the biases with 0 whatever g was -- a compiler error, seen in its output)
     for (int it = first; it < last; ++it, ++b) {
         if (b == n_) { b = 0; ++g; }
@@ -240,22 +324,27 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
             }
             d[tid] = xv0; d[tid + 512] = xv1; d[tid + 1024] = xv2; d[last_vec] = xv3;   // clamped lanes rewrite the last vector with itself
         }
-        const float* w2p = (g == 0 ? w2_0_ : a.w2[g]) + ct * 32 * 256;
-        const float* w3p = a.w3[g] + ct * 36 * 256;
-        tf_f32x4 ring2[D2], ring3[D3], stream[kTfStream];
-        auto weights = [&](int S) { return load_row(S < 32 ? w2p + S * 256 : w3p + (S - 32) * 256, lane); };
-        if constexpr (PARTS == 1) {
+        // This wavefront's weights: conv2's four k-steps, and as each is used up conv3's (steps [s3, s3 + 5) or + 4 of its eighteen).
+        const bf16_t* w2p = (g == 0 ? w2_0_ : a.w2[g]) + (2 * cp * 16 + 4 * kq) * 3 * 512;
+        const int s3 = kq < 2 ? 5 * kq : 2 + 4 * kq;
+        const bf16_t* w3p = a.w3[g] + (2 * cp * 18 + s3) * 3 * 512;
+        bf16x8 wr[5][2][3];
+        auto request2 = [&](auto s_) {
+            constexpr int s = decltype(s_)::value;
 #pragma unroll
-            for (int u = 0; u < D2; ++u) ring2[u] = weights(u);
-        }
-        if (it + 1 < last) {
-            if (b + 1 < n_) fetch_state(g, b + 1); else fetch_state(g + 1, 0);
-            if (DESC && it + 2 < last) {
-                int g2 = g, b2 = b + 2;
-                while (b2 >= n_) { b2 -= n_; ++g2; }
-                fetch_desc(g2, b2);
-            }
-        }
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) wr[s][c][q] = load_row8(w2p + ((c * 16 + s) * 3 + q) * 512, lane);
+        };
+        auto request3 = [&](auto s_) {   // (quarters of four steps request their last one again)
+            constexpr int s = decltype(s_)::value;
+            const bf16_t* p = w3p + (s < 4 || kq < 2 ? s : 3) * 3 * 512;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) wr[s][c][q] = load_row8(p + (c * 18 * 3 + q) * 512, lane);
+        };
+        if constexpr (PARTS == 1) static_for<0, 4>(request2);
         __syncthreads();
 
         // ---- conv1: k = (c, p, q); k-step k covers c = k / 4, p = 2 * (k % 4) + kg, q = 0..7 --------------------------
@@ -267,7 +356,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                 f32x16 acc[NT];
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
-                    const int lpx = (wave + 8 * t) * 32 + lp;
+                    const int lpx = (wave + 8 * t) * 32 + here(lp);
                     const int pc = 2 * r3_lo * 20 + (lpx < n1 ? lpx : n1 - 1);
                     base[t] = sX + (4 * (pc / 20) + kg) * 84 + 4 * (pc % 20);
 #pragma unroll
@@ -286,10 +375,10 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                     for (int t = 0; t < NT; ++t) px[buf][t] = fetch_px(t, k);
                 };
                 fetch(0, 0);
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    if (k + 1 < 16) fetch((k + 1) & 1, k + 1);
-                    if constexpr (PARTS > 1) { stream[2 * k] = weights(2 * k); stream[2 * k + 1] = weights(2 * k + 1); }   // two requests per k-step: all at once they would stand in front of conv1
+                auto step = [&](auto k_) {
+                    constexpr int k = decltype(k_)::value;
+                    if constexpr (k + 1 < 16) fetch((k + 1) & 1, k + 1);
+                    if constexpr (PARTS > 1 && k % 4 == 0) request2(std::integral_constant<int, k / 4>{});   // (all at once they would stand in front of conv1)
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
                         const bf16x8 x = bf16x8_from_bytes(px[k & 1][t].x, px[k & 1][t].y);
@@ -297,11 +386,13 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                         for (int q = 2; q >= 0; --q) mma_32x32x16(acc[t], wf[k & 1][q], x);   // smallest part first
                     }
                     __builtin_amdgcn_sched_barrier(0);
-                }
+                };
+                static_for<0, 16>(step);
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
-                    const int lpx = (wave + 8 * t) * 32 + lp, px1 = 2 * r3_lo * 20 + lpx;
+                    const int lpx = (wave + 8 * t) * 32 + here(lp), px1 = 2 * r3_lo * 20 + lpx;
                     if (lpx < n1) {
+                        const int at = tf_px1(px1 / 20, px1 % 20);
                         constexpr float kScale = 1.f / 255.f;
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
@@ -309,7 +400,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                             const float4 bv = *reinterpret_cast<const float4*>(sB1 + ch);
                             const float v0 = fmaxf(acc[t][4 * q] * kScale + bv.x, 0.f), v1 = fmaxf(acc[t][4 * q + 1] * kScale + bv.y, 0.f);
                             const float v2 = fmaxf(acc[t][4 * q + 2] * kScale + bv.z, 0.f), v3 = fmaxf(acc[t][4 * q + 3] * kScale + bv.w, 0.f);
-                            store4<float>(sA1 + px1 * kTfP1 + ch, v0, v1, v2, v3);
+                            tf_store4<kTfA1Plane>(sA1 + tf_a1(at, q) + 8 * kg, v0, v1, v2, v3);
                             if (g1) store4<float>(g1 + (static_cast<size_t>(b) * 400 + px1) * 32 + ch, v0, v1, v2, v3);
                         }
                     }
@@ -317,81 +408,74 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
             };
             if (T1 > 8 && wave < T1 - 8) run(std::integral_constant<int, 2>{});
             else if (T1 >= 8 || wave < T1) run(std::integral_constant<int, 1>{});
-            else if constexpr (PARTS > 1) {   // no tile of conv1 for this wavefront
+            else if constexpr (PARTS > 1) static_for<0, 4>(request2);   // no tile of conv1 for this wavefront
+        }
+        __syncthreads();
+
+        // ---- conv2: k = (p, q, c); this wavefront's quarter is filter row kq, a k-step is one tap ------------------------
+        {
+            int base[T2];
+            tf_f32x4 acc[T2][2];
 #pragma unroll
-                for (int u = 0; u < kTfStream; ++u) stream[u] = weights(u);
+            for (int t = 0; t < T2; ++t) {
+                const int lpx = t * 16 + here(lq), pc = r3_lo * 9 + (lpx < n2 ? lpx : n2 - 1);
+                base[t] = (2 * (pc / 9) + kq) * 20 + pc % 9;
+                acc[t][0] = acc[t][1] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            auto at = [&](auto s_, int t) { constexpr int s = decltype(s_)::value; return sA1 + tf_a1(base[t] + (s & 1) * 10 + (s >> 1), lk); };
+            tower_f32_mma<T2, 4, kTfA1Plane>(acc, wr, at, request3);
+            request3(std::integral_constant<int, 4>{});
+            __syncthreads();   // act1 has been read
+            float* g2 = a.act2[g];
+            tower_f32_exchange<T2>(acc, sEx, cp, kq, lane, [&](int t, int c, const tf_f32x4& sum) {
+                const int lpx = t * 16 + here(lq), px = r3_lo * 9 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
+                const float4 bv = *reinterpret_cast<const float4*>(sB2 + ch);
+                if (lpx < n2) {
+                    const float v0 = fmaxf(sum[0] + bv.x, 0.f), v1 = fmaxf(sum[1] + bv.y, 0.f), v2 = fmaxf(sum[2] + bv.z, 0.f), v3 = fmaxf(sum[3] + bv.w, 0.f);
+                    tf_store4<kTfA2Plane>(sA2 + tf_a2(px, ch >> 3) + 2 * (ch & 4), v0, v1, v2, v3);
+                    if (g2) store4<float>(g2 + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v0, v1, v2, v3);
+                }
+            });
+        }
+        // the next item's state, behind the layer whose accumulators leave no registers for it
+        if (it + 1 < last) {
+            if (b + 1 < n_) fetch_state(g, b + 1); else fetch_state(g + 1, 0);
+            if (DESC && it + 2 < last) {
+                int g2 = g, b2 = b + 2;
+                while (b2 >= n_) { b2 -= n_; ++g2; }
+                fetch_desc(g2, b2);
             }
         }
-        if constexpr (PARTS == 1) {
-#pragma unroll
-            for (int u = 0; u < D3; ++u) ring3[u] = weights(32 + u);
-        }
         __syncthreads();
 
-        // ---- conv2: k = (p, q, c), eight k-steps per filter row -----------------------------------------------------
+        // ---- conv3: k = (p, q, c), two k-steps per tap ------------------------------------------------------------------
         {
-            const int ch = ct * 16 + 4 * kq;
-            const float4 bv = *reinterpret_cast<const float4*>(sB2 + ch);
-            float* g2 = a.act2[g];
-            auto run = [&](auto nt_) {
-                constexpr int NT = decltype(nt_)::value;
-                const float* base[NT];
-                tf_f32x4 acc[NT];
-                const int lq = here(lane & 15);
+            int base[T3];
+            tf_f32x4 acc[T3][2];
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const int lpx = (ph + 2 * t) * 16 + lq, pc = r3_lo * 9 + (lpx < n2 ? lpx : n2 - 1);
-                    base[t] = sA1 + (2 * (pc / 9) * 20 + 2 * (pc % 9)) * kTfP1 + kq * 4;
-                    acc[t] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-                if constexpr (PARTS == 1) tower_f32_rows<NT, 4, 8, 2, 20 * kTfP1, kTfP1, D2>(acc, base, w2p, lane, ring2);
-                else tower_f32_stream<NT, 0, 32, 8, 2, 20 * kTfP1, kTfP1, 68>(acc, base, stream, weights);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const int lpx = (ph + 2 * t) * 16 + lq, px = r3_lo * 9 + lpx;
-                    if (lpx < n2) {
-                        const float v0 = fmaxf(acc[t][0] + bv.x, 0.f), v1 = fmaxf(acc[t][1] + bv.y, 0.f), v2 = fmaxf(acc[t][2] + bv.z, 0.f), v3 = fmaxf(acc[t][3] + bv.w, 0.f);
-                        store4<float>(sA2 + px * kTfP2 + ch, v0, v1, v2, v3);
-                        if (g2) store4<float>(g2 + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v0, v1, v2, v3);
-                    }
-                }
+            for (int t = 0; t < T3; ++t) {
+                const int lpx = t * 16 + here(lq), pc = r3_lo * 7 + (lpx < n3 ? lpx : n3 - 1);
+                base[t] = (pc / 7) * 9 + pc % 7;
+                acc[t][0] = acc[t][1] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            auto at = [&](auto s_, int t) {
+                const int s = s3 + decltype(s_)::value, tap = s >> 1;
+                return sA2 + tf_a2(base[t] + (tap / 3) * 9 + tap % 3, 4 * (s & 1) + lk);
             };
-            constexpr int NA = (T2 + 1) / 2, NB = T2 / 2;
-            if (NA == NB || ph == 0) run(std::integral_constant<int, NA>{}); else run(std::integral_constant<int, NB>{});
-        }
-        __syncthreads();
-
-        // ---- conv3: k = (p, q, c), twelve k-steps per filter row ----------------------------------------------------
-        {
-            const int ch = ct * 16 + 4 * kq;
-            const float4 bv = *reinterpret_cast<const float4*>(sB3 + ch);
-            auto run = [&](auto nt_) {
-                constexpr int NT = decltype(nt_)::value;
-                const float* base[NT];
-                tf_f32x4 acc[NT];
-                const int lq = here(lane & 15);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const int lpx = (ph + 2 * t) * 16 + lq, pc = r3_lo * 7 + (lpx < n3 ? lpx : n3 - 1);
-                    base[t] = sA2 + ((pc / 7) * 9 + pc % 7) * kTfP2 + kq * 4;
-                    acc[t] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
-                }
-                if constexpr (PARTS == 1) tower_f32_rows<NT, 3, 12, 4, 9 * kTfP2, kTfP2, D3>(acc, base, w3p, lane, ring3);
-                else tower_f32_stream<NT, 32, 36, 12, 4, 9 * kTfP2, kTfP2, 68>(acc, base, stream, weights);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const int lpx = (ph + 2 * t) * 16 + lq, px = r3_lo * 7 + lpx;
-                    if (lpx < n3)
-                        store4<float>(a.act3[g] + (static_cast<size_t>(b) * 49 + px) * 64 + ch, fmaxf(acc[t][0] + bv.x, 0.f), fmaxf(acc[t][1] + bv.y, 0.f),
-                                      fmaxf(acc[t][2] + bv.z, 0.f), fmaxf(acc[t][3] + bv.w, 0.f));
-                }
-            };
-            constexpr int NA = (T3 + 1) / 2, NB = T3 / 2;
-            if (NA == NB || ph == 0) run(std::integral_constant<int, NA>{});
-            else if constexpr (NB > 0) run(std::integral_constant<int, NB>{});
+            auto nothing = [](auto) {};
+            if (kq < 2) tower_f32_mma<T3, 5, kTfA2Plane>(acc, wr, at, nothing);
+            else tower_f32_mma<T3, 4, kTfA2Plane>(acc, wr, at, nothing);
+            tower_f32_exchange<T3>(acc, sEx, cp, kq, lane, [&](int t, int c, const tf_f32x4& sum) {
+                const int lpx = t * 16 + here(lq), px = r3_lo * 7 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
+                const float4 bv = *reinterpret_cast<const float4*>(sB3 + ch);
+                if (lpx < n3)
+                    store4<float>(a.act3[g] + (static_cast<size_t>(b) * 49 + px) * 64 + ch, fmaxf(sum[0] + bv.x, 0.f), fmaxf(sum[1] + bv.y, 0.f),
+                                  fmaxf(sum[2] + bv.z, 0.f), fmaxf(sum[3] + bv.w, 0.f));
+            });
         }
         if constexpr (PARTS > 1) break;
-        // no barrier: conv3 reads act2 only, and the next item writes act2 behind two barriers of its own; state and act1 are free
+        // no barrier: the last exchange's lies behind every read of act2, whose place the next state takes, and the next item's
+        // first barrier behind the exchange's reads, whose place its act1 takes
     }
 }
 

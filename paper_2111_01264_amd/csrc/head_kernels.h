@@ -59,14 +59,29 @@ template <typename T> __host__ __device__ inline size_t bsh_index_wf1(int o, int
     return kBshWf1 + frag_index<T>(f, o, 512);
 }
 
+// Full precision: conv2's and conv3's weights are not in the forward copy's own places but behind its end, as three bf16 parts each
+// (third_index) whose sum is the fp32 weight: 8 + 8 + 8 significand bits.
+constexpr size_t kThirdsW2 = 0, kThirdsW3 = static_cast<size_t>(3) * 64 * 512, kThirdsTotal = kThirdsW3 + static_cast<size_t>(3) * 64 * 576;   // bf16 elements
+__host__ __device__ inline size_t thirds_offset(const Offsets& off) { return (off.total + 63) / 64 * 64; }   // in floats
+inline size_t copy_elements(const Offsets& off, size_t esize) { return esize == 4 ? thirds_offset(off) + kThirdsTotal / 2 : off.total; }
+__device__ inline void store_thirds(bf16_t* thirds, int o, int k, int K, float v)
+{
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        const bf16_t p = static_cast<bf16_t>(v);
+        thirds[third_index(o, k, K, q)] = p;
+        v -= static_cast<float>(p);
+    }
+}
+
 // Where blob element e lives in the forward copy: identical, except that the weights of conv2, conv3 and fc1 (bf16 mode: conv1
 // too) are kept in MFMA fragment order of the kernels that load them.  bf16 mode stores conv1's weights as fp16 (that
 // kernel runs conv1 on the f16 matrix instruction), everything else as bf16: shadow_store converts.
 template <typename T> __host__ __device__ inline size_t shadow_index(const Offsets& off, size_t e)
 {
     if (sizeof(T) == 2 && e >= off.w1 && e < off.b1) { const int r = static_cast<int>(e - off.w1); return off.w1 + tower_frag_index(r / 256, r % 256, 256); }
-    if (e >= off.w2 && e < off.b2) { const int r = static_cast<int>(e - off.w2); return off.w2 + (sizeof(T) == 2 ? tower_frag_index(r / 512, r % 512, 512) : frag16_index(r / 512, r % 512, 512)); }
-    if (e >= off.w3 && e < off.b3) { const int r = static_cast<int>(e - off.w3); return off.w3 + (sizeof(T) == 2 ? tower_frag_index(r / 576, r % 576, 576) : frag16_index(r / 576, r % 576, 576)); }
+    if (e >= off.w2 && e < off.b2) { const int r = static_cast<int>(e - off.w2); return off.w2 + tower_frag_index(r / 512, r % 512, 512); }
+    if (e >= off.w3 && e < off.b3) { const int r = static_cast<int>(e - off.w3); return off.w3 + tower_frag_index(r / 576, r % 576, 576); }
     if (e >= off.wf1 && e < off.bf1) { const int r = static_cast<int>(e - off.wf1); return off.wf1 + frag_index<T>(r / 3136, r % 3136, 3136); }
     return e;
 }
@@ -74,6 +89,11 @@ template <typename T> __host__ __device__ inline size_t shadow_index(const Offse
 template <typename T> __device__ inline void shadow_store(T* sh, const Offsets& off, size_t e, float v)
 {
     if (sizeof(T) == 2 && e >= off.w1 && e < off.b1) reinterpret_cast<_Float16*>(sh)[shadow_index<T>(off, e)] = static_cast<_Float16>(v);
+    else if (sizeof(T) == 4 && ((e >= off.w2 && e < off.b2) || (e >= off.w3 && e < off.b3))) {
+        const bool second = e < off.b2;
+        const int r = static_cast<int>(e - (second ? off.w2 : off.w3)), K = second ? 512 : 576;
+        store_thirds(reinterpret_cast<bf16_t*>(sh + thirds_offset(off)) + (second ? kThirdsW2 : kThirdsW3), r / K, r % K, K, v);
+    }
     else sh[shadow_index<T>(off, e)] = from_float<T>(v);
 }
 
@@ -603,7 +623,8 @@ __device__ inline void rms_conv_block(float* theta, float* grad, float* v, float
         else static_cast<T*>(a.sh)[el] = from_float<T>(th);
     } else {
         constexpr int K = CONV == 1 ? 512 : 576;
-        static_cast<T*>(a.sh)[E0 + (sizeof(T) == 2 ? tower_frag_index(el / K, el % K, K) : frag16_index(el / K, el % K, K))] = from_float<T>(th);
+        if (sizeof(T) == 2) static_cast<T*>(a.sh)[E0 + tower_frag_index(el / K, el % K, K)] = from_float<T>(th);
+        else store_thirds(reinterpret_cast<bf16_t*>(static_cast<T*>(a.sh) + thirds_offset(a.off)) + (CONV == 1 ? kThirdsW2 : kThirdsW3), el / K, el % K, K, th);
         static_cast<T*>(a.bsh)[CONV == 1 ? bsh_index_w2<T>(el) : bsh_index_w3<T>(el)] = from_float<T>(th);
     }
 }
@@ -758,13 +779,11 @@ __global__ __launch_bounds__(256) void build_copies_kernel(const float* __restri
 // theta^- <- theta: fp32 master (bitwise) and the forward operand copy.
 template <typename T>
 __global__ __launch_bounds__(256) void target_copy_kernel(const float* __restrict__ theta, float* __restrict__ theta_t,
-                                                          const T* __restrict__ sh, T* __restrict__ sh_t, size_t n)
+                                                          const T* __restrict__ sh, T* __restrict__ sh_t, size_t n, size_t n_copy)
 {
     const size_t i = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
-    if (i < n) {
-        theta_t[i] = theta[i];
-        sh_t[i] = sh[i];
-    }
+    if (i < n) theta_t[i] = theta[i];
+    if (i < n_copy) sh_t[i] = sh[i];
 }
 
 }  // namespace dqn

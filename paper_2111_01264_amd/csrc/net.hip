@@ -287,7 +287,8 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         for (int g = 0; g < groups; ++g) {
             const T* w = static_cast<const T*>(shadow[g]);
             a.x[g] = x[g];
-            a.w1[g] = w + o.w1; a.w2[g] = w + o.w2; a.w3[g] = w + o.w3;
+            const bf16_t* thirds = reinterpret_cast<const bf16_t*>(w + thirds_offset(o));
+            a.w1[g] = w + o.w1; a.w2[g] = thirds + kThirdsW2; a.w3[g] = thirds + kThirdsW3;
             a.b1[g] = master[g] + o.b1; a.b2[g] = master[g] + o.b2; a.b3[g] = master[g] + o.b3;
             a.act1[g] = (timed && g == 0) ? act1 : nullptr;
             a.act2[g] = (timed && g == 0) ? act2 : nullptr;
@@ -679,8 +680,8 @@ int dqn_create(const dqn_config* cfg, void* act_stream, void* train_stream, dqn_
         }
         DQN_HIP(hipMalloc((void**)&c->blob, n * sizeof(float)));
         for (void** p : {&c->sh, &c->sh_t}) {
-            DQN_HIP(hipMalloc(p, (n + 8) * c->esize));
-            DQN_HIP(hipMemset(*p, 0, (n + 8) * c->esize));
+            DQN_HIP(hipMalloc(p, (copy_elements(c->off, c->esize) + 8) * c->esize));
+            DQN_HIP(hipMemset(*p, 0, (copy_elements(c->off, c->esize) + 8) * c->esize));
         }
         int rc = alloc_ws(c->train_ws, cfg->max_batch, 3, c->A, c->esize);
         if (rc != DQN_OK) return rc;
@@ -1008,12 +1009,12 @@ int dqn_sync_target(dqn_ctx* c, replay* rb, int32_t blocking)
         const int rc = replay_flush_ordered(rb);   // also orders the replay's push stream around the flush
         if (rc != DQN_OK) return rc;
     }
-    const size_t n = c->off.total;
-    const dim3 grid(static_cast<unsigned>((n + 255) / 256)), block(256);
+    const size_t n = c->off.total, n_copy = copy_elements(c->off, c->esize);
+    const dim3 grid(static_cast<unsigned>((n_copy + 255) / 256)), block(256);
     if (c->cfg.precision == DQN_PRECISION_BF16)
-        hipLaunchKernelGGL(target_copy_kernel<bf16_t>, grid, block, 0, c->train_stream, c->theta, c->theta_t, static_cast<const bf16_t*>(c->sh), static_cast<bf16_t*>(c->sh_t), n);
+        hipLaunchKernelGGL(target_copy_kernel<bf16_t>, grid, block, 0, c->train_stream, c->theta, c->theta_t, static_cast<const bf16_t*>(c->sh), static_cast<bf16_t*>(c->sh_t), n, n_copy);
     else
-        hipLaunchKernelGGL(target_copy_kernel<float>, grid, block, 0, c->train_stream, c->theta, c->theta_t, static_cast<const float*>(c->sh), static_cast<float*>(c->sh_t), n);
+        hipLaunchKernelGGL(target_copy_kernel<float>, grid, block, 0, c->train_stream, c->theta, c->theta_t, static_cast<const float*>(c->sh), static_cast<float*>(c->sh_t), n, n_copy);
     DQN_LAUNCH_CHECK();
     DQN_HIP(hipEventRecord(c->ev_sync, c->train_stream));
     DQN_HIP(hipStreamWaitEvent(c->act_stream, c->ev_sync, 0));
