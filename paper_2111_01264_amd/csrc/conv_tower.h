@@ -50,19 +50,14 @@ __host__ __device__ inline size_t tower_frag_index(int o, int k, int K)
     return ((static_cast<size_t>(o >> 5) * (K >> 4) + (k >> 4)) * 64 + (((k >> 3) & 1) << 5) + (o & 31)) * 8 + (k & 7);
 }
 
-// The same for fp32 operands.  16x16x4 instruction (conv layers): 1 KB rows of 16 channels x 16 k, four consecutive k per lane
-// (lane = 16 * ((k % 16) / 4) + o % 16).  32x32x2 (fc layers): two 1 KB halves per 32 rows x 16 k, lanes as above, the lane's
-// k 0..3 in the first half and 4..7 in the second, so that each half is one contiguous load.
-__host__ __device__ inline size_t frag16_index(int o, int k, int K)
-{
-    return (static_cast<size_t>(o >> 4) * (K >> 4) + (k >> 4)) * 256 + ((((k >> 2) & 3) << 4) + (o & 15)) * 4 + (k & 3);
-}
 // An fp32 conv weight as three bf16 parts for the 16x16x32 instruction: 1 KB rows of 16 channels x 32 k, eight consecutive k per lane
 // (lane = 16 * ((k % 32) / 8) + o % 16), the three parts of the same weights in consecutive rows.
 __host__ __device__ inline size_t third_index(int o, int k, int K, int part)
 {
     return ((static_cast<size_t>(o >> 4) * (K >> 5) + (k >> 5)) * 3 + part) * 512 + ((((k >> 3) & 3) << 4) + (o & 15)) * 8 + (k & 7);
 }
+// tower_frag_index's counterpart for fp32 operands of the 32x32x2 instruction (fc layers): two 1 KB halves per 32 rows x 16 k, lanes as
+// there, the lane's k 0..3 in the first half and 4..7 in the second, so that each half is one contiguous load.
 template <typename T> __host__ __device__ inline size_t frag_index(int o, int k, int K)
 {
     if (sizeof(T) == 2) return tower_frag_index(o, k, K);

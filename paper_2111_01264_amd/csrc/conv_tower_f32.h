@@ -6,17 +6,20 @@
 //   * conv1 multiplies pixel BYTES, exact in bf16, by the weights' three parts: all products are exact.  The split is made while
 //     the weights are staged.
 //   * conv2 and conv3 take the six largest of the nine products of parts.  What is left out is below 2^-26 of a product, a quarter of
-//     the rounding of one fp32 addition, and there are fewer additions: six instructions per 32 k instead of eight of four k.  Against
-//     64 bits the error is that of the fp32 instruction (gradients 1e-7 .. 4e-7 of a tensor's norm, batch 16 to 256; Q rows
-//     1e-6 of the network's part, rows of 1 to 256 states).  Six bf16 instructions take 96 cycles of a matrix core where the
-//     fp32 ones take 256: 49 k cycles of a compute unit per sample become 21 k.
+//     the rounding of one fp32 addition, and there are fewer additions: six instructions per 32 k instead of eight of four k.  The
+//     small products are summed by themselves (see tower_f32_mma); the error against 64 bits is then below that of the fp32
+//     instruction (gradients of one step, batch 16 to 256, norms: fc1.w 1.1 .. 2.4e-7 against 1.4 .. 2.5e-7, conv1.w 2.1 .. 3.1e-7
+//     against 3.3 .. 4.6e-7).  Six bf16 instructions take 96 cycles of a matrix core where the fp32 ones take 256: 49 k cycles
+//     of a compute unit per sample become 21 k.
 //   * act1 and act2 are split when they are written to LDS, once, as three planes; conv2's and conv3's weights come split from the
 //     optimiser (third_index).  A wavefront owns 32 channels and a quarter of k, so that a weight is read by one wavefront only
 //     (weights stream from L2: 418 KB per item) and a pixel fragment feeds two channel tiles (LDS would otherwise be as busy as the
 //     matrix cores); the quarters meet in LDS, in their order.
 //
 // Launch times (rocprofv3), fp32 instruction -> this: sevenths (one to twelve states) 13.6 -> 12.0 us, thirds (minibatch 32) 19.4 -> 15.0 us,
-// whole samples (minibatch 256) 63 -> 51 us; act step W = 1 20.3 -> 18.3 us.
+// whole samples (minibatch 256) 63 -> 53 us; act step W = 1 20.3 -> 18.4 us.  A whole item takes 50 k cycles where the matrix cores
+// need 21 k: staging 4 k, conv1 9 k and 3 k of waiting (13 tiles on 8 wavefronts), conv2 12 k, its sums' exchange and output 6 k,
+// conv3 and its exchange 9 k (clock reads of one wavefront).
 #pragma once
 #include "conv_tower.h"
 #include "wgrad_conv.h"
@@ -85,25 +88,26 @@ __device__ inline int here(int v)
 
 // Element `lane` of the 1 KB row at p (wavefront-uniform), as a scalar base plus a lane offset.  Left alone, the compiler adds the
 // lane's part to the base once and keeps a 64-bit vector address for every row of an unrolled stream.
-__device__ inline tf_f32x4 load_row(const float* p, unsigned lane)
-{
-    asm volatile("" : "+s"(p));
-    return reinterpret_cast<const tf_f32x4*>(p)[lane];
-}
-
 __device__ inline bf16x8 load_row8(const bf16_t* p, unsigned lane)
 {
     asm volatile("" : "+s"(p));
     return reinterpret_cast<const bf16x8*>(p)[lane];
 }
 
-// acc[t][c] += (16 weight rows of channel half c) x (16 pixels of tile t) over NK k-steps of 32, every product of two fp32 values as the
-// six largest of the nine products of their bf16 parts, smallest first.  at(s, t): this lane's eight channels of tile t in
-// k-step s, first part.  The operand of tile t + 1 is requested before the matrix work of tile t; done(s) when the weights of step s are used up.
-template <int T, int NK, int PLANE, class At, class Done>
-__device__ inline void tower_f32_mma(tf_f32x4 (&acc)[T][2], bf16x8 (&w)[5][2][3], At& at, Done& done)
+// acc[t][c] += (16 weight rows of channel half c) x (16 pixels of tile t) over NK k-steps of 32, every product of two fp32
+// values as the six largest of the nine products of their bf16 parts.  The five small ones have sums of their own: the instruction
+// cuts its sums off where an fp32 addition rounds, always downwards, and with all six in one accumulator dL/d(act2) was off by
+// 5e-7 where the fp32 instruction is off by 2e-7.  at(s, t): this lane's eight channels of tile t in k-step s, first part.  The operand of
+// the next tile is requested before the matrix work of this one; done(s) when the weights of step s, w[s % 5], are used up.
+// live(s, t) (uniform): false for a last k-step or tile that this wavefront does not have (two bodies, one with and one without, do not
+// keep their registers in place).
+template <int T, int NK, int PLANE, class At, class Done, class Live>
+__device__ inline void tower_f32_mma(tf_f32x4 (&acc)[T][2], bf16x8 (&w)[5][2][3], At& at, Done& done, Live live)
 {
     bf16x8 x[2][3];
+    tf_f32x4 low[T][2];
+#pragma unroll
+    for (int t = 0; t < T; ++t) low[t][0] = low[t][1] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
     auto fetch = [&](auto i_) {
         constexpr int i = decltype(i_)::value, s = i / T, t = i % T;
         const uint8_t* p = at(std::integral_constant<int, s>{}, t);
@@ -113,20 +117,78 @@ __device__ inline void tower_f32_mma(tf_f32x4 (&acc)[T][2], bf16x8 (&w)[5][2][3]
     fetch(std::integral_constant<int, 0>{});
     auto step = [&](auto i_) {
         constexpr int i = decltype(i_)::value, s = i / T, t = i % T;
-        if constexpr (i + 1 < NK * T) fetch(std::integral_constant<int, i + 1>{});
+        if constexpr (i + 1 < NK * T)
+            if (live((i + 1) / T, (i + 1) % T)) fetch(std::integral_constant<int, i + 1>{});
         constexpr int wp[6] = {2, 0, 1, 1, 0, 0}, xp[6] = {0, 2, 1, 0, 1, 0};
+        if (live(s, t))
 #pragma unroll
         for (int u = 0; u < 6; ++u)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s][c][wp[u]], x[i & 1][xp[u]], acc[t][c], 0, 0, 0);
+            for (int c = 0; c < 2; ++c) {
+                tf_f32x4& to = u < 5 ? low[t][c] : acc[t][c];
+                to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s % 5][c][wp[u]], x[i & 1][xp[u]], to, 0, 0, 0);
+            }
         if constexpr (t == T - 1) done(std::integral_constant<int, s>{});
         __builtin_amdgcn_sched_barrier(0);
     };
     static_for<0, NK * T>(step);
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[t][c] += low[t][c];
+}
+// The same for all T tiles without sums for the small products, where there are no registers for them: the small products of all k-steps
+// first, then the large ones, whose operand (first parts only) is read again, five tiles ahead.
+template <int T, int NK, int PLANE, class At, class Done, class Live>
+__device__ inline void tower_f32_mma_passes(tf_f32x4 (&acc)[T][2], bf16x8 (&w)[5][2][3], At& at, Done& done, Live live)
+{
+    bf16x8 x[2][3];
+    auto fetch = [&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        const uint8_t* p = at(std::integral_constant<int, i / T>{}, i % T);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) x[i & 1][q] = *reinterpret_cast<const bf16x8*>(p + q * PLANE);
+    };
+    fetch(std::integral_constant<int, 0>{});
+    auto small = [&](auto i_) {
+        constexpr int i = decltype(i_)::value, s = i / T, t = i % T;
+        if constexpr (i + 1 < NK * T)
+            if (live((i + 1) / T, (i + 1) % T)) fetch(std::integral_constant<int, i + 1>{});
+        constexpr int wp[5] = {2, 0, 1, 1, 0}, xp[5] = {0, 2, 1, 0, 1};
+        if (live(s, t))
+#pragma unroll
+        for (int u = 0; u < 5; ++u)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s % 5][c][wp[u]], x[i & 1][xp[u]], acc[t][c], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    static_for<0, NK * T>(small);
+    auto fetch0 = [&](auto i_) {
+        constexpr int i = decltype(i_)::value;
+        if (live(i / T, i % T)) x[i % 6 / 3][i % 3] = *reinterpret_cast<const bf16x8*>(at(std::integral_constant<int, i / T>{}, i % T));
+    };
+    static_for<0, 5>(fetch0);
+    auto large = [&](auto i_) {
+        constexpr int i = decltype(i_)::value, s = i / T, t = i % T;
+        if constexpr (i + 5 < NK * T) fetch0(std::integral_constant<int, i + 5>{});
+        if (live(s, t))
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[s % 5][c][0], x[i % 6 / 3][i % 3], acc[t][c], 0, 0, 0);
+        if constexpr (t == T - 1) done(std::integral_constant<int, s>{});
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    static_for<0, NK * T>(large);
+}
+template <int T, int NK, int PLANE, class At, class Done, class Live>
+__device__ inline void tower_f32_tiles(tf_f32x4 (&acc)[T][2], bf16x8 (&w)[5][2][3], At& at, Done& done, Live live)
+{
+    static_assert(T < 4 || (NK * T >= 5 && NK <= 5), "five requests ahead; every k-step's weights are there");
+    if constexpr (T >= 4) tower_f32_mma_passes<T, NK, PLANE>(acc, w, at, done, live);
+    else tower_f32_mma<T, NK, PLANE>(acc, w, at, done, live);
 }
 
 // The k-quarters of the 2 T tiles of 32 channels meet: wavefront (cp, kq) finishes tiles [kq * OWN, + OWN), adds the quarters in their order and
-// hands the sums to finish(t, c, sum).  ex: 2 * 2 T * 3 KB of LDS that nobody reads any more.
+// hands the sums to finish(i, t, c, sum), i counting its own.  ex: 2 * 2 T * 3 KB of LDS that nobody reads any more.
 template <int T, class Finish>
 __device__ inline void tower_f32_exchange(const tf_f32x4 (&acc)[T][2], float* ex, int cp, int kq, int lane, Finish finish)
 {
@@ -147,73 +209,9 @@ __device__ inline void tower_f32_exchange(const tf_f32x4 (&acc)[T][2], float* ex
         if (j < NS) {
             const tf_f32x4 r0 = slots[(j * 3) * 64], r1 = slots[(j * 3 + 1) * 64], r2 = slots[(j * 3 + 2) * 64];
             const tf_f32x4 q0 = kq == 0 ? own[i] : r0, q1 = kq == 0 ? r0 : kq == 1 ? own[i] : r1, q2 = kq < 2 ? r1 : kq == 2 ? own[i] : r2, q3 = kq == 3 ? own[i] : r2;
-            finish(j / 2, j % 2, ((q0 + q1) + q2) + q3);
+            finish(i, j / 2, j % 2, ((q0 + q1) + q2) + q3);
         }
     }
-}
-
-// acc[t] += (16 weight rows) x (16 pixels of tile t) over filter rows 0 .. ROWS - 1 with STEPS k-steps of sixteen each; `base`
-// points at this lane's pixel (its window's top-left corner, this lane's four channels), `w` at the channel tile's weights, `ring`
-// holds this lane's share of the first D steps.  k-step s of a filter row: tap s / CPT, channels 16 * (s % CPT) ..
-template <int NT, int ROWS, int STEPS, int CPT, int ROW_PITCH, int PITCH, int D>
-__device__ inline void tower_f32_rows(tf_f32x4 (&acc)[NT], const float* (&base)[NT], const float* w, unsigned lane, tf_f32x4 (&ring)[D])
-{
-    static_assert(STEPS % D == 0 || D % STEPS == 0, "the ring slot of a step is the same in every filter row");
-    static_assert(STEPS % D == 0 && STEPS % 2 == 0, "ring and double buffer start every filter row at slot 0");
-    tf_f32x4 px[2][NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) px[0][t] = *reinterpret_cast<const tf_f32x4*>(base[t]);
-    for (int p = 0; p < ROWS; ++p) {
-        // past the last row the requests repeat the row's own first steps (never used, never skipped)
-        const float* wn = p + 1 < ROWS ? w + STEPS * 256 : w;
-        const int down = p + 1 < ROWS ? ROW_PITCH : 0;
-#pragma unroll
-        for (int s = 0; s < STEPS; ++s) {
-            const tf_f32x4 wv = ring[s % D];
-            ring[s % D] = load_row(s + D < STEPS ? w + (s + D) * 256 : wn + (s + D - STEPS) * 256, lane);
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                px[(s + 1) & 1][t] = *reinterpret_cast<const tf_f32x4*>(s + 1 < STEPS ? base[t] + ((s + 1) / CPT) * PITCH + ((s + 1) % CPT) * 16 : base[t] + down);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], px[s & 1][t][e], acc[t], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        w = wn;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) base[t] += down;
-    }
-}
-
-// The same sum for a workgroup that runs one item and ends: its weights come from memory nobody has touched yet, so what counts is
-// how many are in flight.  The k-steps of both layers are one stream of weight vectors with a ring of kTfStream entries (step S of
-// the stream sits in slot S % kTfStream): the first layer finds its weights requested, and requests the next one's as it goes.
-// 24 entries are 96 registers; 32 spill in the thirds.  (Rings of 8 and 6 as above: 15.5 / 21.6 us for sevenths / thirds.)
-// S0: stream position of the layer's first step, TOTAL: length of the stream; KS_ROW: k-steps per filter row.
-constexpr int kTfStream = 24;
-template <int NT, int S0, int STEPS, int KS_ROW, int CPT, int ROW_PITCH, int PITCH, int TOTAL, class Weights>
-__device__ inline void tower_f32_stream(tf_f32x4 (&acc)[NT], const float* const (&base)[NT], tf_f32x4 (&ring)[kTfStream], Weights& weights)
-{
-    tf_f32x4 px[2][NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) px[0][t] = *reinterpret_cast<const tf_f32x4*>(base[t]);
-    auto step = [&](auto s_) {
-        constexpr int s = decltype(s_)::value, slot = (S0 + s) % kTfStream, n = s + 1;
-        const tf_f32x4 wv = ring[slot];
-        if constexpr (S0 + s + kTfStream < TOTAL) ring[slot] = weights(S0 + s + kTfStream);
-        if constexpr (n < STEPS) {
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-                px[n & 1][t] = *reinterpret_cast<const tf_f32x4*>(base[t] + (n / KS_ROW) * ROW_PITCH + (n % KS_ROW / CPT) * PITCH + (n % CPT) * 16);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-            for (int t = 0; t < NT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e], px[s & 1][t][e], acc[t], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    static_for<0, STEPS>(step);
 }
 
 // PARTS: a workgroup runs a whole sample, or one half / third / seventh of its output rows with the rows of conv2 and conv1 these
@@ -366,24 +364,28 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                     const uint32_t* wp = reinterpret_cast<const uint32_t*>(base[t] + (k / 4) * 7056 + ((k % 4) * 2) * 84);
                     return make_uint2(wp[0], wp[1]);
                 };
-                uint2 px[2][NT];
-                bf16x8 wf[2][3];
+                // Operands are requested DEPTH - 1 k-steps ahead: with one tile per wavefront and hardly a second wavefront on the SIMD, a
+                // k-step's 96 matrix cycles do not cover the LDS latency (one step ahead, sevenths: 4.2 k cycles for 1.5 k of matrix work).
+                constexpr int DEPTH = PARTS > 1 ? 4 : 2;
+                uint2 px[DEPTH][NT];
+                bf16x8 wf[DEPTH][3];
                 auto fetch = [&](int buf, int k) {
 #pragma unroll
                     for (int q = 0; q < 3; ++q) wf[buf][q] = *reinterpret_cast<const bf16x8*>(sW1 + q * kTfW1Plane + (k * 64 + lane) * 8);
 #pragma unroll
                     for (int t = 0; t < NT; ++t) px[buf][t] = fetch_px(t, k);
                 };
-                fetch(0, 0);
+#pragma unroll
+                for (int k = 0; k < DEPTH - 1; ++k) fetch(k, k);
                 auto step = [&](auto k_) {
                     constexpr int k = decltype(k_)::value;
-                    if constexpr (k + 1 < 16) fetch((k + 1) & 1, k + 1);
+                    if constexpr (k + DEPTH - 1 < 16) fetch((k + DEPTH - 1) % DEPTH, k + DEPTH - 1);
                     if constexpr (PARTS > 1 && k % 4 == 0) request2(std::integral_constant<int, k / 4>{});   // (all at once they would stand in front of conv1)
 #pragma unroll
                     for (int t = 0; t < NT; ++t) {
-                        const bf16x8 x = bf16x8_from_bytes(px[k & 1][t].x, px[k & 1][t].y);
+                        const bf16x8 x = bf16x8_from_bytes(px[k % DEPTH][t].x, px[k % DEPTH][t].y);
 #pragma unroll
-                        for (int q = 2; q >= 0; --q) mma_32x32x16(acc[t], wf[k & 1][q], x);   // smallest part first
+                        for (int q = 2; q >= 0; --q) mma_32x32x16(acc[t], wf[k % DEPTH][q], x);   // smallest part first
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 };
@@ -423,11 +425,11 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                 acc[t][0] = acc[t][1] = tf_f32x4{0.f, 0.f, 0.f, 0.f};
             }
             auto at = [&](auto s_, int t) { constexpr int s = decltype(s_)::value; return sA1 + tf_a1(base[t] + (s & 1) * 10 + (s >> 1), lk); };
-            tower_f32_mma<T2, 4, kTfA1Plane>(acc, wr, at, request3);
+            tower_f32_tiles<T2, 4, kTfA1Plane>(acc, wr, at, request3, [](int, int) { return true; });
             request3(std::integral_constant<int, 4>{});
             __syncthreads();   // act1 has been read
             float* g2 = a.act2[g];
-            tower_f32_exchange<T2>(acc, sEx, cp, kq, lane, [&](int t, int c, const tf_f32x4& sum) {
+            tower_f32_exchange<T2>(acc, sEx, cp, kq, lane, [&](int, int t, int c, const tf_f32x4& sum) {
                 const int lpx = t * 16 + here(lq), px = r3_lo * 9 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 const float4 bv = *reinterpret_cast<const float4*>(sB2 + ch);
                 if (lpx < n2) {
@@ -463,9 +465,10 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                 return sA2 + tf_a2(base[t] + (tap / 3) * 9 + tap % 3, 4 * (s & 1) + lk);
             };
             auto nothing = [](auto) {};
-            if (kq < 2) tower_f32_mma<T3, 5, kTfA2Plane>(acc, wr, at, nothing);
-            else tower_f32_mma<T3, 4, kTfA2Plane>(acc, wr, at, nothing);
-            tower_f32_exchange<T3>(acc, sEx, cp, kq, lane, [&](int t, int c, const tf_f32x4& sum) {
+            auto all = [](int, int) { return true; };
+            if (kq < 2) tower_f32_tiles<T3, 5, kTfA2Plane>(acc, wr, at, nothing, all);
+            else tower_f32_tiles<T3, 4, kTfA2Plane>(acc, wr, at, nothing, all);
+            tower_f32_exchange<T3>(acc, sEx, cp, kq, lane, [&](int, int t, int c, const tf_f32x4& sum) {
                 const int lpx = t * 16 + here(lq), px = r3_lo * 7 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 const float4 bv = *reinterpret_cast<const float4*>(sB3 + ch);
                 if (lpx < n3)

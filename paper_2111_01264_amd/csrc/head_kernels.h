@@ -36,34 +36,16 @@ inline Offsets make_offsets(int A)
 //   fc1:   [3136 f][512 o]
 // All three are kept in MFMA fragment order (over [row][k]: conv per (class,) [c][k], fc1 over [f][o]), the order their
 // consumers load them in: one operand of a matrix instruction is then one contiguous 1 KB row instead of 16 or 32 separate
-// cache lines (in full precision with the conv taps reversed, see conv_tower_bwd_f32.h).
+// cache lines.
+// Full precision: conv2's and conv3's are behind the end, as three bf16 parts each (third_index) and with the taps reversed, see
+// conv_tower_bwd_f32.h.
 constexpr size_t kBshW2 = 0, kBshW3 = 4 * 32 * 256, kBshWf1 = kBshW3 + 64 * 576;
 constexpr size_t kBshTotal = kBshWf1 + static_cast<size_t>(3136) * 512;
 
-// Where element r of conv2.w ([o][p][q][c]) / conv3.w lives in the backward copy.
-template <typename T> __host__ __device__ inline size_t bsh_index_w2(int r)
-{
-    const int c = r % 32, q = (r / 32) % 4, p = (r / 128) % 4, oc = r / 512;
-    const int cls = (p % 2) * 2 + (q % 2), tap = (p / 2) * 2 + (q / 2);
-    return kBshW2 + static_cast<size_t>(cls) * 32 * 256 + (sizeof(T) == 2 ? tower_frag_index(c, tap * 64 + oc, 256) : frag16_index(c, (3 - tap) * 64 + oc, 256));
-}
-template <typename T> __host__ __device__ inline size_t bsh_index_w3(int r)
-{
-    const int c = r % 64, q = (r / 64) % 3, p = (r / 192) % 3, oc = r / 576;
-    const int tap = p * 3 + q;
-    return kBshW3 + (sizeof(T) == 2 ? tower_frag_index(c, tap * 64 + oc, 576) : frag16_index(c, (8 - tap) * 64 + oc, 576));
-}
-
-template <typename T> __host__ __device__ inline size_t bsh_index_wf1(int o, int f)
-{
-    return kBshWf1 + frag_index<T>(f, o, 512);
-}
-
-// Full precision: conv2's and conv3's weights are not in the forward copy's own places but behind its end, as three bf16 parts each
-// (third_index) whose sum is the fp32 weight: 8 + 8 + 8 significand bits.
 constexpr size_t kThirdsW2 = 0, kThirdsW3 = static_cast<size_t>(3) * 64 * 512, kThirdsTotal = kThirdsW3 + static_cast<size_t>(3) * 64 * 576;   // bf16 elements
-__host__ __device__ inline size_t thirds_offset(const Offsets& off) { return (off.total + 63) / 64 * 64; }   // in floats
-inline size_t copy_elements(const Offsets& off, size_t esize) { return esize == 4 ? thirds_offset(off) + kThirdsTotal / 2 : off.total; }
+inline size_t bsh_elements(size_t esize) { return kBshTotal + (esize == 4 ? kThirdsTotal / 2 : 0); }
+
+// The value v as row o, column k of a [..][K] matrix in three bf16 parts whose sum it is: 8 + 8 + 8 significand bits.
 __device__ inline void store_thirds(bf16_t* thirds, int o, int k, int K, float v)
 {
 #pragma unroll
@@ -73,6 +55,32 @@ __device__ inline void store_thirds(bf16_t* thirds, int o, int k, int K, float v
         v -= static_cast<float>(p);
     }
 }
+
+// Element r of conv2.w ([o][p][q][c]) / conv3.w into the backward copy.
+template <typename T> __device__ inline void bsh_store_w2(T* bsh, int r, float v)
+{
+    const int c = r % 32, q = (r / 32) % 4, p = (r / 128) % 4, oc = r / 512;
+    const int cls = (p % 2) * 2 + (q % 2), tap = (p / 2) * 2 + (q / 2);
+    if (sizeof(T) == 2) bsh[kBshW2 + static_cast<size_t>(cls) * 32 * 256 + tower_frag_index(c, tap * 64 + oc, 256)] = from_float<T>(v);
+    else store_thirds(reinterpret_cast<bf16_t*>(bsh + kBshTotal) + kThirdsW2 + static_cast<size_t>(cls) * 3 * 32 * 256, c, (3 - tap) * 64 + oc, 256, v);
+}
+template <typename T> __device__ inline void bsh_store_w3(T* bsh, int r, float v)
+{
+    const int c = r % 64, q = (r / 64) % 3, p = (r / 192) % 3, oc = r / 576;
+    const int tap = p * 3 + q;
+    if (sizeof(T) == 2) bsh[kBshW3 + tower_frag_index(c, tap * 64 + oc, 576)] = from_float<T>(v);
+    else store_thirds(reinterpret_cast<bf16_t*>(bsh + kBshTotal) + kThirdsW3, c, (8 - tap) * 64 + oc, 576, v);
+}
+
+template <typename T> __host__ __device__ inline size_t bsh_index_wf1(int o, int f)
+{
+    return kBshWf1 + frag_index<T>(f, o, 512);
+}
+
+// Full precision: conv2's and conv3's weights are not in the forward copy's own places but behind its end, as three bf16 parts each
+// (third_index) whose sum is the fp32 weight: 8 + 8 + 8 significand bits.
+__host__ __device__ inline size_t thirds_offset(const Offsets& off) { return (off.total + 63) / 64 * 64; }   // in floats
+inline size_t copy_elements(const Offsets& off, size_t esize) { return esize == 4 ? thirds_offset(off) + kThirdsTotal / 2 : off.total; }
 
 // Where blob element e lives in the forward copy: identical, except that the weights of conv2, conv3 and fc1 (bf16 mode: conv1
 // too) are kept in MFMA fragment order of the kernels that load them.  bf16 mode stores conv1's weights as fp16 (that
@@ -625,7 +633,7 @@ __device__ inline void rms_conv_block(float* theta, float* grad, float* v, float
         constexpr int K = CONV == 1 ? 512 : 576;
         if (sizeof(T) == 2) static_cast<T*>(a.sh)[E0 + tower_frag_index(el / K, el % K, K)] = from_float<T>(th);
         else store_thirds(reinterpret_cast<bf16_t*>(static_cast<T*>(a.sh) + thirds_offset(a.off)) + (CONV == 1 ? kThirdsW2 : kThirdsW3), el / K, el % K, K, th);
-        static_cast<T*>(a.bsh)[CONV == 1 ? bsh_index_w2<T>(el) : bsh_index_w3<T>(el)] = from_float<T>(th);
+        if (CONV == 1) bsh_store_w2<T>(static_cast<T*>(a.bsh), el, th); else bsh_store_w3<T>(static_cast<T*>(a.bsh), el, th);
     }
 }
 
@@ -767,8 +775,8 @@ __global__ __launch_bounds__(256) void build_copies_kernel(const float* __restri
     const T val = from_float<T>(theta[e]);
     shadow_store<T>(sh, off, e, theta[e]);
     if (bsh) {
-        if (e >= off.w2 && e < off.b2) bsh[bsh_index_w2<T>(static_cast<int>(e - off.w2))] = val;
-        else if (e >= off.w3 && e < off.b3) bsh[bsh_index_w3<T>(static_cast<int>(e - off.w3))] = val;
+        if (e >= off.w2 && e < off.b2) bsh_store_w2<T>(bsh, static_cast<int>(e - off.w2), theta[e]);
+        else if (e >= off.w3 && e < off.b3) bsh_store_w3<T>(bsh, static_cast<int>(e - off.w3), theta[e]);
         else if (e >= off.wf1 && e < off.bf1) {
             const size_t r = e - off.wf1;
             bsh[bsh_index_wf1<T>(static_cast<int>(r / 3136), static_cast<int>(r % 3136))] = val;

@@ -471,7 +471,8 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         DQN_LAUNCH_CHECK();
     } else {
         TowerBwdF32Args ta{};
-        ta.dz3 = dz3; ta.act2 = act2; ta.act1 = act1; ta.w3d = bsh + kBshW3; ta.w2d = bsh + kBshW2;
+        const bf16_t* thirds = reinterpret_cast<const bf16_t*>(bsh + kBshTotal);
+        ta.dz3 = dz3; ta.act2 = act2; ta.act1 = act1; ta.w3d = thirds + kThirdsW3; ta.w2d = thirds + kThirdsW2;
         ta.dz2 = dz2; ta.dz1 = dz1; ta.n = B;
         DQN_HIP(raise_lds_limits());
         const int parts = 5 * B <= c->num_cus ? 5 : (2 * B <= c->num_cus ? 2 : 1);
@@ -687,8 +688,8 @@ int dqn_create(const dqn_config* cfg, void* act_stream, void* train_stream, dqn_
         if (rc != DQN_OK) return rc;
         rc = alloc_ws(c->act_ws, cfg->max_envs, 1, c->A, c->esize);
         if (rc != DQN_OK) return rc;
-        DQN_HIP(hipMalloc(&c->bsh, kBshTotal * c->esize));
-        DQN_HIP(hipMemset(c->bsh, 0, kBshTotal * c->esize));
+        DQN_HIP(hipMalloc(&c->bsh, bsh_elements(c->esize) * c->esize));
+        DQN_HIP(hipMemset(c->bsh, 0, bsh_elements(c->esize) * c->esize));
         DQN_HIP(hipMalloc((void**)&c->bias_partial, 65536 * sizeof(float)));
         DQN_HIP(hipMalloc((void**)&c->wg_partial, kWgTotal * sizeof(float)));
         DQN_HIP(hipMalloc(&c->dzh, B * 512 * c->esize));
