@@ -19,6 +19,7 @@ struct WgradAllArgs {
     int first[6];   // first block of: conv1, conv2, conv3, fc1, small reductions, end
 };
 
+static_assert(kWgF1Cols == 25 && kWgF1Rows == 8, "see xcd_fc1_tile");
 constexpr size_t kWgradAllSmem = []() {
     size_t m = kSmallGradsSmem;
     if (kWgF1Smem > m) m = kWgF1Smem;
@@ -44,12 +45,17 @@ __global__ __launch_bounds__(256, 2) void wgrad_all_kernel(int f1, int f2, int f
         c1.partial = a.c1.partial; c1.bias_partial = a.c1.bias_partial;
         wgrad_conv_block<WgConv1>(c1, blk, 0, wg_smem);
     } else if (blk < f2) {
-        wgrad_conv_block<WgConv2>(a.c2, (blk - f1) / WgConv2::CS, (blk - f1) % WgConv2::CS, wg_smem);
+        int cb;
+        const int slice = xcd_slice<WgConv2::CS>(blk - f1, (f2 - f1) / WgConv2::CS, cb);
+        wgrad_conv_block<WgConv2>(a.c2, slice, cb, wg_smem);
     } else if (blk < f3) {
-        wgrad_conv_block<WgConv3>(a.c3, (blk - f2) / WgConv3::CS, (blk - f2) % WgConv3::CS, wg_smem);
+        int cb;
+        const int slice = xcd_slice<WgConv3::CS>(blk - f2, (f3 - f2) / WgConv3::CS, cb);
+        wgrad_conv_block<WgConv3>(a.c3, slice, cb, wg_smem);
     } else if (blk < f4) {
-        const int i = blk - f3;
-        wgrad_fc1_block(a.f1, i % kWgF1Cols, i / kWgF1Cols, wg_smem);
+        int col, row;
+        xcd_fc1_tile(blk - f3, col, row);
+        wgrad_fc1_block(a.f1, col, row, wg_smem);
     } else {
         small_grads_block<bf16_t>(a.small, blk - f4, wg_smem);
     }

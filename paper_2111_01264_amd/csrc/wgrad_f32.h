@@ -248,12 +248,20 @@ __global__ __launch_bounds__(256, 2) void wgrad_f32_kernel(WgradF32Args a)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char wf_smem[];
     const int blk = blockIdx.x;
-    if (blk < a.first[1]) wgrad_conv_f32_block<WgConv2F32>(a.c2, blk / WgConv2F32::CS, blk % WgConv2F32::CS, wf_smem);
+    int cb;
+    if (blk < a.first[1]) {
+        const int slice = xcd_slice<WgConv2F32::CS>(blk, a.first[1] / WgConv2F32::CS, cb);
+        wgrad_conv_f32_block<WgConv2F32>(a.c2, slice, cb, wf_smem);
+    }
     else if (blk < a.first[2]) wgrad_conv_block<WgConv1F32>(a.c1, blk - a.first[1], 0, wf_smem);
-    else if (blk < a.first[3]) wgrad_conv_f32_block<WgConv3F32>(a.c3, (blk - a.first[2]) / WgConv3F32::CS, (blk - a.first[2]) % WgConv3F32::CS, wf_smem);
+    else if (blk < a.first[3]) {
+        const int slice = xcd_slice<WgConv3F32::CS>(blk - a.first[2], (a.first[3] - a.first[2]) / WgConv3F32::CS, cb);
+        wgrad_conv_f32_block<WgConv3F32>(a.c3, slice, cb, wf_smem);
+    }
     else if (blk < a.first[4]) {
-        const int i = blk - a.first[3];
-        wgrad_fc1_f32_block(a.f1, i % kWgF1fCols, i / kWgF1fCols, wf_smem);
+        int col, row;
+        xcd_fc1_tile(blk - a.first[3], col, row);
+        wgrad_fc1_f32_block(a.f1, col, row, wf_smem);
     } else small_grads_block<float>(a.small, blk - a.first[4], wf_smem);
 }
 
