@@ -11,10 +11,9 @@
 // 16-byte vectors, 512 contiguous bytes per row.
 //
 // Tried and dropped: applying the optimiser step to the tile right here (the workgroup has the final gradient, so theta,
-// v, m could be read and written once and the gradient never read back).  Correct, but slower in sum: the optimiser
-// kernel that remains (conv weights from their split-K slices, biases, fc2) takes about as long as before -- its time
-// is the slice sums' chain of round trips, not the streaming of fc1.w -- while this kernel grows by the 60 MB it then
-// moves (batch 32: 15.5 + 9.6 us against 12.1 + 12.7 us; batch 256: 28.3 + 13.8 against 19.8 + 17.3).
+// v, m could be read and written once and the gradient never read back).  Correct, but slower in sum: 200 workgroups ask for their
+// parameters, wait, update and store 130 KB each in step, where the optimiser kernel's blocks stream past one another (batch 32:
+// 14.9 + 5.3 us against 7.2 + 12.0 us; batch 256: 25.4 + 8.0 against 16.0 + 12.6).
 #pragma once
 #include "gemm_tn_tr.h"
 #include "head_kernels.h"
