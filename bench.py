@@ -70,14 +70,14 @@ _WG_SRC = (_C + "wgrad_all.h", _C + "wgrad_conv.h", _C + "wgrad_fc1.h", _C + "ge
 _TOWER_SRC = (_C + "conv_tower.h", _C + "conv_ws.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
 _TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower.h", _C + "conv_ws.h", _C + "gemm_mfma.h", _C + "net.hip")
 TRAFFIC = {
-    ("rmsprop", 32, "bf16"): (66.16e6, _RMS_SRC, "04b098e8e5afd762a19a4e8bad05d9ea95f77a45", "profiles/hbm_traffic_b32.txt"),
-    ("wgrad_all", 32, "bf16"): (25.63e6, _WG_SRC, "0a99a0aeb00340b719a0eaf1e2dca707da54d3b6", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower", 32, "bf16"): (10.26e6, _TOWER_SRC, "b0874bb25d0a1959b7edaf5b96e267f8279aa4cd", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower_bwd", 32, "bf16"): (4.78e6, _TOWER_BWD_SRC, "bb4819da911de89f68019999026c0078f3c48051", "profiles/hbm_traffic_b32.txt"),
-    ("rmsprop", 256, "bf16"): (71.34e6, _RMS_SRC, "04b098e8e5afd762a19a4e8bad05d9ea95f77a45", "profiles/hbm_traffic_b256.txt"),
-    ("wgrad_all", 256, "bf16"): (85.73e6, _WG_SRC, "0a99a0aeb00340b719a0eaf1e2dca707da54d3b6", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower", 256, "bf16"): (24.22e6, _TOWER_SRC, "b0874bb25d0a1959b7edaf5b96e267f8279aa4cd", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower_bwd", 256, "bf16"): (21.25e6, _TOWER_BWD_SRC, "bb4819da911de89f68019999026c0078f3c48051", "profiles/hbm_traffic_b256.txt"),
+    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "989a1c409b9fa8492a5f2c94b0f6970489c4304e", "profiles/hbm_traffic_b32.txt"),
+    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "c82332da442bce74f0fb9e0741362e0326cd7946", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower", 32, "bf16"): (10.26e6, _TOWER_SRC, "4e1175bdd9160845c60bc0d698c1387317c8f92b", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower_bwd", 32, "bf16"): (4.78e6, _TOWER_BWD_SRC, "d4eba027d282838b1d90c002a557d6416bde4acd", "profiles/hbm_traffic_b32.txt"),
+    ("rmsprop", 256, "bf16"): (71.37e6, _RMS_SRC, "989a1c409b9fa8492a5f2c94b0f6970489c4304e", "profiles/hbm_traffic_b256.txt"),
+    ("wgrad_all", 256, "bf16"): (58.50e6, _WG_SRC, "c82332da442bce74f0fb9e0741362e0326cd7946", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower", 256, "bf16"): (24.22e6, _TOWER_SRC, "4e1175bdd9160845c60bc0d698c1387317c8f92b", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower_bwd", 256, "bf16"): (21.25e6, _TOWER_BWD_SRC, "d4eba027d282838b1d90c002a557d6416bde4acd", "profiles/hbm_traffic_b256.txt"),
 }
 
 

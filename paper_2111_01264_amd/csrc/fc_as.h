@@ -58,7 +58,7 @@ __global__ __launch_bounds__(WAVES * 64) void fc_as_kernel(FcAsArgs<T> a)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are dealt out to the eight XCDs in turn, and each has an L2 of its own: an XCD takes a contiguous eighth of the
     // workgroups in the order (problem and slice, feature block, row tile), so that the row tiles that read the same weights share an L2.
-    // (by_rows, by_cols: division by multiplication.  100 train steps at batch 256, Double DQN: 12.00 -> 11.54 ms; at batch 512: 12.40 -> 12.10.)
+    // (by_rows, by_cols: division by multiplication.  Moved at batch 256: 33 -> 18 MB forward, 31 -> 10 MB data gradient; 100 train steps at batch 256, Double DQN: 12.00 -> 11.54 ms; at batch 512: 12.40 -> 12.10.)
     int bx = blockIdx.x, by = blockIdx.y, bz = blockIdx.z;
     if constexpr (SHARED) {
         const uint32_t total = gridDim.x * gridDim.y * gridDim.z, l = bx + gridDim.x * (by + gridDim.y * bz);
