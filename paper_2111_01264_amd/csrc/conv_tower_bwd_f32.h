@@ -4,7 +4,7 @@
 // forward layers are (32 channels and a quarter of k per wavefront); conv2's stage gives a wavefront one parity class, half of its pixels
 // and all of k.  Launch times (rocprofv3), fp32 instruction -> this: minibatch 32 13.6 -> 11.2 us, minibatch 256 39.6 -> 28.6 us.
 //
-// The weight copies (bsh_thirds) hold the taps in REVERSED order, so that the pixel addresses ascend with the
+// The weight copies (bsh_store_w3, bsh_store_w2) hold the taps in REVERSED order, so that the pixel addresses ascend with the
 // weight stream: k = (p', q', o) with p' = KS - 1 - p reads image position (y + p', x + q').
 #pragma once
 #include "conv_tower_bwd.h"
