@@ -584,8 +584,9 @@ __device__ inline void rms_update(const RmsArgs& a, float& th, float g, float& v
 }
 
 // Conv weights of layer CONV: the gradient arrives as `ns` split-K slices.  LANES adjacent lanes share four weights: lane j requests
-// slices j, j + LANES, ... (TRIP per round trip) and adds them in that order, the sums meet in a fixed tree, lanes 0 .. 3 update one
-// weight each.  What counts is the length of the dependent chain: everything an address needs is a constant or comes with the
+// slices j, j + LANES, ... (TRIP per round trip), the sums meet in a fixed tree, lanes 0 .. 3 update one
+// weight each.  Whatever LANES is, there are eight sums (every eighth slice, in order) and one tree, so that the number of lanes
+// does not show in the gradient's bits: four lanes keep two sums each.  What counts is the length of the dependent chain: everything an address needs is a constant or comes with the
 // wavefront, and the parameters are requested with the slices.  (Offsets and counts read from the argument struct, one lane updating
 // all four weights and eight lanes per quad everywhere: these blocks alone were a launch of 8.1 us, now 4.2 us, and the whole
 // kernel 10.7 / 12.1 us at batch 32 / 256, now 9.2 / 10.5 us, back to back.)
@@ -602,16 +603,22 @@ __device__ inline void rms_conv_block(float* theta, float* grad, float* v, float
     for (int u = 0; u < TRIP; ++u) v4[u] = *reinterpret_cast<const float4*>(p + static_cast<size_t>(min(j + u * LANES, ns - 1)) * TSIZE);
     float th = theta[e], vv = v[e], mm = m[e];
     __builtin_amdgcn_sched_barrier(0);
-    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    constexpr int SUMS = 8 / LANES;
+    static_assert(SUMS * LANES == 8 && TRIP % SUMS == 0, "eight sums, whichever lanes hold them");
+    float4 part[SUMS];
+#pragma unroll
+    for (int k = 0; k < SUMS; ++k) part[k] = make_float4(0.f, 0.f, 0.f, 0.f);
     for (int s0 = j; s0 < ns; s0 += TRIP * LANES) {
 #pragma unroll
         for (int u = 0; u < TRIP; ++u)
-            if (s0 + u * LANES < ns) { sum.x += v4[u].x; sum.y += v4[u].y; sum.z += v4[u].z; sum.w += v4[u].w; }
+            if (s0 + u * LANES < ns) { float4& to = part[u % SUMS]; to.x += v4[u].x; to.y += v4[u].y; to.z += v4[u].z; to.w += v4[u].w; }
         if (s0 + TRIP * LANES < ns) {
 #pragma unroll
             for (int u = 0; u < TRIP; ++u) v4[u] = *reinterpret_cast<const float4*>(p + static_cast<size_t>(min(s0 + (TRIP + u) * LANES, ns - 1)) * TSIZE);
         }
     }
+    float4 sum = part[0];
+    if (SUMS == 2) { sum.x += part[SUMS - 1].x; sum.y += part[SUMS - 1].y; sum.z += part[SUMS - 1].z; sum.w += part[SUMS - 1].w; }
 #pragma unroll
     for (int d = LANES / 2; d >= 1; d >>= 1) {
         sum.x += __shfl_xor(sum.x, d, LANES); sum.y += __shfl_xor(sum.y, d, LANES);
