@@ -6,11 +6,24 @@
 //
 // The weight copies (bsh_store_w3, bsh_store_w2) hold the taps in REVERSED order, so that the pixel addresses ascend with the
 // weight stream: k = (p', q', o) with p' = KS - 1 - p reads image position (y + p', x + q').
+//
+// Every second sample is run with its gradient negated (its images in LDS hold -dz3 and -dz2; what is stored is turned back).  The bf16
+// instruction rounds its sum to nearest, but aligns what it adds to the largest term and cuts the rest off DOWNWARDS: dz2 came out -8e-9 of
+// its mean magnitude off on average (whole samples; up to -1.9e-8 with weights spread over three decades), which is an eighth of
+// its rounding error, but the weight and bias gradients are sums over 81 B of these, the rounding errors average out there and an
+// offset does not: at minibatch 256 dL/d(conv2.b) was off by 1.0e-6 where the fp32 instruction is off by 4.3e-7.  Negated, the
+// cut points upwards, and the offsets of the minibatch's two halves take each other out.
 #pragma once
 #include "conv_tower_bwd.h"
 #include "conv_tower_f32.h"
 
 namespace dqn {
+
+// v, or -v where flip is the sign bit.
+__device__ inline tf_f32x4 tf_flip(const tf_f32x4& v, uint32_t flip)
+{
+    return __builtin_bit_cast(tf_f32x4, __builtin_bit_cast(wg_u32x4, v) ^ flip);
+}
 
 struct TowerBwdF32Args {
     const float* dz3;    // [n][49][64], already through conv3's ReLU mask
@@ -94,6 +107,9 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
                 *reinterpret_cast<uint4*>(sP3 + pl * kTbfPlane + px * 128 + (v & 7) * 16) = make_uint4(0, 0, 0, 0);
             }
         }
+        const uint32_t flip = (b & 1) ? 0x80000000u : 0u;
+        xv0 = tf_flip(xv0, flip);
+        xv1 = tf_flip(xv1, flip);
         tf_store4<kTbfPlane>(slot(here(tid)), xv0[0], xv0[1], xv0[2], xv0[3]);
         tf_store4<kTbfPlane>(slot(here(v1)), xv1[0], xv1[1], xv1[2], xv1[3]);
         __syncthreads();
@@ -124,10 +140,11 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
             tower_f32_exchange<T3>(acc, sEx, cp, kq, lane, [&](int i, int t, int c, const tf_f32x4& sum) {
                 const int lpx = t * 16 + here(lq), px = r2_lo * 9 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 if (lpx < n2) {
-                    float v[4];
+                    tf_f32x4 v;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = mask3[i][e] > 0.f ? sum[e] : 0.f;
                     tf_store4<kTbfPlane>(sP2 + tf_a2((px / 9 + 1) * 11 + px % 9 + 1, ch >> 3) + 2 * (ch & 4), v[0], v[1], v[2], v[3]);
+                    v = tf_flip(v, flip);
                     store4<float>(dz2_ + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v[0], v[1], v[2], v[3]);
                 }
             });
@@ -171,7 +188,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
                 if ((ph + 2 * t) * 16 + lq < NC)
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        const tf_f32x4 sum = acc[t][c];
+                        const tf_f32x4 sum = tf_flip(acc[t][c], flip);
                         store4<float>(dz1_ + (static_cast<size_t>(b) * 400 + place(t)) * 32 + c * 16 + 4 * lk, mask[t][c][0] > 0.f ? sum[0] : 0.f,
                                       mask[t][c][1] > 0.f ? sum[1] : 0.f, mask[t][c][2] > 0.f ? sum[2] : 0.f, mask[t][c][3] > 0.f ? sum[3] : 0.f);
                     }

@@ -1,0 +1,97 @@
+"""Precision of the full-precision train step: the error of every gradient tensor against the fp64 oracle, as a norm, is no larger than
+the error of the same step with every product on the fp32 matrix instruction.
+
+The inputs leave nothing but the backward pass's own rounding: every ReLU has one state for any input (a hidden channel's bias is
+larger than the largest weighted sum its inputs can reach, odd channels have it negative) and every TD error is clipped, so dL/dQ is
+exactly +-1/B.  Weights have both signs, so the data gradients are sums with cancellation, and since the activations are nearly
+constant the weight gradients are, like the bias gradients, sums over all pixels and samples of a data gradient: a rounding
+that is not to nearest but always to one side, which a comparison element by element does not see, adds up there.
+
+RECORDED holds the errors of the kernels that computed everything on the fp32 instruction, layer by layer, on the same inputs (both
+sides are deterministic); a tenth is allowed on top, for sums of the same precision in another order (the tensors whose products
+are still made by that instruction, conv3.b and fc1.w, moved by up to 6 % when only the order of their sums changed).
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+import paper_2111_01264_amd as P
+from datagen import synth
+from oracle import dqn as odqn
+from tests.gpu_util import blob_slices, dev, make_cfg
+
+SLACK = 1.1
+SCALE = {"conv1": 0.25, "conv2": 0.2, "conv3": 0.1, "fc1": 0.02, "fc2": 0.02}
+
+
+def steady_params(seed, A):
+    """init_params scaled by SCALE, each hidden bias 0.5 beyond what the channel's inputs can reach (odd channels: negative)."""
+    theta = synth.init_params(seed, A).astype(np.float64)
+    off, top = 0, 1.0
+    for name, shape, _ in synth.layer_shapes(A):
+        n = int(np.prod(shape))
+        w = theta[off:off + n].reshape(shape[0], -1)
+        w *= SCALE[name]
+        if name != "fc2":
+            reach = np.abs(w).sum(1) * top + 0.5
+            theta[off + n:off + n + shape[0]] = reach * np.where(np.arange(shape[0]) % 2, -1.0, 1.0)
+            top = 2.0 * reach.max()
+        off += n + shape[0]
+    return theta.astype(np.float32)
+
+
+SEEDS = 4
+
+
+def gradient_errors(B, double_dqn):
+    """Root mean square over the seeds: a single draw of 32 bias gradients scatters by a third."""
+    runs = [step_errors(B, double_dqn, 6400 + B + 1000 * k) for k in range(SEEDS)]
+    return {name: float(np.sqrt(np.mean([e[name] ** 2 for e in runs]))) for name in runs[0]}
+
+
+def step_errors(B, double_dqn, seed):
+    A = 6
+    cfg = make_cfg(A, max_batch=B, max_envs=1, precision=P.DQN_PRECISION_FP32, double_dqn=double_dqn, seed=seed)
+    ctx = P.dqn_create(cfg, torch.cuda.Stream(), torch.cuda.Stream())
+    try:
+        theta, theta_t = steady_params(seed, A), steady_params(seed + 1, A)
+        P.dqn_set_params(ctx, P.DQN_PARAMS_ONLINE, theta)
+        P.dqn_set_params(ctx, P.DQN_PARAMS_TARGET, theta_t)
+        orc = odqn.OracleDQN(A, theta, double_dqn=bool(double_dqn), seed=seed)
+        orc.theta_target = theta_t.astype(np.float64)
+        rng = np.random.default_rng(seed)
+        s = synth.block_frames(seed + 10, B * 4).reshape(B, 4, 84, 84)
+        s2 = synth.block_frames(seed + 20, B * 4).reshape(B, 4, 84, 84)
+        a = rng.integers(0, A, size=B).astype(np.int32)
+        r = np.array([-300.0, 300.0], dtype=np.float32)[rng.integers(0, 2, size=B)]     # |Q| stays below 100: every error is clipped
+        d = np.zeros(B, dtype=np.float32)
+        P.dqn_train_step(ctx, dev(s), dev(a), dev(r), dev(s2), dev(d), B, None)
+        torch.cuda.synchronize()
+        g = P.dqn_get_params(ctx, P.DQN_PARAMS_GRAD).astype(np.float64)
+        _, q_sa, _ = orc.train_step(s, a, r, s2, d)
+        assert np.abs(q_sa).max() < 100.0
+        return {name: float(np.linalg.norm(g[slc] - orc.last_grad[slc]) / np.linalg.norm(orc.last_grad[slc])) for name, slc in blob_slices(A).items()}
+    finally:
+        P.dqn_destroy(ctx)
+
+
+CASES = [(16, 0), (32, 0), (64, 1), (128, 0), (131, 0), (256, 1), (512, 0)]
+RECORDED = {   # conv1.w conv1.b conv2.w conv2.b conv3.w conv3.b fc1.w fc1.b fc2.w fc2.b
+    16: (4.39e-07, 2.86e-07, 3.58e-07, 2.73e-07, 3.09e-07, 2.14e-07, 9.59e-08, 7.31e-08, 5.07e-08, 0),
+    32: (6.18e-07, 3.99e-07, 4.63e-07, 4.11e-07, 3.54e-07, 2.84e-07, 1.13e-07, 7.75e-08, 4.81e-08, 0),
+    64: (7.61e-07, 4.9e-07, 5.05e-07, 3.98e-07, 4.7e-07, 3.97e-07, 1.8e-07, 1.29e-07, 8.33e-08, 0),
+    128: (9.09e-07, 3.51e-07, 4.55e-07, 3.01e-07, 3.86e-07, 2.95e-07, 2e-07, 9.11e-08, 7.48e-08, 0),
+    131: (1.01e-06, 4.68e-07, 6.77e-07, 4.07e-07, 5.74e-07, 3.65e-07, 2.85e-07, 1.35e-07, 1.06e-07, 9.94e-08),
+    256: (1.36e-06, 5.28e-07, 7.46e-07, 3.82e-07, 5.85e-07, 3.53e-07, 3.21e-07, 1.12e-07, 1.01e-07, 0),
+    512: (1.64e-06, 4.21e-07, 8.25e-07, 3.48e-07, 6.7e-07, 3.04e-07, 4.52e-07, 1.14e-07, 9.62e-08, 0),
+}
+
+
+@pytest.mark.parametrize("B,double_dqn", CASES)
+def test_f32_gradient_errors(B, double_dqn):
+    errs = gradient_errors(B, double_dqn)
+    print("B=%d " % B + " ".join("%s %.2e" % kv for kv in errs.items()))
+    for (name, err), bound in zip(errs.items(), RECORDED[B]):
+        assert err <= SLACK * bound, (name, err, bound)
