@@ -15,6 +15,10 @@
 //     optimiser (third_index).  A wavefront owns 32 channels and a quarter of k, so that a weight is read by one wavefront only
 //     (weights stream from L2: 418 KB per item) and a pixel fragment feeds two channel tiles (LDS would otherwise be as busy as the
 //     matrix cores); the quarters meet in LDS, in their order.
+//   * An infinity, a NaN or a value that rounds past the largest bf16 has no such parts: its second or third one is a NaN, and so is every
+//     sum that it enters.  The ReLUs of conv1 and conv2 hand a NaN on (tf_relu), every activation is in some window of the next layer,
+//     so conv3's sums tell: a workgroup in which one of them is no finite number runs its items once more, at its end, in plain fp32
+//     (tower_f32_plain), and what such values lead to is what fp32 arithmetic makes of them.
 //
 // Launch times (rocprofv3), fp32 instruction -> this: sevenths (one to twelve states) 13.6 -> 12.0 us, thirds (minibatch 32) 19.4 -> 15.0 us,
 // whole samples (minibatch 256) 63 -> 53 us; act step W = 1 20.3 -> 18.4 us.  A whole item takes 50 k cycles where the matrix cores
@@ -41,6 +45,8 @@ struct TowerF32Args {
     const float* b1[kMaxGroups];
     const float* b2[kMaxGroups];
     const float* b3[kMaxGroups];
+    const float* w2_plain[kMaxGroups];   // fp32 [64][512], [64][576]: for tower_f32_plain
+    const float* w3_plain[kMaxGroups];
     float* act1[kMaxGroups];       // [n][400][32] or null
     float* act2[kMaxGroups];       // [n][81][64] or null
     float* act3[kMaxGroups];       // [n][49][64]
@@ -50,8 +56,10 @@ struct TowerF32Args {
 constexpr int kTfW1Plane = 32 * 256;                   // one bf16 part of conv1's weights, fragment order (elements)
 constexpr int kTfA1Plane = 400 * 64, kTfA2Plane = 81 * 128;   // one bf16 part of act1 / act2 (bytes)
 constexpr int kTfXBytes = kTowerXBytes > 3 * kTfA2Plane ? kTowerXBytes : 3 * kTfA2Plane;
-constexpr size_t kTowerF32Smem = kTfXBytes + 3 * kTfW1Plane * 2 + 3 * kTfA1Plane + kTowerThreads * 4;
+constexpr size_t kTowerF32Smem = kTfXBytes + 3 * kTfW1Plane * 2 + 3 * kTfA1Plane + kTowerThreads * 4 + 16;
 static_assert(kTowerF32Smem <= 160 * 1024, "one workgroup per compute unit");
+constexpr size_t kTfPlainSmem = (12800 + 5184) * 4 + kTowerXBytes;
+static_assert(kTfPlainSmem <= kTowerF32Smem, "tower_f32_plain's activations and state");
 static_assert(kTfXBytes % 16 == 0, "16-byte vectors");
 
 // act1 in LDS: a pixel is 64 bytes, four chunks of eight channels.  The even columns of a row come before the odd ones, so that the
@@ -214,6 +222,60 @@ __device__ inline void tower_f32_exchange(const tf_f32x4 (&acc)[T][2], float* ex
     }
 }
 
+// max(v, 0), but NaN stays NaN (fmaxf drops it); one instruction as well.
+__device__ inline float tf_relu(float v) { return __builtin_elementwise_maximum(v, 0.f); }
+
+// One item (its conv3 rows [r3, r3 + rows3) and what they depend on) in plain fp32: a thread per output, sums in the order of k.
+// For values that have no three bf16 parts; cold, and as short as it can be.
+template <bool DESC>
+__device__ inline void tower_f32_plain(const TowerF32Args& a, int g, int b, int r3, int rows3, unsigned char* smem)
+{
+    const int tid = threadIdx.x;
+    float* s1 = reinterpret_cast<float*>(smem);      // act1, act2 of the sample, channels last
+    float* s2 = s1 + 12800;
+    uint8_t* sx = reinterpret_cast<uint8_t*>(s2 + 5184);
+    __threadfence();
+    __syncthreads();   // every earlier store of these activations and every read of this LDS is done
+    for (int v = tid; v < kTowerXBytes / 16; v += kTowerThreads) {
+        uint4 px = make_uint4(0, 0, 0, 0);
+        if (DESC) {
+            const int slot = a.desc[static_cast<size_t>(b) * kDescInts + (g > 0 ? 4 : 0) + v / kFrameVec16];
+            if (slot >= 0) px = reinterpret_cast<const uint4*>(a.ring)[static_cast<size_t>(slot) * kFrameVec16 + v % kFrameVec16];
+        } else px = reinterpret_cast<const uint4*>(a.x[g] + static_cast<size_t>(b) * kTowerXBytes)[v];
+        reinterpret_cast<uint4*>(sx)[v] = px;
+    }
+    __syncthreads();
+    // rows of act1 and act2 that the next part has as well are stored by that part (see the kernel)
+    const bool to_end = r3 + rows3 == 7;
+    for (int i = tid; i < 20 * (2 * rows3 + 6) * 32; i += kTowerThreads) {
+        const int o = i & 31, px = 40 * r3 + (i >> 5), y = px / 20, x = px % 20;
+        float sum = 0.f;
+#pragma unroll 1
+        for (int k = 0; k < 256; ++k) sum = fmaf(a.w1[g][o * 256 + k], static_cast<float>(sx[(k >> 6) * 7056 + (4 * y + ((k >> 3) & 7)) * 84 + 4 * x + (k & 7)]), sum);
+        const float v = fmaxf(sum * (1.f / 255.f) + a.b1[g][o], 0.f);
+        s1[px * 32 + o] = v;
+        if (a.act1[g] && (to_end || i < 40 * rows3 * 32)) a.act1[g][(static_cast<size_t>(b) * 400 + px) * 32 + o] = v;
+    }
+    __syncthreads();
+    for (int i = tid; i < 9 * (rows3 + 2) * 64; i += kTowerThreads) {
+        const int o = i & 63, px = 9 * r3 + (i >> 6), y = px / 9, x = px % 9;
+        float sum = 0.f;
+#pragma unroll 1
+        for (int k = 0; k < 512; ++k) sum = fmaf(a.w2_plain[g][o * 512 + k], s1[((2 * y + (k >> 7)) * 20 + 2 * x + ((k >> 5) & 3)) * 32 + (k & 31)], sum);
+        const float v = fmaxf(sum + a.b2[g][o], 0.f);
+        s2[px * 64 + o] = v;
+        if (a.act2[g] && (to_end || i < 9 * rows3 * 64)) a.act2[g][(static_cast<size_t>(b) * 81 + px) * 64 + o] = v;
+    }
+    __syncthreads();
+    for (int i = tid; i < 7 * rows3 * 64; i += kTowerThreads) {
+        const int o = i & 63, px = 7 * r3 + (i >> 6), y = px / 7, x = px % 7;
+        float sum = 0.f;
+#pragma unroll 1
+        for (int k = 0; k < 576; ++k) sum = fmaf(a.w3_plain[g][o * 576 + k], s2[((y + k / 192) * 9 + x + k / 64 % 3) * 64 + (k & 63)], sum);
+        a.act3[g][(static_cast<size_t>(b) * 49 + px) * 64 + o] = fmaxf(sum + a.b3[g][o], 0.f);
+    }
+}
+
 // PARTS: a workgroup runs a whole sample, or one half / third / seventh of its output rows with the rows of conv2 and conv1 these
 // depend on (see conv_tower_kernel; thirds and sevenths are the same bands); the host takes the smallest part for which the
 // chip still holds every workgroup at once.
@@ -233,6 +295,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
     float* sB1 = reinterpret_cast<float*>(sA1 + 3 * kTfA1Plane);   // biases: conv1 [32], conv2 [64], conv3 [64]
     float* sB2 = sB1 + 32;
     float* sB3 = sB2 + 64;
+    int* sPlain = reinterpret_cast<int*>(sB1 + kTowerThreads);     // not zero: a sum of these items was no finite number
 
     if (static_cast<int>(blockIdx.x) >= tower_blocks_) {
         push_step_block(a.push, static_cast<int>(blockIdx.x) - tower_blocks_);
@@ -243,10 +306,14 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
     const int part = PARTS == 1 ? 0 : static_cast<int>(blockIdx.x % PARTS);
     const int first = PARTS == 1 ? blockIdx.x * per_ : static_cast<int>(blockIdx.x / PARTS), last = PARTS == 1 ? min(total, first + per_) : min(total, first + 1);
     if (first >= last) return;
+    if (tid == 0) *sPlain = 0;
     // first conv3 row and pixel counts of this part (conv3 rows [r, r') need conv2 rows [r, r' + 2), those conv1 rows [2 r, 2 r' + 6))
     const int r3_lo = PARTS == 1 ? 0 : PARTS == 2 ? 4 * part : PARTS == 7 ? part : (part == 0 ? 0 : part == 1 ? 3 : 5);
     const int rows3 = PARTS == 1 ? 7 : PARTS == 2 ? 4 - part : PARTS == 7 ? 1 : (part == 0 ? 3 : 2);
     const int n3 = 7 * rows3, n2 = 9 * (rows3 + 2), n1 = 20 * (2 * rows3 + 6);
+    // of act1 and act2, a part stores the rows that no later part has (both would store the same values, but for tower_f32_plain)
+    const bool to_end = PARTS == 1 || r3_lo + rows3 == 7;
+    const int own2 = to_end ? n2 : 9 * rows3, own1 = to_end ? n1 : 40 * rows3;
     constexpr int T2 = PARTS == 1 ? 6 : PARTS == 2 ? 4 : PARTS == 3 ? 3 : 2, T3 = PARTS == 1 ? 4 : PARTS == 7 ? 1 : 2;   // 16-pixel tiles of conv2 / conv3
     constexpr int T1 = PARTS == 1 ? 13 : PARTS == 2 ? 9 : PARTS == 3 ? 8 : 5;                                            // 32-pixel tiles of conv1
 
@@ -400,10 +467,10 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                         for (int q = 0; q < 4; ++q) {
                             const int ch = 8 * q + 4 * kg;
                             const float4 bv = *reinterpret_cast<const float4*>(sB1 + ch);
-                            const float v0 = fmaxf(acc[t][4 * q] * kScale + bv.x, 0.f), v1 = fmaxf(acc[t][4 * q + 1] * kScale + bv.y, 0.f);
-                            const float v2 = fmaxf(acc[t][4 * q + 2] * kScale + bv.z, 0.f), v3 = fmaxf(acc[t][4 * q + 3] * kScale + bv.w, 0.f);
+                            const float v0 = tf_relu(acc[t][4 * q] * kScale + bv.x), v1 = tf_relu(acc[t][4 * q + 1] * kScale + bv.y);
+                            const float v2 = tf_relu(acc[t][4 * q + 2] * kScale + bv.z), v3 = tf_relu(acc[t][4 * q + 3] * kScale + bv.w);
                             tf_store4<kTfA1Plane>(sA1 + tf_a1(at, q) + 8 * kg, v0, v1, v2, v3);
-                            if (g1) store4<float>(g1 + (static_cast<size_t>(b) * 400 + px1) * 32 + ch, v0, v1, v2, v3);
+                            if (g1 && lpx < own1) store4<float>(g1 + (static_cast<size_t>(b) * 400 + px1) * 32 + ch, v0, v1, v2, v3);
                         }
                     }
                 }
@@ -433,9 +500,9 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                 const int lpx = t * 16 + here(lq), px = r3_lo * 9 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 const float4 bv = *reinterpret_cast<const float4*>(sB2 + ch);
                 if (lpx < n2) {
-                    const float v0 = fmaxf(sum[0] + bv.x, 0.f), v1 = fmaxf(sum[1] + bv.y, 0.f), v2 = fmaxf(sum[2] + bv.z, 0.f), v3 = fmaxf(sum[3] + bv.w, 0.f);
+                    const float v0 = tf_relu(sum[0] + bv.x), v1 = tf_relu(sum[1] + bv.y), v2 = tf_relu(sum[2] + bv.z), v3 = tf_relu(sum[3] + bv.w);
                     tf_store4<kTfA2Plane>(sA2 + tf_a2(px, ch >> 3) + 2 * (ch & 4), v0, v1, v2, v3);
-                    if (g2) store4<float>(g2 + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v0, v1, v2, v3);
+                    if (g2 && lpx < own2) store4<float>(g2 + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v0, v1, v2, v3);
                 }
             });
         }
@@ -468,6 +535,12 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
             auto all = [](int, int) { return true; };
             if (kq < 2) tower_f32_tiles<T3, 5, kTfA2Plane>(acc, wr, at, nothing, all);
             else tower_f32_tiles<T3, 4, kTfA2Plane>(acc, wr, at, nothing, all);
+            // one sum over everything that this lane has is a finite number only if all are (or may overflow: no matter).  In front of the
+            // exchange's barrier: behind it every wavefront knows
+            tf_f32x4 all_of = acc[0][0] + acc[0][1];
+#pragma unroll
+            for (int t = 1; t < T3; ++t) all_of += acc[t][0] + acc[t][1];
+            if (!__builtin_isfinite((all_of[0] + all_of[1]) + (all_of[2] + all_of[3]))) *sPlain = 1;
             tower_f32_exchange<T3>(acc, sEx, cp, kq, lane, [&](int, int t, int c, const tf_f32x4& sum) {
                 const int lpx = t * 16 + here(lq), px = r3_lo * 7 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 const float4 bv = *reinterpret_cast<const float4*>(sB3 + ch);
@@ -479,6 +552,13 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
         if constexpr (PARTS > 1) break;
         // no barrier: the last exchange's lies behind every read of act2, whose place the next state takes, and the next item's
         // first barrier behind the exchange's reads, whose place its act1 takes
+    }
+    if (*sPlain == 0) return;
+    g = 0; b = first;
+    while (b >= n_) { b -= n_; ++g; }
+    for (int it = first; it < last; ++it, ++b) {
+        if (b == n_) { b = 0; ++g; }
+        tower_f32_plain<DESC>(a, g, b, r3_lo, rows3, tf_smem);
     }
 }
 

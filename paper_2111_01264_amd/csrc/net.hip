@@ -290,6 +290,7 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
             const bf16_t* thirds = reinterpret_cast<const bf16_t*>(w + thirds_offset(o));
             a.w1[g] = w + o.w1; a.w2[g] = thirds + kThirdsW2; a.w3[g] = thirds + kThirdsW3;
             a.b1[g] = master[g] + o.b1; a.b2[g] = master[g] + o.b2; a.b3[g] = master[g] + o.b3;
+            a.w2_plain[g] = master[g] + o.w2; a.w3_plain[g] = master[g] + o.w3;
             a.act1[g] = (timed && g == 0) ? act1 : nullptr;
             a.act2[g] = (timed && g == 0) ? act2 : nullptr;
             a.act3[g] = act3 + g * e_act3;
