@@ -276,9 +276,18 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
                 for (int p = 0; p < PL; ++p) *reinterpret_cast<bf16x4*>(dst + p * PLANE) = part[p];
             }
             if (cb == 0) {
-                const float w = (G::DZ_VECS % 256 == 0 || tid + u * 256 < G::DZ_VECS) ? 1.f : 0.f;   // surplus threads hold a copy
+                // surplus threads hold a copy that does not count (fp32: its bits are cleared, as 0 * infinity would be a NaN in every
+                // channel's sum; bf16, whose kernel has no registers left for that, multiplies)
+                const bool counts = G::DZ_VECS % 256 == 0 || tid + u * 256 < G::DZ_VECS;
+                if constexpr (PL == 1) {
+                    const float w = counts ? 1.f : 0.f;
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) bsum[e] += w * static_cast<float>(dv[e]);
+                    for (int e = 0; e < EPV; ++e) bsum[e] += w * static_cast<float>(dv[e]);
+                } else {
+                    const dz_vec once = __builtin_bit_cast(dz_vec, d & (counts ? ~0u : 0u));
+#pragma unroll
+                    for (int e = 0; e < EPV; ++e) bsum[e] += static_cast<float>(once[e]);
+                }
             }
         }
 #pragma unroll

@@ -85,7 +85,7 @@ __device__ inline void wgrad_conv_f32_block(const WgConvArgs& a, int wg, int cb,
 #pragma unroll
         for (int u = 0; u < NVD; ++u) {
             reinterpret_cast<wg_f32x4*>(sDz)[min(tid + u * 256, G::DZ_VECS - 1)] = pdz[u];
-            if (cb == 0) bsum += (G::DZ_VECS % 256 == 0 || tid + u * 256 < G::DZ_VECS ? 1.f : 0.f) * pdz[u];
+            if (cb == 0) bsum += __builtin_bit_cast(wg_f32x4, __builtin_bit_cast(wg_u32x4, pdz[u]) & (G::DZ_VECS % 256 == 0 || tid + u * 256 < G::DZ_VECS ? ~0u : 0u));
         }
 #pragma unroll
         for (int u = 0; u < NVI; ++u) reinterpret_cast<wg_f32x4*>(sIn)[min(tid + u * 256, G::IN_VECS - 1)] = pin[u];
@@ -99,7 +99,10 @@ __device__ inline void wgrad_conv_f32_block(const WgConvArgs& a, int wg, int cb,
             const int d = 2 * ks + 1 == G::KPIX ? 0 : j + 1 == G::WOUT ? d_wrap : d_step;
             fa[buf] = arow[2 * ks * G::COUT];
 #pragma unroll
-            for (int t = 0; t < NTW; ++t) fb[buf][t] = (col[t] + d)[off];
+            for (int t = 0; t < NTW; ++t) {
+                fb[buf][t] = (col[t] + d)[off];
+                if (2 * ks + 1 == G::KPIX) fb[buf][t] = kg ? 0.f : fb[buf][t];   // the padding pixel: zero on both sides, for an infinite input
+            }
         };
         frags(std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
         auto step = [&](auto ks_) {
@@ -172,7 +175,7 @@ __device__ inline void wgrad_fc1_f32_block(const WgFc1F32Args& a, int bx, int bz
     const float* pa = a.dz + m0 + ca;
     const float* pb = a.x + (okb ? n0 + cbv : 0);
     wg_f32x4 ra[NA], rb[NB];
-    auto fetch = [&](int k0) {   // rows past the minibatch repeat its last row and count as zero (dZ's copy is zeroed when it is stored)
+    auto fetch = [&](int k0) {   // rows past the minibatch repeat its last row and count as zero (cleared on both sides when they are stored)
 #pragma unroll
         for (int i = 0; i < NA; ++i) ra[i] = *reinterpret_cast<const wg_f32x4*>(pa + static_cast<size_t>(min(k0 + ka + i * (256 / CVA), B - 1)) * 512);
 #pragma unroll
@@ -186,7 +189,10 @@ __device__ inline void wgrad_fc1_f32_block(const WgFc1F32Args& a, int bx, int bz
             *reinterpret_cast<wg_u32x4*>(sA + k * BM + ca) = v;
         }
 #pragma unroll
-        for (int i = 0; i < NB; ++i) *reinterpret_cast<wg_f32x4*>(sB + (kb + i * (256 / CVB)) * BN + cbv) = rb[i];
+        for (int i = 0; i < NB; ++i) {
+            const int k = kb + i * (256 / CVB);
+            *reinterpret_cast<wg_u32x4*>(sB + k * BN + cbv) = __builtin_bit_cast(wg_u32x4, rb[i]) & (k0 + k < B ? ~0u : 0u);
+        }
     };
     f32x16 acc[2];
 #pragma unroll

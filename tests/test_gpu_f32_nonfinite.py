@@ -128,3 +128,111 @@ def test_act_with_nonfinite_values(W, kind):
         same_values(q.cpu().numpy(), want3[pick], kind)
     finally:
         P.dqn_destroy(ctx)
+
+
+# ---- gradients ------------------------------------------------------------------------------------------------------
+
+def f32(x):
+    return x.astype(np.float32).astype(np.float64)
+
+
+def reference_gradient(theta, state, action, dq):
+    """name -> gradient of one sample whose dLoss/dQ[action] is dq, every product formed (a data gradient's filter taps that fall
+    outside the output too: as products with zero), every layer's sums rounded to float32."""
+    sl = blob_slices(A)
+
+    def tensor(name, shape):
+        return theta[sl[name]].astype(np.float64).reshape(shape)
+
+    with np.errstate(all="ignore"):
+        _, acts = reference_q(theta, state[None])
+        a1, a2, a3 = (x[0] for x in acts)
+        w1, w2 = tensor("fc1.w", (512, 3136)), tensor("fc2.w", (A, 512))
+        h = np.fmax((f32((a3.reshape(-1) * w1).sum(1)) + theta[sl["fc1.b"]]).astype(np.float32), np.float32(0)).astype(np.float64)
+        g = {}
+        g["fc2.w"], g["fc2.b"] = np.zeros((A, 512)), np.zeros(A)
+        g["fc2.w"][action], g["fc2.b"][action] = dq * h, dq
+        dzh = np.where(h > 0, f32(dq * w2[action]), 0.0)
+        g["fc1.w"], g["fc1.b"] = dzh[:, None] * a3.reshape(-1)[None], dzh
+        dz = np.where(a3 > 0, f32((dzh[:, None] * w1).sum(0)).reshape(64, 7, 7), 0.0)
+        x0 = state.astype(np.float64) / 255.0
+        for name, shape, stride, x, below in (("conv3", (64, 64, 3, 3), 1, a2, a2), ("conv2", (64, 32, 4, 4), 2, a1, a1), ("conv1", (32, 4, 8, 8), 4, x0, None)):
+            k, out = shape[2], dz.shape[1]
+            g[name + ".b"] = f32(dz).sum((1, 2))
+            gw = np.zeros(shape)
+            for p in range(k):
+                for q in range(k):
+                    win = x[:, p:p + stride * (out - 1) + 1:stride, q:q + stride * (out - 1) + 1:stride]
+                    for c in range(shape[1]):
+                        gw[:, c, p, q] = (dz * win[None, c]).sum((1, 2))
+            g[name + ".w"] = gw
+            if below is None:
+                break
+            w, size = tensor(name + ".w", shape), x.shape[1]
+            pad = np.zeros((64, out + 2 * (k // stride - 1), out + 2 * (k // stride - 1)))
+            o0 = k // stride - 1
+            pad[:, o0:o0 + out, o0:o0 + out] = dz
+            dx = np.zeros_like(x)
+            n = size // stride
+            for py in range(stride):
+                for px in range(stride):
+                    acc = np.zeros((shape[1], n, n))
+                    for p2 in range(k // stride):
+                        for q2 in range(k // stride):
+                            tap = pad[:, o0 - p2:o0 - p2 + n, o0 - q2:o0 - q2 + n]
+                            for o in range(64):
+                                acc += w[o, :, stride * p2 + py, stride * q2 + px][:, None, None] * tap[o][None]
+                    dx[:, py::stride, px::stride] = acc
+            dz = np.where(below > 0, f32(dx), 0.0)
+    return {name: v.reshape(-1) for name, v in g.items()}
+
+
+GRADIENT_KINDS = ["conv1.b=inf aligned", "conv2.b=inf aligned", "conv3.b=inf aligned", "conv2.w=-inf aligned", "conv3.w=nan"]
+
+
+@pytest.mark.parametrize("kind", GRADIENT_KINDS)
+@pytest.mark.parametrize("B,sampled", [(1, False), (5, False), (64, False), (130, False), (300, False), (101, True)])
+def test_gradient_with_nonfinite_values(B, sampled, kind):
+    seed = 4400
+    cfg = make_cfg(A, max_batch=B, max_envs=1, precision=P.DQN_PRECISION_FP32, seed=seed)
+    cfg.huber_delta = 1.0
+    st = torch.cuda.Stream()
+    ctx = P.dqn_create(cfg, st, st)
+    rb = None
+    try:
+        theta = params(kind, seed)
+        P.dqn_set_params(ctx, P.DQN_PARAMS_ONLINE, theta)
+        P.dqn_set_params(ctx, P.DQN_PARAMS_TARGET, synth.init_params(seed, A))
+        few, few_a = np.maximum(synth.act_states(seed, 0, 3), 1), np.array([0, 1, 2], dtype=np.int32)
+        if sampled:       # one lane of six frames, none of them terminal: two transitions
+            n = 6
+            rb = P.replay_create(n, 1, n, seed, st, st)
+            frames = few.reshape(12, 84, 84)[:n]
+            acts = np.array([0, 0, 0, 0, 1, 0], dtype=np.int32)
+            P.replay_push(rb, 0, dev(frames), dev(acts), dev(np.full(n, -1000.0, dtype=np.float32)), dev(np.zeros(n, dtype=np.uint8)), n)
+            P.replay_flush(rb, 1)
+            s, a, r = (torch.empty(shape, dtype=t, device="cuda") for shape, t in (((B, 4, 84, 84), torch.uint8), (B, torch.int32), (B, torch.float32)))
+            s2, d, idx = torch.empty_like(s), torch.empty_like(r), torch.empty(B, dtype=torch.int64, device="cuda")
+            P.replay_sample_gather(rb, B, 0, None, s, s2, a, r, d, idx)
+            torch.cuda.synchronize()
+            pick = idx.cpu().numpy() - 3
+            few, few_a = np.stack([frames[0:4], frames[1:5]]), acts[3:5]
+            P.dqn_train_step_sampled(ctx, rb, B, 0, 0, None)
+        else:
+            pick = np.arange(B) % 3
+            P.dqn_train_step(ctx, dev(few[pick]), dev(few_a[pick]), dev(np.full(B, -1000.0, dtype=np.float32)), dev(few[pick]), dev(np.ones(B, dtype=np.float32)),
+                             B, None)
+        torch.cuda.synchronize()
+        g = P.dqn_get_params(ctx, P.DQN_PARAMS_GRAD)
+        # a finite or positively infinite Q is above every target here: dLoss/dQ is 1/B; a negative infinity gives -1/B, a NaN too (fmax, then fmin)
+        q, _ = reference_q(theta, few)
+        dq = np.where(q[np.arange(len(few)), few_a] > -1e30, 1.0, -1.0).astype(np.float32) / np.float32(B)
+        refs = [reference_gradient(theta, few[k], few_a[k], np.float64(dq[k])) for k in range(len(few))]
+        with np.errstate(all="ignore"):
+            for name, slc in blob_slices(A).items():
+                want = sum(refs[k][name] * count for k, count in enumerate(np.bincount(pick, minlength=len(few))) if count)
+                same_values(g[slc], want, "%s %s" % (kind, name))
+    finally:
+        if rb is not None:
+            P.replay_destroy(rb)
+        P.dqn_destroy(ctx)
