@@ -13,6 +13,9 @@
 // its rounding error, but the weight and bias gradients are sums over 81 B of these, the rounding errors average out there and an
 // offset does not: at minibatch 256 dL/d(conv2.b) was off by 1.0e-6 where the fp32 instruction is off by 4.3e-7.  Negated, the
 // cut points upwards, and the offsets of the minibatch's two halves take each other out.
+//
+// Values that have no three bf16 parts (see conv_tower_f32.h) are found by what they leave behind the masks, dz2 or dz1 that are no finite
+// number; the workgroup then runs its samples again in plain fp32 (tower_bwd_f32_plain).
 #pragma once
 #include "conv_tower_bwd.h"
 #include "conv_tower_f32.h"
@@ -33,25 +36,70 @@ struct TowerBwdF32Args {
     const bf16_t* w2d;   // four classes of [c 32][k 256]
     float* dz2;          // [n][81][64]
     float* dz1;          // [n][400][32]
+    const float* w3_plain;   // fp32 [o][p][q][c]: for tower_bwd_f32_plain
+    const float* w2_plain;
     int n, per;          // samples, samples per workgroup
 };
 
 constexpr int kTbfPlane = 11 * 11 * 128;                 // one bf16 part of an image (bytes; layout as act2's, see tf_a2)
 constexpr int kTbfXchg = 2 * 12 * 3 * 1024;              // partial sums between wavefronts: over dz3's image once that has been read
-constexpr size_t kTowerBwdF32Smem = 3 * kTbfPlane + kTbfXchg;
+constexpr size_t kTowerBwdF32Smem = 3 * kTbfPlane + kTbfXchg + 16;
+static_assert((3136 + 5184) * 4 + 16 <= kTowerBwdF32Smem, "tower_bwd_f32_plain's images");
 static_assert(kTbfXchg >= 3 * kTbfPlane, "the image of dz3 and the partial sums share their place");
+
+// One sample's rows [y, y + rows) of every parity class of dz1, and the rows of dz2 that they depend on, in plain fp32: a thread per output.
+// Taps that fall outside the gradient below are products with zero, as in the zero-bordered images.  Cold.
+__device__ inline void tower_bwd_f32_plain(const float* dz3, const float* w3, const float* w2, const float* act2, const float* act1, float* dz2, float* dz1,
+                                           int b, int y_lo, int rows, unsigned char* smem)
+{
+    const int tid = threadIdx.x;
+    float* s3 = reinterpret_cast<float*>(smem);   // dz3, dz2 of the sample, channels last
+    float* s2 = s3 + 3136;
+    __threadfence();
+    __syncthreads();   // every earlier store of these gradients and every read of this LDS is done
+    for (int v = tid; v < 3136; v += kTowerThreads) s3[v] = dz3[static_cast<size_t>(b) * 3136 + v];
+    __syncthreads();
+    const int r2_lo = max(y_lo - 1, 0), n2 = 9 * (min(y_lo + rows, 9) - r2_lo);
+    for (int i = tid; i < n2 * 64; i += kTowerThreads) {
+        const int c = i & 63, px = 9 * r2_lo + (i >> 6), y = px / 9, x = px % 9;
+        float sum = 0.f;
+#pragma unroll 1
+        for (int k = 0; k < 576; ++k) {
+            const int o = k & 63, p = k / 192, q = k / 64 % 3, yy = y - p, xx = x - q;
+            sum = fmaf(w3[o * 576 + (p * 3 + q) * 64 + c], yy >= 0 && yy < 7 && xx >= 0 && xx < 7 ? s3[(yy * 7 + xx) * 64 + o] : 0.f, sum);
+        }
+        const size_t at = (static_cast<size_t>(b) * 81 + px) * 64 + c;
+        const float v = act2[at] > 0.f ? sum : 0.f;
+        s2[px * 64 + c] = v;
+        if (px >= 9 * y_lo) dz2[at] = v;   // (the row above belongs to the part above)
+    }
+    __syncthreads();
+    for (int i = tid; i < 2 * rows * 20 * 32; i += kTowerThreads) {
+        const int c = i & 31, px = 40 * y_lo + (i >> 5), y = px / 20, x = px % 20;
+        float sum = 0.f;
+#pragma unroll 1
+        for (int k = 0; k < 256; ++k) {
+            const int o = k & 63, p2 = k >> 7, q2 = (k >> 6) & 1, yy = (y >> 1) - p2, xx = (x >> 1) - q2;
+            sum = fmaf(w2[o * 512 + ((2 * p2 + (y & 1)) * 4 + 2 * q2 + (x & 1)) * 32 + c], yy >= 0 && yy < 9 && xx >= 0 && xx < 9 ? s2[(yy * 9 + xx) * 64 + o] : 0.f, sum);
+        }
+        const size_t at = (static_cast<size_t>(b) * 400 + px) * 32 + c;
+        dz1[at] = act1[at] > 0.f ? sum : 0.f;
+    }
+}
 
 // PARTS: whole samples, or one half / fifth of one: rows [5 part, + 5) / [2 part, + 2) of every parity class of dz1 with the rows
 // of dz2 they depend on (see conv_tower_bwd_kernel).
 template <int PARTS>
 __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n_, int per_, const float* dz3_, const bf16_t* w3d_, const bf16_t* w2d_,
-                                                                           const float* act2_, const float* act1_, float* dz2_, float* dz1_)
+                                                                           const float* act2_, const float* act1_, float* dz2_, float* dz1_,
+                                                                           const float* w3_plain, const float* w2_plain)
 {
     static_assert(PARTS == 1 || PARTS == 2 || PARTS == 5, "whole samples, halves or fifths");
     extern __shared__ __attribute__((aligned(16))) unsigned char tbf_smem[];
     uint8_t* sP2 = tbf_smem;                             // dz2, 9x9 at offset (1, 1)
     uint8_t* sP3 = tbf_smem + 3 * kTbfPlane;             // dz3, 7x7 at offset (2, 2) of an 11x11 image
     float* sEx = reinterpret_cast<float*>(sP3);
+    int* sPlain = reinterpret_cast<int*>(tbf_smem + kTowerBwdF32Smem - 16);   // not zero: a gradient of these samples is no finite number
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lq = lane & 15, lk = lane >> 4;
     const int cp = wave & 1, kq = wave >> 1;             // conv3 stage: 32 channels, k-quarter
@@ -97,6 +145,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
     };
     static_for<0, 5>(request3);
     for (int v = tid; v < 6 * kTbfPlane / 16; v += kTowerThreads) reinterpret_cast<uint4*>(tbf_smem)[v] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) *sPlain = 0;
     __syncthreads();   // the zero fill is complete
 
     for (int b = first; b < last; ++b) {
@@ -137,6 +186,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
                 mask3[i] = *reinterpret_cast<const tf_f32x4*>(act2_ + (static_cast<size_t>(b) * 81 + pc) * 64 + cp * 32 + (j & 1) * 16 + 4 * lk);
             }
             __syncthreads();   // dz3 has been read
+            tf_f32x4 all_of = {0.f, 0.f, 0.f, 0.f};   // the sum of what this lane finishes is a finite number only if all of it is
             tower_f32_exchange<T3>(acc, sEx, cp, kq, lane, [&](int i, int t, int c, const tf_f32x4& sum) {
                 const int lpx = t * 16 + here(lq), px = r2_lo * 9 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 if (lpx < n2) {
@@ -145,9 +195,11 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
                     for (int e = 0; e < 4; ++e) v[e] = mask3[i][e] > 0.f ? sum[e] : 0.f;
                     tf_store4<kTbfPlane>(sP2 + tf_a2((px / 9 + 1) * 11 + px % 9 + 1, ch >> 3) + 2 * (ch & 4), v[0], v[1], v[2], v[3]);
                     v = tf_flip(v, flip);
-                    store4<float>(dz2_ + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v[0], v[1], v[2], v[3]);
+                    all_of += v;
+                    if (px >= 9 * y_lo) store4<float>(dz2_ + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v[0], v[1], v[2], v[3]);
                 }
             });
+            if (!__builtin_isfinite((all_of[0] + all_of[1]) + (all_of[2] + all_of[3]))) *sPlain = 1;
         }
         __syncthreads();
 
@@ -183,20 +235,27 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
                             mask[t][c] = *reinterpret_cast<const tf_f32x4*>(act1_ + (static_cast<size_t>(b) * 400 + place(t)) * 32 + c * 16 + 4 * lk);
             };
             tower_f32_mma<NT, 8, kTbfPlane>(acc, wr, at, next, [ph](int, int t) { return TA == TB || t < TA - 1 || ph == 0; });
+            tf_f32x4 all_of = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int t = 0; t < NT; ++t)
                 if ((ph + 2 * t) * 16 + lq < NC)
 #pragma unroll
                     for (int c = 0; c < 2; ++c) {
-                        const tf_f32x4 sum = tf_flip(acc[t][c], flip);
-                        store4<float>(dz1_ + (static_cast<size_t>(b) * 400 + place(t)) * 32 + c * 16 + 4 * lk, mask[t][c][0] > 0.f ? sum[0] : 0.f,
-                                      mask[t][c][1] > 0.f ? sum[1] : 0.f, mask[t][c][2] > 0.f ? sum[2] : 0.f, mask[t][c][3] > 0.f ? sum[3] : 0.f);
+                        tf_f32x4 v = tf_flip(acc[t][c], flip);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] = mask[t][c][e] > 0.f ? v[e] : 0.f;
+                        store4<float>(dz1_ + (static_cast<size_t>(b) * 400 + place(t)) * 32 + c * 16 + 4 * lk, v[0], v[1], v[2], v[3]);
+                        all_of += v;
                     }
+            if (!__builtin_isfinite((all_of[0] + all_of[1]) + (all_of[2] + all_of[3]))) *sPlain = 1;
         }
         if constexpr (PARTS > 1) break;
         if (b + 1 < last) static_for<0, 5>(request3);
         // no barrier here: the next sample's writes to both images sit behind barriers that follow their last readers
     }
+    __syncthreads();
+    if (*sPlain == 0) return;
+    for (int b = first; b < last; ++b) tower_bwd_f32_plain(dz3_, w3_plain, w2_plain, act2_, act1_, dz2_, dz1_, b, y_lo, ROWS, tbf_smem);
 }
 
 }  // namespace dqn

@@ -475,13 +475,15 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         const bf16_t* thirds = reinterpret_cast<const bf16_t*>(bsh + kBshTotal);
         ta.dz3 = dz3; ta.act2 = act2; ta.act1 = act1; ta.w3d = thirds + kThirdsW3; ta.w2d = thirds + kThirdsW2;
         ta.dz2 = dz2; ta.dz1 = dz1; ta.n = B;
+        ta.w3_plain = c->theta + o.w3; ta.w2_plain = c->theta + o.w2;
         DQN_HIP(raise_lds_limits());
         const int parts = 5 * B <= c->num_cus ? 5 : (2 * B <= c->num_cus ? 2 : 1);
         const int grid = parts > 1 ? parts * B : (B < c->num_cus ? B : c->num_cus);
         ta.per = parts > 1 ? 1 : (B + grid - 1) / grid;
         const ProfPair pr = prof_pair(c, K_TOWER_BWD);
         auto kern = parts == 5 ? conv_tower_bwd_f32_kernel<5> : parts == 2 ? conv_tower_bwd_f32_kernel<2> : conv_tower_bwd_f32_kernel<1>;
-        launch_timed(kern, dim3(grid), dim3(kTowerThreads), kTowerBwdF32Smem, st, pr.begin, pr.end, ta.n, ta.per, ta.dz3, ta.w3d, ta.w2d, ta.act2, ta.act1, ta.dz2, ta.dz1);
+        launch_timed(kern, dim3(grid), dim3(kTowerThreads), kTowerBwdF32Smem, st, pr.begin, pr.end, ta.n, ta.per, ta.dz3, ta.w3d, ta.w2d, ta.act2, ta.act1, ta.dz2, ta.dz1,
+                     ta.w3_plain, ta.w2_plain);
         DQN_LAUNCH_CHECK();
     }
 

@@ -187,7 +187,20 @@ def reference_gradient(theta, state, action, dq):
     return {name: v.reshape(-1) for name, v in g.items()}
 
 
-GRADIENT_KINDS = ["conv1.b=inf aligned", "conv2.b=inf aligned", "conv3.b=inf aligned", "conv2.w=-inf aligned", "conv3.w=nan"]
+def gradient_params(kind, seed):
+    if kind == "fc2.w=inf aligned":          # dL/d(fc1's output) infinite for the samples with action 0
+        theta = params("aligned", seed)
+        theta[blob_slices(A)["fc2.w"]][6] = np.inf
+    elif kind.startswith("fc1.w=inf"):       # one element of dL/d(act3) infinite: channel 62 of the last pixel
+        theta = params("aligned" if "aligned" in kind else "", seed)
+        theta[blob_slices(A)["fc1.w"]][3136 * 8 + 62 * 49 + 48] = np.inf
+    else:
+        theta = params(kind, seed)
+    return theta
+
+
+GRADIENT_KINDS = ["fc1.w=inf", "conv1.b=inf aligned", "conv2.b=inf aligned", "conv3.b=inf aligned",
+                  "conv2.w=-inf aligned", "conv3.w=nan", "beyond bf16"]
 
 
 @pytest.mark.parametrize("kind", GRADIENT_KINDS)
@@ -200,7 +213,7 @@ def test_gradient_with_nonfinite_values(B, sampled, kind):
     ctx = P.dqn_create(cfg, st, st)
     rb = None
     try:
-        theta = params(kind, seed)
+        theta = gradient_params(kind, seed)
         P.dqn_set_params(ctx, P.DQN_PARAMS_ONLINE, theta)
         P.dqn_set_params(ctx, P.DQN_PARAMS_TARGET, synth.init_params(seed, A))
         few, few_a = np.maximum(synth.act_states(seed, 0, 3), 1), np.array([0, 1, 2], dtype=np.int32)
