@@ -36,7 +36,8 @@ typedef uint32_t wg_u32x4 __attribute__((ext_vector_type(4)));   // a 16-byte ve
 // significand bits: hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid).  The other operand, a pixel byte, is exact in bf16,
 // so every product is exact and what is summed in fp32 is what the fp32 matrix instruction would sum -- at three bf16
 // instructions (96 cycles) instead of eight fp32 ones (512 cycles) per sixteen pixels.  Against the fp64 oracle conv1's gradient
-// is off by 3.1e-7 (l2, batch 32), with fp32 instructions it was 4.7e-7.  ITEMS_: items per sample.
+// is off by 3.1e-7 (l2, batch 32), with fp32 instructions it was 4.7e-7.  (Values that have no such parts: see the end of
+// wgrad_conv_block.)  ITEMS_: items per sample.
 template <int CIN_, int HIN_, int WIN_, int COUT_, int HOUT_, int WOUT_, int KS_, int S_, int PITCH_, bool U8_, int CS_, typename DZ_ = bf16_t, int ITEMS_ = U8_ ? 2 : 1>
 struct WgGeo {
     typedef DZ_ DZ;
@@ -402,6 +403,45 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
                 out[static_cast<size_t>(m) * G::N + n] = acc[i][j][v];
             }
         }
+    if constexpr (PL == 3) {
+        // A gradient that has no three parts (an infinity, a NaN, beyond the largest bf16) left a NaN in every sum that it entered: a lane
+        // that has one makes its sums again in plain fp32.  (Their sum is a finite number only if all are.)
+        static_assert(G::U8 && MT == 1 && NT % 4 == 0, "conv1");
+        float all_of = 0.f;
+#pragma unroll
+        for (int j = 0; j < NTW; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; v += 4) all_of += (acc[0][j][v] + acc[0][j][v + 1]) + (acc[0][j][v + 2] + acc[0][j][v + 3]);
+        if (!__builtin_isfinite(all_of)) {
+            float sum[16][NTW];
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+#pragma unroll
+                for (int j = 0; j < NTW; ++j) sum[v][j] = 0.f;
+#pragma unroll 2
+            for (int k = first * G::KPIX; k < last * G::KPIX; ++k) {   // pixel k % 400 of sample k / 400
+                const int b = k / (G::HOUT * G::WOUT), px = k % (G::HOUT * G::WOUT), at = G::S * (px / G::WOUT) * G::WIN + G::S * (px % G::WOUT);
+                float x[NTW];
+#pragma unroll
+                for (int j = 0; j < NTW; ++j) {
+                    const int n = (wave + 4 * j) * 32 + (lane & 31), c = n >> 6, slot = a.desc ? a.desc[static_cast<size_t>(b) * kDescInts + c] : b * G::CIN + c;
+                    const uint8_t* frame = (a.desc ? a.ring : static_cast<const uint8_t*>(a.in)) + static_cast<size_t>(max(slot, 0)) * kFrameBytes;
+                    const float byte = static_cast<float>(frame[at + ((n >> 3) & 7) * G::WIN + (n & 7)]);
+                    x[j] = slot < 0 ? 0.f : byte;
+                }
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float d = static_cast<const float*>(a.dz)[static_cast<size_t>(k) * G::COUT + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)];
+#pragma unroll
+                    for (int j = 0; j < NTW; ++j) sum[v][j] = fmaf(d, x[j], sum[v][j]);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+#pragma unroll
+                for (int j = 0; j < NTW; ++j) out[static_cast<size_t>(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * G::N + (wave + 4 * j) * 32 + (lane & 31)] = sum[v][j];
+        }
+    }
 }
 
 }  // namespace dqn

@@ -199,7 +199,7 @@ def gradient_params(kind, seed):
     return theta
 
 
-GRADIENT_KINDS = ["fc1.w=inf", "conv1.b=inf aligned", "conv2.b=inf aligned", "conv3.b=inf aligned",
+GRADIENT_KINDS = ["fc2.w=inf aligned", "fc1.w=inf", "fc1.w=inf aligned", "conv1.b=inf aligned", "conv2.b=inf aligned", "conv3.b=inf aligned",
                   "conv2.w=-inf aligned", "conv3.w=nan", "beyond bf16"]
 
 
