@@ -63,7 +63,7 @@ __device__ inline void tower_bwd_f32_plain(const float* dz3, const float* w3, co
     for (int i = tid; i < n2 * 64; i += kTowerThreads) {
         const int c = i & 63, px = 9 * r2_lo + (i >> 6), y = px / 9, x = px % 9;
         float sum = 0.f;
-#pragma unroll 1
+#pragma unroll 16
         for (int k = 0; k < 576; ++k) {
             const int o = k & 63, p = k / 192, q = k / 64 % 3, yy = y - p, xx = x - q;
             sum = fmaf(w3[o * 576 + (p * 3 + q) * 64 + c], yy >= 0 && yy < 7 && xx >= 0 && xx < 7 ? s3[(yy * 7 + xx) * 64 + o] : 0.f, sum);
@@ -77,7 +77,7 @@ __device__ inline void tower_bwd_f32_plain(const float* dz3, const float* w3, co
     for (int i = tid; i < 2 * rows * 20 * 32; i += kTowerThreads) {
         const int c = i & 31, px = 40 * y_lo + (i >> 5), y = px / 20, x = px % 20;
         float sum = 0.f;
-#pragma unroll 1
+#pragma unroll 16
         for (int k = 0; k < 256; ++k) {
             const int o = k & 63, p2 = k >> 7, q2 = (k >> 6) & 1, yy = (y >> 1) - p2, xx = (x >> 1) - q2;
             sum = fmaf(w2[o * 512 + ((2 * p2 + (y & 1)) * 4 + 2 * q2 + (x & 1)) * 32 + c], yy >= 0 && yy < 9 && xx >= 0 && xx < 9 ? s2[(yy * 9 + xx) * 64 + o] : 0.f, sum);

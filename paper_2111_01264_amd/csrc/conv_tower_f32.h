@@ -250,7 +250,7 @@ __device__ inline void tower_f32_plain(const TowerF32Args& a, int g, int b, int 
     for (int i = tid; i < 20 * (2 * rows3 + 6) * 32; i += kTowerThreads) {
         const int o = i & 31, px = 40 * r3 + (i >> 5), y = px / 20, x = px % 20;
         float sum = 0.f;
-#pragma unroll 1
+#pragma unroll 16
         for (int k = 0; k < 256; ++k) sum = fmaf(a.w1[g][o * 256 + k], static_cast<float>(sx[(k >> 6) * 7056 + (4 * y + ((k >> 3) & 7)) * 84 + 4 * x + (k & 7)]), sum);
         const float v = fmaxf(sum * (1.f / 255.f) + a.b1[g][o], 0.f);
         s1[px * 32 + o] = v;
@@ -260,7 +260,7 @@ __device__ inline void tower_f32_plain(const TowerF32Args& a, int g, int b, int 
     for (int i = tid; i < 9 * (rows3 + 2) * 64; i += kTowerThreads) {
         const int o = i & 63, px = 9 * r3 + (i >> 6), y = px / 9, x = px % 9;
         float sum = 0.f;
-#pragma unroll 1
+#pragma unroll 16
         for (int k = 0; k < 512; ++k) sum = fmaf(a.w2_plain[g][o * 512 + k], s1[((2 * y + (k >> 7)) * 20 + 2 * x + ((k >> 5) & 3)) * 32 + (k & 31)], sum);
         const float v = fmaxf(sum + a.b2[g][o], 0.f);
         s2[px * 64 + o] = v;
@@ -270,7 +270,7 @@ __device__ inline void tower_f32_plain(const TowerF32Args& a, int g, int b, int 
     for (int i = tid; i < 7 * rows3 * 64; i += kTowerThreads) {
         const int o = i & 63, px = 7 * r3 + (i >> 6), y = px / 7, x = px % 7;
         float sum = 0.f;
-#pragma unroll 1
+#pragma unroll 16
         for (int k = 0; k < 576; ++k) sum = fmaf(a.w3_plain[g][o * 576 + k], s2[((y + k / 192) * 9 + x + k / 64 % 3) * 64 + (k & 63)], sum);
         a.act3[g][(static_cast<size_t>(b) * 49 + px) * 64 + o] = fmaxf(sum + a.b3[g][o], 0.f);
     }
