@@ -353,12 +353,10 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
     const int lp = lane & 31, kg = lane >> 5;        // conv1: pixel / row of a 32x32 tile, k-half
     const int lq = lane & 15, lk = lane >> 4;        // conv2, conv3: pixel / row of a 16x16 tile, eight of 32 k
     const int cp = wave & 1, kq = wave >> 1;         // conv2, conv3: 32 channels, k-quarter
-    int cur_g = kMaxGroups;   // no group (and not -1: the part variants then indexed the biases with 0 whatever g was -- a compiler error, seen in its output)
     for (int it = first; it < last; ++it, ++b) {
         if (b == n_) { b = 0; ++g; }
-        if (PARTS > 1 || g != cur_g) {   // first item, or the range crosses into the next group: conv1's weights and the biases
+        if (PARTS > 1 || it == first || b == 0) {   // first item, or the range crosses into the next group: conv1's weights and the biases
             if (it != first) __syncthreads();   // the previous item's biases have been read
-            cur_g = g;
             const float* w1g = g == 0 ? w1_0_ : a.w1[g];
             const int o = tid >> 4, kc = tid & 15;   // row o, k = 16 * kc .. + 15
             tf_f32x4 w[4];
