@@ -305,17 +305,19 @@ def test_act_push_step_equals_the_two_calls(precision):
     assert rep_a[2].min() >= 0            # real transitions, not the invalid-index marker
 
 
+@pytest.mark.parametrize("double_dqn", [0, 1], ids=["single", "double"])
 @pytest.mark.parametrize("B", [24, 96, 300], ids=["b24", "b96", "b300"])
 @pytest.mark.parametrize("precision", [P.DQN_PRECISION_BF16, P.DQN_PRECISION_FP32], ids=["bf16", "fp32"])
-def test_train_step_sampled_equals_the_two_calls(precision, B):
+def test_train_step_sampled_equals_the_two_calls(precision, B, double_dqn):
     """dqn_train_step_sampled == replay_sample_gather + dqn_train_step, bit for bit (parameters and loss after every
     step), also when the minibatch gathered ahead goes stale (a flush in between) or is not the one asked for next.
     Batch 24 assembles the next minibatch with extra workgroups of the head kernel; batches 96 (the smallest such size)
-    and 300 do the same in full precision and, in reduced precision, take the descriptor path (no assembled states: the conv kernels read the replay
-    memory's frames themselves)."""
+    and 300 take the descriptor path (no assembled states: the conv kernels read the replay memory's frames themselves).  Double DQN
+    adds a third network, which reads the frames of s' once more; theta^- is another network here, so that none of the three
+    passes can stand in for another."""
     seed, A, lanes, per_lane = 2111012662, 6, 4, 300
     N = lanes * 1024
-    cfg = make_cfg(A, max_batch=max(B, 32), max_envs=8, precision=precision, seed=seed)
+    cfg = make_cfg(A, max_batch=max(B, 32), max_envs=8, precision=precision, double_dqn=double_dqn, seed=seed)
     theta = synth.init_params(seed, A)
     sample_steps = [0, 1, 2, 3, 5, 6, 7]      # after 3 comes 5: the minibatch of 4 was gathered ahead and is dropped
     flush_before = {2, 6}                     # new experiences become visible before these positions
@@ -326,7 +328,7 @@ def test_train_step_sampled_equals_the_two_calls(precision, B):
         rb = P.replay_create(N, lanes, 320, seed, st, st)
         try:
             P.dqn_set_params(ctx, P.DQN_PARAMS_ONLINE, theta)
-            P.dqn_set_params(ctx, P.DQN_PARAMS_TARGET, theta)
+            P.dqn_set_params(ctx, P.DQN_PARAMS_TARGET, synth.init_params(seed + 1, A))
             device_fill(rb, seed, lanes, per_lane, A, st, 0.3, 0.02, chunk=per_lane)
             s = torch.empty((B, 4, 84, 84), dtype=torch.uint8, device="cuda")
             s2 = torch.empty_like(s)
