@@ -1,4 +1,4 @@
-"""Precision of the full-precision train step: the error of every gradient tensor against the fp64 oracle, as a norm, is no larger than
+"""Precision of the full-precision mode.  Train step: the error of every gradient tensor against the fp64 oracle, as a norm, is no larger than
 the error of the same step with every product on the fp32 matrix instruction.
 
 The inputs leave nothing but the backward pass's own rounding: every ReLU has one state for any input (a hidden channel's bias is
@@ -10,6 +10,8 @@ that is not to nearest but always to one side, which a comparison element by ele
 RECORDED holds the errors of the kernels that computed everything on the fp32 instruction, layer by layer, on the same inputs (both
 sides are deterministic); a tenth is allowed on top, for sums of the same precision in another order (the tensors whose products
 are still made by that instruction, conv3.b and fc1.w, moved by up to 6 % when only the order of their sums changed).
+
+Act step: likewise the network's part of the Q rows (without fc2's biases), on weights as they are initialised.
 """
 import numpy as np
 import pytest
@@ -95,3 +97,33 @@ def test_f32_gradient_errors(B, double_dqn):
     print("B=%d " % B + " ".join("%s %.2e" % kv for kv in errs.items()))
     for (name, err), bound in zip(errs.items(), RECORDED[B]):
         assert err <= SLACK * bound, (name, err, bound)
+
+
+ACT_RECORDED = {36: 2.89e-07, 85: 4.10e-07, 128: 4.67e-07, 200: 3.10e-07}      # states: error of the kernels on the fp32 instruction
+
+
+def act_error(W):
+    A, errs = 6, []
+    for seed in range(2900 + W, 2900 + W + 1000 * SEEDS, 1000):
+        ctx = P.dqn_create(make_cfg(A, max_batch=1, max_envs=W, precision=P.DQN_PRECISION_FP32, seed=seed), torch.cuda.Stream(), torch.cuda.Stream())
+        try:
+            theta = synth.init_params(seed, A)
+            P.dqn_set_params(ctx, P.DQN_PARAMS_ONLINE, theta)
+            P.dqn_set_params(ctx, P.DQN_PARAMS_TARGET, theta)
+            states = synth.act_states(seed, 0, W)
+            actions = torch.empty(W, dtype=torch.int32, device="cuda")
+            q = torch.empty((W, A), dtype=torch.float32, device="cuda")
+            P.dqn_act(ctx, dev(states), W, 0.0, 0, 1, actions, q)
+            torch.cuda.synchronize()
+            want = odqn.forward(odqn.nature_desc(A), theta.astype(np.float64), odqn.scale_states(states))[0]
+            errs.append(np.linalg.norm(q.cpu().numpy() - want) / np.linalg.norm(want - theta[blob_slices(A)["fc2.b"]]))
+        finally:
+            P.dqn_destroy(ctx)
+    return float(np.sqrt(np.mean(np.square(errs))))
+
+
+@pytest.mark.parametrize("W", [36, 85, 128, 200])
+def test_f32_act_error(W):
+    err = act_error(W)
+    print("W=%d %.2e" % (W, err))
+    assert err <= SLACK * ACT_RECORDED[W], (err, ACT_RECORDED[W])
