@@ -97,9 +97,25 @@ def measured_traffic(name, B, precision):
     return (nbytes, where) if h.hexdigest() == sha else (None, None)
 
 
+def matrix_peak(name, B, A, groups, precision):
+    """Rate (TFLOP/s) at which the matrix cores can do a kernel's work with the instructions that the kernel issues.  Full precision runs
+    conv1 (forward and weight gradient) as three bf16 products per value, conv2's and conv3's forward and data gradients as six,
+    everything else on the fp32 instruction; a kernel of several kinds gets the rate of its mix."""
+    bf16, f32 = PEAK["bf16"][0], PEAK["f32"][0]
+    if precision == "bf16":
+        return bf16
+    parts = {"conv_tower": {"conv1_fwd": bf16 / 3, "conv2_fwd": bf16 / 6, "conv3_fwd": bf16 / 6},
+             "conv_tower_bwd": {"conv3_dgrad": bf16 / 6, "conv2_dgrad": bf16 / 6},
+             "wgrad_all": {"conv1_wgrad": bf16 / 3, "conv2_wgrad": f32, "conv3_wgrad": f32, "fc1_wgrad": f32}}.get(name)
+    if parts is None:
+        return f32
+    flops = {k: kernel_work(k, B, A, groups, precision)[0] for k in parts}
+    return sum(flops.values()) / sum(flops[k] / rate for k, rate in parts.items())
+
+
 def roofline_for(name, avg_ms, B, A, groups, precision):
     flops, nbytes = kernel_work(name, B, A, groups, precision)
-    peak_f = PEAK["bf16" if precision == "bf16" else "f32"][0]
+    peak_f = matrix_peak(name, B, A, groups, precision)
     ridge = peak_f * 1e12 / (PEAK["hbm"][0] * 1e9)
     sec = avg_ms * 1e-3
     if flops / max(nbytes, 1) >= ridge * 0.25 and name not in ("rmsprop", "small_grads", "(unused)", "head_td"):

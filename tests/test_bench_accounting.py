@@ -68,6 +68,23 @@ def test_roofline_object_fields_and_bound():
     assert np.isclose(t["frac"], bench.kernel_work("conv_tower", 256, 18, 2, "bf16")[0] / 20e-6 / 1e12 / 2500.0)
 
 
+def test_full_precision_roofline_is_that_of_the_instructions_used():
+    # full precision: conv1's forward and weight gradient are three bf16 products per value, conv2's and conv3's forward and data
+    # gradients six, the rest is on the fp32 instruction: the time of a kernel at the peak is the sum of its layers' times
+    A, B, G = 18, 256, 2
+    m = macs_per_sample(A)
+    t = 2.0 * G * B * (3 * m["conv1"] + 6 * (m["conv2"] + m["conv3"])) / 2500.0
+    assert np.isclose(bench.matrix_peak("conv_tower", B, A, G, "fp32"), 2.0 * G * B * (m["conv1"] + m["conv2"] + m["conv3"]) / t)
+    assert np.isclose(bench.matrix_peak("conv_tower_bwd", B, A, G, "fp32"), 2500.0 / 6)
+    t = 2.0 * B * (3 * m["conv1"] / 2500.0 + (m["conv2"] + m["conv3"] + m["fc1"]) / 157.3)
+    assert np.isclose(bench.matrix_peak("wgrad_all", B, A, G, "fp32"), 2.0 * B * (m["conv1"] + m["conv2"] + m["conv3"] + m["fc1"]) / t)
+    assert bench.matrix_peak("fc1_fwd", B, A, G, "fp32") == 157.3
+    for k in ("conv_tower", "conv_tower_bwd", "wgrad_all", "fc1_fwd"):
+        assert bench.matrix_peak(k, B, A, G, "bf16") == 2500.0
+    r = bench.roofline_for("conv_tower", 0.053, B, A, G, "fp32")
+    assert np.isclose(r["peak"], bench.matrix_peak("conv_tower", B, A, G, "fp32")) and r["frac"] < 0.5
+
+
 def test_measured_traffic_is_withheld_when_sources_changed(monkeypatch):
     assert bench.measured_traffic("no_such_kernel", 32, "bf16") == (None, None)
     key = ("rmsprop", 32, "bf16")
