@@ -55,8 +55,7 @@ typedef struct {
     int32_t num_actions;   /* A, 1..32 (the paper's games use 4..18)                              */
     int32_t max_batch;     /* largest minibatch dqn_train_step will see (Table 5: 32)              */
     int32_t max_envs;      /* largest W dqn_act will see (Section 4)                              */
-    int32_t precision;     /* DQN_PRECISION_FP32: fp32 operands on fp32 MFMA (conv1, whose other operand is a
-                              byte: as exact sums of three bf16 parts on bf16 MFMA), fp32 accumulation;
+    int32_t precision;     /* DQN_PRECISION_FP32: fp32 operands, fp32 accumulation, see below;
                               DQN_PRECISION_BF16: bf16 operands on bf16 MFMA, fp32 accumulation,
                               fp32 master parameters and optimiser state                           */
     int32_t double_dqn;    /* 0: Eq. 1 (max over theta^-); 1: argmax from theta, value from theta^- */
@@ -68,6 +67,18 @@ typedef struct {
     float rms_eps;         /* Appendix B: 0.01, added to the denominator outside the square root   */
     uint64_t seed;         /* key of the counter-based generator used by the epsilon-greedy draws  */
 } dqn_config;
+
+/* What DQN_PRECISION_FP32 computes.  Parameters, activations, gradients and sums are fp32 throughout.  fc1, fc2 and the weight
+ * gradients of conv2, conv3 and fc1 multiply on the fp32 matrix instructions.  conv1 (forward and weight gradient), conv2's and conv3's
+ * forward and their data gradients multiply on the bf16 ones, every fp32 operand as the sum of three bf16 parts:
+ *   - the sum is exact for magnitudes from 2^-110 (7.7e-34) to the largest bf16 (3.39e38); below, at most 2^-134 is cut off;
+ *   - conv1's products with a pixel byte are exact; the others take six of the nine products of parts, which leaves out at most 2^-24 of a
+ *     product (2^-27.5 root mean square): the size of the rounding of one fp32 operation;
+ *   - measured against 64 bits (as norms), Q rows and every gradient tensor are as near as with all products on the fp32 instructions,
+ *     within a tenth, or nearer (minibatch 16 to 512);
+ *   - a workgroup that meets an infinity, a NaN or a value beyond the largest bf16 computes its samples in plain fp32: infinities pass the
+ *     ReLUs and show in Q and in the gradients, a NaN becomes 0 in a ReLU, as in fp32 arithmetic with fmax.  (Such a step is slower:
+ *     up to fifteen times where all values are NaN.) */
 
 /* ---- lifetime ------------------------------------------------------------------------------- */
 

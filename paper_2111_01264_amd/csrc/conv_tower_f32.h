@@ -1,15 +1,15 @@
 // Fused conv1 -> conv2 -> conv3 of the Q-network in full precision: the fp32 counterpart of conv_tower.h (same workgroups of 8
 // wavefronts walking (group, sample) items or bands of one, activations of conv1 and conv2 in LDS), on the bf16 matrix
-// instructions.  An fp32 value is EXACTLY the sum of three bf16 parts (8 + 8 + 8 significand bits; values beyond the largest bf16, 3.39e38,
-// are the exception), a product of two bf16 is exact in fp32, and sums are kept in fp32 as the fp32 instruction keeps them:
+// instructions.  An fp32 value from 2^-110 to the largest bf16, 3.39e38, is EXACTLY the sum of three bf16 parts (8 + 8 + 8 significand bits;
+// a smaller value loses at most 2^-134, the last bit of the smallest bf16), a product of two bf16 is exact in fp32, and sums are kept in fp32:
 //
 //   * conv1 multiplies pixel BYTES, exact in bf16, by the weights' three parts: all products are exact.  The split is made while
 //     the weights are staged.
-//   * conv2 and conv3 take the six largest of the nine products of parts.  What is left out is below 2^-26 of a product, a quarter of
-//     the rounding of one fp32 addition, and there are fewer additions: six instructions per 32 k instead of eight of four k.  The
-//     small products are summed by themselves (see tower_f32_mma); the error against 64 bits is then below that of the fp32
-//     instruction (gradients of one step, batch 16 to 256, norms: fc1.w 1.1 .. 2.4e-7 against 1.4 .. 2.5e-7, conv1.w 2.1 .. 3.1e-7
-//     against 3.3 .. 4.6e-7).  Six bf16 instructions take 96 cycles of a matrix core where the fp32 ones take 256: 49 k cycles
+//   * conv2 and conv3 take the six largest of the nine products of parts.  What is left out is at most 2^-24 of a product (2^-27.5 root mean
+//     square: 8 million random pairs), as much as the rounding of one fp32 addition, and there are fewer additions: six instructions
+//     per 32 k instead of eight of four k.  The small products are summed by themselves (see tower_f32_mma); the error against 64 bits is
+//     then below that of the fp32 instruction (Q rows of 36 to 200 states 2.7 .. 4.0e-7 of the network's part against 2.9 .. 4.7e-7;
+//     gradients: see conv_tower_bwd_f32.h).  Six bf16 instructions take 96 cycles of a matrix core where the fp32 ones take 256: 49 k cycles
 //     of a compute unit per sample become 21 k.
 //   * act1 and act2 are split when they are written to LDS, once, as three planes; conv2's and conv3's weights come split from the
 //     optimiser (third_index).  A wavefront owns 32 channels and a quarter of k, so that a weight is read by one wavefront only
@@ -104,8 +104,8 @@ __device__ inline bf16x8 load_row8(const bf16_t* p, unsigned lane)
 
 // acc[t][c] += (16 weight rows of channel half c) x (16 pixels of tile t) over NK k-steps of 32, every product of two fp32
 // values as the six largest of the nine products of their bf16 parts.  The five small ones have sums of their own: the instruction
-// cuts its sums off where an fp32 addition rounds, always downwards, and with all six in one accumulator dL/d(act2) was off by
-// 5e-7 where the fp32 instruction is off by 2e-7.  at(s, t): this lane's eight channels of tile t in k-step s, first part.  The operand of
+// rounds its result to nearest, but cuts off, downwards, what lies more than 24 bits below the largest term that it adds (accumulator
+// and products alike), and with all six in one accumulator dL/d(act2) was off by 5e-7 where the fp32 instruction is off by 2e-7.  at(s, t): this lane's eight channels of tile t in k-step s, first part.  The operand of
 // the next tile is requested before the matrix work of this one; done(s) when the weights of step s, w[s % 5], are used up.
 // live(s, t) (uniform): false for a last k-step or tile that this wavefront does not have (two bodies, one with and one without, do not
 // keep their registers in place).

@@ -114,8 +114,8 @@ template <typename T> __device__ inline void shadow_store(T* sh, const Offsets& 
 // group -- slices added in slice order, bias, ReLU, rounded to the operand type so that forward and
 // backward see the same h -- into an LDS tile; the fc2 weight fragments are requested before that,
 // so both latencies overlap.  (2) Per group the four wavefronts each take a quarter of K = 512 of
-// the fc2 product as 32x32 MFMAs (A = W2 rows, B = the h tile); the partial accumulators meet in LDS
-// and are added in wavefront order.  (3) One thread per sample runs the tail.
+// the fc2 product as 16x16 MFMAs (A = W2 rows, B = the h tile); the partial accumulators meet in LDS
+// and are added in wavefront order.  (3) One wavefront runs the tail, 32 lanes per sample.
 constexpr int kHeadRows = 2;
 
 struct HeadArgs {

@@ -282,7 +282,7 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         else launch_timed(conv_tower_kernel<false, 1>, g3, b3, kTowerSmem, st, pr.begin, pr.end, a.n, a.groups, a.per, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
         DQN_LAUNCH_CHECK();
     } else {
-        // the same fusion on the fp32 matrix instructions
+        // the same fusion in full precision (values in three bf16 parts, see conv_tower_f32.h)
         TowerF32Args a{};
         for (int g = 0; g < groups; ++g) {
             const T* w = static_cast<const T*>(shadow[g]);
