@@ -67,8 +67,8 @@ def kernel_work(name, B, A, groups, precision):
 _C = "paper_2111_01264_amd/csrc/"
 _RMS_SRC = (_C + "head_kernels.h", _C + "net.hip")
 _WG_SRC = (_C + "wgrad_all.h", _C + "wgrad_conv.h", _C + "wgrad_fc1.h", _C + "gemm_tn_tr.h", _C + "gemm_mfma.h", _C + "head_kernels.h", _C + "common.h", _C + "net.hip")
-_TOWER_SRC = (_C + "conv_tower.h", _C + "conv_ws.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
-_TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower.h", _C + "conv_ws.h", _C + "gemm_mfma.h", _C + "net.hip")
+_TOWER_SRC = (_C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
+_TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "net.hip")
 TRAFFIC = {
     ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "989a1c409b9fa8492a5f2c94b0f6970489c4304e", "profiles/hbm_traffic_b32.txt"),
     ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "c82332da442bce74f0fb9e0741362e0326cd7946", "profiles/hbm_traffic_b32.txt"),

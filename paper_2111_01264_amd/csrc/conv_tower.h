@@ -36,7 +36,7 @@
 #pragma once
 #include <type_traits>
 
-#include "conv_ws.h"
+#include "vec4.h"
 
 namespace dqn {
 

@@ -17,7 +17,7 @@
 #pragma once
 #include <atomic>
 
-#include "conv_ws.h"
+#include "vec4.h"
 
 namespace dqn {
 

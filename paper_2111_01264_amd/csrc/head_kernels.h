@@ -4,7 +4,7 @@
 #pragma once
 #include "common.h"
 #include "conv_tower.h"
-#include "conv_ws.h"
+#include "vec4.h"
 #include "philox.h"
 
 namespace dqn {
@@ -22,11 +22,9 @@ constexpr size_t kOffW1 = 0, kOffB1 = kOffW1 + 32 * 256, kOffW2 = kOffB1 + 32, k
 inline Offsets make_offsets(int A)
 {
     Offsets o;
-    o.w1 = 0;            o.b1 = o.w1 + 32 * 256;
-    o.w2 = o.b1 + 32;    o.b2 = o.w2 + 64 * 512;
-    o.w3 = o.b2 + 64;    o.b3 = o.w3 + 64 * 576;
-    o.wf1 = o.b3 + 64;   o.bf1 = o.wf1 + 512 * 3136;
-    o.wf2 = o.bf1 + 512; o.bf2 = o.wf2 + static_cast<size_t>(A) * 512;
+    o.w1 = kOffW1;   o.b1 = kOffB1;   o.w2 = kOffW2;   o.b2 = kOffB2;   o.w3 = kOffW3;   o.b3 = kOffB3;
+    o.wf1 = kOffWf1; o.bf1 = kOffBf1; o.wf2 = kOffWf2;
+    o.bf2 = o.wf2 + static_cast<size_t>(A) * 512;
     o.total = o.bf2 + A;
     return o;
 }
@@ -82,14 +80,16 @@ template <typename T> __host__ __device__ inline size_t bsh_index_wf1(int o, int
 __host__ __device__ inline size_t thirds_offset(const Offsets& off) { return (off.total + 63) / 64 * 64; }   // in floats
 inline size_t copy_elements(const Offsets& off, size_t esize) { return esize == 4 ? thirds_offset(off) + kThirdsTotal / 2 : off.total; }
 
-// Where blob element e lives in the forward copy: identical, except that the weights of conv2, conv3 and fc1 (bf16 mode: conv1
-// too) are kept in MFMA fragment order of the kernels that load them.  bf16 mode stores conv1's weights as fp16 (that
-// kernel runs conv1 on the f16 matrix instruction), everything else as bf16: shadow_store converts.
+// Where blob element e lives in the forward copy: identical, except that the weights of fc1 and, in bf16 mode, of the conv layers are kept
+// in MFMA fragment order of the kernels that load them (full precision: conv2's and conv3's are elsewhere, see shadow_store).  bf16
+// mode stores conv1's weights as fp16 (that kernel runs conv1 on the f16 matrix instruction), everything else as bf16: shadow_store converts.
 template <typename T> __host__ __device__ inline size_t shadow_index(const Offsets& off, size_t e)
 {
-    if (sizeof(T) == 2 && e >= off.w1 && e < off.b1) { const int r = static_cast<int>(e - off.w1); return off.w1 + tower_frag_index(r / 256, r % 256, 256); }
-    if (e >= off.w2 && e < off.b2) { const int r = static_cast<int>(e - off.w2); return off.w2 + tower_frag_index(r / 512, r % 512, 512); }
-    if (e >= off.w3 && e < off.b3) { const int r = static_cast<int>(e - off.w3); return off.w3 + tower_frag_index(r / 576, r % 576, 576); }
+    if (sizeof(T) == 2) {
+        if (e >= off.w1 && e < off.b1) { const int r = static_cast<int>(e - off.w1); return off.w1 + tower_frag_index(r / 256, r % 256, 256); }
+        if (e >= off.w2 && e < off.b2) { const int r = static_cast<int>(e - off.w2); return off.w2 + tower_frag_index(r / 512, r % 512, 512); }
+        if (e >= off.w3 && e < off.b3) { const int r = static_cast<int>(e - off.w3); return off.w3 + tower_frag_index(r / 576, r % 576, 576); }
+    }
     if (e >= off.wf1 && e < off.bf1) { const int r = static_cast<int>(e - off.wf1); return off.wf1 + frag_index<T>(r / 3136, r % 3136, 3136); }
     return e;
 }
@@ -395,14 +395,14 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && G == 3 && NTA == 2 ? 1 : 2) 
 }
 
 // Small reductions of the backward pass, one launch:
-//  * blocks [0, first_block[4]): bias gradients = column sums of the four dZ matrices ([rows][C], T),
-//    first stage: a block sums up to kBiasRows rows (all channels) into partial[layer][chunk][C];
-//    the optimiser kernel adds the chunks in order, so no atomics and no extra launch are needed;
+//  * blocks [0, bias_blocks): fc1's bias gradient = column sums of dzh ([B][512], T), first stage: a block sums kFc1BiasRows rows into
+//    partial[block][512]; the optimiser kernel adds the chunks in order, so no atomics and no extra launch are needed (the conv
+//    layers' bias gradients come out of their weight-gradient workgroups, where dZ is in LDS);
 //  * the last 33 blocks: fc2's weight gradient (32 blocks of 16 columns) and its bias gradient + loss.  dQ has one non-zero per row (the taken action):
 //    dW2[a][o] = sum_{b: a_b = a} dq_b h[b][o];  db2[a] = sum_{b: a_b = a} dq_b;  loss = mean_b loss_b.
 //    Each block owns 16 columns o; thread (o, part) accumulates the samples b = part (mod 16) in
 //    increasing order into its own LDS column, the sixteen parts are then added in order.
-constexpr int kBiasRows = 1024;
+constexpr int kFc1BiasRows = 64;   // a workgroup covers four rows per pass: one round trip of 16 loads in flight
 // The optimiser's conv blocks: lanes per four weights, slices per lane and round trip (64 of conv1's at most 128 slices in flight, 48
 // of the at most 44 -- fp32: 64 -- of the others).
 constexpr int kRmsLanes1 = 8, kRmsTrip1 = 8, kRmsLanes23 = 4, kRmsTrip23 = 12;
@@ -419,14 +419,9 @@ constexpr size_t kWgTotal = kWgOff3 + kWgMaxSplits * 64 * 576;
 constexpr int kRmsBiasLanes = 8;                                    // lanes per channel in the optimiser's bias blocks
 constexpr int kRmsBiasBlocks = (672 * kRmsBiasLanes + 255) / 256;  // 32 + 64 + 64 + 512 hidden-layer bias channels
 struct BiasGradArgs {
-    const void* dz[4];
-    int rows[4];
-    int chans[4];
-    int chunks[4];
-    int chunk_rows[4];      // rows per chunk (a workgroup sums one chunk of one layer)
-    int first_block[5];
-    int first_partial[4];   // offsets into `partial` (floats)
-    float* partial;
+    const void* dzh;        // T [B][512]
+    int bias_blocks;
+    float* partial;         // [bias_blocks][512]
     // fc2 weight gradient
     const void* h;          // T [B][512]
     const int32_t* act;
@@ -452,7 +447,7 @@ __device__ inline void small_grads_block(const BiasGradArgs& args, int block, un
     int* s_a = reinterpret_cast<int*>(s_dq + kMaxBatch);
     float (*s_acc)[256] = reinterpret_cast<float (*)[256]>(s_a + kMaxBatch);
     const int tid = threadIdx.x;
-    if (block >= args.first_block[4]) {
+    if (block >= args.bias_blocks) {
         const int B = args.B, A = args.A;
         const T* h = static_cast<const T*>(args.h);
         float* s_loss = &red[0][0];   // 256 * 9 floats: room for kMaxBatch loss terms
@@ -466,7 +461,7 @@ __device__ inline void small_grads_block(const BiasGradArgs& args, int block, un
         __syncthreads();
         // 16 columns per block; thread (o, part): samples b = part (mod 16) in increasing order.
         // Block 32 is the bias "column" (h = 1) and also owns the batch-mean loss.
-        const int ob = block - args.first_block[4];
+        const int ob = block - args.bias_blocks;
         const int oo = tid & 15, part = tid >> 4;
         const bool bias_block = ob == 32;
         const int o = ob * 16 + oo;
@@ -515,19 +510,18 @@ __device__ inline void small_grads_block(const BiasGradArgs& args, int block, un
     }
     // column sums of one chunk of rows, all channels: thread -> (16-byte vector of the row, row mod RP), so a
     // pass of the workgroup reads RP whole rows, fully coalesced; the RP partial rows meet in LDS in row order
-    int layer = 0;
-    while (layer < 3 && block >= args.first_block[layer + 1]) ++layer;
-    const int chunk = block - args.first_block[layer];
-    const int C = args.chans[layer], rows = args.rows[layer], VR = C / 8, RP = 256 / VR;
+    constexpr int C = 512, VR = C / 8, RP = 256 / VR;
+    static_assert(RP == 4, "four lanes per channel add the partial rows");
     const int vec = tid % VR, rsub = tid / VR;
-    const T* dz = static_cast<const T*>(args.dz[layer]) + vec * 8;
-    const int crows = args.chunk_rows[layer];
-    const int r_end = min(rows, (chunk + 1) * crows);
+    const T* dz = static_cast<const T*>(args.dzh) + vec * 8;
+    const int r_end = min(args.B, (block + 1) * kFc1BiasRows);
     float acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.f;
     // sixteen rows in flight per thread (clamped address, masked value: no load is ever skipped)
-    for (int r = chunk * crows + rsub; r < r_end; r += 16 * RP) {
+    static_assert(16 * RP == kFc1BiasRows, "one pass");
+    {
+        const int r = block * kFc1BiasRows + rsub;
         V8 v[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
@@ -542,15 +536,13 @@ __device__ inline void small_grads_block(const BiasGradArgs& args, int block, un
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[tid][e] = acc[e];
     __syncthreads();
-    // RP partial rows per channel, added in row order; four lanes per channel take every fourth partial
-    // and meet in a fixed tree (RP is 64, 32 or 4)
+    // four lanes per channel hold one partial row each and meet in a fixed tree
     for (int i = tid; i < 4 * C; i += 256) {
         const int c = i >> 2, j = i & 3;
-        float sum = 0.f;
-        for (int q = j; q < RP; q += 4) sum += red[q * VR + (c >> 3)][c & 7];
+        float sum = red[j * VR + (c >> 3)][c & 7];
         sum += __shfl_down(sum, 2, 4);
         sum += __shfl_down(sum, 1, 4);
-        if (j == 0) args.partial[args.first_partial[layer] + chunk * C + c] = sum;
+        if (j == 0) args.partial[static_cast<size_t>(block) * C + c] = sum;
     }
 }
 

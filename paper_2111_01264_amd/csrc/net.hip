@@ -46,7 +46,6 @@ struct Workspace {
     void* h = nullptr;      // [cap][512]: fc1 output of the online pass on s (kept for the backward pass)
     float* q = nullptr;     // [G*cap][A]
     float* partial = nullptr;   // fc1 k-slices
-    size_t partial_cap = 0;
 
 };
 
@@ -158,8 +157,7 @@ static int alloc_ws(Workspace& ws, int cap, int groups, int A, size_t esize)
     DQN_HIP(hipMalloc(&ws.act3, n * 3136 * esize));
     DQN_HIP(hipMalloc(&ws.h, static_cast<size_t>(cap) * 512 * esize));
     DQN_HIP(hipMalloc((void**)&ws.q, n * A * sizeof(float)));
-    ws.partial_cap = n * kMaxFc1Slices * 512;
-    DQN_HIP(hipMalloc((void**)&ws.partial, ws.partial_cap * sizeof(float)));
+    DQN_HIP(hipMalloc((void**)&ws.partial, n * kMaxFc1Slices * 512 * sizeof(float)));
     return DQN_OK;
 }
 
@@ -490,30 +488,13 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     // ---- weight gradients and small reductions ------------------------------------------------------
     int bias_chunks[4], bias_first[4];
     BiasGradArgs bg;
-    bg.dz[0] = dz1; bg.rows[0] = B * 400; bg.chans[0] = 32;
-    bg.dz[1] = dz2; bg.rows[1] = B * 81;  bg.chans[1] = 64;
-    bg.dz[2] = dz3; bg.rows[2] = B * 49;  bg.chans[2] = 64;
-    bg.dz[3] = dzh; bg.rows[3] = B;       bg.chans[3] = 512;
-    // the conv layers' bias gradients come out of their weight-gradient workgroups (dZ is in LDS there)
-    bg.rows[0] = bg.rows[1] = bg.rows[2] = 0;
-    bg.first_block[0] = 0;
-    {
-        int pofs = 0;
-        for (int l = 0; l < 4; ++l) {
-            // fc1's dZ is [B][512]: a workgroup covers four rows per pass, so 64 rows per chunk are one round trip of 16 loads in flight
-            bg.chunk_rows[l] = l == 3 ? 64 : kBiasRows;
-            bg.chunks[l] = (bg.rows[l] + bg.chunk_rows[l] - 1) / bg.chunk_rows[l];
-            bg.first_block[l + 1] = bg.first_block[l] + bg.chunks[l];
-            bg.first_partial[l] = pofs;
-            pofs += bg.chunks[l] * bg.chans[l];
-            bias_chunks[l] = bg.chunks[l];
-            bias_first[l] = bg.first_partial[l];
-        }
-    }
+    bg.dzh = dzh;
+    bg.bias_blocks = (B + kFc1BiasRows - 1) / kFc1BiasRows;
     bg.partial = c->bias_partial;
+    bias_chunks[3] = bg.bias_blocks; bias_first[3] = 0;
     bg.h = h; bg.act = a; bg.dqv = c->dqv; bg.lossv = c->lossv; bg.B = B; bg.A = c->A;
     bg.g_w2 = c->grad + o.wf2; bg.g_b2 = c->grad + o.bf2; bg.loss_out = loss_out; bg.loss_keep = c->loss_keep;
-    const int small_blocks = bg.first_block[4] + kSmallGradsExtraBlocks;
+    const int small_blocks = bg.bias_blocks + kSmallGradsExtraBlocks;
 
     // one launch: conv1/conv2/conv3/fc1 weight gradients and the small reductions.  Conv layers: split-K over samples, workgroup
     // j writes slice j (conv1's unit is half a sample, fp32: a quarter)
@@ -840,7 +821,6 @@ int dqn_act_static(dqn_ctx* c, const uint8_t* states, int32_t W, float epsilon, 
     Workspace ws;
     ws.act1 = p + kActStaticAct1; ws.act2 = p + kActStaticAct2; ws.act3 = p + kActStaticAct3;
     ws.partial = reinterpret_cast<float*>(p + kActStaticPartial);
-    ws.partial_cap = static_cast<size_t>(7) * kActStaticMaxEnvs * 512;
     return act_call(c, ws, "dqn_act_static", states, W, epsilon, act_step, use_target, actions, q_out);
 }
 
