@@ -272,7 +272,9 @@ inline hipError_t launch_fc_as(hipStream_t st, FcAsArgs<T> a, int K, int groups,
         constexpr int TB = 1;
         const size_t smem = static_cast<size_t>(TB) * 32 * (kc + 8) * sizeof(T);
         // Few workgroups keep the plain order: at 112 and 100 of them (128 states, minibatch 45) the other made no difference, and
-        // finding it cost 0.1 us.
+        // finding it cost 0.1 us.  From 140 on it gains (plain order -> this one, whole call): 160 states (140 workgroups) 19.9 -> 19.2 us, fp32
+        // 41.1 -> 39.7, 192 states (168) 20.2 -> 19.6, 256 (224) 21.1 -> 20.5; train step at minibatch 96 (168, forward only) 69.8 -> 69.2,
+        // 128 (224) 72.2 -> 71.1, 160 (280, and 125 in the data gradient) 82.9 -> 80.9.
         const uint32_t rows = (a.M + TB * 32 - 1) / (TB * 32), cols = n_blocks, total = rows * cols * groups * slices;
         const bool shared = total >= 128 && rows > 1 && static_cast<uint64_t>(total) * rows < (1u << 20) && static_cast<uint64_t>(total) * cols < (1u << 20);
         a.by_rows = ((1u << 20) + rows - 1) / rows;

@@ -147,7 +147,8 @@ constexpr int kWgSlicesF32_1 = 128, kWgSlicesF32_2 = 64, kWgSlicesF32_3 = 44;
 // rides for free in the previous step's head kernel (which leaves most of the chip idle at small batches), and the
 // fused conv kernel starts on states that are contiguous and cache-warm instead of after a descriptor round trip
 // (per train step through descriptors / through assembled states: batch 32: 52.4 / 51.8 us, batch 64: 62.8 / 62.9,
-// batch 96: 64.9 / 67.1, batch 128: 68.1 / 72.0).
+// batch 96: 64.9 / 67.1, batch 128: 68.1 / 72.0; full precision, where samples by descriptor are always whole ones: batch 40:
+// 106.1 / 96.0, 64: 112.8 / 105.1, 72: 113.8 / 113.8, 96: 121.5 / 120.8, 128: 124.4 / 125.1, 256: 185.2 / 186.3).
 constexpr int kDescMinBatch = 96;
 static int alloc_ws(Workspace& ws, int cap, int groups, int A, size_t esize)
 {
