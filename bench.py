@@ -70,14 +70,14 @@ _WG_SRC = (_C + "wgrad_all.h", _C + "wgrad_conv.h", _C + "wgrad_fc1.h", _C + "ge
 _TOWER_SRC = (_C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
 _TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "net.hip")
 TRAFFIC = {
-    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "989a1c409b9fa8492a5f2c94b0f6970489c4304e", "profiles/hbm_traffic_b32.txt"),
-    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "c82332da442bce74f0fb9e0741362e0326cd7946", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower", 32, "bf16"): (10.26e6, _TOWER_SRC, "4e1175bdd9160845c60bc0d698c1387317c8f92b", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower_bwd", 32, "bf16"): (4.78e6, _TOWER_BWD_SRC, "d4eba027d282838b1d90c002a557d6416bde4acd", "profiles/hbm_traffic_b32.txt"),
-    ("rmsprop", 256, "bf16"): (71.37e6, _RMS_SRC, "989a1c409b9fa8492a5f2c94b0f6970489c4304e", "profiles/hbm_traffic_b256.txt"),
-    ("wgrad_all", 256, "bf16"): (58.50e6, _WG_SRC, "c82332da442bce74f0fb9e0741362e0326cd7946", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower", 256, "bf16"): (24.22e6, _TOWER_SRC, "4e1175bdd9160845c60bc0d698c1387317c8f92b", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower_bwd", 256, "bf16"): (21.25e6, _TOWER_BWD_SRC, "d4eba027d282838b1d90c002a557d6416bde4acd", "profiles/hbm_traffic_b256.txt"),
+    ("rmsprop", 32, "bf16"): (66.21e6, _RMS_SRC, "0e44fc10b874b7d9149f4a9cebfd74e978b7c1a1", "profiles/hbm_traffic_b32.txt"),
+    ("wgrad_all", 32, "bf16"): (22.08e6, _WG_SRC, "3bb3da81df246c3787b10d768ba2467e8fb21b06", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower", 32, "bf16"): (10.26e6, _TOWER_SRC, "0a89036664eae62fef3c763b35b2d894f309ad17", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "07d1d9c6ac430e6afbd7187528cdc1697eb5dbdc", "profiles/hbm_traffic_b32.txt"),
+    ("rmsprop", 256, "bf16"): (71.39e6, _RMS_SRC, "0e44fc10b874b7d9149f4a9cebfd74e978b7c1a1", "profiles/hbm_traffic_b256.txt"),
+    ("wgrad_all", 256, "bf16"): (58.57e6, _WG_SRC, "3bb3da81df246c3787b10d768ba2467e8fb21b06", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower", 256, "bf16"): (24.21e6, _TOWER_SRC, "0a89036664eae62fef3c763b35b2d894f309ad17", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower_bwd", 256, "bf16"): (21.24e6, _TOWER_BWD_SRC, "07d1d9c6ac430e6afbd7187528cdc1697eb5dbdc", "profiles/hbm_traffic_b256.txt"),
 }
 
 

@@ -21,9 +21,10 @@
 //     (tower_f32_plain), and what such values lead to is what fp32 arithmetic makes of them.
 //
 // Launch times (rocprofv3), fp32 instruction -> this: sevenths (one to twelve states) 13.6 -> 12.0 us, thirds (minibatch 32) 19.4 -> 15.0 us,
-// whole samples (minibatch 256) 63 -> 53 us; act step W = 1 20.3 -> 18.4 us.  A whole item takes 50 k cycles where the matrix cores
-// need 21 k: staging 4 k, conv1 9 k and 3 k of waiting (13 tiles on 8 wavefronts), conv2 12 k, its sums' exchange and output 6 k,
-// conv3 and its exchange 9 k (clock reads of one wavefront).
+// whole samples (minibatch 256) 63 -> 52 us; act step W = 1 20.3 -> 18.5 us (18.4 before it watched for values without parts).  A whole
+// item takes 50 k cycles where the matrix cores need 21 k: staging 4 k, conv1 9 k and 3 k of waiting (13 tiles on 8 wavefronts), conv2 12 k,
+// its sums' exchange and output 6 k, conv3 and its exchange 9 k (clock reads of one wavefront); by the counters the matrix cores are busy
+// for 35 % of the launch.  The whole-sample variants use all 256 registers and 40 (by descriptors 68) bytes of scratch per lane.
 #pragma once
 #include "conv_tower.h"
 #include "wgrad_conv.h"
