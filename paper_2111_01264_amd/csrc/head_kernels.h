@@ -559,9 +559,9 @@ struct RmsArgs {
     float lr, alpha, eps;
     int centered;
     // second stage of the bias gradients (conv1..3, fc1): chunk sums (conv layers: one per weight-gradient slice)
-    const float* bias_partial;
+    const float* bias_partial;   // (full precision: conv layers fp64)
     int bias_chunks[4];
-    int bias_first[4];
+    int bias_first[4];           // in floats
 };
 
 __device__ inline void rms_update(const RmsArgs& a, float& th, float g, float& vv, float& mm)
@@ -745,14 +745,17 @@ __global__ __launch_bounds__(256) void rmsprop_kernel(float* theta_, float* grad
         else if (ch < 160) { layer = 2; c = ch - 96; e = a.off.b3 + c; }
         else if (live) { layer = 3; c = ch - 160; e = a.off.bf1 + c; }
         const int C = layer == 0 ? 32 : (layer == 3 ? 512 : 64);
-        const float* part = a.bias_partial + a.bias_first[layer] + c;
-        float g = 0.f;
+        const float* part = a.bias_partial + a.bias_first[layer];
+        typedef typename std::conditional<sizeof(T) == 4, double, float>::type Sum;   // full precision: the conv layers' partials are fp64
+        Sum total = 0;
         if (live)
-            for (int k = j; k < a.bias_chunks[layer]; k += kRmsBiasLanes) g += part[k * C];
-        g += __shfl_down(g, 4, kRmsBiasLanes);
-        g += __shfl_down(g, 2, kRmsBiasLanes);
-        g += __shfl_down(g, 1, kRmsBiasLanes);
+            for (int k = j; k < a.bias_chunks[layer]; k += kRmsBiasLanes)
+                total += layer < 3 ? reinterpret_cast<const Sum*>(part)[k * C + c] : part[k * C + c];
+        total += __shfl_down(total, 4, kRmsBiasLanes);
+        total += __shfl_down(total, 2, kRmsBiasLanes);
+        total += __shfl_down(total, 1, kRmsBiasLanes);
         if (!live || j != 0) return;
+        const float g = static_cast<float>(total);
         grad_[e] = g;
         float th = theta_[e], vv = v_[e], mm = m_[e];
         rms_update(a, th, g, vv, mm);

@@ -518,10 +518,11 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     // their bias gradients: one partial row [C_out] per slice, added in slice order by the optimiser kernel
     constexpr int kConvBiasOff = 16384;
     static_assert(kSl1 <= static_cast<int>(kWgMaxSplits1) && kSl2 <= static_cast<int>(kWgMaxSplits) && kSl3 <= static_cast<int>(kWgMaxSplits), "slices fit their buffer");
-    static_assert(kConvBiasOff + kSl1 * 32 + (kSl2 + kSl3) * 64 <= 65536, "bias partials fit their buffer");
+    constexpr int kBiasWords = kBf16 ? 1 : 2;   // fp32: the conv layers' partial sums are fp64
+    static_assert(kConvBiasOff + kBiasWords * (kSl1 * 32 + (kSl2 + kSl3) * 64) <= 65536, "bias partials fit their buffer");
     bias_first[0] = kConvBiasOff;
-    bias_first[1] = bias_first[0] + kSl1 * 32;
-    bias_first[2] = bias_first[1] + kSl2 * 64;
+    bias_first[1] = bias_first[0] + kBiasWords * kSl1 * 32;
+    bias_first[2] = bias_first[1] + kBiasWords * kSl2 * 64;
     for (int l = 0; l < 3; ++l) bias_chunks[l] = wg_splits[l];
     w1.bias_partial = c->bias_partial + bias_first[0];
     w2.bias_partial = c->bias_partial + bias_first[1];

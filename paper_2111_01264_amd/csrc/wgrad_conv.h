@@ -63,6 +63,10 @@ struct WgGeo {
     static_assert(!U8_ || (IN_ROWS * WIN_) % 16 == 0, "a channel's rows of one item are whole 16-byte vectors");
     static_assert(!U8_ || (S_ * ROWS * WIN_) % 16 == 0, "the second item of a sample starts on a 16-byte boundary");
     static_assert(IN_ELEMS % 8 == 0 && (KPAD * LDA) % 2 == 0, "LDS regions stay 16-byte / 4-byte aligned");
+    // Bias sums.  A slice is one sample or a few, and samples whose TD errors differ in sign cancel: with slice totals rounded to fp32 in
+    // front of that, full precision's conv3.b was up to four times as far from 64 bits as when the rows of twenty samples were
+    // added in one sum.  A thread's values of an item are still added in fp32, everything after that in fp64 (no time: a few additions).
+    typedef typename std::conditional<PL == 3, double, float>::type Sum;
 };
 typedef WgGeo<4, 84, 84, 32, 20, 20, 8, 4, 0, true, 1> WgConv1;
 typedef WgGeo<4, 84, 84, 32, 20, 20, 8, 4, 0, true, 1, float, 4> WgConv1F32;
@@ -73,7 +77,7 @@ struct WgConvArgs {
     const void* dz;          // bf16 or fp32 [n][HOUT][WOUT][COUT]
     const void* in;          // conv2 / conv3: bf16 [n][HIN][WIN][CIN];  conv1: uint8 [n][4][84][84], unused with desc
     float* partial;          // [slices][COUT][N] fp32
-    float* bias_partial;     // [slices][COUT] fp32: column sums of dZ over the slice's items (the bias gradient)
+    float* bias_partial;     // [slices][COUT]: column sums of dZ over the slice's items (the bias gradient); bf16 fp32, full precision fp64
     int n;                   // samples
     int per;                 // items per workgroup (the host sizes the grid so that every workgroup has at least one)
     const int32_t* desc;     // conv1: [n][kDescInts] (entries 0..3: replay slots of the frames of s, -1 = zero frame) or null
@@ -196,9 +200,9 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
     // (fp32: four) channels (256 is a multiple of the vectors per row), so it adds them up in as many registers while it stores them to
     // LDS; the threads' sums meet in LDS once, at the end, in thread order.  (A reduction kernel of its own read every
     // dZ tensor from memory a second time.)
-    float bsum[EPV];
+    typename G::Sum bsum[EPV];
 #pragma unroll
-    for (int e = 0; e < EPV; ++e) bsum[e] = 0.f;
+    for (int e = 0; e < EPV; ++e) bsum[e] = 0;
     static_assert(256 % (G::COUT / EPV) == 0, "a thread's dZ vectors share their channel chunk");
 
     // Operands are requested TWO items ahead into registers (one dependent round trip to memory takes about as long as
@@ -257,6 +261,7 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
     // predicate around a store the compiler no longer counts the loads in flight and waits for ALL of them, the next items' included.
     auto stash = [&](auto ps_) {
         constexpr int ps = decltype(ps_)::value;
+        [[maybe_unused]] float isum[EPV] = {};   // full precision: this item's share of bsum
 #pragma unroll
         for (int u = 0; u < NVD; ++u) {
             const int v = min(tid + u * 256, G::DZ_VECS - 1);
@@ -287,9 +292,13 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
                 } else {
                     const dz_vec once = __builtin_bit_cast(dz_vec, d & (counts ? ~0u : 0u));
 #pragma unroll
-                    for (int e = 0; e < EPV; ++e) bsum[e] += static_cast<float>(once[e]);
+                    for (int e = 0; e < EPV; ++e) isum[e] += static_cast<float>(once[e]);
                 }
             }
+        }
+        if constexpr (PL == 3) {
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) bsum[e] += isum[e];
         }
 #pragma unroll
         for (int u = 0; u < NVI; ++u) {
@@ -365,9 +374,10 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
 
     if (cb == 0) {   // workgroup-uniform
         __syncthreads();   // the last item has been read; sIn is free
-        constexpr int LDS_E = 256 + 8;                  // padded: the reads below stride through the threads in steps of CH
-        float* sSum = reinterpret_cast<float*>(smem);   // [8][256 threads]
-        static_assert(8 * LDS_E * 4 <= G::SMEM, "the partial sums fit the operand buffers");
+        typedef typename G::Sum Sum;
+        constexpr int LDS_E = 256 + 8;              // padded: the reads below stride through the threads in steps of CH
+        Sum* sSum = reinterpret_cast<Sum*>(smem);   // [EPV][256 threads]
+        static_assert(EPV * LDS_E * sizeof(Sum) <= G::SMEM, "the partial sums fit the operand buffers");
 #pragma unroll
         for (int e = 0; e < EPV; ++e) sSum[e * LDS_E + tid] = bsum[e];
         __syncthreads();
@@ -378,15 +388,15 @@ __device__ inline void wgrad_conv_block(const WgConvArgs& a, int wg, int cb, uns
             constexpr int CH = G::COUT / EPV, P = 256 / G::COUT, PER = 256 / CH / P;
             static_assert(PER == EPV && (P == 4 || P == 8), "a few values per lane, a power-of-two group of lanes per channel");
             const int ch = tid / P, p = tid % P;
-            float v[PER];
+            Sum v[PER];
 #pragma unroll
             for (int k = 0; k < PER; ++k) v[k] = sSum[(ch % EPV) * LDS_E + ch / EPV + CH * (p * PER + k)];
-            float sum = 0.f;
+            Sum sum = 0;
 #pragma unroll
             for (int k = 0; k < PER; ++k) sum += v[k];
 #pragma unroll
             for (int d = P / 2; d >= 1; d >>= 1) sum += __shfl_down(sum, d, P);
-            if (p == 0) a.bias_partial[static_cast<size_t>(wg) * G::COUT + ch] = sum;
+            if (p == 0) reinterpret_cast<Sum*>(a.bias_partial)[static_cast<size_t>(wg) * G::COUT + ch] = sum;
         }
     }
     float* out = a.partial + static_cast<size_t>(wg) * G::COUT * G::N;

@@ -69,7 +69,7 @@ __device__ inline void wgrad_conv_f32_block(const WgConvArgs& a, int wg, int cb,
     for (int j = 0; j < NTW; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-    wg_f32x4 bsum = {0.f, 0.f, 0.f, 0.f};   // bias gradient: column sums of dZ (a thread's vectors share their four channels)
+    double bsum[4] = {0, 0, 0, 0};   // bias gradient: column sums of dZ (a thread's vectors share their four channels; fp64: see WgGeo's Sum)
     static_assert(256 % (G::COUT / 4) == 0, "a thread's dZ vectors share their channel chunk");
 
     wg_f32x4 pin[NVI], pdz[NVD];
@@ -82,11 +82,14 @@ __device__ inline void wgrad_conv_f32_block(const WgConvArgs& a, int wg, int cb,
         for (int u = 0; u < NVI; ++u) pin[u] = inp[min(tid + u * 256, G::IN_VECS - 1)];
     };
     auto stash = [&]() {   // surplus threads store a copy of the last vector again (same bytes, same place)
+        wg_f32x4 isum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int u = 0; u < NVD; ++u) {
             reinterpret_cast<wg_f32x4*>(sDz)[min(tid + u * 256, G::DZ_VECS - 1)] = pdz[u];
-            if (cb == 0) bsum += __builtin_bit_cast(wg_f32x4, __builtin_bit_cast(wg_u32x4, pdz[u]) & (G::DZ_VECS % 256 == 0 || tid + u * 256 < G::DZ_VECS ? ~0u : 0u));
+            if (cb == 0) isum += __builtin_bit_cast(wg_f32x4, __builtin_bit_cast(wg_u32x4, pdz[u]) & (G::DZ_VECS % 256 == 0 || tid + u * 256 < G::DZ_VECS ? ~0u : 0u));
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bsum[e] += isum[e];
 #pragma unroll
         for (int u = 0; u < NVI; ++u) reinterpret_cast<wg_f32x4*>(sIn)[min(tid + u * 256, G::IN_VECS - 1)] = pin[u];
     };
@@ -127,17 +130,18 @@ __device__ inline void wgrad_conv_f32_block(const WgConvArgs& a, int wg, int cb,
     if (cb == 0) {   // workgroup-uniform: the threads' channel sums meet in LDS (see wgrad_conv_block)
         __syncthreads();
         constexpr int LDS_E = 256 + 8, CH = G::COUT / 4, P = 256 / G::COUT, PER = 256 / CH / P;
-        float* sSum = reinterpret_cast<float*>(smem);
+        double* sSum = reinterpret_cast<double*>(smem);
+        static_assert(4 * LDS_E * sizeof(double) <= G::SMEM, "the partial sums fit the operand buffers");
 #pragma unroll
         for (int e = 0; e < 4; ++e) sSum[e * LDS_E + tid] = bsum[e];
         __syncthreads();
         const int ch = tid / P, p = tid % P;
-        float sum = 0.f;
+        double sum = 0;
 #pragma unroll
         for (int k = 0; k < PER; ++k) sum += sSum[(ch & 3) * LDS_E + (ch >> 2) + CH * (p * PER + k)];
 #pragma unroll
         for (int d = P / 2; d >= 1; d >>= 1) sum += __shfl_down(sum, d, P);
-        if (p == 0) a.bias_partial[static_cast<size_t>(wg) * G::COUT + ch] = sum;
+        if (p == 0) reinterpret_cast<double*>(a.bias_partial)[static_cast<size_t>(wg) * G::COUT + ch] = sum;
     }
     float* out = a.partial + static_cast<size_t>(wg) * G::COUT * G::N;
 #pragma unroll

@@ -44,21 +44,37 @@ def steady_params(seed, A):
     return theta.astype(np.float32)
 
 
+def one_sign_params(seed, A):
+    """The same weights with one sign per channel (odd channels negative, their bias too): a data gradient is then a sum of one sign, a
+    sample's bias gradient is large, and what is left over the samples, whose errors are clipped to either side, is small."""
+    theta = synth.init_params(seed, A).astype(np.float64)
+    off = 0
+    for name, shape, _ in synth.layer_shapes(A):
+        n = int(np.prod(shape))
+        w = theta[off:off + n].reshape(shape[0], -1)
+        sign = np.where(np.arange(shape[0]) % 2, -1.0, 1.0) if name != "fc2" else np.ones(shape[0])
+        w[:] = np.abs(w) * SCALE[name] * sign[:, None]
+        if name != "fc2":
+            theta[off + n:off + n + shape[0]] = 0.5 * sign
+        off += n + shape[0]
+    return theta.astype(np.float32)
+
+
 SEEDS = 4
 
 
-def gradient_errors(B, double_dqn):
+def gradient_errors(B, double_dqn, params=steady_params):
     """Root mean square over the seeds: a single draw of 32 bias gradients scatters by a third."""
-    runs = [step_errors(B, double_dqn, 6400 + B + 1000 * k) for k in range(SEEDS)]
+    runs = [step_errors(B, double_dqn, 6400 + B + 1000 * k, params) for k in range(SEEDS)]
     return {name: float(np.sqrt(np.mean([e[name] ** 2 for e in runs]))) for name in runs[0]}
 
 
-def step_errors(B, double_dqn, seed):
+def step_errors(B, double_dqn, seed, params):
     A = 6
     cfg = make_cfg(A, max_batch=B, max_envs=1, precision=P.DQN_PRECISION_FP32, double_dqn=double_dqn, seed=seed)
     ctx = P.dqn_create(cfg, torch.cuda.Stream(), torch.cuda.Stream())
     try:
-        theta, theta_t = steady_params(seed, A), steady_params(seed + 1, A)
+        theta, theta_t = params(seed, A), params(seed + 1, A)
         P.dqn_set_params(ctx, P.DQN_PARAMS_ONLINE, theta)
         P.dqn_set_params(ctx, P.DQN_PARAMS_TARGET, theta_t)
         orc = odqn.OracleDQN(A, theta, double_dqn=bool(double_dqn), seed=seed)
@@ -96,6 +112,25 @@ def test_f32_gradient_errors(B, double_dqn):
     errs = gradient_errors(B, double_dqn)
     print("B=%d " % B + " ".join("%s %.2e" % kv for kv in errs.items()))
     for (name, err), bound in zip(errs.items(), RECORDED[B]):
+        assert err <= SLACK * bound, (name, err, bound)
+
+
+ONE_SIGN_RECORDED = {
+    16: (8.87e-07, 3.29e-05, 2.64e-06, 6.91e-06, 3.45e-06, 3.59e-06, 2.1e-07, 9.43e-08, 5.6e-08, 0),
+    32: (3.13e-07, 7.42e-08, 1.41e-07, 5.59e-08, 1.39e-07, 4.77e-08, 1.07e-07, 6.54e-08, 5.45e-08, 0),
+    64: (9.34e-07, 1.35e-07, 4.21e-07, 8.43e-08, 3.88e-07, 9.46e-08, 1.75e-07, 1.14e-07, 1.11e-07, 0),
+    128: (1.64e-06, 1.94e-07, 8.12e-07, 1.57e-07, 7.14e-07, 2.49e-07, 2.69e-07, 1.43e-07, 8.99e-08, 0),
+    131: (2.2e-06, 4.06e-07, 2e-06, 2.47e-07, 1.49e-06, 3.24e-07, 3.45e-07, 1.94e-07, 1.27e-07, 9.94e-08),
+    256: (4.5e-06, 1.44e-06, 1.98e-05, 1.39e-06, 2.12e-05, 1.39e-06, 5.66e-07, 1.67e-07, 1.13e-07, 0),
+    512: (3.05e-06, 2.22e-07, 1.61e-06, 1.8e-07, 1.21e-06, 1.68e-07, 5.08e-07, 1.25e-07, 1.15e-07, 0),
+}
+
+
+@pytest.mark.parametrize("B,double_dqn", CASES)
+def test_f32_gradient_errors_weights_of_one_sign(B, double_dqn):
+    errs = gradient_errors(B, double_dqn, one_sign_params)
+    print("B=%d " % B + " ".join("%s %.2e" % kv for kv in errs.items()))
+    for (name, err), bound in zip(errs.items(), ONE_SIGN_RECORDED[B]):
         assert err <= SLACK * bound, (name, err, bound)
 
 
