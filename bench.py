@@ -70,14 +70,14 @@ _WG_SRC = (_C + "wgrad_all.h", _C + "wgrad_conv.h", _C + "wgrad_fc1.h", _C + "ge
 _TOWER_SRC = (_C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
 _TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "net.hip")
 TRAFFIC = {
-    ("rmsprop", 32, "bf16"): (66.21e6, _RMS_SRC, "0e44fc10b874b7d9149f4a9cebfd74e978b7c1a1", "profiles/hbm_traffic_b32.txt"),
-    ("wgrad_all", 32, "bf16"): (22.08e6, _WG_SRC, "3bb3da81df246c3787b10d768ba2467e8fb21b06", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower", 32, "bf16"): (10.26e6, _TOWER_SRC, "0a89036664eae62fef3c763b35b2d894f309ad17", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "07d1d9c6ac430e6afbd7187528cdc1697eb5dbdc", "profiles/hbm_traffic_b32.txt"),
-    ("rmsprop", 256, "bf16"): (71.39e6, _RMS_SRC, "0e44fc10b874b7d9149f4a9cebfd74e978b7c1a1", "profiles/hbm_traffic_b256.txt"),
-    ("wgrad_all", 256, "bf16"): (58.57e6, _WG_SRC, "3bb3da81df246c3787b10d768ba2467e8fb21b06", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower", 256, "bf16"): (24.21e6, _TOWER_SRC, "0a89036664eae62fef3c763b35b2d894f309ad17", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower_bwd", 256, "bf16"): (21.24e6, _TOWER_BWD_SRC, "07d1d9c6ac430e6afbd7187528cdc1697eb5dbdc", "profiles/hbm_traffic_b256.txt"),
+    ("rmsprop", 32, "bf16"): (66.21e6, _RMS_SRC, "26b495281cf015bdef224d9df2da2ceedeabf616", "profiles/hbm_traffic_b32.txt"),
+    ("wgrad_all", 32, "bf16"): (22.08e6, _WG_SRC, "2696c4e78975d1b7b453853988c78340702719e4", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower", 32, "bf16"): (10.26e6, _TOWER_SRC, "e3df90cdbbc306e87824d8318ccc90afb9242698", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower_bwd", 32, "bf16"): (4.78e6, _TOWER_BWD_SRC, "91a268801719880890adaece14c982e6777d0472", "profiles/hbm_traffic_b32.txt"),
+    ("rmsprop", 256, "bf16"): (71.39e6, _RMS_SRC, "26b495281cf015bdef224d9df2da2ceedeabf616", "profiles/hbm_traffic_b256.txt"),
+    ("wgrad_all", 256, "bf16"): (58.52e6, _WG_SRC, "2696c4e78975d1b7b453853988c78340702719e4", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower", 256, "bf16"): (24.22e6, _TOWER_SRC, "e3df90cdbbc306e87824d8318ccc90afb9242698", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower_bwd", 256, "bf16"): (21.25e6, _TOWER_BWD_SRC, "91a268801719880890adaece14c982e6777d0472", "profiles/hbm_traffic_b256.txt"),
 }
 
 

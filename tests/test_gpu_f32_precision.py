@@ -8,8 +8,8 @@ constant the weight gradients are, like the bias gradients, sums over all pixels
 that is not to nearest but always to one side, which a comparison element by element does not see, adds up there.
 
 RECORDED holds the errors of the kernels that computed everything on the fp32 instruction, layer by layer, on the same inputs (both
-sides are deterministic); a tenth is allowed on top, for sums of the same precision in another order (the tensors whose products
-are still made by that instruction, conv3.b and fc1.w, moved by up to 6 % when only the order of their sums changed).
+sides are deterministic); a tenth is allowed on top, for sums of the same precision in another order (fc1.w, whose products
+are still made by that instruction, moved by up to 4 % when only the order of its sums changed).
 
 Act step: likewise the network's part of the Q rows (without fc2's biases), on weights as they are initialised.
 """
