@@ -14,6 +14,7 @@
 
 #include "conv_tower.h"
 #include "conv_tower_bwd.h"
+#include "conv_tower_many.h"
 #include "conv_tower_f32.h"
 #include "conv_tower_bwd_f32.h"
 #include "fc_as.h"
@@ -180,6 +181,8 @@ static hipError_t raise_lds_limits()
             {reinterpret_cast<const void*>(conv_tower_kernel<false, 3>), kTowerSmem},
             {reinterpret_cast<const void*>(conv_tower_kernel<false, 7>), kTowerSmem},
             {reinterpret_cast<const void*>(conv_tower_kernel<true, 1>), kTowerSmem},
+            {reinterpret_cast<const void*>(conv_tower_many_kernel<false>), kTowerManySmem},
+            {reinterpret_cast<const void*>(conv_tower_many_kernel<true>), kTowerManySmem},
             {reinterpret_cast<const void*>(conv_tower_bwd_kernel<1>), kTowerBwdSmem},
             {reinterpret_cast<const void*>(conv_tower_bwd_kernel<5>), kTowerBwdSmem},
             {reinterpret_cast<const void*>(conv_tower_f32_kernel<false, 1>), kTowerF32Smem},
@@ -262,23 +265,26 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         a.n = n; a.groups = groups;
         if (src) { a.desc = src->desc; a.ring = src->ring; }
         DQN_HIP(raise_lds_limits());
-        // Few items (a round of synchronized samplers, a minibatch of 32): seven or three workgroups per item, a seventh or
-        // a third of its output rows each, while that still fits the chip -- the chain of layers of one sample is what the
-        // launch waits for
-        const int total = n * groups;
-        const int parts = a.desc ? 1 : (7 * total <= c->num_cus ? 7 : (3 * total <= c->num_cus ? 3 : 1));
-        const int grid = parts > 1 ? parts * total : (total < c->num_cus ? total : c->num_cus);
-        a.per = parts > 1 ? 1 : (total + grid - 1) / grid;
+        // Up to 256 items: one workgroup each, or the smallest part of an item for which every workgroup is resident at once -- the chain of
+        // layers of one sample is what the launch waits for.  More items: two persistent workgroups of half the size per compute unit.
+        const int total = n * groups, cus = c->num_cus;
+        const bool many = total > cus;
+        const int parts = a.desc || 3 * total > cus ? 1 : 7 * total <= cus ? 7 : 3;
+        const int grid = many ? (total < 2 * cus ? total : 2 * cus) : parts * total;
         a.tower_blocks = grid;
         a.push.L = 0;
         if (push) a.push = *push;
         const ProfPair pr = pp(K_CONV1_FWD);
+        const dim3 g3(grid + a.push.L);
         // (the leading arguments repeat the fields a workgroup needs first: see the kernel)
-        const dim3 g3(grid + a.push.L), b3(kTowerThreads);
-        if (a.desc) launch_timed(conv_tower_kernel<true, 1>, g3, b3, kTowerSmem, st, pr.begin, pr.end, a.n, a.groups, a.per, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
-        else if (parts == 7) launch_timed(conv_tower_kernel<false, 7>, g3, b3, kTowerSmem, st, pr.begin, pr.end, a.n, a.groups, a.per, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
-        else if (parts == 3) launch_timed(conv_tower_kernel<false, 3>, g3, b3, kTowerSmem, st, pr.begin, pr.end, a.n, a.groups, a.per, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
-        else launch_timed(conv_tower_kernel<false, 1>, g3, b3, kTowerSmem, st, pr.begin, pr.end, a.n, a.groups, a.per, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
+        if (many) {
+            const int share = (total / grid) << 16 | total % grid;   // items per workgroup, and how many run one more
+            launch_timed(a.desc ? conv_tower_many_kernel<true> : conv_tower_many_kernel<false>, g3, dim3(kManyThreads), kTowerManySmem, st, pr.begin, pr.end,
+                         a.n, a.groups, share, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
+        } else {
+            auto kern = a.desc ? conv_tower_kernel<true, 1> : parts == 7 ? conv_tower_kernel<false, 7> : parts == 3 ? conv_tower_kernel<false, 3> : conv_tower_kernel<false, 1>;
+            launch_timed(kern, g3, dim3(kTowerThreads), kTowerSmem, st, pr.begin, pr.end, a.n, a.groups, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
+        }
         DQN_LAUNCH_CHECK();
     } else {
         // the same fusion in full precision (values in three bf16 parts, see conv_tower_f32.h)
