@@ -154,7 +154,8 @@ static_assert(kTowerXBytes <= kTowerXchgBytes, "the state buffer overlays the ex
 // pixel tiles for eight wavefronts), two pixel tiles of conv2 instead of three and one of conv3 instead of two.  Every
 // output element is computed by the same instructions in the same order as with PARTS = 1 (rows that two parts both need
 // are computed twice), so the results are equal bit for bit (rows of act1 / act2 that two parts write get the same bytes).  PARTS = 7, for a single round of samplers: one output row of
-// conv3 per workgroup (three rows of conv2: one pixel tile, eight rows of conv1: five tiles).
+// conv3 per workgroup (three rows of conv2: one pixel tile, eight rows of conv1: five tiles).  PARTS = 2 (rows 0-2 / 3-6 of conv3): as
+// thirds, but that the second half has nine tiles of conv1, one of its wavefronts two.
 template <bool DESC, int PARTS>
 __global__ __launch_bounds__(kTowerThreads) void conv_tower_kernel(int n_, int groups_, int tower_blocks_, const uint8_t* x0_,
                                                                    const uint8_t* x1_, const int32_t* desc_, const uint8_t* ring_,
@@ -181,17 +182,17 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_kernel(int n_, int g
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lp = lane & 31, kg = lane >> 5;
     const int nt = wave >> 2, kq = wave & 3;
-    static_assert(PARTS == 1 || PARTS == 3 || PARTS == 7, "whole samples, thirds, or sevenths");
+    static_assert(PARTS == 1 || PARTS == 2 || PARTS == 3 || PARTS == 7, "whole samples, halves, thirds, or sevenths");
     // workgroup j runs part j % PARTS of item j / PARTS
     const int part = static_cast<int>(blockIdx.x % PARTS), item = static_cast<int>(blockIdx.x / PARTS);
     if (item >= n_ * groups_) return;
     // first row and pixel count of this part in each layer's output (whole sample: all of it)
     // (conv3 rows [r, r') need conv2 rows [r, r' + 2), and those need conv1 rows [2 r, 2 r' + 6))
-    const int r3_lo = PARTS == 1 ? 0 : PARTS == 7 ? part : (part == 0 ? 0 : part == 1 ? 3 : 5);
+    const int r3_lo = PARTS == 1 ? 0 : PARTS == 7 ? part : PARTS == 2 ? 3 * part : (part == 0 ? 0 : part == 1 ? 3 : 5);
     const int r2_lo = r3_lo, r1_lo = 2 * r3_lo;
-    const int n3 = PARTS == 1 ? 49 : PARTS == 7 ? 7 : (part == 0 ? 21 : 14);
-    const int n2 = PARTS == 1 ? 81 : PARTS == 7 ? 27 : (part == 0 ? 45 : 36);
-    const int n1 = PARTS == 1 ? 400 : PARTS == 7 ? 160 : (part == 0 ? 240 : 200);
+    const int n3 = PARTS == 1 ? 49 : PARTS == 7 ? 7 : PARTS == 2 ? (part == 0 ? 21 : 28) : (part == 0 ? 21 : 14);
+    const int n2 = PARTS == 1 ? 81 : PARTS == 7 ? 27 : PARTS == 2 ? (part == 0 ? 45 : 54) : (part == 0 ? 45 : 36);
+    const int n1 = PARTS == 1 ? 400 : PARTS == 7 ? 160 : PARTS == 2 ? (part == 0 ? 240 : 280) : (part == 0 ? 240 : 200);
     constexpr int T2 = PARTS == 1 ? 3 : PARTS == 7 ? 1 : 2, T3 = PARTS == 1 ? 2 : 1;   // pixel tiles of conv2 / conv3 per wavefront
 
     // The state, 16 bytes per lane and load (the last load is clamped, not predicated);
@@ -326,7 +327,8 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_kernel(int n_, int g
                 }
             }
         };
-        if (PARTS == 1 && wave < 5) run(std::integral_constant<int, 2>{}); else run(std::integral_constant<int, 1>{});   // 13 tiles (a third: at most 8)
+        // 13 tiles (the second half: 9, the others at most 8)
+        if ((PARTS == 1 && wave < 5) || (PARTS == 2 && part == 1 && wave == 0)) run(std::integral_constant<int, 2>{}); else run(std::integral_constant<int, 1>{});
     }
     __syncthreads();
 

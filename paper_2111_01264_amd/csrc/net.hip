@@ -178,6 +178,7 @@ static hipError_t raise_lds_limits()
     std::call_once(once, [] {
         const struct { const void* kernel; size_t bytes; } big[] = {
             {reinterpret_cast<const void*>(conv_tower_kernel<false, 1>), kTowerSmem},
+            {reinterpret_cast<const void*>(conv_tower_kernel<false, 2>), kTowerSmem},
             {reinterpret_cast<const void*>(conv_tower_kernel<false, 3>), kTowerSmem},
             {reinterpret_cast<const void*>(conv_tower_kernel<false, 7>), kTowerSmem},
             {reinterpret_cast<const void*>(conv_tower_kernel<true, 1>), kTowerSmem},
@@ -269,7 +270,7 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         // layers of one sample is what the launch waits for.  More items: two persistent workgroups of half the size per compute unit.
         const int total = n * groups, cus = c->num_cus;
         const bool many = total > cus;
-        const int parts = a.desc || 3 * total > cus ? 1 : 7 * total <= cus ? 7 : 3;
+        const int parts = a.desc || 2 * total > cus ? 1 : 7 * total <= cus ? 7 : 3 * total <= cus ? 3 : 2;
         const int grid = many ? (total < 2 * cus ? total : 2 * cus) : parts * total;
         a.tower_blocks = grid;
         a.push.L = 0;
@@ -282,7 +283,8 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
             launch_timed(a.desc ? conv_tower_many_kernel<true> : conv_tower_many_kernel<false>, g3, dim3(kManyThreads), kTowerManySmem, st, pr.begin, pr.end,
                          a.n, a.groups, share, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
         } else {
-            auto kern = a.desc ? conv_tower_kernel<true, 1> : parts == 7 ? conv_tower_kernel<false, 7> : parts == 3 ? conv_tower_kernel<false, 3> : conv_tower_kernel<false, 1>;
+            auto kern = a.desc ? conv_tower_kernel<true, 1> : parts == 7 ? conv_tower_kernel<false, 7> : parts == 3 ? conv_tower_kernel<false, 3>
+                      : parts == 2 ? conv_tower_kernel<false, 2> : conv_tower_kernel<false, 1>;
             launch_timed(kern, g3, dim3(kTowerThreads), kTowerSmem, st, pr.begin, pr.end, a.n, a.groups, a.tower_blocks, a.x[0], a.x[1], a.desc, a.ring, a.w1[0], a);
         }
         DQN_LAUNCH_CHECK();
