@@ -1,6 +1,8 @@
 // Fused data-gradient chain conv3 -> conv2 of the Q-network's backward pass (Section 2.1, Eq. 1: the gradient of
 // the TD loss with respect to theta needs dLoss/d(activation) of every layer), reduced-precision mode: the mirror
-// image of conv_tower.h.  A persistent workgroup of 8 wavefronts walks a contiguous range of samples; per sample
+// image of conv_tower.h, for minibatches that leave most of the chip idle (5 B <= compute units; larger ones: conv_tower_bwd_many.h).  A workgroup of
+// 8 wavefronts runs a FIFTH of a sample -- rows 2 j, 2 j + 1 of every parity class of dz1 (four rows of dz1) with the two or three rows of
+// dz2 they depend on --: one pixel tile per stage (a whole sample per workgroup took 8.4 us at batch 32, this 4.0).  Per sample
 //
 //   dz2[y][x][c] = [act2 > 0] * sum_{p,q,o} dz3[y-p][x-q][o]   * W3[o][p][q][c]          (9x9x64 from 7x7x64, 3x3 taps)
 //   dz1[y][x][c] = [act1 > 0] * sum_{p,q,o} dz2[(y-p)/2][(x-q)/2][o] * W2[o][p][q][c]    (20x20x32 from 9x9x64, stride 2)
@@ -25,12 +27,13 @@ struct TowerBwdArgs {
     const bf16_t* w2d;    // four classes, each fragment order of [c 32][k = (p2, q2, o) 256]
     bf16_t* dz2;          // [n][81][64]
     bf16_t* dz1;          // [n][400][32]
-    int n, per;           // samples, samples per workgroup
+    int n;                // samples
 };
 
 constexpr int kTbPitch = 72;                          // elements per pixel of the padded LDS images
 constexpr int kTbImg = 11 * 11 * kTbPitch;            // one padded image
-constexpr size_t kTowerBwdSmem = kTowerXchgBytes + 2 * kTbImg * 2;
+constexpr int kTbXchgBytes = 2 * 4 * 3 * 64 * 16;     // conv3 stage: [nt][finisher][slot][lane] float4; conv2 stage: [wavefront][lane][2]
+constexpr size_t kTowerBwdSmem = kTbXchgBytes + 2 * kTbImg * 2;
 
 // Sum of the four k-quarters' rows 4 * KQ .. + 3 (no bias, no activation); layout as tower_send.
 template <int KQ> __device__ inline float4 tower_sum(const float4* x, const f32x16& acc, int lane)
@@ -74,42 +77,36 @@ template <int KH> __device__ inline float4 tower_sum_half(const float4* theirs, 
 // The arguments are TowerBwdArgs' fields one by one, in the order a workgroup needs them: the first 14 dwords of the
 // kernel arguments are preloaded into scalar registers when a wavefront starts (see conv_tower_kernel).
 //
-// PARTS = 5: an item is a FIFTH of a sample -- rows 2 j, 2 j + 1 of every parity class of dz1 (four rows of dz1) with the
-// two or three rows of dz2 they depend on -- and every workgroup runs exactly one item: one pixel tile per stage instead of
-// three and four.  For minibatches that leave most of the chip idle (see conv_tower_kernel's PARTS); every element is
-// computed by the same instructions in the same order as with PARTS = 1, rows of dz2 that two parts need are computed and
-// stored by both.
-template <int PARTS>
-__global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_kernel(int n_, int per_, const bf16_t* dz3_, const bf16_t* w3d_, const bf16_t* w2d_,
+// Every element is computed by the same instructions in the same order as in conv_tower_bwd_many.h; rows of dz2 that two parts need are
+// computed and stored by both.
+constexpr int kTbParts = 5;
+__global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_kernel(int n_, const bf16_t* dz3_, const bf16_t* w3d_, const bf16_t* w2d_,
                                                                        const bf16_t* act2_, const bf16_t* act1_, bf16_t* dz2_, bf16_t* dz1_)
 {
     typedef bf16_t T;
     typedef bf16x8 V8;
     extern __shared__ __attribute__((aligned(16))) unsigned char tb_smem[];
     float4* sXchg = reinterpret_cast<float4*>(tb_smem);
-    T* sP3 = reinterpret_cast<T*>(tb_smem + kTowerXchgBytes);   // dz3, 7x7 at offset (2, 2) of an 11x11 image
+    T* sP3 = reinterpret_cast<T*>(tb_smem + kTbXchgBytes);   // dz3, 7x7 at offset (2, 2) of an 11x11 image
     T* sP2 = sP3 + kTbImg;                                      // dz2, 9x9 at offset (1, 1)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lp = lane & 31, kg = lane >> 5;
     const int nt = wave >> 2, kq = wave & 3;     // conv3 stage
     const int cls = wave >> 1, kh = wave & 1;    // conv2 stage: class (py, px) = (cls >> 1, cls & 1)
-    static_assert(PARTS == 1 || PARTS == 5, "whole samples, or fifths");
-    const int part = PARTS == 1 ? 0 : static_cast<int>(blockIdx.x % PARTS);
-    const int first = PARTS == 1 ? blockIdx.x * per_ : static_cast<int>(blockIdx.x / PARTS), last = PARTS == 1 ? min(n_, first + per_) : min(n_, first + 1);
-    if (first >= last) return;
+    const int part = static_cast<int>(blockIdx.x % kTbParts), b = static_cast<int>(blockIdx.x / kTbParts);
+    if (b >= n_) return;
     // this part's rows: [y_lo, y_lo + 2) of each parity class of dz1 (20 pixels), rows [r2_lo, y_lo + 2) of dz2
-    const int y_lo = PARTS == 1 ? 0 : 2 * part, nc = PARTS == 1 ? 100 : 20;
-    const int r2_lo = PARTS == 1 ? 0 : (part == 0 ? 0 : 2 * part - 1), n2 = PARTS == 1 ? 81 : (part == 0 || part == 4 ? 18 : 27);   // rows 2 part - 1 .. 2 part + 1 of dz2's nine
-    constexpr int T3 = PARTS == 1 ? 3 : 1, T2 = PARTS == 1 ? 4 : 1;   // pixel tiles per wavefront: conv3 stage, conv2 stage
+    const int y_lo = 2 * part, nc = 20;
+    const int r2_lo = part == 0 ? 0 : 2 * part - 1, n2 = part == 0 || part == 4 ? 18 : 27;   // rows 2 part - 1 .. 2 part + 1 of dz2's nine
 
-    // a sample's dz3: 49 pixels x 128 bytes = 392 vectors, one per thread, fetched one sample ahead.  The first sample's is
-    // requested before the weights: loads return in order, and behind 139 KB of fragments the staging below waited ~1 us
+    // a sample's dz3: 49 pixels x 128 bytes = 392 vectors, one per thread, requested before the weights: loads return in
+    // order, and behind 139 KB of fragments the staging below waited ~1 us
     uint4 xv = make_uint4(0, 0, 0, 0);
-    if (tid < 392) xv = reinterpret_cast<const uint4*>(dz3_ + static_cast<size_t>(first) * 3136)[tid];
+    if (tid < 392) xv = reinterpret_cast<const uint4*>(dz3_ + static_cast<size_t>(b) * 3136)[tid];
     __builtin_amdgcn_sched_barrier(0);
 
-    // zero both images once: the borders are never written again
+    // zero both images
     for (int v = tid; v < 2 * kTbImg / 8; v += kTowerThreads) reinterpret_cast<uint4*>(sP3)[v] = make_uint4(0, 0, 0, 0);
 
     V8 wf3[9], wf2[8];
@@ -134,137 +131,86 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_kernel(int n_, i
     const int my_dst = (((my_px / 7) + 2) * 11 + (my_px % 7) + 2) * kTbPitch + my_part * 8;
     __syncthreads();   // the zero fill is complete
 
-    for (int b = first; b < last; ++b) {
-        if (tid < 392) *reinterpret_cast<uint4*>(sP3 + my_dst) = xv;
-        if (b + 1 < last && tid < 392) xv = reinterpret_cast<const uint4*>(dz3_ + static_cast<size_t>(b + 1) * 3136)[tid];
-        // ReLU masks of both stages: requested now, used after the exchanges
-        uint2 m2[T3], m1[T2][2];
-        {
-            const int ch = nt * 32 + 8 * kq + 4 * kg;
+    if (tid < 392) *reinterpret_cast<uint4*>(sP3 + my_dst) = xv;
+    // ReLU masks of both stages: requested now, used after the exchanges
+    const int ch = nt * 32 + 8 * kq + 4 * kg;                                   // conv3 stage: this lane's channels,
+    const int px2 = r2_lo * 9 + min(lp, n2 - 1);                                // pixel of dz2,
+    const int px1 = y_lo * 10 + min(lp, nc - 1);                                // conv2 stage: pixel of the class,
+    const int pix = (2 * (px1 / 10) + (cls >> 1)) * 20 + 2 * (px1 % 10) + (cls & 1);   // of dz1
+    const uint2 m2 = *reinterpret_cast<const uint2*>(act2_ + (static_cast<size_t>(b) * 81 + px2) * 64 + ch);
+    uint2 m1[2];
 #pragma unroll
-            for (int t = 0; t < T3; ++t) {
-                const int lpx = t * 32 + lp;
-                m2[t] = *reinterpret_cast<const uint2*>(act2_ + (static_cast<size_t>(b) * 81 + r2_lo * 9 + (lpx < n2 ? lpx : n2 - 1)) * 64 + ch);
-            }
-#pragma unroll
-            for (int t = 0; t < T2; ++t) {
-                const int lpx = t * 32 + lp, pc = y_lo * 10 + (lpx < nc ? lpx : nc - 1);
-                const int pix = (2 * (pc / 10) + (cls >> 1)) * 20 + 2 * (pc % 10) + (cls & 1);
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    m1[t][h] = *reinterpret_cast<const uint2*>(act1_ + (static_cast<size_t>(b) * 400 + pix) * 32 + 8 * (2 * kh + h) + 4 * kg);
-            }
-        }
-        __syncthreads();
+    for (int h = 0; h < 2; ++h) m1[h] = *reinterpret_cast<const uint2*>(act1_ + (static_cast<size_t>(b) * 400 + pix) * 32 + 8 * (2 * kh + h) + 4 * kg);
+    __syncthreads();
+    // ReLU mask: a bf16 activation is positive iff its bit pattern is in 0x0001 .. 0x7FFF (no NaNs here)
+    auto masked = [](const float4& v, const uint2& m) {
+        return make_float4(static_cast<int16_t>(m.x & 0xFFFF) > 0 ? v.x : 0.f, static_cast<int16_t>(m.x >> 16) > 0 ? v.y : 0.f,
+                           static_cast<int16_t>(m.y & 0xFFFF) > 0 ? v.z : 0.f, static_cast<int16_t>(m.y >> 16) > 0 ? v.w : 0.f);
+    };
+    constexpr int D = 6;
 
-        // ---- conv3 data gradient: 81 pixels = 3 tiles, channel tile nt, k-quarter kq (9 k-steps) ------------
-        {
-            f32x16 acc[T3];
-            const T* base[T3];
+    // ---- conv3 data gradient: at most 27 pixels, channel tile nt, k-quarter kq (9 k-steps) ------------
+    {
+        f32x16 acc;
 #pragma unroll
-            for (int t = 0; t < T3; ++t) {
-                const int lpx = t * 32 + lp, pc = r2_lo * 9 + (lpx < n2 ? lpx : n2 - 1);
-                base[t] = sP3 + ((pc / 9 + 2) * 11 + pc % 9 + 2) * kTbPitch + kg * 8;
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        const T* base = sP3 + ((px2 / 9 + 2) * 11 + px2 % 9 + 2) * kTbPitch + kg * 8;
+        V8 ring[D];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-            }
-            {
-                constexpr int D = 6;
-                auto fetch = [&](int step) { return *reinterpret_cast<const V8*>(base[step / 9] + off3[step % 9]); };
-                V8 ring[D];
+        for (int u = 0; u < D; ++u) ring[u] = *reinterpret_cast<const V8*>(base + off3[u]);
 #pragma unroll
-                for (int u = 0; u < D; ++u) ring[u] = fetch(u);
-#pragma unroll
-                for (int step = 0; step < 9 * T3; ++step) {
-                    const V8 cur = ring[step % D];
-                    if (step + D < 9 * T3) ring[step % D] = fetch(step + D);
-                    mma_32x32x16(acc[step / 9], wf3[step % 9], cur);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            float4* xc = sXchg + static_cast<size_t>(nt * 3) * (4 * 3 * 64);
-#pragma unroll
-            for (int t = 0; t < T3; ++t) {
-                float4* x = xc + t * (4 * 3 * 64);
-                if (kq == 0) tower_send<0>(x, acc[t], lane); else if (kq == 1) tower_send<1>(x, acc[t], lane);
-                else if (kq == 2) tower_send<2>(x, acc[t], lane); else tower_send<3>(x, acc[t], lane);
-            }
-            __syncthreads();
-            const int ch = nt * 32 + 8 * kq + 4 * kg;
-#pragma unroll
-            for (int t = 0; t < T3; ++t) {
-                const float4* x = xc + t * (4 * 3 * 64);
-                float4 v;
-                if (kq == 0) v = tower_sum<0>(x, acc[t], lane); else if (kq == 1) v = tower_sum<1>(x, acc[t], lane);
-                else if (kq == 2) v = tower_sum<2>(x, acc[t], lane); else v = tower_sum<3>(x, acc[t], lane);
-                const int lpx = t * 32 + lp, px = r2_lo * 9 + lpx;
-                if (lpx < n2) {
-                    // ReLU mask: a bf16 activation is positive iff its bit pattern is in 0x0001 .. 0x7FFF (no NaNs here)
-                    const uint32_t lo = m2[t].x, hi = m2[t].y;
-                    const float v0 = static_cast<int16_t>(lo & 0xFFFF) > 0 ? v.x : 0.f, v1 = static_cast<int16_t>(lo >> 16) > 0 ? v.y : 0.f;
-                    const float v2 = static_cast<int16_t>(hi & 0xFFFF) > 0 ? v.z : 0.f, v3 = static_cast<int16_t>(hi >> 16) > 0 ? v.w : 0.f;
-                    store4<T>(sP2 + ((px / 9 + 1) * 11 + px % 9 + 1) * kTbPitch + ch, v0, v1, v2, v3);
-                    store4<T>(dz2_ + (static_cast<size_t>(b) * 81 + px) * 64 + ch, v0, v1, v2, v3);
-                }
-            }
+        for (int k = 0; k < 9; ++k) {
+            const V8 cur = ring[k % D];
+            if (k + D < 9) ring[k % D] = *reinterpret_cast<const V8*>(base + off3[k + D]);
+            mma_32x32x16(acc, wf3[k], cur);
+            __builtin_amdgcn_sched_barrier(0);
         }
+        float4* x = sXchg + nt * (4 * 3 * 64);
+        if (kq == 0) tower_send<0>(x, acc, lane); else if (kq == 1) tower_send<1>(x, acc, lane);
+        else if (kq == 2) tower_send<2>(x, acc, lane); else tower_send<3>(x, acc, lane);
         __syncthreads();
+        float4 v;
+        if (kq == 0) v = tower_sum<0>(x, acc, lane); else if (kq == 1) v = tower_sum<1>(x, acc, lane);
+        else if (kq == 2) v = tower_sum<2>(x, acc, lane); else v = tower_sum<3>(x, acc, lane);
+        if (lp < n2) {
+            const float4 d = masked(v, m2);
+            store4<T>(sP2 + ((px2 / 9 + 1) * 11 + px2 % 9 + 1) * kTbPitch + ch, d.x, d.y, d.z, d.w);
+            store4<T>(dz2_ + (static_cast<size_t>(b) * 81 + px2) * 64 + ch, d.x, d.y, d.z, d.w);
+        }
+    }
+    __syncthreads();
 
-        // ---- conv2 data gradient: class (py, px), 100 pixels = 4 tiles, k-half kh (8 k-steps) --------------------
-        {
-            f32x16 acc[T2];
-            const T* base[T2];
+    // ---- conv2 data gradient: class (py, px), 20 pixels, k-half kh (8 k-steps) --------------------
+    {
+        f32x16 acc;
 #pragma unroll
-            for (int t = 0; t < T2; ++t) {
-                const int lpx = t * 32 + lp, pc = y_lo * 10 + (lpx < nc ? lpx : nc - 1);
-                // k-step 8 * kh + k: tap (p2, q2) = (kh, k / 4), channels 16 * (k % 4) + 8 * kg .. + 7 of dz2 at (y2 - p2, x2 - q2)
-                base[t] = sP2 + ((pc / 10 + 1 - kh) * 11 + pc % 10 + 1) * kTbPitch + kg * 8;
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        // k-step 8 * kh + k: tap (p2, q2) = (kh, k / 4), channels 16 * (k % 4) + 8 * kg .. + 7 of dz2 at (y2 - p2, x2 - q2)
+        const T* base = sP2 + ((px1 / 10 + 1 - kh) * 11 + px1 % 10 + 1) * kTbPitch + kg * 8;
+        auto fetch = [&](int k) { return *reinterpret_cast<const V8*>(base - (k >> 2) * kTbPitch + (k & 3) * 16); };
+        V8 ring[D];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-            }
-            {
-                constexpr int D = 6;
-                auto fetch = [&](int step) {
-                    const int t = step / 8, k = step % 8;
-                    return *reinterpret_cast<const V8*>(base[t] - (k >> 2) * kTbPitch + (k & 3) * 16);
-                };
-                V8 ring[D];
+        for (int u = 0; u < D; ++u) ring[u] = fetch(u);
 #pragma unroll
-                for (int u = 0; u < D; ++u) ring[u] = fetch(u);
+        for (int k = 0; k < 8; ++k) {
+            const V8 cur = ring[k % D];
+            if (k + D < 8) ring[k % D] = fetch(k + D);
+            mma_32x32x16(acc, wf2[k], cur);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        // exchange block reused as [wavefront][lane][2] float4; conv3's readers are behind the barrier above
+        if (kh) tower_send_half<1>(sXchg + wave * 128, acc, lane); else tower_send_half<0>(sXchg + wave * 128, acc, lane);
+        __syncthreads();
+        const float4* theirs = sXchg + (wave ^ 1) * 128;
 #pragma unroll
-                for (int step = 0; step < 8 * T2; ++step) {
-                    const V8 cur = ring[step % D];
-                    if (step + D < 8 * T2) ring[step % D] = fetch(step + D);
-                    mma_32x32x16(acc[step / 8], wf2[step % 8], cur);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            // exchange block reused as [wavefront][tile][lane][2] float4 (64 KB); conv3's readers are behind the barrier above
-            float4* mine = sXchg + static_cast<size_t>(wave) * (4 * 64 * 2);
-            const float4* theirs = sXchg + static_cast<size_t>(wave ^ 1) * (4 * 64 * 2);
-#pragma unroll
-            for (int t = 0; t < T2; ++t) {
-                if (kh) tower_send_half<1>(mine + t * 128, acc[t], lane); else tower_send_half<0>(mine + t * 128, acc[t], lane);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int t = 0; t < T2; ++t) {
-                const int lpx = t * 32 + lp, px = y_lo * 10 + lpx;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    float4 v;
-                    if (kh) v = tower_sum_half<1>(theirs + t * 128, acc[t], lane, h); else v = tower_sum_half<0>(theirs + t * 128, acc[t], lane, h);
-                    if (lpx < nc) {
-                        const int pix = (2 * (px / 10) + (cls >> 1)) * 20 + 2 * (px % 10) + (cls & 1);
-                        const uint32_t lo = m1[t][h].x, hi = m1[t][h].y;
-                        store4<T>(dz1_ + (static_cast<size_t>(b) * 400 + pix) * 32 + 8 * (2 * kh + h) + 4 * kg,
-                                  static_cast<int16_t>(lo & 0xFFFF) > 0 ? v.x : 0.f, static_cast<int16_t>(lo >> 16) > 0 ? v.y : 0.f,
-                                  static_cast<int16_t>(hi & 0xFFFF) > 0 ? v.z : 0.f, static_cast<int16_t>(hi >> 16) > 0 ? v.w : 0.f);
-                    }
-                }
+        for (int h = 0; h < 2; ++h) {
+            float4 v;
+            if (kh) v = tower_sum_half<1>(theirs, acc, lane, h); else v = tower_sum_half<0>(theirs, acc, lane, h);
+            if (lp < nc) {
+                const float4 d = masked(v, m1[h]);
+                store4<T>(dz1_ + (static_cast<size_t>(b) * 400 + pix) * 32 + 8 * (2 * kh + h) + 4 * kg, d.x, d.y, d.z, d.w);
             }
         }
-        // no barrier here: the next sample's first writes to the images and the exchange block sit behind its own barriers
     }
 }
 

@@ -34,6 +34,52 @@ static_assert((kManyXchgBytes + 32 * 256 * 2) % 64 == 0, "act1's chunks are exch
 __device__ inline int many_pixel(int y, int x) { return (y * 20 + (x & 1) * 10 + (x >> 1)) * 64; }
 __device__ inline int many_flip(int y, int x) { return ((x >> 3) ^ (y & 2)) & 3; }
 
+// The four k-quarters of a tile, held by two wavefronts: half kh has the partial sums pa, pb of quarters 2 kh, 2 kh + 1.  Half 0 keeps the
+// sum of both and sends rows 8 .. 15 of it; half 1 keeps both and sends rows 0 .. 7 of either; x: this lane's place in the tile's [6][64] float4.
+// (The markers keep the compiler from folding the wavefront-uniform branches into run-time register indexing.)
+__device__ inline void many_send(float4* x, int kh, const f32x16& pa, const f32x16& pb, float (&keep)[16])
+{
+    if (kh == 0) {
+        asm volatile("; send, k-half 0");
+        float s[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = pa[v] + pb[v];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) x[q * 64] = make_float4(s[8 + 4 * q], s[9 + 4 * q], s[10 + 4 * q], s[11 + 4 * q]);
+#pragma unroll
+        for (int v = 0; v < 8; ++v) { keep[v] = s[v]; keep[8 + v] = 0.f; }
+        asm volatile("; sent, k-half 0" ::: "memory");
+    } else {
+        asm volatile("; send, k-half 1");
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            x[(2 + q) * 64] = make_float4(pa[4 * q], pa[4 * q + 1], pa[4 * q + 2], pa[4 * q + 3]);
+            x[(4 + q) * 64] = make_float4(pb[4 * q], pb[4 * q + 1], pb[4 * q + 2], pb[4 * q + 3]);
+        }
+#pragma unroll
+        for (int v = 0; v < 8; ++v) { keep[v] = pa[8 + v]; keep[8 + v] = pb[8 + v]; }
+        asm volatile("; sent, k-half 1" ::: "memory");
+    }
+}
+// Rows 8 kh + 4 q .. + 3: ((p0 + p1) + p2) + p3
+__device__ inline float4 many_sum(const float4* x, int kh, int q, const float (&keep)[16])
+{
+    float4 r;
+    if (kh == 0) {
+        asm volatile("; sum, k-half 0");
+        const float4 c = x[(2 + q) * 64], d = x[(4 + q) * 64];
+        r = make_float4((keep[4 * q] + c.x) + d.x, (keep[4 * q + 1] + c.y) + d.y, (keep[4 * q + 2] + c.z) + d.z, (keep[4 * q + 3] + c.w) + d.w);
+        asm volatile("; summed, k-half 0" ::: "memory");
+    } else {
+        asm volatile("; sum, k-half 1");
+        const float4 s = x[q * 64];
+        r = make_float4((s.x + keep[4 * q]) + keep[8 + 4 * q], (s.y + keep[4 * q + 1]) + keep[9 + 4 * q], (s.z + keep[4 * q + 2]) + keep[10 + 4 * q],
+                        (s.w + keep[4 * q + 3]) + keep[11 + 4 * q]);
+        asm volatile("; summed, k-half 1" ::: "memory");
+    }
+    return r;
+}
+
 template <bool DESC>
 __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_many_kernel(int n_, int groups_, int share_, int tower_blocks_, const uint8_t* x0_, const uint8_t* x1_,
                                                                           const int32_t* desc_, const uint8_t* ring_, const _Float16* w1_0_, TowerArgs a)
@@ -205,48 +251,9 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_many_kernel(int n_
         __syncthreads();
 
         
-        // What half kh keeps of a tile's two quarters, and what it sends: half 0 the sum of both, rows 8 .. 15 to half 1; half 1 both, rows
-        // 0 .. 7 to half 0.  (The markers keep the compiler from folding the branches into run-time register indexing.)
-        auto send = [&](int t, const f32x16& pa, const f32x16& pb, float (&keep)[16]) {
-            float4* x = sXchg + (nt * 3 + t) * (6 * 64) + (fresh(tid) & 63);
-            if (kh == 0) {
-                asm volatile("; send, k-half 0");
-                float s[16];
-#pragma unroll
-                for (int v = 0; v < 16; ++v) s[v] = pa[v] + pb[v];
-#pragma unroll
-                for (int q = 0; q < 2; ++q) x[q * 64] = make_float4(s[8 + 4 * q], s[9 + 4 * q], s[10 + 4 * q], s[11 + 4 * q]);
-#pragma unroll
-                for (int v = 0; v < 8; ++v) { keep[v] = s[v]; keep[8 + v] = 0.f; }
-                asm volatile("; sent, k-half 0" ::: "memory");
-            } else {
-                asm volatile("; send, k-half 1");
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    x[(2 + q) * 64] = make_float4(pa[4 * q], pa[4 * q + 1], pa[4 * q + 2], pa[4 * q + 3]);
-                    x[(4 + q) * 64] = make_float4(pb[4 * q], pb[4 * q + 1], pb[4 * q + 2], pb[4 * q + 3]);
-                }
-#pragma unroll
-                for (int v = 0; v < 8; ++v) { keep[v] = pa[8 + v]; keep[8 + v] = pb[8 + v]; }
-                asm volatile("; sent, k-half 1" ::: "memory");
-            }
-        };
-        // Rows 8 kh + 4 q .. + 3: the four parts in k order, + bias, ReLU
+        // Rows 8 kh + 4 q .. + 3 of a tile, + bias, ReLU
         auto finish = [&](int ln, int t, int q, const float (&keep)[16], const float4& bias) {
-            const float4* x = sXchg + (nt * 3 + t) * (6 * 64) + ln;
-            float4 r;
-            if (kh == 0) {
-                asm volatile("; finish, k-half 0");
-                const float4 c = x[(2 + q) * 64], d = x[(4 + q) * 64];
-                r = make_float4((keep[4 * q] + c.x) + d.x, (keep[4 * q + 1] + c.y) + d.y, (keep[4 * q + 2] + c.z) + d.z, (keep[4 * q + 3] + c.w) + d.w);
-                asm volatile("; finished, k-half 0" ::: "memory");
-            } else {
-                asm volatile("; finish, k-half 1");
-                const float4 s = x[q * 64];
-                r = make_float4((s.x + keep[4 * q]) + keep[8 + 4 * q], (s.y + keep[4 * q + 1]) + keep[9 + 4 * q], (s.z + keep[4 * q + 2]) + keep[10 + 4 * q],
-                                (s.w + keep[4 * q + 3]) + keep[11 + 4 * q]);
-                asm volatile("; finished, k-half 1" ::: "memory");
-            }
+            const float4 r = many_sum(sXchg + (nt * 3 + t) * (6 * 64) + ln, kh, q, keep);
             return make_float4(fmaxf(r.x + bias.x, 0.f), fmaxf(r.y + bias.y, 0.f), fmaxf(r.z + bias.z, 0.f), fmaxf(r.w + bias.w, 0.f));
         };
 
@@ -297,7 +304,7 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_many_kernel(int n_
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
-            for (int t = 0; t < 3; ++t) send(t, acc[0][t], acc[1][t], keep[t]);
+            for (int t = 0; t < 3; ++t) many_send(sXchg + (nt * 3 + t) * (6 * 64) + (td & 63), kh, acc[0][t], acc[1][t], keep[t]);
             if (it + 1 < last) fetch_state(gn, bn);   // the next item's state: in flight while conv3 runs
             else {
 #pragma unroll
@@ -360,7 +367,7 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_many_kernel(int n_
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
-            for (int t = 0; t < 2; ++t) send(t, acc[0][t], acc[1][t], keep[t]);
+            for (int t = 0; t < 2; ++t) many_send(sXchg + (nt * 3 + t) * (6 * 64) + (td & 63), kh, acc[0][t], acc[1][t], keep[t]);
             __syncthreads();
 #pragma unroll
             for (int q = 0; q < 2; ++q) {

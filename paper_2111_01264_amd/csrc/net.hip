@@ -15,6 +15,7 @@
 #include "conv_tower.h"
 #include "conv_tower_bwd.h"
 #include "conv_tower_many.h"
+#include "conv_tower_bwd_many.h"
 #include "conv_tower_f32.h"
 #include "conv_tower_bwd_f32.h"
 #include "fc_as.h"
@@ -184,8 +185,9 @@ static hipError_t raise_lds_limits()
             {reinterpret_cast<const void*>(conv_tower_kernel<true, 1>), kTowerSmem},
             {reinterpret_cast<const void*>(conv_tower_many_kernel<false>), kTowerManySmem},
             {reinterpret_cast<const void*>(conv_tower_many_kernel<true>), kTowerManySmem},
-            {reinterpret_cast<const void*>(conv_tower_bwd_kernel<1>), kTowerBwdSmem},
-            {reinterpret_cast<const void*>(conv_tower_bwd_kernel<5>), kTowerBwdSmem},
+            {reinterpret_cast<const void*>(conv_tower_bwd_many_kernel<1>), kTowerBwdManySmem},
+            {reinterpret_cast<const void*>(conv_tower_bwd_many_kernel<2>), kTowerBwdManySmem},
+            {reinterpret_cast<const void*>(conv_tower_bwd_kernel), kTowerBwdSmem},
             {reinterpret_cast<const void*>(conv_tower_f32_kernel<false, 1>), kTowerF32Smem},
             {reinterpret_cast<const void*>(conv_tower_f32_kernel<true, 1>), kTowerF32Smem},
             {reinterpret_cast<const void*>(conv_tower_f32_kernel<false, 2>), kTowerF32Smem},
@@ -465,17 +467,20 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         ta.dz3 = dz3; ta.act2 = act2; ta.act1 = act1; ta.w3d = bsh + kBshW3; ta.w2d = bsh + kBshW2;
         ta.dz2 = dz2; ta.dz1 = dz1; ta.n = B;
         DQN_HIP(raise_lds_limits());
-        // small minibatches: five workgroups per sample (a fifth of its rows each) while that fits the chip
-        const bool fifths = 5 * B <= c->num_cus;
-        const int grid = fifths ? 5 * B : (B < c->num_cus ? B : c->num_cus);
-        ta.per = fifths ? 1 : (B + grid - 1) / grid;
+        // Small minibatches: five workgroups per sample while that fits the chip; then two of half the size, and one from where two per compute
+        // unit no longer hold all halves (kernel times: minibatch 32 5.7 us as fifths, 6.5 as halves; 56 6.6 as halves, 10.6 whole; 256 9.4 and 11.8).
+        const int cus = c->num_cus;
         const ProfPair pr = prof_pair(c, K_TOWER_BWD);
-        if (fifths)
-            launch_timed(conv_tower_bwd_kernel<5>, dim3(grid), dim3(kTowerThreads), kTowerBwdSmem, st, pr.begin, pr.end, ta.n, ta.per, ta.dz3, ta.w3d, ta.w2d,
-                         ta.act2, ta.act1, ta.dz2, ta.dz1);
-        else
-            launch_timed(conv_tower_bwd_kernel<1>, dim3(grid), dim3(kTowerThreads), kTowerBwdSmem, st, pr.begin, pr.end, ta.n, ta.per, ta.dz3, ta.w3d, ta.w2d,
-                         ta.act2, ta.act1, ta.dz2, ta.dz1);
+        if (kTbParts * B <= cus) {
+            launch_timed(conv_tower_bwd_kernel, dim3(kTbParts * B), dim3(kTowerThreads), kTowerBwdSmem, st, pr.begin, pr.end, ta.n, ta.dz3, ta.w3d, ta.w2d, ta.act2, ta.act1,
+                         ta.dz2, ta.dz1);
+        } else {
+            const bool halves = B <= cus;
+            const int items = halves ? 2 * B : B, grid = items < 2 * cus ? items : 2 * cus;
+            const int share = (items / grid) << 16 | items % grid;   // items per workgroup, and how many run one more
+            launch_timed(halves ? conv_tower_bwd_many_kernel<2> : conv_tower_bwd_many_kernel<1>, dim3(grid), dim3(kManyThreads), kTowerBwdManySmem, st, pr.begin, pr.end,
+                         ta.n, share, ta.dz3, ta.w3d, ta.w2d, ta.act2, ta.act1, ta.dz2, ta.dz1);
+        }
         DQN_LAUNCH_CHECK();
     } else {
         TowerBwdF32Args ta{};
