@@ -7,7 +7,7 @@
 //   * dz1 is collected in LDS (over the exchange block, in act1's order of conv_tower_many.h) and goes to memory 16 bytes per lane, masked there
 //     by act1, which is read the same way: a lane's own elements are 8 bytes at a stride of 128.
 // Bound by the matrix instructions (1.6 us per sample and compute unit), the vector unit's addresses and sums, and the start until the weights
-// have arrived (2 us).  Against eight wavefronts on one sample, kernel times: minibatch 512 18.9 -> 15.6 us; 256 11.4 - 12.0 -> 9.4 us and 128 10.8 -> 6.6 us as halves.
+// have arrived (2 us).  Against eight wavefronts on one sample, kernel times: minibatch 512 18.9 -> 14.0 us; 256 11.4 - 12.0 -> 9.4 us and 128 10.8 -> 6.6 us as halves.
 #pragma once
 #include "conv_tower_bwd.h"
 #include "conv_tower_many.h"
@@ -50,9 +50,9 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_bwd_many_kernel(in
     u32x4 xv[2];
     auto fetch_dz3 = [&](int b) {
         const int t = fresh(tid);
-        const u32x4* p = reinterpret_cast<const u32x4*>(dz3_ + static_cast<size_t>(b) * 3136);
-        xv[0] = p[t];
-        xv[1] = p[min(t + kManyThreads, kVecs3 - 1)];
+        const unsigned char* p = reinterpret_cast<const unsigned char*>(dz3_ + static_cast<size_t>(b) * 3136);
+        xv[0] = *reinterpret_cast<const u32x4*>(p + static_cast<uint32_t>(t) * 16);
+        xv[1] = *reinterpret_cast<const u32x4*>(p + static_cast<uint32_t>(min(t + kManyThreads, kVecs3 - 1)) * 16);
     };
     fetch_dz3(sample_of(first));
     __builtin_amdgcn_sched_barrier(0);
@@ -152,18 +152,18 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_bwd_many_kernel(in
         {
             const int td = fresh(tid), lp = td & 31, kg = (td >> 5) & 1;
             {   // dz2 to memory
-                u32x4* out = reinterpret_cast<u32x4*>(dz2_ + static_cast<size_t>(b) * 5184);
+                unsigned char* out = reinterpret_cast<unsigned char*>(dz2_ + static_cast<size_t>(b) * 5184);
 #pragma unroll
                 for (int i = 0; i < V2; ++i) {
                     const int v = r2_lo * 72 + min(td + i * kManyThreads, N2 * 8 - 1), p2x = v >> 3;
-                    out[v] = *reinterpret_cast<const u32x4*>(sP2 + ((p2x / 9 + 1) * 11 + p2x % 9 + 1) * kTbPitch + (v & 7) * 8);
+                    *reinterpret_cast<u32x4*>(out + static_cast<uint32_t>(v) * 16) = *reinterpret_cast<const u32x4*>(sP2 + ((p2x / 9 + 1) * 11 + p2x % 9 + 1) * kTbPitch + (v & 7) * 8);
                 }
             }
             if (PARTS == 1) fetch_dz3(it + 1 < last ? it + 1 : it);   // the next item's: in flight while conv2's stage runs
             u32x4 m1[V1];   // conv2's ReLU masks
-            const u32x4* in1 = reinterpret_cast<const u32x4*>(act1_ + static_cast<size_t>(b) * 12800);
+            const unsigned char* in1 = reinterpret_cast<const unsigned char*>(act1_ + static_cast<size_t>(b) * 12800);
 #pragma unroll
-            for (int i = 0; i < V1; ++i) m1[i] = in1[y_lo * 160 + min(td + i * kManyThreads, 16 * NC - 1)];
+            for (int i = 0; i < V1; ++i) m1[i] = *reinterpret_cast<const u32x4*>(in1 + static_cast<uint32_t>(y_lo * 160 + min(td + i * kManyThreads, 16 * NC - 1)) * 16);
             const T* p3 = w3_of();
 #pragma unroll
             for (int pass = 0; pass < PASSES; ++pass) {
@@ -213,14 +213,15 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_bwd_many_kernel(in
                                   acc[0][t][4 * q + 2] + acc[1][t][4 * q + 2], acc[0][t][4 * q + 3] + acc[1][t][4 * q + 3]);
             }
             __syncthreads();
-            u32x4* out = reinterpret_cast<u32x4*>(dz1_ + static_cast<size_t>(b) * 12800);
+            unsigned char* out = reinterpret_cast<unsigned char*>(dz1_ + static_cast<size_t>(b) * 12800);
+            const int te = fresh(tid);
 #pragma unroll
             for (int i = 0; i < V1; ++i) {
-                typedef int16_t i16x8 __attribute__((ext_vector_type(8)));
-                const int v = y_lo * 160 + min(td + i * kManyThreads, 16 * NC - 1), p1 = v >> 2, y = p1 / 20, x = p1 - 20 * y;
-                const i16x8 act = __builtin_bit_cast(i16x8, m1[i]);
-                const u32x4 positive = __builtin_bit_cast(u32x4, act > static_cast<i16x8>(0));   // all ones or zero per element
-                out[v] = *reinterpret_cast<const u32x4*>(sD1 + many_pixel(y, x) + (((v & 3) ^ many_flip(y, x)) << 4)) & positive;
+                const int v = y_lo * 160 + min(te + i * kManyThreads, 16 * NC - 1), p1 = v >> 2, y = p1 / 20, x = p1 - 20 * y;
+                // all ones where a bf16 activation is positive (0x0001 .. 0x7FFF): without its sign bit it carries into it, and the sign bit was clear
+                const u32x4 act = m1[i], bit = ((((act & 0x7FFF7FFFu) + 0x7FFF7FFFu) & ~act) >> 15) & 0x00010001u, positive = (bit << 16) - bit;
+                *reinterpret_cast<u32x4*>(out + static_cast<uint32_t>(v) * 16) =
+                    *reinterpret_cast<const u32x4*>(sD1 + many_pixel(y, x) + (((v & 3) ^ many_flip(y, x)) << 4)) & positive;
             }
         }
         // no barrier here: the next item's writes to the images, the exchange block and over it sit behind its own barriers

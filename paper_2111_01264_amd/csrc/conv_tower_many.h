@@ -261,11 +261,11 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_many_kernel(int n_
         {
             const int td = fresh(tid), lp = td & 31, kg = (td >> 5) & 1;
             if (T* g1 = a.act1[g]) {   // act1 to memory, whole lines
-                u32x4* out = reinterpret_cast<u32x4*>(g1 + static_cast<size_t>(b) * 12800);
+                unsigned char* out = reinterpret_cast<unsigned char*>(g1 + static_cast<size_t>(b) * 12800);
 #pragma unroll
                 for (int i = 0; i < 7; ++i) {
                     const int v = min(td + i * kManyThreads, 1599), px = v >> 2, y = px / 20, x = px - 20 * y;
-                    out[v] = *reinterpret_cast<const u32x4*>(sA1 + many_pixel(y, x) + (((v & 3) ^ many_flip(y, x)) << 4));
+                    *reinterpret_cast<u32x4*>(out + static_cast<uint32_t>(v) * 16) = *reinterpret_cast<const u32x4*>(sA1 + many_pixel(y, x) + (((v & 3) ^ many_flip(y, x)) << 4));
                 }
             }
             const T* p3 = a.w3[g] + ((nt * 36 + kh * 18) * 64 + (td & 63)) * 8;
@@ -329,11 +329,11 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_many_kernel(int n_
         {
             const int td = fresh(tid), lp = td & 31, kg = (td >> 5) & 1;
             if (T* g2 = a.act2[g]) {
-                u32x4* out = reinterpret_cast<u32x4*>(g2 + static_cast<size_t>(b) * 5184);
+                unsigned char* out = reinterpret_cast<unsigned char*>(g2 + static_cast<size_t>(b) * 5184);
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     const int v = min(td + i * kManyThreads, 647);
-                    out[v] = *reinterpret_cast<const u32x4*>(sA2 + (v >> 3) * kTowerP2 + (v & 7) * 8);
+                    *reinterpret_cast<u32x4*>(out + static_cast<uint32_t>(v) * 16) = *reinterpret_cast<const u32x4*>(sA2 + (v >> 3) * kTowerP2 + (v & 7) * 8);
                 }
             }
             float keep[2][16];
