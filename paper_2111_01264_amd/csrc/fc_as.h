@@ -17,6 +17,7 @@
 #pragma once
 #include <atomic>
 
+#include "head_kernels.h"
 #include "vec4.h"
 
 namespace dqn {
@@ -27,13 +28,17 @@ template <typename T> struct FcAsArgs {
     float* partial;              // kFcPartial: [group][slice][M][N] fp32
     T* dz;                       // kFcReluMask: [M][N]
     const T* mask;               // kFcReluMask: activation indexed like dz
-    int M, N, K, ldx, ldw;      // K is a multiple of 64
-    int kc;                      // k per slice, multiple of 64 (the last slice may be shorter)
-    int slices;
+    int M, N, ldx, ldw;
     uint32_t by_rows, by_cols;   // ceil(2^20 / row tiles), ceil(2^20 / feature blocks)
 };
 
 constexpr int kFcPartial = 0, kFcReluMask = 1;
+
+// fc1 forward: 3136 in seven slices of 448, whose columns of X fit in LDS; its data gradient: 512, one slice.  Compile-time constants: the slab's
+// index arithmetic (a division per vector, twice) and the stream's ends were more than half of the kernel's 690 vector instructions per wavefront, and
+// it was those that bounded it (act step of 128 states 16.7 -> 15.2 us; train step at minibatch 48 52.7 -> 49.2 us, 160 71.4 -> 67.2, 256 with Double DQN
+// 86.1 -> 82.7, 512 110.6 -> 104.3; fp32 at 256 195.1 -> 191.5).
+template <int EPI> constexpr int kFcK = EPI == kFcPartial ? 448 : 512;
 
 // This lane's 8 weights of k-step ks (16 k each) of the 32-feature tile nt; w is [N][K] in fragment order.
 template <typename T> __device__ inline typename Vec8<T>::type fc_weights(const T* w, int nt, int ks, int K, int lane)
@@ -54,7 +59,7 @@ __global__ __launch_bounds__(WAVES * 64) void fc_as_kernel(FcAsArgs<T> a)
     typedef typename Vec8<T>::type V8;
     extern __shared__ __attribute__((aligned(32))) unsigned char as_smem[];
     T* sX = reinterpret_cast<T*>(as_smem);
-    const int ldk = a.kc + 8;
+    constexpr int KC = kFcK<EPI>, STEPS = KC / 16, LDK = KC + 8;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Workgroups are dealt out to the eight XCDs in turn, and each has an L2 of its own: an XCD takes a contiguous eighth of the
     // workgroups in the order (problem and slice, feature block, row tile), so that the row tiles that read the same weights share an L2.
@@ -68,10 +73,9 @@ __global__ __launch_bounds__(WAVES * 64) void fc_as_kernel(FcAsArgs<T> a)
         bz = static_cast<int>(col * a.by_cols >> 20);
         bx = static_cast<int>(col - bz * gridDim.x);
     }
-    const int g = bz / a.slices, slice = bz % a.slices;
+    const int g = EPI == kFcPartial ? bz / kFc1Slices : bz, slice = EPI == kFcPartial ? bz % kFc1Slices : 0;
     const int m0 = by * (TB * 32);
-    const int k0 = slice * a.kc;
-    const int klen = min(a.kc, a.K - k0);
+    const int k0 = slice * KC;
     const int lane_r = lane & 31, kg = lane >> 5;
     const int n = (bx * WAVES + wave) * 32 + lane_r;
     const bool n_ok = n < a.N;
@@ -81,10 +85,9 @@ __global__ __launch_bounds__(WAVES * 64) void fc_as_kernel(FcAsArgs<T> a)
     // is staged so that both latencies overlap.  Loads are never skipped (the k-step is clamped): the count of
     // loads in flight stays known to the compiler, which then waits for one slot only.
     constexpr int D = sizeof(T) == 2 ? 16 : 8;   // 16 KB per wavefront in flight: a step waits for the fragment requested D steps earlier, so the stream runs at D fragments per memory round trip
-    const int steps = klen >> 4;
-    auto wload = [&](int st) {
-        return fc_weights<T>(a.w[g], ntile, ks0 + (st < steps ? st : steps - 1), a.ldw, lane);
-    };
+    static_assert(STEPS >= D, "the ring fills");
+    const T* wg = a.w[g];
+    auto wload = [&](int st) { return fc_weights<T>(wg, ntile, ks0 + st, a.ldw, lane); };
     V8 ring[D];
 #pragma unroll
     for (int u = 0; u < D; ++u) ring[u] = wload(u);
@@ -105,21 +108,24 @@ __global__ __launch_bounds__(WAVES * 64) void fc_as_kernel(FcAsArgs<T> a)
         // the slab of X: eight 16-byte vectors in flight per thread (clamped address, masked value), then their LDS stores --
         // one vector per trip of a plain loop would be a chain of dependent memory round trips
         const T* xg = a.x[g];
-        const int vec_per_row = klen / 8, total = TB * 32 * vec_per_row;
-        for (int v0 = tid; v0 < total; v0 += 8 * WAVES * 64) {
+        constexpr int VPR = KC / 8, VECS = TB * 32 * VPR, THREADS = WAVES * 64, N = (VECS + THREADS - 1) / THREADS;
+        static_assert(VECS % THREADS == 0, "no ragged vectors");
+#pragma unroll
+        for (int i0 = 0; i0 < N; i0 += 8) {
             V8 val[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int v = v0 + u * WAVES * 64 < total ? v0 + u * WAVES * 64 : total - 1;
-                const int r = v / vec_per_row, kc8 = v % vec_per_row;
-                const int row = m0 + r < a.M ? m0 + r : a.M - 1;
-                val[u] = vec8_keep<T>(*reinterpret_cast<const V8*>(xg + static_cast<size_t>(row) * a.ldx + k0 + kc8 * 8), m0 + r < a.M);
-            }
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u < N) {
+                    const int v = tid + (i0 + u) * THREADS, r = v / VPR, kc8 = v % VPR;
+                    const int row = m0 + r < a.M ? m0 + r : a.M - 1;
+                    val[u] = vec8_keep<T>(*reinterpret_cast<const V8*>(xg + static_cast<size_t>(row) * a.ldx + k0 + kc8 * 8), m0 + r < a.M);
+                }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int v = v0 + u * WAVES * 64;
-                if (v < total) *reinterpret_cast<V8*>(&sX[(v / vec_per_row) * ldk + (v % vec_per_row) * 8]) = val[u];
-            }
+            for (int u = 0; u < 8; ++u)
+                if (i0 + u < N) {
+                    const int v = tid + (i0 + u) * THREADS;
+                    *reinterpret_cast<V8*>(&sX[(v / VPR) * LDK + (v % VPR) * 8]) = val[u];
+                }
         }
     }
     __syncthreads();
@@ -130,30 +136,17 @@ __global__ __launch_bounds__(WAVES * 64) void fc_as_kernel(FcAsArgs<T> a)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
 
-    // steps is a multiple of 4 (k per slice is a multiple of 64): whole chunks of D steps, then the rest
     const T* xrow[TB];
 #pragma unroll
-    for (int t = 0; t < TB; ++t) xrow[t] = &sX[(t * 32 + lane_r) * ldk + kg * 8];
-    int base = 0;
-    for (; base + D <= steps; base += D) {
+    for (int t = 0; t < TB; ++t) xrow[t] = &sX[(t * 32 + lane_r) * LDK + kg * 8];
 #pragma unroll
-        for (int u = 0; u < D; ++u) {
-            const V8 w = ring[u];
-            ring[u] = wload(base + u + D);
+    for (int st = 0; st < STEPS; ++st) {
+        const V8 w = ring[st % D];
+        if (st + D < STEPS) ring[st % D] = wload(st + D);
 #pragma unroll
-            for (int t = 0; t < TB; ++t) mma_32x32x16(acc[t], w, *reinterpret_cast<const V8*>(xrow[t] + (base + u) * 16));
-            __builtin_amdgcn_sched_barrier(0);
-        }
+        for (int t = 0; t < TB; ++t) mma_32x32x16(acc[t], w, *reinterpret_cast<const V8*>(xrow[t] + st * 16));
+        __builtin_amdgcn_sched_barrier(0);
     }
-    // what is left (fewer than D steps, a multiple of four) sits in the ring already
-#pragma unroll
-    for (int u = 0; u < D; u += 4)
-        if (base + u < steps) {
-#pragma unroll
-            for (int w = 0; w < 4; ++w)
-#pragma unroll
-                for (int t = 0; t < TB; ++t) mma_32x32x16(acc[t], ring[u + w], *reinterpret_cast<const V8*>(xrow[t] + (base + u + w) * 16));
-        }
 
     // lane: sample b = m0 + t*32 + lane_r; values: features 8*q + 4*kg + e of this wavefront's 32
     const int n_base = (bx * WAVES + wave) * 32;
@@ -166,7 +159,7 @@ __global__ __launch_bounds__(WAVES * 64) void fc_as_kernel(FcAsArgs<T> a)
             const int nn = n_base + 8 * q + 4 * kg;
             if (nn >= a.N) continue;   // N is a multiple of 4
             if constexpr (EPI == kFcPartial) {
-                float* dst = a.partial + ((static_cast<size_t>(g) * a.slices + slice) * a.M + b) * a.N + nn;
+                float* dst = a.partial + ((static_cast<size_t>(g) * kFc1Slices + slice) * a.M + b) * a.N + nn;
                 *reinterpret_cast<float4*>(dst) = make_float4(acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]);
             } else {
                 const size_t idx = static_cast<size_t>(b) * a.N + nn;
@@ -253,24 +246,16 @@ __global__ __launch_bounds__(256) void fc_sk_kernel(const T* x0_, const T* x1_, 
 }
 
 template <typename T, int EPI>
-inline hipError_t launch_fc_as(hipStream_t st, FcAsArgs<T> a, int K, int groups, int want_slices, int* slices_used,
-                               hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr)
+inline hipError_t launch_fc_as(hipStream_t st, FcAsArgs<T> a, int groups, hipEvent_t ev_begin = nullptr, hipEvent_t ev_end = nullptr)
 {
-    constexpr int WAVES = 4;
-    int slices = want_slices < 1 ? 1 : want_slices;
-    int kc = ((K + slices - 1) / slices + 63) / 64 * 64;
-    slices = (K + kc - 1) / kc;
-    if (slices_used) *slices_used = slices;
-    a.K = K;
-    a.kc = kc;
-    a.slices = slices;
+    constexpr int WAVES = 4, slices = EPI == kFcPartial ? kFc1Slices : 1;
     const int n_blocks = (a.N + WAVES * 32 - 1) / (WAVES * 32);
     hipError_t e = hipSuccess;
     {
-        // One 32-row tile of X per workgroup: with two, the grid of a batch-256 step was 100-224 workgroups on 256 CUs,
-        // one per CU, and nothing overlapped a workgroup's staging, streaming and storing phases.
+        // One 32-row tile of X per workgroup: with two, half as many workgroups read half as many weights and less of one's staging, streaming and
+        // storing overlaps another's (train step at minibatch 160: 67 -> 70 us, 256 with Double DQN 82.6 -> 85.3, 512 104.3 -> 106.2).
         constexpr int TB = 1;
-        const size_t smem = static_cast<size_t>(TB) * 32 * (kc + 8) * sizeof(T);
+        const size_t smem = static_cast<size_t>(TB) * 32 * (kFcK<EPI> + 8) * sizeof(T);
         // Few workgroups keep the plain order: at 112 and 100 of them (128 states, minibatch 45) the other made no difference, and
         // finding it cost 0.1 us.  From 140 on it gains (plain order -> this one, whole call): 160 states (140 workgroups) 19.9 -> 19.2 us, fp32
         // 41.1 -> 39.7, 192 states (168) 20.2 -> 19.6, 256 (224) 21.1 -> 20.5; train step at minibatch 96 (168, forward only) 69.8 -> 69.2,

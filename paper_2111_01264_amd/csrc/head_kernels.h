@@ -108,7 +108,7 @@ template <typename T> __device__ inline void shadow_store(T* sh, const Offsets& 
 // ---- network head, forward: finish fc1, fc2 on the matrix cores, then action selection (act step)
 // or TD target / error / loss (train step, Eq. 1) -------------------------------------------------
 //
-// fc1 arrives as k-slices of fp32 partial sums [groups][slices][rows][512].  A workgroup owns
+// fc1 arrives as kFc1Slices k-slices of fp32 partial sums [groups][slice][rows][512].  A workgroup owns
 // kHeadRows samples (few rows per workgroup: the slice sums are plain loads, and what bounds them is
 // how many compute units pull at once).  (1) Thread t finishes four features of one row for every
 // group -- slices added in slice order, bias, ReLU, rounded to the operand type so that forward and
@@ -117,10 +117,11 @@ template <typename T> __device__ inline void shadow_store(T* sh, const Offsets& 
 // the fc2 product as 16x16 MFMAs (A = W2 rows, B = the h tile); the partial accumulators meet in LDS
 // and are added in wavefront order.  (3) One wavefront runs the tail, 32 lanes per sample.
 constexpr int kHeadRows = 2;
+constexpr int kFc1Slices = 7;
 
 struct HeadArgs {
-    const float* partial;        // [groups][slices][rows][512]
-    int slices, rows, A;
+    const float* partial;        // [groups][kFc1Slices][rows][512]
+    int rows, A;
     int head_blocks;             // workgroups of the head proper (the first ones of the grid)
     const float* b1[3];
     const void* w2[3];           // T [A][512]
@@ -167,11 +168,11 @@ template <> struct HeadMma<float> {
     }
 };
 
-// G: problems (act step: 1, else train step: 2, with Double DQN 3); NTA: 16-action tiles (1 for A <= 16, else 2).  The leading scalar parameters repeat HeadArgs::partial, slices, rows, A,
+// G: problems (act step: 1, else train step: 2, with Double DQN 3); NTA: 16-action tiles (1 for A <= 16, else 2).  The leading scalar parameters repeat HeadArgs::partial, rows, A,
 // head_blocks, w2[0], b1[0], b2[0] and epsilon: the kernel arguments' first 14 dwords are preloaded into scalar registers when a
 // wavefront starts (see conv_tower_kernel); everything else is read from the struct.
 template <typename T, int G, int NTA>
-__global__ __launch_bounds__(256, sizeof(T) == 4 && G == 3 && NTA == 2 ? 1 : 2) void head_fwd_kernel(const float* partial_, int slices_, int rows_, int A_, int head_blocks_,
+__global__ __launch_bounds__(256, sizeof(T) == 4 && G == 3 && NTA == 2 ? 1 : 2) void head_fwd_kernel(const float* partial_, int rows_, int A_, int head_blocks_,
                                                        const void* w2_0_, const float* b1_0_, const float* b2_0_, float epsilon_, HeadArgs a)
 {
     typedef HeadMma<T> M;
@@ -202,16 +203,15 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && G == 3 && NTA == 2 ? 1 : 2) 
     // Every global operand is requested here, before anything waits (a cold round trip to memory costs over a microsecond), in the
     // order in which they are needed, and first those whose addresses came with the wavefront: fc1's slices of ALL groups, fc2's
     // weights, the biases; then what the struct's pointers lead to (a load of them stands in front of every later request).
-    const size_t sstride = static_cast<size_t>(rows_) * 512, gstride = sstride * slices_;
+    const size_t sstride = static_cast<size_t>(rows_) * 512, gstride = sstride * kFc1Slices;
     const float* p0 = partial_ + static_cast<size_t>(hrow) * 512 + hf0;
-    float4 v[G][7];
-    auto fetch_slices = [&](int s0) {   // seven at a time from a clamped row and slice: no load is ever skipped
+    float4 v[G][kFc1Slices];
+    {   // from a clamped row: no load is ever skipped
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int u = 0; u < 7; ++u) v[g][u] = *reinterpret_cast<const float4*>(p0 + g * gstride + static_cast<size_t>(min(s0 + u, slices_ - 1)) * sstride);
-    };
-    fetch_slices(0);
+            for (int u = 0; u < kFc1Slices; ++u) v[g][u] = *reinterpret_cast<const float4*>(p0 + g * gstride + u * sstride);
+    }
     float4 b1v[G];
     b1v[0] = *reinterpret_cast<const float4*>(b1_0_ + hf0);
     V wf[G][NTA][STEPS];
@@ -266,14 +266,10 @@ __global__ __launch_bounds__(256, sizeof(T) == 4 && G == 3 && NTA == 2 ? 1 : 2) 
         float4 acc[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) acc[g] = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int s0 = 0; s0 < slices_; s0 += 7) {
-            if (s0 != 0) fetch_slices(s0);
 #pragma unroll
-            for (int g = 0; g < G; ++g)
+        for (int g = 0; g < G; ++g)
 #pragma unroll
-                for (int u = 0; u < 7; ++u)
-                    if (s0 + u < slices_) { acc[g].x += v[g][u].x; acc[g].y += v[g][u].y; acc[g].z += v[g][u].z; acc[g].w += v[g][u].w; }
-        }
+            for (int u = 0; u < kFc1Slices; ++u) { acc[g].x += v[g][u].x; acc[g].y += v[g][u].y; acc[g].z += v[g][u].z; acc[g].w += v[g][u].w; }
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const float4 bv = b1v[g];

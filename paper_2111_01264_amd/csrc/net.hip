@@ -136,7 +136,6 @@ struct dqn_ctx {
 
 namespace dqn {
 
-constexpr int kMaxFc1Slices = 49;
 // Reduced precision: slices per conv layer at most (conv2 / conv3 run 2 / 3 workgroups per slice, one per column block).
 // 44 and not the 64 the buffers allow: with 128 + 2 * 64 + 3 * 64 conv workgroups next to fc1's 200 tiles the grid was far
 // beyond the 512 workgroups that are resident at once and fc1's tiles started when the first conv workgroups left;
@@ -160,7 +159,7 @@ static int alloc_ws(Workspace& ws, int cap, int groups, int A, size_t esize)
     DQN_HIP(hipMalloc(&ws.act3, n * 3136 * esize));
     DQN_HIP(hipMalloc(&ws.h, static_cast<size_t>(cap) * 512 * esize));
     DQN_HIP(hipMalloc((void**)&ws.q, n * A * sizeof(float)));
-    DQN_HIP(hipMalloc((void**)&ws.partial, n * kMaxFc1Slices * 512 * sizeof(float)));
+    DQN_HIP(hipMalloc((void**)&ws.partial, n * kFc1Slices * 512 * sizeof(float)));
     return DQN_OK;
 }
 
@@ -217,18 +216,6 @@ static ProfPair prof_pair(dqn_ctx* c, int id)
     return p;
 }
 
-// Number of fc1 k-slices for n rows per group: enough workgroups to fill the chip, few enough that
-// the consumer's slice sum stays small.
-static int fc1_slices(int n, int groups)
-{
-    const int row_tiles = (n + 31) / 32;
-    const int blocks = 4 * row_tiles * groups;
-    int s = 64 / blocks;         // few slices: the head kernel re-reads every slice
-    if (s < 7) s = 7;            // 3136 / 7 = 448 columns of X per workgroup fit in LDS
-    if (s > kMaxFc1Slices) s = kMaxFc1Slices;
-    return s;
-}
-
 // A minibatch given by descriptors (sample_desc) instead of assembled states: the fused conv kernel reads the frames
 // from the replay memory's frame array itself.
 struct StateSource {
@@ -243,10 +230,10 @@ __global__ __launch_bounds__(256) void sample_desc_kernel(GatherPlan plan, int32
 }
 
 // Forward pass of `groups` independent (input, parameter set) pairs with n samples each, up to the
-// fc1 k-slices; the number of slices comes back through *slices_out.
+// fc1 k-slices.
 template <typename T>
 static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups, const uint8_t* const* x,
-                          const void* const* shadow, const float* const* master, int n, bool timed, int* slices_out,
+                          const void* const* shadow, const float* const* master, int n, bool timed,
                           const PushStepPlan* push = nullptr, const StateSource* src = nullptr)
 {
     const Offsets& o = c->off;
@@ -331,10 +318,9 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         a.partial = ws.partial;
         a.M = n; a.N = 512; a.ldx = 3136; a.ldw = 3136;
         const ProfPair pr = pp(K_FC1_FWD);
-        launch_timed(fc_sk_kernel<T, kFcPartial, 7, 7>, dim3(16, groups, 7), dim3(256), 0, st, pr.begin, pr.end, a.x[0], a.x[1], a.w[0], a.w[1], a.M, a.N,
+        launch_timed(fc_sk_kernel<T, kFcPartial, 7, kFc1Slices>, dim3(16, groups, kFc1Slices), dim3(256), 0, st, pr.begin, pr.end, a.x[0], a.x[1], a.w[0], a.w[1], a.M, a.N,
                      a.ldx, a.ldw, a.partial, a);
         DQN_LAUNCH_CHECK();
-        *slices_out = 7;
     } else {
         FcAsArgs<T> a{};
         for (int g = 0; g < groups; ++g) {
@@ -344,9 +330,7 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         a.partial = ws.partial;
         a.M = n; a.N = 512; a.ldx = 3136; a.ldw = 3136;
         const ProfPair pr = pp(K_FC1_FWD);
-        int used = 0;
-        DQN_HIP((launch_fc_as<T, kFcPartial>(st, a, 3136, groups, fc1_slices(n, groups), &used, pr.begin, pr.end)));
-        *slices_out = used;
+        DQN_HIP((launch_fc_as<T, kFcPartial>(st, a, groups, pr.begin, pr.end)));
     }
     return DQN_OK;
 }
@@ -377,17 +361,16 @@ static int act_impl(dqn_ctx* c, Workspace& ws, const uint8_t* states, int W, flo
     const uint8_t* x[1] = {states};
     const void* shadow[1] = {use_target ? c->sh_t : c->sh};
     const float* master[1] = {use_target ? c->theta_t : c->theta};
-    int slices = 0;
-    const int rc = forward_to_fc1<T>(c, c->act_stream, ws, 1, x, shadow, master, W, false, &slices, push);
+    const int rc = forward_to_fc1<T>(c, c->act_stream, ws, 1, x, shadow, master, W, false, push);
     if (rc != DQN_OK) return rc;
     HeadArgs ha{};
-    ha.partial = ws.partial; ha.slices = slices; ha.rows = W; ha.A = c->A;
+    ha.partial = ws.partial; ha.rows = W; ha.A = c->A;
     ha.b1[0] = master[0] + c->off.bf1; ha.w2[0] = static_cast<const T*>(shadow[0]) + c->off.wf2; ha.b2[0] = master[0] + c->off.bf2;
     ha.epsilon = epsilon; ha.seed = c->cfg.seed; ha.act_step = act_step; ha.actions = actions; ha.q_out = q_out;
     ha.head_blocks = (W + kHeadRows - 1) / kHeadRows;
     ha.gather.B = 0;
     auto kern = c->A <= 16 ? head_fwd_kernel<T, 1, 1> : head_fwd_kernel<T, 1, 2>;
-    hipLaunchKernelGGL(kern, dim3(ha.head_blocks), dim3(256), 0, c->act_stream, ha.partial, ha.slices, ha.rows, ha.A, ha.head_blocks,
+    hipLaunchKernelGGL(kern, dim3(ha.head_blocks), dim3(256), 0, c->act_stream, ha.partial, ha.rows, ha.A, ha.head_blocks,
                        ha.w2[0], ha.b1[0], ha.b2[0], ha.epsilon, ha);
     DQN_LAUNCH_CHECK();
     return DQN_OK;
@@ -409,8 +392,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         const ProfPair pr = prof_pair(c, K_EVENT_PAIR);
         if (pr.begin) { (void)hipEventRecord(pr.begin, st); (void)hipEventRecord(pr.end, st); }
     }
-    int slices = 0;
-    int rc = forward_to_fc1<T>(c, st, ws, groups, x, shadow, master, B, true, &slices, nullptr, src);
+    int rc = forward_to_fc1<T>(c, st, ws, groups, x, shadow, master, B, true, nullptr, src);
     if (rc != DQN_OK) return rc;
 
     const T* sh = static_cast<const T*>(c->sh);
@@ -425,7 +407,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
     {
         const ProfPair pr = prof_pair(c, K_FC2_TD);
         HeadArgs ha{};
-        ha.partial = ws.partial; ha.slices = slices; ha.rows = B; ha.A = c->A;
+        ha.partial = ws.partial; ha.rows = B; ha.A = c->A;
         for (int g = 0; g < groups; ++g) {
             ha.b1[g] = master[g] + o.bf1; ha.w2[g] = static_cast<const T*>(shadow[g]) + o.wf2; ha.b2[g] = master[g] + o.bf2;
         }
@@ -439,7 +421,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         if (ride) ha.gather = *ride;
         const int riders = !ride ? 0 : (ride_desc ? (ride->B + 255) / 256 : 5 * ride->B);
         auto kern = groups == 2 ? (c->A <= 16 ? head_fwd_kernel<T, 2, 1> : head_fwd_kernel<T, 2, 2>) : (c->A <= 16 ? head_fwd_kernel<T, 3, 1> : head_fwd_kernel<T, 3, 2>);
-        launch_timed(kern, dim3(ha.head_blocks + riders), dim3(256), 0, st, pr.begin, pr.end, ha.partial, ha.slices, ha.rows, ha.A,
+        launch_timed(kern, dim3(ha.head_blocks + riders), dim3(256), 0, st, pr.begin, pr.end, ha.partial, ha.rows, ha.A,
                      ha.head_blocks, ha.w2[0], ha.b1[0], ha.b2[0], ha.epsilon, ha);
         DQN_LAUNCH_CHECK();
     }
@@ -458,8 +440,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         fa.dz = dz3; fa.mask = act3;
         fa.M = B; fa.N = 3136; fa.ldx = 512; fa.ldw = 512;
         const ProfPair pr = prof_pair(c, K_FC1_DGRAD);
-        int used = 0;
-        DQN_HIP((launch_fc_as<T, kFcReluMask>(st, fa, 512, 1, 1, &used, pr.begin, pr.end)));
+        DQN_HIP((launch_fc_as<T, kFcReluMask>(st, fa, 1, pr.begin, pr.end)));
     }
     if constexpr (std::is_same<T, bf16_t>::value) {
         // conv3 and conv2 data gradients in one persistent launch, dz2 handed over in LDS
