@@ -29,7 +29,7 @@ struct WgFc1Args {
 };
 
 constexpr int kWgF1BM = 64, kWgF1BN = 128, kWgF1KC = 128;
-constexpr int kWgF1LDA = kWgF1BM + 16, kWgF1LDB = kWgF1BN + 16;
+constexpr int kWgF1LDA = kWgF1BM + 32, kWgF1LDB = kWgF1BN + 32;   // (192 and 320 bytes: see WgGeo::LDA)
 constexpr size_t kWgF1Smem = static_cast<size_t>(kWgF1KC) * (kWgF1LDA + kWgF1LDB) * 2;
 constexpr int kWgF1Cols = (3136 + kWgF1BN - 1) / kWgF1BN, kWgF1Rows = 512 / kWgF1BM;   // 25 x 8 workgroups
 
