@@ -116,12 +116,12 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
     constexpr int T3 = PARTS == 1 ? 6 : PARTS == 2 ? 3 : 2, OWN = (2 * T3 + 3) / 4;      // tiles of the conv3 stage; sums a wavefront finishes
 
     // dz3 of a sample: 784 16-byte vectors, one or two per thread (the second clamped, not predicated)
-    const int v1 = min(tid + 512, 783);
     auto slot = [&](int v) { const int px = v >> 4; return sP3 + tf_a2((px / 7 + 2) * 11 + px % 7 + 2, (v & 15) >> 1) + 8 * (v & 1); };
     tf_f32x4 xv0, xv1;
     auto fetch = [&](int b) {
+        const int t = here(tid);
         const tf_f32x4* p = reinterpret_cast<const tf_f32x4*>(dz3_ + static_cast<size_t>(b) * 3136);
-        xv0 = p[tid]; xv1 = p[v1];
+        xv0 = p[t]; xv1 = p[min(t + 512, 783)];
     };
     fetch(first);
     __builtin_amdgcn_sched_barrier(0);
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
 
     for (int b = first; b < last; ++b) {
         if (PARTS == 1 && b != first) {   // dz3's border again, where partial sums have been: 22 + 22 pixels above and below, 28 beside
-            for (int v = tid; v < 3 * 72 * 8; v += kTowerThreads) {
+            for (int v = here(tid); v < 3 * 72 * 8; v += kTowerThreads) {
                 const int pl = v / 576, i = v % 576 >> 3, j = i - 44;
                 const int px = i < 22 ? i : i < 44 ? 77 + i : (2 + (j >> 2)) * 11 + ((j & 3) < 2 ? j & 3 : 7 + (j & 3));
                 *reinterpret_cast<uint4*>(sP3 + pl * kTbfPlane + px * 128 + (v & 7) * 16) = make_uint4(0, 0, 0, 0);
@@ -162,11 +162,12 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
         xv0 = tf_flip(xv0, flip);
         xv1 = tf_flip(xv1, flip);
         tf_store4<kTbfPlane>(slot(here(tid)), xv0[0], xv0[1], xv0[2], xv0[3]);
-        tf_store4<kTbfPlane>(slot(here(v1)), xv1[0], xv1[1], xv1[2], xv1[3]);
+        tf_store4<kTbfPlane>(slot(min(here(tid) + 512, 783)), xv1[0], xv1[1], xv1[2], xv1[3]);
         __syncthreads();
 
         // ---- conv3 data gradient ------------------------------------------------------------------------------------
         {
+            const int lk = here(lane) >> 4;
             int base[T3];
             tf_f32x4 acc[T3][2];
 #pragma unroll
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
             }
             __syncthreads();   // dz3 has been read
             tf_f32x4 all_of = {0.f, 0.f, 0.f, 0.f};   // the sum of what this lane finishes is a finite number only if all of it is
-            tower_f32_exchange<T3>(acc, sEx, cp, kq, lane, [&](int i, int t, int c, const tf_f32x4& sum) {
+            tower_f32_exchange<T3>(acc, sEx, cp, kq, here(lane), [&](int i, int t, int c, const tf_f32x4& sum) {
                 const int lpx = t * 16 + here(lq), px = r2_lo * 9 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 if (lpx < n2) {
                     tf_f32x4 v;
@@ -208,6 +209,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
         // ---- conv2 data gradient: class cls, NC pixels -----------------------------------------------------------------
         {
             constexpr int NT = TA;
+            const int lk = here(lane) >> 4;
             int base[NT];
             tf_f32x4 acc[NT][2], mask[NT][2];
             auto place = [&](int t) {   // this lane's pixel of tile t in dz1
@@ -228,7 +230,10 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_bwd_f32_kernel(int n
             auto next = [&](auto s_) {   // the last three k-steps' weights, then (in their predecessors' registers) the masks
                 constexpr int s = decltype(s_)::value;
                 if constexpr (s < 3) request2(std::integral_constant<int, s + 5>{});
-                if constexpr (s == 5 && PARTS == 1) { if (b + 1 < last) fetch(b + 1); }
+                if constexpr (s == 5 && PARTS == 1) {
+                    if (b + 1 < last) fetch(b + 1);
+                    else asm volatile("" : "=v"(xv0), "=v"(xv1));   // (or the old ones keep their registers until here)
+                }
                 if constexpr (s == 4)
 #pragma unroll
                     for (int t = 0; t < NT; ++t)

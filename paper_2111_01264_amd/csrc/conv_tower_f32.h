@@ -88,7 +88,9 @@ template <int PLANE> __device__ inline void tf_store4(uint8_t* dst, float v0, fl
 }
 
 // The value, computed no earlier than here: addresses that depend on a lane's pixel are the same for every item, and the compiler
-// otherwise computes those of all stages in front of the item loop and keeps them in registers throughout.
+// otherwise computes those of all stages in front of the item loop and keeps them in registers throughout.  (Whole samples, forward and
+// backward, spilled 40 to 84 bytes per lane of them, and a register read back behind outstanding loads waits for those: train step at
+// minibatch 256 187 -> 175 us without, 140 153 -> 145 us.)
 __device__ inline int here(int v)
 {
     asm volatile("" : "+v"(v));
@@ -319,11 +321,10 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
     constexpr int T1 = PARTS == 1 ? 13 : PARTS == 2 ? 9 : PARTS == 3 ? 8 : 5;                                            // 32-pixel tiles of conv1
 
     constexpr int kXVecs = kTowerXBytes / 16;   // 1764
-    const int last_vec = tid + 1536 < kXVecs ? tid + 1536 : kXVecs - 1;
+    auto last_of = [](int t) { return t + 1536 < kXVecs ? t + 1536 : kXVecs - 1; };
     uint4 xv0, xv1, xv2, xv3;                   // the state of the item to come, 16 bytes per lane and load (the last one clamped)
     // DESC: vector v of the state belongs to frame v / 441, so each of a thread's loads chooses between two neighbouring frames; a zero
     // frame (slot -1) is loaded from slot 0 and masked when it is stored.  The slots of an item are requested an item ahead.
-    const bool hi0 = tid >= 441, hi1 = tid + 512 >= 882, hi2 = tid + 1024 >= 1323;
     int dn[4] = {0, 0, 0, 0};
     uint32_t keep = 15u;
     auto fetch_desc = [&](int g_, int b_) {
@@ -332,9 +333,11 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
         for (int f = 0; f < 4; ++f) dn[f] = dp[f];
     };
     auto fetch_state = [&](int g_, int b_) {
+        const int t = here(tid), last_vec = last_of(t);   // (kept over the loop, these addresses would be spilled)
         if constexpr (DESC) {
+            const bool hi0 = t >= 441, hi1 = t + 512 >= 882, hi2 = t + 1024 >= 1323;
             const int s[4] = {hi0 ? dn[1] : dn[0], hi1 ? dn[2] : dn[1], hi2 ? dn[3] : dn[2], dn[3]};
-            const int w[4] = {tid - (hi0 ? 441 : 0), tid + 512 - (hi1 ? 882 : 441), tid + 1024 - (hi2 ? 1323 : 882), last_vec - 1323};
+            const int w[4] = {t - (hi0 ? 441 : 0), t + 512 - (hi1 ? 882 : 441), t + 1024 - (hi2 ? 1323 : 882), last_vec - 1323};
             const uint4* r = reinterpret_cast<const uint4*>(a.ring);
             auto vec = [&](int i) { return r[static_cast<size_t>(s[i] < 0 ? 0 : s[i]) * kFrameVec16 + w[i]]; };
             xv0 = vec(0); xv1 = vec(1); xv2 = vec(2); xv3 = vec(3);
@@ -342,7 +345,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
         } else {
             const uint8_t* xg = g_ == 0 ? x0_ : g_ == 1 ? x1_ : a.x[g_];
             const uint4* xs = reinterpret_cast<const uint4*>(xg + static_cast<size_t>(b_) * kTowerXBytes);
-            xv0 = xs[tid]; xv1 = xs[tid + 512]; xv2 = xs[tid + 1024]; xv3 = xs[last_vec];
+            xv0 = xs[t]; xv1 = xs[t + 512]; xv2 = xs[t + 1024]; xv3 = xs[last_vec];
         }
     };
     int g = 0, b = first;
@@ -386,7 +389,8 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                 auto mask = [&](uint4& v, int i) { const uint32_t m = (keep >> i) & 1u ? ~0u : 0u; v.x &= m; v.y &= m; v.z &= m; v.w &= m; };
                 mask(xv0, 0); mask(xv1, 1); mask(xv2, 2); mask(xv3, 3);
             }
-            d[tid] = xv0; d[tid + 512] = xv1; d[tid + 1024] = xv2; d[last_vec] = xv3;   // clamped lanes rewrite the last vector with itself
+            const int t = here(tid);
+            d[t] = xv0; d[t + 512] = xv1; d[t + 1024] = xv2; d[last_of(t)] = xv3;   // clamped lanes rewrite the last vector with itself
         }
         // This wavefront's weights: conv2's four k-steps, and as each is used up conv3's (steps [s3, s3 + 5) or + 4 of its eighteen).
         const bf16_t* w2p = (g == 0 ? w2_0_ : a.w2[g]) + (2 * cp * 16 + 4 * kq) * 3 * 512;
@@ -415,6 +419,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
         {
             float* g1 = a.act1[g];
             auto run = [&](auto nt_) {
+                const int lane = here(tid) & 63, kg = lane >> 5;
                 constexpr int NT = decltype(nt_)::value;   // pixel tiles of this wavefront: w (and w + 8)
                 const uint8_t* base[NT];
                 f32x16 acc[NT];
@@ -482,6 +487,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
 
         // ---- conv2: k = (p, q, c); this wavefront's quarter is filter row kq, a k-step is one tap ------------------------
         {
+            const int lk = here(lane) >> 4;
             int base[T2];
             tf_f32x4 acc[T2][2];
 #pragma unroll
@@ -495,7 +501,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
             request3(std::integral_constant<int, 4>{});
             __syncthreads();   // act1 has been read
             float* g2 = a.act2[g];
-            tower_f32_exchange<T2>(acc, sEx, cp, kq, lane, [&](int, int t, int c, const tf_f32x4& sum) {
+            tower_f32_exchange<T2>(acc, sEx, cp, kq, here(lane), [&](int, int t, int c, const tf_f32x4& sum) {
                 const int lpx = t * 16 + here(lq), px = r3_lo * 9 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 const float4 bv = *reinterpret_cast<const float4*>(sB2 + ch);
                 if (lpx < n2) {
@@ -513,11 +519,15 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
                 while (b2 >= n_) { b2 -= n_; ++g2; }
                 fetch_desc(g2, b2);
             }
+        } else if constexpr (PARTS == 1) {   // (or the old state keeps its registers from its stores to here)
+            auto gone = [](uint4& v) { asm volatile("" : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w)); };
+            gone(xv0); gone(xv1); gone(xv2); gone(xv3);
         }
         __syncthreads();
 
         // ---- conv3: k = (p, q, c), two k-steps per tap ------------------------------------------------------------------
         {
+            const int lk = here(lane) >> 4;
             int base[T3];
             tf_f32x4 acc[T3][2];
 #pragma unroll
@@ -540,7 +550,7 @@ __global__ __launch_bounds__(kTowerThreads) void conv_tower_f32_kernel(int n_, i
 #pragma unroll
             for (int t = 1; t < T3; ++t) all_of += acc[t][0] + acc[t][1];
             if (!__builtin_isfinite((all_of[0] + all_of[1]) + (all_of[2] + all_of[3]))) *sPlain = 1;
-            tower_f32_exchange<T3>(acc, sEx, cp, kq, lane, [&](int, int t, int c, const tf_f32x4& sum) {
+            tower_f32_exchange<T3>(acc, sEx, cp, kq, here(lane), [&](int, int t, int c, const tf_f32x4& sum) {
                 const int lpx = t * 16 + here(lq), px = r3_lo * 7 + lpx, ch = cp * 32 + c * 16 + 4 * lk;
                 const float4 bv = *reinterpret_cast<const float4*>(sB3 + ch);
                 if (lpx < n3)
