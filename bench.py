@@ -67,17 +67,17 @@ def kernel_work(name, B, A, groups, precision):
 _C = "paper_2111_01264_amd/csrc/"
 _RMS_SRC = (_C + "head_kernels.h", _C + "net.hip")
 _WG_SRC = (_C + "wgrad_all.h", _C + "wgrad_conv.h", _C + "wgrad_fc1.h", _C + "gemm_tn_tr.h", _C + "gemm_mfma.h", _C + "head_kernels.h", _C + "common.h", _C + "net.hip")
-_TOWER_SRC = (_C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
-_TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "net.hip")
+_TOWER_SRC = (_C + "conv_tower.h", _C + "conv_tower_many.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
+_TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower_bwd_many.h", _C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "net.hip")
 TRAFFIC = {
-    ("rmsprop", 32, "bf16"): (66.21e6, _RMS_SRC, "26b495281cf015bdef224d9df2da2ceedeabf616", "profiles/hbm_traffic_b32.txt"),
-    ("wgrad_all", 32, "bf16"): (22.08e6, _WG_SRC, "2696c4e78975d1b7b453853988c78340702719e4", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower", 32, "bf16"): (10.26e6, _TOWER_SRC, "e3df90cdbbc306e87824d8318ccc90afb9242698", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower_bwd", 32, "bf16"): (4.78e6, _TOWER_BWD_SRC, "91a268801719880890adaece14c982e6777d0472", "profiles/hbm_traffic_b32.txt"),
-    ("rmsprop", 256, "bf16"): (71.39e6, _RMS_SRC, "26b495281cf015bdef224d9df2da2ceedeabf616", "profiles/hbm_traffic_b256.txt"),
-    ("wgrad_all", 256, "bf16"): (58.52e6, _WG_SRC, "2696c4e78975d1b7b453853988c78340702719e4", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower", 256, "bf16"): (24.22e6, _TOWER_SRC, "e3df90cdbbc306e87824d8318ccc90afb9242698", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower_bwd", 256, "bf16"): (21.25e6, _TOWER_BWD_SRC, "91a268801719880890adaece14c982e6777d0472", "profiles/hbm_traffic_b256.txt"),
+    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "8f659c48af7c793d969c1515a17f8f34fb1c1105", "profiles/hbm_traffic_b32.txt"),
+    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "1e23a78a6534b6cbd816f7f646880f4a07961b97", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower", 32, "bf16"): (10.24e6, _TOWER_SRC, "4e93ceeb02d8cc7d5a5484e9c8c276ea22d7545d", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "bd4c41d7d319a392f70935738a7cd5d8541ce2ca", "profiles/hbm_traffic_b32.txt"),
+    ("rmsprop", 256, "bf16"): (71.38e6, _RMS_SRC, "8f659c48af7c793d969c1515a17f8f34fb1c1105", "profiles/hbm_traffic_b256.txt"),
+    ("wgrad_all", 256, "bf16"): (58.66e6, _WG_SRC, "1e23a78a6534b6cbd816f7f646880f4a07961b97", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower", 256, "bf16"): (24.35e6, _TOWER_SRC, "4e93ceeb02d8cc7d5a5484e9c8c276ea22d7545d", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower_bwd", 256, "bf16"): (23.43e6, _TOWER_BWD_SRC, "bd4c41d7d319a392f70935738a7cd5d8541ce2ca", "profiles/hbm_traffic_b256.txt"),
 }
 
 
