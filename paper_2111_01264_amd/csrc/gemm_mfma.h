@@ -13,7 +13,7 @@
 //   conv3 out     T     [n][7][7][64]            = fc1 input, feature index (h*7 + w)*64 + c
 //   conv1 weights [32][c][p][q]  (k = c*64 + p*8 + q, eight q's = eight adjacent input bytes)
 //   conv2 weights [64][p][q][c]  conv3 weights [64][p][q][c]  fc1 weights [512][(h*7+w)*64 + c]
-// dqn_set_params and dqn_get_params convert from and to the public blob layout, on the device (import_blob_kernel, export_blob_kernel).
+// dqn_set_params and dqn_get_params convert from and to the public blob layout, on the device (permute_blob_kernel).
 #pragma once
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>

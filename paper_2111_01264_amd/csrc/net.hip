@@ -89,8 +89,6 @@ static hipError_t static_scratch_of(int device, void** out)
     return hipSuccess;
 }
 
-constexpr int kBlobChunks = 12;   // dqn_get_params: pieces in flight between device, bus and the caller's memory
-
 struct dqn_ctx {
     dqn_config cfg;
     int device = 0;
@@ -101,9 +99,7 @@ struct dqn_ctx {
     float *theta = nullptr, *theta_t = nullptr, *v = nullptr, *m = nullptr, *grad = nullptr;
     void *sh = nullptr, *sh_t = nullptr;   // forward operand copies
     void* bsh = nullptr;                   // backward operand copies of theta
-    float* blob = nullptr;                 // a blob in the public layout on its way in (dqn_set_params),
-    float* blob_host = nullptr;            // and out (dqn_get_params; pinned host memory)
-    hipEvent_t ev_blob[kBlobChunks] = {};
+    float* blob = nullptr;                 // a blob in the public layout, on its way in or out (dqn_set_params / dqn_get_params)
     std::mutex blob_mu;
     Workspace train_ws, act_ws;
     void *dzh = nullptr, *dz3 = nullptr, *dz2 = nullptr, *dz1 = nullptr;
@@ -587,34 +583,14 @@ __device__ inline size_t public_index(const Offsets& o, size_t e)
     }
     return e;
 }
-// The inverse: where the device layout keeps element p of the public blob.
-__device__ inline size_t device_index(const Offsets& o, size_t p)
-{
-    auto conv = [&](size_t off, int C, int K) {
-        const int r = static_cast<int>(p - off), kk = r % (K * K), c = r / (K * K) % C, oc = r / (K * K * C);
-        return off + (static_cast<size_t>(oc) * K * K + kk) * C + c;
-    };
-    if (p >= o.w2 && p < o.b2) return conv(o.w2, 32, 4);
-    if (p >= o.w3 && p < o.b3) return conv(o.w3, 64, 3);
-    if (p >= o.wf1 && p < o.bf1) {
-        const int r = static_cast<int>(p - o.wf1), hw = r % 49, c = r / 49 % 64, oc = r / 3136;
-        return o.wf1 + static_cast<size_t>(oc) * 3136 + hw * 64 + c;
-    }
-    return p;
-}
 // The change of layout runs on the device (a few microseconds; on the host it was most of the 1 ms that either call took).
-__global__ __launch_bounds__(256) void import_blob_kernel(const float* __restrict__ src, float* __restrict__ dst, Offsets off)
+template <bool TO_DEVICE>
+__global__ __launch_bounds__(256) void permute_blob_kernel(const float* __restrict__ src, float* __restrict__ dst, Offsets off)
 {
     const size_t e = blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x;
-    if (e < off.total) dst[e] = src[public_index(off, e)];
-}
-// Elements first .. end - 1 of the public blob into host memory, sixteen bytes per lane across the bus (first is a multiple of four).
-__global__ __launch_bounds__(256) void export_blob_kernel(const float* __restrict__ src, float* __restrict__ host, Offsets off, size_t first, size_t end)
-{
-    const size_t p = first + (blockIdx.x * static_cast<size_t>(blockDim.x) + threadIdx.x) * 4;
-    if (p + 4 <= end) *reinterpret_cast<float4*>(host + p) = make_float4(src[device_index(off, p)], src[device_index(off, p + 1)], src[device_index(off, p + 2)], src[device_index(off, p + 3)]);
-    else
-        for (size_t q = p; q < end; ++q) host[q] = src[device_index(off, q)];
+    if (e >= off.total) return;
+    const size_t pub = public_index(off, e);
+    if (TO_DEVICE) dst[e] = src[pub]; else dst[pub] = src[e];
 }
 
 static float* blob_of(dqn_ctx* c, int which)
@@ -684,8 +660,6 @@ int dqn_create(const dqn_config* cfg, void* act_stream, void* train_stream, dqn_
             DQN_HIP(hipMemset(*p, 0, (n + 8) * sizeof(float)));
         }
         DQN_HIP(hipMalloc((void**)&c->blob, n * sizeof(float)));
-        DQN_HIP(hipHostMalloc((void**)&c->blob_host, n * sizeof(float), hipHostMallocDefault));
-        for (hipEvent_t& e : c->ev_blob) DQN_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         for (void** p : {&c->sh, &c->sh_t}) {
             DQN_HIP(hipMalloc(p, (copy_elements(c->off, c->esize) + 8) * c->esize));
             DQN_HIP(hipMemset(*p, 0, (copy_elements(c->off, c->esize) + 8) * c->esize));
@@ -737,9 +711,6 @@ int dqn_destroy(dqn_ctx* c)
     (void)hipStreamSynchronize(c->act_stream);
     (void)hipStreamSynchronize(c->train_stream);
     (void)hipFree(c->sh); (void)hipFree(c->sh_t); (void)hipFree(c->blob);
-    if (c->blob_host) (void)hipHostFree(c->blob_host);
-    for (hipEvent_t e : c->ev_blob)
-        if (e) (void)hipEventDestroy(e);
     (void)hipFree(c->theta); (void)hipFree(c->theta_t); (void)hipFree(c->v); (void)hipFree(c->m); (void)hipFree(c->grad);
     free_ws(c->train_ws); free_ws(c->act_ws);
     (void)hipFree(c->dzh); (void)hipFree(c->dz3); (void)hipFree(c->dz2); (void)hipFree(c->dz1);
@@ -770,7 +741,7 @@ int dqn_set_params(dqn_ctx* c, int which, const float* host_src, size_t n)
     const unsigned blocks = static_cast<unsigned>((n + 255) / 256);
     std::lock_guard<std::mutex> blob_lock(c->blob_mu);
     DQN_HIP(hipMemcpyAsync(c->blob, host_src, n * sizeof(float), hipMemcpyHostToDevice, c->train_stream));
-    hipLaunchKernelGGL(import_blob_kernel, dim3(blocks), dim3(256), 0, c->train_stream, c->blob, dst, c->off);
+    hipLaunchKernelGGL(permute_blob_kernel<true>, dim3(blocks), dim3(256), 0, c->train_stream, c->blob, dst, c->off);
     DQN_LAUNCH_CHECK();
     if (which == DQN_PARAMS_ONLINE || which == DQN_PARAMS_TARGET) {   // the network's operand copies (backward ones: theta only)
         const bool online = which == DQN_PARAMS_ONLINE;
@@ -793,22 +764,11 @@ int dqn_get_params(dqn_ctx* c, int which, float* host_dst, size_t n)
     if (!src) return fail(DQN_EINVAL, "dqn_get_params: which = %d", which);
     int rc = sync_both(c);
     if (rc != DQN_OK) return rc;
-    // In chunks through the context's pinned buffer: the kernel that writes chunk k + 1 across the bus runs while the host copies chunk k
-    // to the caller's memory.  6.8 MB: 135 us for the bus alone, then 230 us more for the copy, from memory that is in no cache yet; a copy command into
-    // memory that is not pinned is staged by the runtime, 400 us.  In 2, 6 and 12 chunks 283, 293 and 243 us, and no less with two to four threads that copy.
     std::lock_guard<std::mutex> blob_lock(c->blob_mu);
-    const size_t per = ((n + kBlobChunks - 1) / kBlobChunks + 3) / 4 * 4;
-    for (int k = 0; k < kBlobChunks; ++k) {
-        const size_t first = k * per, end = first + per < n ? first + per : n;
-        hipLaunchKernelGGL(export_blob_kernel, dim3(static_cast<unsigned>((end - first + 1023) / 1024)), dim3(256), 0, c->train_stream, src, c->blob_host, c->off, first, end);
-        DQN_LAUNCH_CHECK();
-        DQN_HIP(hipEventRecord(c->ev_blob[k], c->train_stream));
-    }
-    for (int k = 0; k < kBlobChunks; ++k) {
-        const size_t first = k * per, end = first + per < n ? first + per : n;
-        DQN_HIP(hipEventSynchronize(c->ev_blob[k]));
-        memcpy(host_dst + first, c->blob_host + first, (end - first) * sizeof(float));
-    }
+    hipLaunchKernelGGL(permute_blob_kernel<false>, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, c->train_stream, src, c->blob, c->off);
+    DQN_LAUNCH_CHECK();
+    DQN_HIP(hipMemcpyAsync(host_dst, c->blob, n * sizeof(float), hipMemcpyDeviceToHost, c->train_stream));
+    DQN_HIP(hipStreamSynchronize(c->train_stream));
     return DQN_OK;
 }
 
