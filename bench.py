@@ -70,14 +70,14 @@ _WG_SRC = (_C + "wgrad_all.h", _C + "wgrad_conv.h", _C + "wgrad_fc1.h", _C + "ge
 _TOWER_SRC = (_C + "conv_tower.h", _C + "conv_tower_many.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
 _TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower_bwd_many.h", _C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "net.hip")
 TRAFFIC = {
-    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "8f659c48af7c793d969c1515a17f8f34fb1c1105", "profiles/hbm_traffic_b32.txt"),
-    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "1e23a78a6534b6cbd816f7f646880f4a07961b97", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower", 32, "bf16"): (10.24e6, _TOWER_SRC, "4e93ceeb02d8cc7d5a5484e9c8c276ea22d7545d", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "bd4c41d7d319a392f70935738a7cd5d8541ce2ca", "profiles/hbm_traffic_b32.txt"),
-    ("rmsprop", 256, "bf16"): (71.38e6, _RMS_SRC, "8f659c48af7c793d969c1515a17f8f34fb1c1105", "profiles/hbm_traffic_b256.txt"),
-    ("wgrad_all", 256, "bf16"): (58.67e6, _WG_SRC, "1e23a78a6534b6cbd816f7f646880f4a07961b97", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower", 256, "bf16"): (24.35e6, _TOWER_SRC, "4e93ceeb02d8cc7d5a5484e9c8c276ea22d7545d", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower_bwd", 256, "bf16"): (23.43e6, _TOWER_BWD_SRC, "bd4c41d7d319a392f70935738a7cd5d8541ce2ca", "profiles/hbm_traffic_b256.txt"),
+    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "2ace6c53035fb9a745e712ffdce4b77a19bf8e90", "profiles/hbm_traffic_b32.txt"),
+    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "44b81c3b33999ba1d303dc3aa8268b49d4788469", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower", 32, "bf16"): (10.24e6, _TOWER_SRC, "2f2c16998b4a82d5d96e9474e58728c509a5f99e", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "486913897edd95f79055b31df2b16d6eb2625371", "profiles/hbm_traffic_b32.txt"),
+    ("rmsprop", 256, "bf16"): (71.38e6, _RMS_SRC, "2ace6c53035fb9a745e712ffdce4b77a19bf8e90", "profiles/hbm_traffic_b256.txt"),
+    ("wgrad_all", 256, "bf16"): (58.67e6, _WG_SRC, "44b81c3b33999ba1d303dc3aa8268b49d4788469", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower", 256, "bf16"): (24.35e6, _TOWER_SRC, "2f2c16998b4a82d5d96e9474e58728c509a5f99e", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower_bwd", 256, "bf16"): (23.43e6, _TOWER_BWD_SRC, "486913897edd95f79055b31df2b16d6eb2625371", "profiles/hbm_traffic_b256.txt"),
 }
 
 
