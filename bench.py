@@ -17,6 +17,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -65,19 +66,38 @@ def kernel_work(name, B, A, groups, precision):
 # {(kernel, batch, precision): (bytes, source files of the kernel, sha1 over their concatenation when the counters
 # were taken)}.  Reported only while the kernel's sources still hash to that value.
 _C = "paper_2111_01264_amd/csrc/"
-_RMS_SRC = (_C + "head_kernels.h", _C + "net.hip")
-_WG_SRC = (_C + "wgrad_all.h", _C + "wgrad_conv.h", _C + "wgrad_fc1.h", _C + "gemm_tn_tr.h", _C + "gemm_mfma.h", _C + "head_kernels.h", _C + "common.h", _C + "net.hip")
-_TOWER_SRC = (_C + "conv_tower.h", _C + "conv_tower_many.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "common.h", _C + "net.hip")
-_TOWER_BWD_SRC = (_C + "conv_tower_bwd.h", _C + "conv_tower_bwd_many.h", _C + "conv_tower.h", _C + "vec4.h", _C + "gemm_mfma.h", _C + "net.hip")
+
+
+def _sources(*heads):
+    """The files a kernel is made of: these headers and common.h, every header that they include, and net.hip, which launches it."""
+    found = []
+
+    def walk(src):
+        if src in found:
+            return
+        found.append(src)
+        with open(os.path.join(ROOT, src)) as f:
+            for h in re.findall(r'^#include "([^"]+)"', f.read(), re.M):
+                walk(os.path.normpath(os.path.join(os.path.dirname(src), h)))
+
+    for h in ("common.h", *heads):
+        walk(_C + h)
+    return (*sorted(found), _C + "net.hip")
+
+
+_RMS_SRC = _sources("head_kernels.h")
+_WG_SRC = _sources("wgrad_all.h")
+_TOWER_SRC = _sources("conv_tower.h", "conv_tower_many.h")
+_TOWER_BWD_SRC = _sources("conv_tower_bwd.h", "conv_tower_bwd_many.h")
 TRAFFIC = {
-    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "2ace6c53035fb9a745e712ffdce4b77a19bf8e90", "profiles/hbm_traffic_b32.txt"),
-    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "44b81c3b33999ba1d303dc3aa8268b49d4788469", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower", 32, "bf16"): (10.24e6, _TOWER_SRC, "2f2c16998b4a82d5d96e9474e58728c509a5f99e", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "486913897edd95f79055b31df2b16d6eb2625371", "profiles/hbm_traffic_b32.txt"),
-    ("rmsprop", 256, "bf16"): (71.38e6, _RMS_SRC, "2ace6c53035fb9a745e712ffdce4b77a19bf8e90", "profiles/hbm_traffic_b256.txt"),
-    ("wgrad_all", 256, "bf16"): (58.67e6, _WG_SRC, "44b81c3b33999ba1d303dc3aa8268b49d4788469", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower", 256, "bf16"): (24.35e6, _TOWER_SRC, "2f2c16998b4a82d5d96e9474e58728c509a5f99e", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower_bwd", 256, "bf16"): (23.43e6, _TOWER_BWD_SRC, "486913897edd95f79055b31df2b16d6eb2625371", "profiles/hbm_traffic_b256.txt"),
+    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "d4cbf06645b992392e8573ca995e7646569061d8", "profiles/hbm_traffic_b32.txt"),
+    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "8426a677e203c5b5f74c6e372f6cb2951909b04f", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower", 32, "bf16"): (10.24e6, _TOWER_SRC, "d7341cbacc0b7a5ddf0d45203270074d59190ef3", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "fa6d3a99abdc22731133ec12419c7ec557ec0b66", "profiles/hbm_traffic_b32.txt"),
+    ("rmsprop", 256, "bf16"): (71.38e6, _RMS_SRC, "d4cbf06645b992392e8573ca995e7646569061d8", "profiles/hbm_traffic_b256.txt"),
+    ("wgrad_all", 256, "bf16"): (58.67e6, _WG_SRC, "8426a677e203c5b5f74c6e372f6cb2951909b04f", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower", 256, "bf16"): (24.35e6, _TOWER_SRC, "d7341cbacc0b7a5ddf0d45203270074d59190ef3", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower_bwd", 256, "bf16"): (23.43e6, _TOWER_BWD_SRC, "fa6d3a99abdc22731133ec12419c7ec557ec0b66", "profiles/hbm_traffic_b256.txt"),
 }
 
 

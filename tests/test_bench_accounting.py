@@ -1,6 +1,7 @@
 """Host-side accounting of bench.py: the algorithmic work per kernel launch that the roofline figures divide by, the
 rule that withholds the measured-traffic figure once a kernel's sources have changed, and the one-GPU guard."""
 import os
+import re
 import subprocess
 import sys
 
@@ -96,6 +97,23 @@ def test_measured_traffic_is_withheld_when_sources_changed(monkeypatch):
     stale[key] = (nbytes, srcs, "0" * 40, where)
     monkeypatch.setattr(bench, "TRAFFIC", stale)
     assert bench.measured_traffic(*key) == (None, None)
+
+
+def test_traffic_hashes_cover_everything_a_kernel_is_made_of():
+    # a header that one of a kernel's sources includes is a source of the kernel (net.hip, which includes all of them, only launches it)
+    csrc = "paper_2111_01264_amd/csrc/"
+    for key, (_, srcs, _, _) in bench.TRAFFIC.items():
+        assert csrc + "net.hip" in srcs and csrc + "common.h" in srcs and len(set(srcs)) == len(srcs), key
+        for src in srcs:
+            if src == csrc + "net.hip":
+                continue
+            with open(os.path.join(ROOT, src)) as f:
+                included = re.findall(r'^#include "([^"]+)"', f.read(), re.M)
+            missing = [h for h in included if os.path.relpath(os.path.join(os.path.dirname(src), h)) not in srcs]
+            assert not missing, (key, src, missing)
+    heads = {"rmsprop": "head_kernels.h", "wgrad_all": "wgrad_all.h", "conv_tower": "conv_tower_many.h", "conv_tower_bwd": "conv_tower_bwd_many.h"}
+    for (kernel, _, _), (_, srcs, _, _) in bench.TRAFFIC.items():
+        assert csrc + heads[kernel] in srcs
 
 
 def test_more_than_one_gpu_is_refused():
