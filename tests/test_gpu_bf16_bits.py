@@ -1,7 +1,8 @@
 """The bits of bf16 training: what a train step computes does not depend on how its reductions are spread over lanes and workgroups,
 so a stretch of steps gives the recorded parameters, gradient and loss bit for bit.  tests/golden/bf16_train_sha256.txt was recorded with
 the optimiser kernel that adds the conv layers' slices with eight lanes per weight (eight sums, each over every eighth slice, and a tree).
-Sizes: one, some and all of conv2's and conv3's slices; five and whole samples per workgroup in the data gradients; descriptors."""
+Sizes: one, some and all of conv2's and conv3's slices; fifths (up to 51), halves (70, 256) and whole samples (512) in the data gradients;
+thirds, halves, whole samples and the persistent workgroups in the forward.  (dqn_train_step: no descriptors here.)"""
 import hashlib
 import os
 
