@@ -15,8 +15,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hi
          # the first kernel arguments arrive in scalar registers with the wavefront instead of through a load from cold
          # memory (14 dwords on gfx950; the hot kernels' signatures lead with what they need first)
          "-mllvm", "-amdgpu-kernarg-preload-count=16",
-         # every kernel starts on a page of its own: where a kernel of 1.6 KB came to lie decided whether it missed the instruction cache 69 or 137
-         # times, so the size of one kernel changed the time of the next (train step at minibatch 45 12.89 -> 12.72 ms for 250, others 0 - 0.8 %)
+         # every kernel starts on a page of its own: where a small kernel came to lie decided how often it missed the instruction cache (minibatch
+         # 45, misses per launch without -> with: fc1's data gradient 84 -> 42, the conv data gradients 281 -> 140, the act head 12 -> 4; counters in
+         # profiles/instruction_cache_b45.txt), so the size of one kernel changed the time of the next (250 train steps at minibatch 45 12.89 -> 12.72 ms)
          "-Xarch_device", "-falign-functions=4096"]
 
 

@@ -2,7 +2,8 @@
 // the TD loss with respect to theta needs dLoss/d(activation) of every layer), reduced-precision mode: the mirror
 // image of conv_tower.h, for minibatches that leave most of the chip idle (5 B <= compute units; larger ones: conv_tower_bwd_many.h).  A workgroup of
 // 8 wavefronts runs a FIFTH of a sample -- rows 2 j, 2 j + 1 of every parity class of dz1 (four rows of dz1) with the two or three rows of
-// dz2 they depend on --: one pixel tile per stage (a whole sample per workgroup took 8.4 us at batch 32, this 4.0).  Per sample
+// dz2 they depend on --: one pixel tile per stage (minibatch 32, kernel trace: 5.7 us, as
+// halves on four wavefronts 6.5).  Per sample
 //
 //   dz2[y][x][c] = [act2 > 0] * sum_{p,q,o} dz3[y-p][x-q][o]   * W3[o][p][q][c]          (9x9x64 from 7x7x64, 3x3 taps)
 //   dz1[y][x][c] = [act1 > 0] * sum_{p,q,o} dz2[(y-p)/2][(x-q)/2][o] * W2[o][p][q][c]    (20x20x32 from 9x9x64, stride 2)

@@ -2,8 +2,8 @@
 // images of dz3 and dz2 in LDS, conv2 as four stride-1 problems) on the bf16 matrix instructions with values in three exact parts, see
 // conv_tower_f32.h: 56 k cycles of a compute unit per sample on the fp32 instruction, 24 k so.  conv3's stage is divided as the
 // forward layers are (32 channels and a quarter of k per wavefront); conv2's stage gives a wavefront one parity class, half of its pixels
-// and all of k.  Launch times (rocprofv3), fp32 instruction -> this: minibatch 32 13.6 -> 11.4 us, minibatch 256 39.6 -> 29.1 us
-// (matrix cores busy for 31 %; whole samples use all 256 registers and 84 bytes of scratch per lane).
+// and all of k.  Launch times (rocprofv3), fp32 instruction -> this: minibatch 32 13.6 -> 11.4 us, minibatch 256 39.6 -> 24.6 us
+// (matrix cores busy for 36 %; whole samples use 245 registers, no scratch memory, and keep 160 scalars in lanes of vector registers).
 //
 // The weight copies (bsh_store_w3, bsh_store_w2) hold the taps in REVERSED order, so that the pixel addresses ascend with the
 // weight stream: k = (p', q', o) with p' = KS - 1 - p reads image position (y + p', x + q').

@@ -1,13 +1,14 @@
 // Fused data-gradient chain conv3 -> conv2, reduced precision, for minibatches that fill the chip: the layers, operands, instructions and
-// orders of addition of conv_tower_bwd.h -- every element has the same bits -- in persistent workgroups of four wavefronts, two per
-// compute unit (see conv_tower_many.h).
+// orders of addition of conv_tower_bwd.h -- every element has the same bits -- in workgroups of four wavefronts, two per
+// compute unit (see conv_tower_many.h): one item each up to two samples per compute unit, above that (513 .. 1024 on 256) persistent.
 //   * conv3 stage: wavefront (nt, kh) owns channel tile nt and k-quarters 2 kh, 2 kh + 1, as in conv_tower_many.h.
 //   * conv2 stage: wavefront = parity class of the output pixel, both k-halves: nothing is exchanged.  Its four pixel tiles in two passes of two.
 //   * The weight fragments of both stages stream through the same eighteen registers.
 //   * dz1 is collected in LDS (over the exchange block, in act1's order of conv_tower_many.h) and goes to memory 16 bytes per lane, masked there
 //     by act1, which is read the same way: a lane's own elements are 8 bytes at a stride of 128.
 // Bound by the matrix instructions (1.6 us per sample and compute unit), the vector unit's addresses and sums, and the start until the weights
-// have arrived (2 us).  Against eight wavefronts on one sample, kernel times: minibatch 512 18.9 -> 14.0 us; 256 11.4 - 12.0 -> 9.4 us and 128 10.8 -> 6.6 us as halves.
+// have arrived (2 us).  Against eight wavefronts on one sample, kernel times: minibatch 512 18.9 -> 14.1 us; 256 11.4 - 12.0 -> 9.4 us and 128 10.8 -> 6.6 us as halves;
+// train step at minibatch 1024 194.5 -> 169.3 us with the other changes of its kind.
 #pragma once
 #include "conv_tower_bwd.h"
 #include "conv_tower_many.h"

@@ -21,10 +21,10 @@
 //     (tower_f32_plain), and what such values lead to is what fp32 arithmetic makes of them.
 //
 // Launch times (rocprofv3), fp32 instruction -> this: sevenths (one to twelve states) 13.6 -> 12.0 us, thirds (minibatch 32) 19.4 -> 15.0 us,
-// whole samples (minibatch 256) 63 -> 52 us; act step W = 1 20.3 -> 18.5 us (18.4 before it watched for values without parts).  A whole
-// item takes 50 k cycles where the matrix cores need 21 k: staging 4 k, conv1 9 k and 3 k of waiting (13 tiles on 8 wavefronts), conv2 12 k,
-// its sums' exchange and output 6 k, conv3 and its exchange 9 k (clock reads of one wavefront); by the counters the matrix cores are busy
-// for 35 % of the launch.  The whole-sample variants use all 256 registers and 40 (by descriptors 68) bytes of scratch per lane.
+// whole samples (minibatch 256) 63 -> 45 us; act step W = 1 20.3 -> 18.5 us (18.4 before it watched for values without parts).  Of a whole
+// item's cycles the matrix cores need 21 k; the rest is staging, waiting in conv1 (13 tiles on 8 wavefronts) and the exchange of the sums and
+// their output; by the counters the matrix cores are busy for 39 % of the launch (minibatch 256).  The whole-sample variants use 223 (by descriptors 231)
+// registers and no scratch memory; 23 (29) scalars are kept in lanes of vector registers.
 #pragma once
 #include "conv_tower.h"
 #include "wgrad_conv.h"
@@ -89,8 +89,9 @@ template <int PLANE> __device__ inline void tf_store4(uint8_t* dst, float v0, fl
 
 // The value, computed no earlier than here: addresses that depend on a lane's pixel are the same for every item, and the compiler
 // otherwise computes those of all stages in front of the item loop and keeps them in registers throughout.  (Whole samples, forward and
-// backward, spilled 40 to 84 bytes per lane of them, and a register read back behind outstanding loads waits for those: train step at
-// minibatch 256 187 -> 175 us without, 140 153 -> 145 us.)
+// backward, had 40 to 84 bytes per lane of them in scratch memory, and a register read back behind outstanding loads waits for those: train step at
+// minibatch 256 187 -> 175 us without, 140 153 -> 145 us.  Scalars in lanes of vector registers went from 12, 24 and 148 -- forward by
+// states, by descriptors, backward -- to 23, 29 and 160: no memory, a few moves per item.)
 __device__ inline int here(int v)
 {
     asm volatile("" : "+v"(v));

@@ -1,11 +1,11 @@
 // Fused conv1 -> conv2 -> conv3 of the Q-network, reduced precision, for more (group, sample) items than compute units: the layers,
 // operands, instructions and orders of addition of conv_tower.h -- every element has the same bits -- in persistent workgroups of four
-// wavefronts, two of them per compute unit.
+// wavefronts, two of them per compute unit (one item each up to two items per compute unit, then as equal shares as can be).
 //
 // What bounds it: eight wavefronts on one sample (conv_tower.h) took 6.4 us per further sample of a compute unit, of which 1.8 us
 // are matrix instructions: the two wavefronts of a SIMD stand at the same barriers.  Two workgroups on two samples fill each other's
 // waits: 4 us per sample, of which the vector unit issues for 2.2 us and LDS works for 2.6 us.  512 items (two networks at minibatch 256, no
-// weights to change) 19.9 -> 16.7 us, 768 items 25.6 -> 21.8 us, 1024 items 32.7 -> 27.1 us; 100 train steps at minibatch 512 12.05 -> 11.61 ms.
+// weights to change) 19.9 -> 16.7 us, 768 items 25.6 -> 21.8 us, 1024 items 32.7 -> 27.1 us; 100 train steps at minibatch 512 12.07 -> 11.64 ms.
 // 3.5 us of a launch are its start, until the first frames have arrived.
 //   * Wavefront (nt, kh): channel tile nt, k-quarters 2 kh and 2 kh + 1 of conv2 and conv3, one accumulator each (a sum is
 //     ((p0 + p1) + p2) + p3 whoever holds the parts).  Half as many parts are exchanged as between quarters.
@@ -250,7 +250,6 @@ __global__ __launch_bounds__(kManyThreads, 2) void conv_tower_many_kernel(int n_
         }
         __syncthreads();
 
-        
         // Rows 8 kh + 4 q .. + 3 of a tile, + bias, ReLU
         auto finish = [&](int ln, int t, int q, const float (&keep)[16], const float4& bias) {
             const float4 r = many_sum(sXchg + (nt * 3 + t) * (6 * 64) + ln, kh, q, keep);

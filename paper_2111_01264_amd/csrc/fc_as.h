@@ -257,9 +257,9 @@ inline hipError_t launch_fc_as(hipStream_t st, FcAsArgs<T> a, int groups, hipEve
         constexpr int TB = 1;
         const size_t smem = static_cast<size_t>(TB) * 32 * (kFcK<EPI> + 8) * sizeof(T);
         // Few workgroups keep the plain order: at 112 and 100 of them (128 states, minibatch 45) the other made no difference, and
-        // finding it cost 0.1 us.  From 140 on it gains (plain order -> this one, whole call): 160 states (140 workgroups) 19.9 -> 19.2 us, fp32
-        // 41.1 -> 39.7, 192 states (168) 20.2 -> 19.6, 256 (224) 21.1 -> 20.5; train step at minibatch 96 (168, forward only) 69.8 -> 69.2,
-        // 128 (224) 72.2 -> 71.1, 160 (280, and 125 in the data gradient) 82.9 -> 80.9.
+        // finding it cost 0.1 us.  Plain order -> this one, whole call: 160 states (140 workgroups) 16.6 -> 16.7 us, fp32
+        // 36.9 -> 36.5, 192 states (168) 16.9 -> 16.9, 256 (224) 17.6 -> 17.4, 512 24.7 -> 24.1; train step at minibatch 96 (168, forward only) 56.6 -> 55.6,
+        // 128 (224) 59.2 -> 58.2, 160 (280, and 125 in the data gradient) 68.2 -> 67.2, 256 76.4 -> 73.2, 512 107.4 -> 103.7.
         const uint32_t rows = (a.M + TB * 32 - 1) / (TB * 32), cols = n_blocks, total = rows * cols * groups * slices;
         const bool shared = total >= 128 && rows > 1 && static_cast<uint64_t>(total) * rows < (1u << 20) && static_cast<uint64_t>(total) * cols < (1u << 20);
         a.by_rows = ((1u << 20) + rows - 1) / rows;

@@ -147,9 +147,9 @@ constexpr int kWgSlicesF32_1 = 128, kWgSlicesF32_2 = 64, kWgSlicesF32_3 = 44;
 // Smallest minibatch handled through descriptors.  Below it the assembled states are the faster form: the byte gather
 // rides for free in the previous step's head kernel (which leaves most of the chip idle at small batches), and the
 // fused conv kernel starts on states that are contiguous and cache-warm instead of after a descriptor round trip
-// (per train step through descriptors / through assembled states: batch 32: 52.4 / 51.8 us, batch 64: 62.8 / 62.9,
-// batch 96: 64.9 / 67.1, batch 128: 68.1 / 72.0; full precision, where samples by descriptor are always whole ones: batch 40:
-// 106.1 / 96.0, 64: 112.8 / 105.1, 72: 113.8 / 113.8, 96: 121.5 / 120.8, 128: 124.4 / 125.1, 256: 185.2 / 186.3).
+// (per train step through descriptors / through assembled states: batch 40: 51.1 / 49.2 us, 64: 54.9 / 53.0, 80: 54.1 / 53.7, 96: 55.7 / 55.2,
+// 128: 58.4 / 58.2, 160: 67.0 / 68.1, 256: 72.6 / 76.2; full precision, where samples by descriptor are always whole ones: 40: 98.2 / 91.1,
+// 64: 106.7 / 102.0, 72: 107.0 / 107.5, 96: 114.2 / 114.3, 128: 118.2 / 119.3, 256: 180.8 / 184.8: the line lies where the two are within 1 %).
 constexpr int kDescMinBatch = 96;
 static int alloc_ws(Workspace& ws, int cap, int groups, int A, size_t esize)
 {
@@ -255,8 +255,12 @@ static int forward_to_fc1(dqn_ctx* c, hipStream_t st, Workspace& ws, int groups,
         a.n = n; a.groups = groups;
         if (src) { a.desc = src->desc; a.ring = src->ring; }
         DQN_HIP(raise_lds_limits());
-        // Up to 256 items: one workgroup each, or the smallest part of an item for which every workgroup is resident at once -- the chain of
-        // layers of one sample is what the launch waits for.  More items: two persistent workgroups of half the size per compute unit.
+        // Up to one item per compute unit: one workgroup each, or the smallest part of an item for which every workgroup is resident at once --
+        // the chain of layers of one sample is what the launch waits for.  More items: two persistent workgroups of half the size per compute
+        // unit.  Both sides of that line (256 compute units): whole samples on four wavefronts below it, act step of 130, 192 and 256 states 17.4,
+        // 18.0 and 18.4 us where eight wavefronts take 16.5, 17.0 and 17.5, train step at minibatch 80 and 128 55.5 and 59.7 where they take 53.7 and 58.3;
+        // eight wavefronts with two samples one after the other above it, act step of 257, 300 and 512 states 24.8, 26.1 and 27.7 us, four 22.1, 23.8 and 25.5
+        // (before the changes to fc1).
         const int total = n * groups, cus = c->num_cus;
         const bool many = total > cus;
         const int parts = a.desc || 2 * total > cus ? 1 : 7 * total <= cus ? 7 : 3 * total <= cus ? 3 : 2;
@@ -443,7 +447,7 @@ static int train_impl(dqn_ctx* c, const uint8_t* s, const int32_t* a, const floa
         DQN_HIP((launch_fc_as<T, kFcReluMask>(st, fa, 1, pr.begin, pr.end)));
     }
     if constexpr (std::is_same<T, bf16_t>::value) {
-        // conv3 and conv2 data gradients in one persistent launch, dz2 handed over in LDS
+        // conv3 and conv2 data gradients in one launch, dz2 handed over in LDS
         TowerBwdArgs ta{};
         ta.dz3 = dz3; ta.act2 = act2; ta.act1 = act1; ta.w3d = bsh + kBshW3; ta.w2d = bsh + kBshW2;
         ta.dz2 = dz2; ta.dz1 = dz1; ta.n = B;

@@ -54,8 +54,9 @@ struct WgGeo {
     static constexpr int CS = CS_;                             // column blocks: a workgroup owns N / CS filter elements (its accumulators must fit the register file twice per SIMD)
     static constexpr int MT = COUT_ / 32, NT = N / 32 / CS_, NTW = (NT + 3) / 4;   // 32 x 32 tiles per workgroup, per wavefront
     // LDS pitch of a dZ row.  Half a wavefront's transposing read takes 64 bytes of four rows (here, and of four windows in the input image):
-    // pitches of 64 or 192 bytes modulo 256 put them side by side over the banks (pitches 16 elements shorter: 42 % of the LDS cycles were conflicts;
-    // 100 train steps at minibatch 512 10.25 -> 10.20 ms, 125 at 256 with Double DQN 10.10 -> 10.03 ms).
+    // pitches of 64 or 192 bytes modulo 256 put them side by side over the banks.  (Before, in elements: dZ of conv1 48, of conv2 and conv3 80, fc1's
+    // operands 80 and 144, the images of conv2 40 and of conv3 72 per pixel.  LDS cycles lost to conflicts in the launch at minibatch 512, all accesses:
+    // 42 -> 26 %, profiles/lds_conflicts_b512.txt; 100 train steps 10.25 -> 10.20 ms, 125 at 256 with Double DQN 10.10 -> 10.03 ms.)
     static constexpr int LDA = U8_ ? COUT_ : COUT_ + 32;
     static constexpr int IN_ROWS = U8_ ? S_ * (ROWS - 1) + KS_ : HIN_;           // conv1: 44 (24) image rows per item
     static constexpr int IN_ELEMS = U8_ ? CIN_ * IN_ROWS * WIN_ : HIN_ * WIN_ * PITCH_;
