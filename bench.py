@@ -90,14 +90,14 @@ _WG_SRC = _sources("wgrad_all.h")
 _TOWER_SRC = _sources("conv_tower.h", "conv_tower_many.h")
 _TOWER_BWD_SRC = _sources("conv_tower_bwd.h", "conv_tower_bwd_many.h")
 TRAFFIC = {
-    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "d4cbf06645b992392e8573ca995e7646569061d8", "profiles/hbm_traffic_b32.txt"),
-    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "8426a677e203c5b5f74c6e372f6cb2951909b04f", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower", 32, "bf16"): (10.24e6, _TOWER_SRC, "d7341cbacc0b7a5ddf0d45203270074d59190ef3", "profiles/hbm_traffic_b32.txt"),
-    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "fa6d3a99abdc22731133ec12419c7ec557ec0b66", "profiles/hbm_traffic_b32.txt"),
-    ("rmsprop", 256, "bf16"): (71.38e6, _RMS_SRC, "d4cbf06645b992392e8573ca995e7646569061d8", "profiles/hbm_traffic_b256.txt"),
-    ("wgrad_all", 256, "bf16"): (58.67e6, _WG_SRC, "8426a677e203c5b5f74c6e372f6cb2951909b04f", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower", 256, "bf16"): (24.35e6, _TOWER_SRC, "d7341cbacc0b7a5ddf0d45203270074d59190ef3", "profiles/hbm_traffic_b256.txt"),
-    ("conv_tower_bwd", 256, "bf16"): (23.43e6, _TOWER_BWD_SRC, "fa6d3a99abdc22731133ec12419c7ec557ec0b66", "profiles/hbm_traffic_b256.txt"),
+    ("rmsprop", 32, "bf16"): (66.20e6, _RMS_SRC, "8cbae2b860d69fefef9582ea26e260f08712c172", "profiles/hbm_traffic_b32.txt"),
+    ("wgrad_all", 32, "bf16"): (22.07e6, _WG_SRC, "882e419a11adc4326731447c91a0266e08b7422e", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower", 32, "bf16"): (10.24e6, _TOWER_SRC, "1590c2e5fdc21f0314dc40904824c6fe24df86e8", "profiles/hbm_traffic_b32.txt"),
+    ("conv_tower_bwd", 32, "bf16"): (4.77e6, _TOWER_BWD_SRC, "983c5dee7408c4be83a3fec7593449e349d81c0f", "profiles/hbm_traffic_b32.txt"),
+    ("rmsprop", 256, "bf16"): (71.38e6, _RMS_SRC, "8cbae2b860d69fefef9582ea26e260f08712c172", "profiles/hbm_traffic_b256.txt"),
+    ("wgrad_all", 256, "bf16"): (58.68e6, _WG_SRC, "882e419a11adc4326731447c91a0266e08b7422e", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower", 256, "bf16"): (24.35e6, _TOWER_SRC, "1590c2e5fdc21f0314dc40904824c6fe24df86e8", "profiles/hbm_traffic_b256.txt"),
+    ("conv_tower_bwd", 256, "bf16"): (23.43e6, _TOWER_BWD_SRC, "983c5dee7408c4be83a3fec7593449e349d81c0f", "profiles/hbm_traffic_b256.txt"),
 }
 
 
